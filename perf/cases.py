@@ -245,6 +245,21 @@ class _FcChain:
         return dict(y=self.x[self.L].whole, dW=[d.whole for d in self.dW], dX=self.g[0].whole)
 
 
+def _conv_layer(case):
+    return tt.layer("conv", "none", case["C"], case["K"], H=case["H"], W=case["W"], R=case["R"], S=case["R"], pad=case["pad"])
+
+
+def _conv_plan(case):
+    """tilings of X, W, Y, dY, dX and the three form sequences"""
+    k = case["k"]
+    if case["split"] == "planner":
+        p = tt.tt_plan_chain([_conv_layer(case)], case["N"], k)
+        return (p.x()[0], p.w()[0], p.x()[1], p.g()[1], p.g()[0]), [p.forms(1, op) for op in range(3)]
+    if case["split"] == "batch":
+        return ("R" * k, "r" * k, "R" * k, "R" * k, "R" * k), ["1" * k, "1" * k, "3" * k]
+    return ("r" * k, "C" * k, "C" * k, "C" * k, "r" * k), ["2" * k, "3" * k, "2" * k]
+
+
 class _Conv:
     """One convolution layer's training step."""
 
@@ -253,17 +268,8 @@ class _Conv:
         k = self.k = case["k"]
         self.N = N
         P, Q = H + 2 * pad - R + 1, W + 2 * pad - R + 1
-        self.lay = tt.layer("conv", "none", C, K, H=H, W=W, R=R, S=R, pad=pad)
-        if case["split"] == "planner":
-            p = tt.tt_plan_chain([self.lay], N, k)
-            self.t = (p.x()[0], p.w()[0], p.x()[1], p.g()[1], p.g()[0])
-            self.f = [p.forms(1, op) for op in range(3)]
-        elif case["split"] == "batch":
-            self.t = ("R" * k, "r" * k, "R" * k, "R" * k, "R" * k)
-            self.f = ["1" * k, "1" * k, "3" * k]
-        else:
-            self.t = ("r" * k, "C" * k, "C" * k, "C" * k, "r" * k)
-            self.f = ["2" * k, "3" * k, "2" * k]
+        self.lay = _conv_layer(case)
+        self.t, self.f = _conv_plan(case)
         tX, tW, tY, tdY, tdX = self.t
         bf, make = torch.bfloat16, _Maker(seed)
         self.X = make.normal(N * H * W, C, tX, 1.0, bf)
@@ -284,17 +290,25 @@ class _Conv:
         return dict(y=self.Y.whole, dW=self.dW.whole, dX=self.dX.whole)
 
 
+def _net_plan(case):
+    """the convolution, the fully-connected layers, the plan of the chain"""
+    conv = tt.layer("conv", "relu", case["C"], case["K"], H=case["H"], W=case["W"], R=3, S=3, pad=1)
+    dims = [case["K"] * case["H"] * case["W"]] + _widths(case)
+    n = len(dims) - 1
+    fcs = [tt.layer("fc", "relu" if i + 1 < n else "none", dims[i], dims[i + 1]) for i in range(n)]
+    return conv, fcs, tt.tt_plan_chain([conv] + fcs, case["N"], case["k"])
+
+
 class _Net:
     """3 x 3 convolution (ReLU) | flatten | fully-connected layers (ReLU between), the whole chain under one plan."""
 
     def __init__(self, case, seed):
         N, C, K, H, W, k = (case[n] for n in ("N", "C", "K", "H", "W", "k"))
         self.N, self.C, self.K, self.HW, self.k = N, C, K, H * W, k
-        conv = self.conv = tt.layer("conv", "relu", C, K, H=H, W=W, R=3, S=3, pad=1)
         dims = self.dims = [K * H * W] + _widths(case)
         n = len(dims) - 1
-        self.fcs = [tt.layer("fc", "relu" if i + 1 < n else "none", dims[i], dims[i + 1]) for i in range(n)]
-        p = tt.tt_plan_chain([conv] + self.fcs, N, k)
+        conv, self.fcs, p = _net_plan(case)
+        self.conv = conv
         tx, tg, tw = self.tx, self.tg, self.tw = p.x(), p.g(), p.w()
         f = self.f = [[p.forms(l, op) for op in range(3)] for l in range(1, n + 2)]
         bf, make = torch.bfloat16, _Maker(seed)
@@ -398,3 +412,120 @@ def tolerance(case):
     if case["kind"] == "fc" and case["mode"] == "forward":
         return dict(rel=4e-3)
     return dict(rel=1e-2 if len(_widths(case)) <= 4 else 4e-2)
+
+
+# -------------------------------------------------------------------------------------------- the same in 64 bits
+
+def _whole64(full, t, elem):
+    """the shards of tiling t of a float64 matrix, one after the other at the 256-byte boundaries of `elem`-byte values"""
+    rows, cols, unit = full.shape[0] >> t.count("R"), full.shape[1] >> t.count("C"), 256 // elem
+    pitch = -(-rows * cols // unit) * unit
+    whole = torch.zeros((1 << len(t)) * pitch, dtype=torch.float64, device=full.device)
+    for s in range(1 << len(t)):
+        rb, cb = _block_of(t, s)
+        whole[s * pitch:s * pitch + rows * cols].view(rows, cols).copy_(full[rb * rows:(rb + 1) * rows, cb * cols:(cb + 1) * cols])
+    return whole
+
+
+def _full64(make, rows, cols, std, dtype):
+    """the tensor `make.normal` cuts shards from, uncut"""
+    return make.normal(rows, cols, "", std, dtype)[0].double()
+
+
+def _fc64(x0, Ws, relus):
+    """activations x[0..L] of a chain of fully-connected layers"""
+    x = [x0]
+    for W, relu in zip(Ws, relus):
+        z = x[-1] @ W
+        x.append(z.clamp_(min=0) if relu else z)
+    return x
+
+
+def _fc64_backward(x, Ws, relus, g):
+    """weight gradients, and the gradient of x[0]"""
+    dW = [None] * len(Ws)
+    for l in reversed(range(len(Ws))):
+        if relus[l]:
+            g = g * (x[l + 1] > 0)
+        dW[l] = x[l].t() @ g
+        g = g @ Ws[l].t()
+    return dW, g
+
+
+def _windows(n, taps, pad, out):
+    """per tap: (first input, first output, length) along one image dimension"""
+    for r in range(taps):
+        lo, hi = max(0, pad - r), min(out, n + pad - r)
+        if hi > lo:
+            yield r, lo + r - pad, lo, hi - lo
+
+
+def _conv64(X, W, R, pad):
+    """X: N,H,W,C; W: K,R,R,C -> N,P,Q,K"""
+    n, h, w, _ = X.shape
+    p, q = h + 2 * pad - R + 1, w + 2 * pad - R + 1
+    Y = torch.zeros((n, p, q, W.shape[0]), dtype=torch.float64, device=X.device)
+    for r, i, o, m in _windows(h, R, pad, p):
+        for s, j, u, v in _windows(w, R, pad, q):
+            Y[:, o:o + m, u:u + v] += (X[:, i:i + m, j:j + v].reshape(n * m * v, -1) @ W[:, r, s].t()).view(n, m, v, -1)
+    return Y
+
+
+def _conv64_backward(X, W, G, R, pad):
+    """gradients of X and of W from that of the result"""
+    n, h, w, c = X.shape
+    p, q = G.shape[1:3]
+    dX, dW = torch.zeros_like(X), torch.zeros_like(W)
+    for r, i, o, m in _windows(h, R, pad, p):
+        for s, j, u, v in _windows(w, R, pad, q):
+            x = X[:, i:i + m, j:j + v].reshape(n * m * v, c)
+            g = G[:, o:o + m, u:u + v].reshape(n * m * v, -1)
+            dX[:, i:i + m, j:j + v] += (g @ W[:, r, s].contiguous()).view(n, m, v, c)
+            dW[:, r, s] = g.t() @ x
+    return dX, dW
+
+
+def exact(case, seed):
+    """What `run` returns on the same inputs, computed in 64 bits throughout (no stored value rounded in between).
+    A conversion has no such value: its bytes are compared."""
+    make = _Maker(seed)
+    if case["kind"] == "retile":
+        return None
+    if case["kind"] == "fc":
+        w, dt = _widths(case), _torch_dtype(case["dtype"])
+        L, elem = len(w) - 1, 4 if case["dtype"] == "f32" else 2
+        tx, tg, tw, _ = _fc_plan(tuple(w), case["batch"], case["k"], case["tiling"])
+        x0 = _full64(make, case["batch"], w[0], 1.0, dt)
+        Ws = [_full64(make, w[l], w[l + 1], case["w_std"], dt) for l in range(L)]
+        relus = [l + 1 < L for l in range(L)]
+        x = _fc64(x0, Ws, relus)
+        if case["mode"] == "forward":
+            return dict(x=[_whole64(x[l], tx[l], elem) for l in range(1, L + 1)])
+        dW, g0 = _fc64_backward(x, Ws, relus, _full64(make, case["batch"], w[L], 1.0, dt))
+        return dict(y=_whole64(x[L], tx[L], elem), dW=[_whole64(d, t, elem) for d, t in zip(dW, tw)],
+                    dX=_whole64(g0, tg[0], elem))
+    N, C, K, H, W = (case[n] for n in ("N", "C", "K", "H", "W"))
+    R, pad, bf = case.get("R", 3), case.get("pad", 1), torch.bfloat16
+    P, Q = H + 2 * pad - R + 1, W + 2 * pad - R + 1
+    if case["kind"] == "conv":
+        tX, tW, tY, tdY, tdX = _conv_plan(case)[0]
+        X = _full64(make, N * H * W, C, 1.0, bf).view(N, H, W, C)
+        F = _full64(make, K * R * R, C, 0.02, bf).view(K, R, R, C)
+        G = _full64(make, N * P * Q, K, 1.0, bf).view(N, P, Q, K)
+        dX, dF = _conv64_backward(X, F, G, R, pad)
+        return dict(y=_whole64(_conv64(X, F, R, pad).view(-1, K), tY, 2), dW=_whole64(dF.view(-1, C), _swap(tW), 2),
+                    dX=_whole64(dX.view(-1, C), tdX, 2))
+    dims = [K * H * W] + _widths(case)
+    n = len(dims) - 1
+    p = _net_plan(case)[2]
+    tx, tg, tw = p.x(), p.g(), p.w()
+    X = _full64(make, N * H * W, C, 1.0, bf).view(N, H, W, C)
+    F = _full64(make, K * 9, C, 1.5 / math.sqrt(9 * C), bf).view(K, 3, 3, C)
+    Ws = [_full64(make, dims[i], dims[i + 1], 1.5 / math.sqrt(dims[i]), bf) for i in range(n)]
+    relus = [i + 1 < n for i in range(n)]
+    y1 = _conv64(X, F, 3, 1).clamp_(min=0)
+    x = _fc64(y1.permute(0, 3, 1, 2).reshape(N, -1), Ws, relus)
+    dW, g0 = _fc64_backward(x, Ws, relus, _full64(make, N, dims[n], 1.0, bf))
+    dX, dF = _conv64_backward(X, F, g0.view(N, K, H, W).permute(0, 2, 3, 1) * (y1 > 0), 3, 1)
+    return dict(y=_whole64(x[n], tx[n + 1], 2), dWf=[_whole64(d, t, 2) for d, t in zip(dW, tw[1:])],
+                dWc=_whole64(dF.view(-1, C), _swap(tw[0]), 2), dX=_whole64(dX.view(-1, C), tg[0], 2))
