@@ -2,7 +2,7 @@
 // after input conversion every device runs the same sub-operator on its own tiles).
 //
 // bf16 path: the MFMA tile engine of gemm_core.h with dense-matrix loaders (NN, NT, TN, TT all share one main loop).
-// fp32 path / shapes without 16-byte rows: a plain LDS-tiled FMA kernel with arbitrary strides.
+// fp32 path / shapes without 16-byte rows: MFMAs on fragments loaded straight into registers (gemm_small.hip).
 #include "tt_device.h"
 #include <cstdint>
 #include <cstdlib>
@@ -100,111 +100,6 @@ template <bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_v2(Gem
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
 
-// ---------------------------------------------------------------- generic kernel (fp32, or any unaligned shape)
-// C[m][n] = sum_k A(m,k) B(k,n) with element strides; 64x64 tile, 16x16 threads, 4x4 outputs per thread.
-struct GenericParams {
-    const void *A[kMaxShards];
-    const void *B[kMaxShards];
-    void *C[kMaxShards];
-    int32_t M, N, K;
-    int64_t sam, sak, sbk, sbn;
-    int32_t ldc;
-    int32_t tiles_m, tiles_n;
-    int32_t ksplit, kchunk;
-};
-
-template <bool IN_BF16> __device__ __forceinline__ float load_in(const void *p, int64_t off)
-{
-    if (IN_BF16) return __uint_as_float((uint32_t) reinterpret_cast<const uint16_t *>(p)[off] << 16);
-    return reinterpret_cast<const float *>(p)[off];
-}
-
-template <bool IN_BF16, bool OUT_BF16, bool RELU>
-__global__ __launch_bounds__(kThreads) void gemm_generic_kernel(const GenericParams p)
-{
-    constexpr int T = 64, KB = 16;
-    __shared__ float As[KB][T + 1];
-    __shared__ float Bs[KB][T + 1];
-    int tiles = p.tiles_m * p.tiles_n;
-    int vshard = blockIdx.x / tiles;
-    int t = blockIdx.x - vshard * tiles;
-    int m0 = (t % p.tiles_m) * T, n0 = (t / p.tiles_m) * T;
-    const int shard = vshard / p.ksplit;
-    const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
-    const int kend = kbeg + p.kchunk < p.K ? kbeg + p.kchunk : p.K;
-    const void *A = p.A[shard];
-    const void *B = p.B[shard];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4] = {};
-    // A tile's elements come into registers first (four of each operand per thread, all loads in flight together, from
-    // clamped addresses with the out-of-range ones zeroed afterwards) and go to LDS when their step comes; the fetch
-    // runs PD tiles ahead of the arithmetic.  These products are small and the chip is nearly idle while they run: what
-    // a step costs is one trip to memory (about 2 us here), and PD of them are now under way at a time.
-    constexpr int PT = T * KB / kThreads, PD = 4;
-    float ra[PD][PT], rb[PD][PT];
-    auto fetch = [&](int k0, float (&xa)[PT], float (&xb)[PT]) {
-#pragma unroll
-        for (int u = 0; u < PT; ++u) {
-            const int i = threadIdx.x + u * kThreads;
-            // pick the loop order that walks the contiguous stride
-            int kk, mm;
-            if (p.sak == 1) { kk = i % KB; mm = i / KB; } else { mm = i % T; kk = i / T; }
-            const int gm = m0 + mm, gk = k0 + kk;
-            const float va = load_in<IN_BF16>(A, (int64_t)(gm < p.M ? gm : p.M - 1) * p.sam + (int64_t)(gk < kend ? gk : kend - 1) * p.sak);
-            xa[u] = (gm < p.M && gk < kend) ? va : 0.0f;
-            int kb, nn;
-            if (p.sbk == 1) { kb = i % KB; nn = i / KB; } else { nn = i % T; kb = i / T; }
-            const int gn = n0 + nn, gkb = k0 + kb;
-            const float vb = load_in<IN_BF16>(B, (int64_t)(gkb < kend ? gkb : kend - 1) * p.sbk + (int64_t)(gn < p.N ? gn : p.N - 1) * p.sbn);
-            xb[u] = (gn < p.N && gkb < kend) ? vb : 0.0f;
-        }
-    };
-#pragma unroll
-    for (int d = 0; d < PD; ++d)
-        if (kbeg + d * KB < kend) fetch(kbeg + d * KB, ra[d], rb[d]);
-    for (int k0 = kbeg; k0 < kend; k0 += PD * KB) {
-#pragma unroll
-        for (int d = 0; d < PD; ++d) { // (unrolled: the register ring is indexed by constants)
-            const int kd = k0 + d * KB;
-            if (kd >= kend) break;
-#pragma unroll
-            for (int u = 0; u < PT; ++u) {
-                const int i = threadIdx.x + u * kThreads;
-                int kk, mm;
-                if (p.sak == 1) { kk = i % KB; mm = i / KB; } else { mm = i % T; kk = i / T; }
-                As[kk][mm] = ra[d][u];
-                int kb, nn;
-                if (p.sbk == 1) { kb = i % KB; nn = i / KB; } else { nn = i % T; kb = i / T; }
-                Bs[kb][nn] = rb[d][u];
-            }
-            __syncthreads();
-            if (kd + PD * KB < kend) fetch(kd + PD * KB, ra[d], rb[d]);
-#pragma unroll
-            for (int kk = 0; kk < KB; ++kk) {
-                float a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-            }
-            __syncthreads();
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-            if (row >= p.M || col >= p.N) continue;
-            float v = acc[i][j];
-            if (RELU) v = v > 0.0f ? v : 0.0f;
-            if (OUT_BF16) reinterpret_cast<uint16_t *>(p.C[vshard])[(size_t)row * p.ldc + col] = (uint16_t)f32_to_bf16_bits(v);
-            else reinterpret_cast<float *>(p.C[vshard])[(size_t)row * p.ldc + col] = v;
-        }
-}
-
 template <int BM, int BN, int WM, int WN, int DEPTH, bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC>
 tt_status launch_mfma_cfg(GemmParams &p, int count, hipStream_t s)
 {
@@ -267,20 +162,6 @@ template <bool A_KC, bool B_KC> tt_status launch_mfma_out(GemmParams &p, int cou
     if (out_dtype == TT_BF16)
         return vec ? launch_mfma_kmask<A_KC, B_KC, true, true>(p, count, s) : launch_mfma_kmask<A_KC, B_KC, true, false>(p, count, s);
     return vec ? launch_mfma_kmask<A_KC, B_KC, false, true>(p, count, s) : launch_mfma_kmask<A_KC, B_KC, false, false>(p, count, s);
-}
-
-template <bool IN_BF16> tt_status launch_generic_in(const GenericParams &p, int count, int out_dtype, int act, hipStream_t s)
-{
-    const bool relu = act == TT_ACT_RELU;
-    dim3 grid((uint32_t)(p.tiles_m * p.tiles_n * count * p.ksplit)), block(kThreads);
-    if (out_dtype == TT_BF16) {
-        if (relu) hipLaunchKernelGGL((gemm_generic_kernel<IN_BF16, true, true>), grid, block, 0, s, p);
-        else hipLaunchKernelGGL((gemm_generic_kernel<IN_BF16, true, false>), grid, block, 0, s, p);
-    } else {
-        if (relu) hipLaunchKernelGGL((gemm_generic_kernel<IN_BF16, false, true>), grid, block, 0, s, p);
-        else hipLaunchKernelGGL((gemm_generic_kernel<IN_BF16, false, false>), grid, block, 0, s, p);
-    }
-    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
 
 bool all_aligned16(const void *const *ptrs, int n)
@@ -381,23 +262,8 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
         if (!a_kc && !b_kc) return launch_mfma_out<false, false>(p, count, out_dtype, act, vec, s);
         return launch_mfma_out<false, true>(p, count, out_dtype, act, vec, s);
     }
-    GenericParams g;
-    for (int i = 0; i < kMaxShards; ++i) {
-        g.A[i] = i < count ? A[i] : nullptr;
-        g.B[i] = i < count ? B[i] : nullptr;
-        g.C[i] = i < count * ksplit ? C[i] : nullptr;
-    }
-    g.M = (int32_t)M; g.N = (int32_t)N; g.K = (int32_t)K;
-    g.sam = trans_a ? 1 : K; g.sak = trans_a ? M : 1;
-    g.sbk = trans_b ? 1 : N; g.sbn = trans_b ? K : 1;
-    g.ldc = (int32_t)N;
-    g.tiles_m = (int32_t)((M + 63) / 64);
-    g.tiles_n = (int32_t)((N + 63) / 64);
-    g.ksplit = ksplit;
-    g.kchunk = (int32_t)kchunk;
-    if ((int64_t)g.tiles_m * g.tiles_n * count * ksplit >= (int64_t(1) << 31)) return TT_EUNSUPPORTED;
-    return in_dtype == TT_BF16 ? launch_generic_in<true>(g, count, out_dtype, act, s)
-                               : launch_generic_in<false>(g, count, out_dtype, act, s);
+    return launch_gemm_small(count, A, B, C, M, N, K, a_contig, b_contig, !trans_a, trans_b != 0, in_dtype, out_dtype,
+                             act == TT_ACT_RELU, ksplit, kchunk, stream);
 }
 
 } // namespace tt

@@ -10,6 +10,7 @@ alignas(16) thread_local char smem2[160 * 1024], smem3[160 * 1024], smem4[160 * 
 } // namespace tt
 #include "gemm.hip"
 #include "gemm3.hip"
+#include "gemm_small.hip"
 
 // (registered by the thread that loads the library, which is the one that calls it)
 static const int g_registered = (emu_register_lds(tt::smem, sizeof(tt::smem)), emu_register_lds(tt::smem2, sizeof(tt::smem2)),

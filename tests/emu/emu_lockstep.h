@@ -32,6 +32,7 @@ struct WaveState {
     unsigned gen = 0;
     uint16_t a[kWave][8], b[kWave][8];
     float c[kWave][16];
+    float fa[kWave], fb[kWave];
     uint16_t tr[kWave][4];
 };
 
@@ -145,6 +146,27 @@ template <class AB, class C> inline C mfma_32x32x16_bf16(AB a, AB b, C c)
     return c;
 }
 
+// v_mfma_f32_32x32x2_f32: A: row lane % 32, k = lane / 32; B: column lane % 32, the same k; C, D as above; two fp32 fused
+// multiply-adds per result, k in increasing order
+template <class C> inline C mfma_32x32x2_f32(float a, float b, C c)
+{
+    WaveState &w = my_wave();
+    const int l = lane();
+    w.fa[l] = a;
+    w.fb[l] = b;
+    std::memcpy(w.c[l], &c, 64);
+    wave_collective(4, [](WaveState &v) {
+        if (v.live != kWave) die("MFMA in a wave with ended lanes");
+        for (int ln = 0; ln < kWave; ++ln)
+            for (int r = 0; r < 16; ++r) {
+                const int i = 8 * (r / 4) + 4 * (ln / 32) + r % 4, j = ln % 32;
+                for (int k = 0; k < 2; ++k) v.c[ln][r] = std::fma(v.fa[i + 32 * k], v.fb[j + 32 * k], v.c[ln][r]);
+            }
+    });
+    std::memcpy(&c, w.c[l], 64);
+    return c;
+}
+
 // the caller has put its own 8 bytes into tr[lane]
 inline void transpose_groups_of_16()
 {
@@ -222,3 +244,4 @@ inline void __syncthreads() { emu::block_barrier(); }
 #define __builtin_amdgcn_s_waitcnt(x) emu::wait_counts(x)
 #define __builtin_amdgcn_wave_barrier() emu::wave_sync()
 #define __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, x, y, z) emu::mfma_32x32x16_bf16(a, b, c)
+#define __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, x, y, z) emu::mfma_32x32x2_f32(a, b, c)

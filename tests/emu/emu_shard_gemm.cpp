@@ -18,6 +18,7 @@ alignas(16) thread_local char smem2[160 * 1024], smem3[160 * 1024], smem4[160 * 
 } // namespace tt
 #include "gemm.hip"
 #include "gemm3.hip"
+#include "gemm_small.hip"
 
 namespace tt {
 ProfileScope::ProfileScope(void *, int, int, int64_t, int64_t, int64_t, uint64_t, uint64_t) : slot(-1), stream(nullptr) {}

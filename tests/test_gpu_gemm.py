@@ -77,6 +77,24 @@ def test_fp32(ta, tb):
 
 
 @pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_odd_sized_products(ta, tb, dt):
+    # K over one, two, four and eight waves with tails; single results; enough 64 x 64 blocks for those, with one row or
+    # column left over (the row pairs of bf16 operands)
+    for i, (n, M, N, K) in enumerate([(2, 33, 47, 1051), (1, 1, 1, 1), (3, 40, 31, 263), (1, 5, 67, 131), (4, 577, 449, 515), (8, 257, 450, 97)]):
+        check(n, M, N, K, ta, tb, dt, dt if i % 2 else "f32", bool(i & 1), 60 + i)
+
+
+def test_fp32_keeps_subnormal_products_and_sums():
+    # results below the smallest normal fp32 number (1.2e-38): K = 64 products of 2^-70 x 2^-65
+    a = torch.full((40, 64), 2.0 ** -70, dtype=torch.float32, device=DEV)
+    b = torch.full((64, 33), 2.0 ** -65, dtype=torch.float32, device=DEV)
+    c = torch.empty((40, 33), dtype=torch.float32, device=DEV)
+    tt.tt_shard_gemm([a], [b], [c], 40, 33, 64, 0, 0, "f32", "f32")
+    assert np.all(dev_to_np(c).astype(np.float64) == 2.0 ** -129)
+
+
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
 def test_bf16_large_launch_eight_wave_tiles(ta, tb):
     # enough 256 x 256 tiles for the eight-wave kernels (both tile engines, chosen by layout), ragged M, N and K
     check(8, 1000, 1016, 200, ta, tb, "bf16", "bf16", True, 39)

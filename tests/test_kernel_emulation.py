@@ -269,6 +269,17 @@ def test_shard_product_entry_point_stays_inside_its_buffers(emu_shard_gemm, case
         assert int(r.stdout.split()[2]) == threads, r.stdout
 
 
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("bf", [0, 1])
+def test_small_kernel_stays_inside_its_buffers(emu_shard_gemm, layout, bf, monkeypatch):
+    # operands of exactly their size, odd in every dimension: 32 x 32 and 64 x 64 blocks, K below one MFMA step, K tails
+    for t2 in ("256", "1"):
+        monkeypatch.setenv("TT_SMALL_T2", t2)
+        for M, N, K in [(1, 1, 1), (65, 129, 97), (129, 65, 9), (97, 193, 515), (63, 35, 1051), (34, 66, 64)]:
+            r = run(emu_shard_gemm, (2, M, N, K) + layout + (bf, bf, 1, 1))
+            assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (t2, M, N, K, r.stdout[-400:] + r.stderr[-1500:])
+
+
 def test_shard_product_entry_point_rejects_what_the_library_rejects(emu_shard_gemm):
     # a K split that would leave the last chunk empty (chunks are rounded up to the tile depth: two of 64 cover K = 128)
     r = run(emu_shard_gemm, (2, 64, 64, 128, 0, 0, 1, 0, 0, 3))

@@ -194,6 +194,18 @@ def test_generic_kernel_values(lockstep_gemm, tmp_path, ta, tb):
     check(lockstep_gemm, str(tmp_path), 1, 33, 10, 17, ta, tb, "bf16", "f32", False, 36, ksplit=1)
 
 
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_small_kernel_waves_and_blocks_values(lockstep_gemm, tmp_path, dt, ta, tb):
+    # every split of the waves (K of one, two, four and eight waves, the last with a tail that is no whole MFMA step),
+    # single results, and 64 x 64 blocks with one row or column in the last one (the row pairs of bf16 operands)
+    for i, (M, N, K) in enumerate([(33, 47, 1051), (1, 1, 1), (40, 31, 263), (5, 67, 131)]):
+        check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, dt, "f32", False, 80 + i)
+    for i, (M, N, K) in enumerate([(65, 129, 97), (66, 127, 515), (129, 65, 9)]):
+        check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, dt, dt, True, 90 + i, env={"TT_SMALL_T2": "1"})
+    check(lockstep_gemm, str(tmp_path), 2, 35, 37, 323, ta, tb, dt, "f32", False, 99, ksplit=3)
+
+
 def test_random_products_values(lockstep_gemm, tmp_path):
     # seeded random shapes, layouts, types and tuning switches (sizes mostly multiples of eight, some odd): whatever
     # engine the launch code picks or falls back to has to give the product
