@@ -22,18 +22,21 @@ __device__ __forceinline__ uint32_t lds_addr(char *p)
 }
 
 // global -> LDS, 16 bytes per lane: lane i's chunk lands at lds_wave_addr + 16 i (M0 holds the wave-uniform LDS
-// address; s_nop: one wait state between the write of M0 and its use).  Assembly on purpose: for the builtin form the
+// address; s_nop 4: the ISA's five wait states between a vector instruction that writes M0, v_readfirstlane, and its use).  Assembly on purpose: for the builtin form the
 // compiler's wait-count pass assumes that any later LDS read may alias the incoming data and puts s_waitcnt vmcnt(0) in
 // front of the next fragment read; here the waits are the explicit s_waitcnt + barrier pairs of the main loops.
 // ... every lane supplies a full global address
 __device__ __forceinline__ void lds_dma16(const void *g, uint32_t lds_wave_addr)
 {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "{m0}"(lds_wave_addr), "v"(g) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, off" : : "{m0}"(lds_wave_addr), "v"(g) : "memory");
 }
-// ... a wave-uniform base (scalar registers) plus a 32-bit offset per lane
+// ... a wave-uniform base (scalar registers) plus a 32-bit offset per lane.  Where the base comes out of a vector instruction
+// (v_readfirstlane), the ISA asks for five wait states before a vector-memory instruction reads it, and the compiler, which
+// puts them in front of its own instructions, does not look into assembly: s_nop 4 (without it a kernel whose base was
+// read two instructions earlier loaded from a stale address and faulted).
 __device__ __forceinline__ void lds_dma16(uint32_t lane_offset, uint64_t uniform_base, uint32_t lds_wave_addr)
 {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_offset), "s"(uniform_base), "{m0}"(lds_wave_addr) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_offset), "s"(uniform_base), "{m0}"(lds_wave_addr) : "memory");
 }
 
 // 16-byte global store.  A named function because kernels that leave stores in flight over a wait count them

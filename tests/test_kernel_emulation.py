@@ -385,3 +385,16 @@ def test_convolution_steps_under_random_tilings_stay_inside_their_buffers(emu_st
         t = {n: ts[j] for n, j in zip(("X", "W", "Y", "dY", "dX"), rng.integers(0, len(ts), 5))}
         r = run(emu_step, conv_step_args(4, 2, 32, 64, 9, 9, 3, 3, 1, bool(i % 2), t, [None] * 3))
         assert r.returncode == 0 and r.stdout.startswith("ok conv step"), (t, r.stdout[-400:] + r.stderr[-1500:])
+
+
+def test_assembly_loads_leave_the_wait_states_their_scalar_operands_need():
+    # A vector instruction that writes a scalar register (v_readfirstlane: the base address, M0) and a vector-memory
+    # instruction that reads it must be five wait states apart.  The compiler sees to that for its own instructions, not
+    # for loads written in assembly, so each of those has to start with s_nop 4 (five states) or more.
+    import re
+    src = open(os.path.join(ROOT, "paper_1805_04170_amd", "csrc", "tt_device.h")).read()
+    loads = re.findall(r'asm volatile\("([^"]*global_load_lds[^"]*)"', src)
+    assert len(loads) == 2
+    for text in loads:
+        m = re.match(r"s_nop (\d+)\\n\\tglobal_load_lds", text)
+        assert m and int(m.group(1)) >= 4, text
