@@ -89,6 +89,11 @@ def test_flatten_tile_tails_and_sizes():
     flatten_case(1, 4, 1, 1, "", "", np.uint16, 403)              # no cut, one pixel
 
 
+def test_flatten_large_tensors_take_the_large_tiles():
+    flatten_case(256, 128, 10, 7, "RC", "CR", np.uint16, 404)     # 1024 tiles of 64 x 64, the second pixel tile ragged
+    flatten_case(512, 72, 9, 7, "Rr", "CC", np.float32, 405)      # ragged in both
+
+
 def test_flatten_refusals():
     x = [torch.zeros(4096, dtype=torch.int16, device=DEV)] * 4
     with pytest.raises(tt.TilingError) as e:                       # 6 channels cannot be cut twice
