@@ -49,8 +49,9 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN / 4) * (DEPTH == 0 ? (BM == 
     const int klen = p.K - kbeg < p.kchunk ? p.K - kbeg : p.kchunk;
 
     constexpr int NT = WM * WN * 64;
-    using LA = std::conditional_t<A_KC, core::DenseKC<core::Slots<BM, true, NT>::value>, core::DenseRC<core::Slots<BM, false, NT>::value>>;
-    using LB = std::conditional_t<B_KC, core::DenseKC<core::Slots<BN, true, NT>::value>, core::DenseRC<core::Slots<BN, false, NT>::value>>;
+    constexpr int SA = core::Slots<BM, A_KC, NT>::value, SB = core::Slots<BN, B_KC, NT>::value;
+    using LA = std::conditional_t<A_KC, core::DenseKC<SA>, core::DenseRC<SA>>;
+    using LB = std::conditional_t<B_KC, core::DenseKC<SB>, core::DenseRC<SB>>;
     LA la;
     la.base = reinterpret_cast<const char *>(p.A[shard]) + (size_t)kbeg * (A_KC ? 2 : 2 * (size_t)p.lda);
     la.ld = p.lda; la.rows = p.M; la.K = klen;
@@ -141,6 +142,20 @@ template <bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status l
     if (tile == 3) return launch_mfma_cfg<256, 128, 2, 2, 0, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     if (tile == 2) return launch_mfma_cfg<256, 256, 2, 2, 1, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     if (tile == 0) return launch_mfma_cfg<256, 128, 2, 2, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
+    if (tuning_int("TT_GEMM_TILE", -1) < 0) {
+        // Few rows (a small batch against streamed weights): a 128-row tile would take in, store to LDS and multiply rows that
+        // do not exist; what counts is how much of the weights is on its way, and the narrower tiles have two K tiles of
+        // it in registers and several workgroups per CU.  8 x (16 x 4096 x 1152) 29.2 -> 19.4 us, 8 x (8 x 4096 x 9216) 189 -> 120
+        // (5 TB/s of weights), 64 x 4096 x 4096 68 -> 42 us.  (32 rows: A K-contiguous only, its loader needs a chunk per thread.)
+        if constexpr (A_KC) {
+            if (p.M <= 32) return launch_mfma_cfg<32, 128, 1, 4, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
+            if (p.M <= 64) return launch_mfma_cfg<64, 128, 1, 4, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
+        }
+        // at most one workgroup per CU: its registers are free for a second K tile on its way (8 x (128 x 512 x 512)
+        // 11.9 -> 10.4 us)
+        if ((int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) * count * p.ksplit <= 256)
+            return launch_mfma_cfg<128, 128, 2, 2, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
+    }
     return launch_mfma_cfg<128, 128, 2, 2, 1, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
 }
 

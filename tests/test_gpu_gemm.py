@@ -64,6 +64,15 @@ def test_bf16_small_and_tall(ta, tb):
     check(1, 520, 72, 40, ta, tb, "bf16", "bf16", False, 34)        # three row tiles, one short K tile
 
 
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M", [1, 16, 32, 33, 64, 65])
+def test_bf16_few_rows(M, tb):
+    # a small batch against wide weights: 32- and 64-row tiles, ragged columns, K with and without a tail, K of one tile
+    check(8, M, 1000, 328, 0, tb, "bf16", "bf16", True, 70)
+    check(3, M, 264, 64, 0, tb, "bf16", "f32", False, 71)
+    check(1, M, 136, 1024, 0, tb, "bf16", "f32", False, 72)
+
+
 @pytest.mark.parametrize("ta,tb", LAYOUTS)
 def test_bf16_unaligned_falls_back(ta, tb):
     check(2, 37, 125, 50, ta, tb, "bf16", "bf16", True, 35)         # 125-wide rows: no 16-byte vectors
