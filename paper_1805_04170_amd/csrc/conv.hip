@@ -626,7 +626,14 @@ template <int OP, bool OUT_BF16, bool ONE_TAP> tt_status launch_gather_a_t(ConvP
     // at most 64 output columns per shard (channels cut eight ways): 256 x 64 tiles, four waves of 64 x 64, so that no
     // wave multiplies columns that do not exist
     if constexpr (OP == 0) // (the filter loader of the direct data-gradient path needs 128 columns for its 256 threads)
-    if (p.N <= 64 && p.M > 128 && tuning_int("TT_CONV_TILE", -1) < 0) {
+    if (p.N <= 64 && tuning_int("TT_CONV_TILE", -1) < 0) {
+        // 128 x 64 tiles (four waves of 32 x 64) while 256-row tiles do not give every CU two workgroups: the gather's
+        // address arithmetic and the trips to memory per K tile are what a lone workgroup spends its time on (784 x 64 x 576, eight shards: 19.8 -> 13.8 us)
+        if ((int64_t)((p.M + 255) / 256) * count < 512) {
+            constexpr size_t sm = core::smem_bytes<128, 64, 2>();
+            return kmask ? launch(conv_gather_a_kernel<128, 64, 1, 2, true, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 128, 64, 256, count, s)
+                         : launch(conv_gather_a_kernel<128, 64, 1, 2, false, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 128, 64, 256, count, s);
+        }
         constexpr size_t sm = core::smem_bytes<256, 64, 2>();
         return kmask ? launch(conv_gather_a_kernel<256, 64, 1, 2, true, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 256, 64, 256, count, s)
                      : launch(conv_gather_a_kernel<256, 64, 1, 2, false, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 256, 64, 256, count, s);
@@ -636,14 +643,15 @@ template <int OP, bool OUT_BF16, bool ONE_TAP> tt_status launch_gather_a_t(ConvP
         return kmask ? launch(conv_gather_a_kernel<256, 256, 4, 1, true, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s)
                      : launch(conv_gather_a_kernel<256, 256, 4, 1, false, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s);
     }
-    if (tile == 0) {
+    // too few 256 x 128 tiles for half the CUs: 128 x 128 ones
+    if (tile == 0 && ((int64_t)((p.M + 255) / 256) * ((p.N + 127) / 128) * count > 128 || tuning_int("TT_CONV_TILE", -1) == 0)) {
         constexpr size_t sm = core::smem_bytes<256, 128>();
         return kmask ? launch(conv_gather_a_kernel<256, 128, 2, 2, true, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 128, 256, count, s)
                      : launch(conv_gather_a_kernel<256, 128, 2, 2, false, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 128, 256, count, s);
     }
     constexpr size_t sm = core::smem_bytes<128, 128>();
-    return kmask ? launch(conv_gather_a_kernel<128, 128, 2, 1, true, OP, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s)
-                 : launch(conv_gather_a_kernel<128, 128, 2, 1, false, OP, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s);
+    return kmask ? launch(conv_gather_a_kernel<128, 128, 2, 2, true, OP, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s)
+                 : launch(conv_gather_a_kernel<128, 128, 2, 2, false, OP, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s);
 }
 
 template <int OP, bool OUT_BF16> tt_status launch_gather_a(ConvParams &p, int count, hipStream_t s)
@@ -670,8 +678,8 @@ template <bool OUT_BF16> tt_status launch_wgrad(ConvParams &p, int count, hipStr
                      : launch(conv_wgrad_kernel<256, 128, 2, 2, false, OUT_BF16>, sm, p, 256, 128, 256, count, s);
     }
     constexpr size_t sm = core::smem_bytes<128, 128>();
-    return kmask ? launch(conv_wgrad_kernel<128, 128, 2, 1, true, OUT_BF16>, sm, p, 128, 128, 256, count, s)
-                 : launch(conv_wgrad_kernel<128, 128, 2, 1, false, OUT_BF16>, sm, p, 128, 128, 256, count, s);
+    return kmask ? launch(conv_wgrad_kernel<128, 128, 2, 2, true, OUT_BF16>, sm, p, 128, 128, 256, count, s)
+                 : launch(conv_wgrad_kernel<128, 128, 2, 2, false, OUT_BF16>, sm, p, 128, 128, 256, count, s);
 }
 
 bool aligned16(const void *const *ptrs, int n)

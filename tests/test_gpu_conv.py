@@ -99,6 +99,14 @@ def test_single_shard_and_one_cut():
     run_conv(4, 16, 32, 6, 6, 3, 3, 1, 1, False, "C", "R", "r", "r", "C", "3", "2", "1", 103)
 
 
+def test_few_channels_and_many_pixels():
+    # at most 64 output columns: 128 x 64 tiles, ragged in both; eight output channels and 1920 pixels: the filter
+    # gradient's reduction cut into four sub-products
+    run_conv(4, 16, 56, 12, 10, 3, 3, 1, 0, True, "", "", "", "", "", "", "", "", 104)
+    run_conv(16, 24, 8, 12, 10, 3, 3, 1, 0, False, "", "", "", "", "", "", "", "", 105)
+    run_conv(8, 64, 16, 9, 9, 1, 1, 0, 1, False, "r", "C", "C", "C", "r", "2", "3", "2", 106)
+
+
 @pytest.mark.parametrize("relu", [False, True])
 def test_every_form_sequence_two_cuts(relu):
     for f in ["".join(p) for p in itertools.product("123", repeat=2)]:
