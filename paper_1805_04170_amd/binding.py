@@ -5,6 +5,7 @@ Tilings are strings over "RCr" (cut 0 first); form sequences are strings over "1
 TilingError.  The HIP stream defaults to torch's current stream.
 """
 import ctypes
+import functools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -174,6 +175,16 @@ def tiling(t):
     return out
 
 
+@functools.lru_cache(maxsize=4096)
+def _tiling_of(t):
+    return tiling(t)
+
+
+def _tiling(t):
+    """tiling(t) for a call (the library takes it by value): the structure of a string is made once"""
+    return _tiling_of(t) if type(t) is str else tiling(t)
+
+
 def tiling_str(t, k):
     return "".join(_NAMES[t.cut[j]] for j in range(k))
 
@@ -185,17 +196,36 @@ def forms(f):
     return (ctypes.c_uint8 * max(len(f), 1))(*[int(ch) - 1 for ch in f])
 
 
+@functools.lru_cache(maxsize=4096)
+def _forms_of(f):
+    return forms(f)
+
+
+def _forms(f):
+    """forms(f) for a call (the library only reads it): the array of a string is made once"""
+    return _forms_of(f) if type(f) is str else forms(f)
+
+
 def layer(kind="fc", act="none", n_in=0, n_out=0, H=0, W=0, R=0, S=0, pad=0):
     return tt_layer(TT_FC if kind == "fc" else TT_CONV2D, TT_ACT_RELU if act == "relu" else TT_ACT_NONE, n_in, n_out,
                     H, W, R, S, pad)
+
+
+@functools.lru_cache(maxsize=128)
+def _ptr_array(n):
+    return ctypes.c_void_p * n
 
 
 def ptrs(shards):
     """sequence of tensors / addresses -> void*[]; None -> NULL"""
     if shards is None:
         return None
-    vals = [(s.data_ptr() if hasattr(s, "data_ptr") else int(s)) for s in shards]
-    return (ctypes.c_void_p * max(len(vals), 1))(*vals)
+    shards = list(shards)
+    try:
+        vals = [s.data_ptr() for s in shards]
+    except AttributeError:
+        vals = [(s.data_ptr() if hasattr(s, "data_ptr") else int(s)) for s in shards]
+    return _ptr_array(max(len(vals), 1))(*vals)
 
 
 def _stream(stream):
@@ -421,25 +451,25 @@ def tt_graph_eval(tensors, ops, k, tilings):
 
 def tt_retile(dst, B, src, A, rows, cols, elem_bytes, k=None, stream=None):
     k = len(A) if k is None else k
-    _check(lib().tt_retile(ptrs(dst), tiling(B), ptrs(src), tiling(A), k, rows, cols, elem_bytes, _stream(stream)),
+    _check(lib().tt_retile(ptrs(dst), _tiling(B), ptrs(src), _tiling(A), k, rows, cols, elem_bytes, _stream(stream)),
            "tt_retile")
 
 
 def tt_flatten(dst, B, src, A, batch, channels, pixels, elem_bytes, to_matrix=True, k=None, stream=None):
     k = len(A) if k is None else k
-    _check(lib().tt_flatten(ptrs(dst), tiling(B), ptrs(src), tiling(A), k, batch, channels, pixels, elem_bytes,
+    _check(lib().tt_flatten(ptrs(dst), _tiling(B), ptrs(src), _tiling(A), k, batch, channels, pixels, elem_bytes,
                             1 if to_matrix else 0, _stream(stream)), "tt_flatten")
 
 
 def tt_retile_gate(dst, B, src, A, mask, Am, rows, cols, dtype, k=None, stream=None):
     k = len(A) if k is None else k
-    _check(lib().tt_retile_gate(ptrs(dst), tiling(B), ptrs(src), tiling(A), ptrs(mask), tiling(Am if mask is not None else A),
+    _check(lib().tt_retile_gate(ptrs(dst), _tiling(B), ptrs(src), _tiling(A), ptrs(mask), _tiling(Am if mask is not None else A),
                                 k, rows, cols, _dtype(dtype), _stream(stream)), "tt_retile_gate")
 
 
 def tt_reduce(dst, B, out_dtype, partials, form_seq, rows, cols, act=TT_ACT_NONE, k=None, stream=None):
     k = len(form_seq) if k is None else k
-    _check(lib().tt_reduce(ptrs(dst), tiling(B), _dtype(out_dtype), ptrs(partials), forms(form_seq), k, rows, cols, act,
+    _check(lib().tt_reduce(ptrs(dst), _tiling(B), _dtype(out_dtype), ptrs(partials), _forms(form_seq), k, rows, cols, act,
                            _stream(stream)), "tt_reduce")
 
 
@@ -460,13 +490,13 @@ def _ws(workspace):
 
 
 def _t_or(t, default):
-    return tiling(default if t is None else t)
+    return _tiling(default if t is None else t)
 
 
 def _workspace_bytes(fn, what, lay, batch, k, dtype, op, tX, tW, tY, tdY, tdX, forms_a, forms_b, with_dx):
     out = ctypes.c_size_t()
-    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), op, tiling(tX), tiling(tW), tiling(tY), _t_or(tdY, tY),
-              _t_or(tdX, tX), forms(forms_a), forms(forms_b), 1 if with_dx else 0, ctypes.byref(out)), what)
+    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), op, _tiling(tX), _tiling(tW), _tiling(tY), _t_or(tdY, tY),
+              _t_or(tdX, tX), _forms(forms_a), _forms(forms_b), 1 if with_dx else 0, ctypes.byref(out)), what)
     return out.value
 
 
@@ -484,15 +514,15 @@ def tt_conv_workspace_bytes(lay, batch, k, dtype, op, tX, tW, tY, tdY=None, tdX=
 
 def _forward(fn, what, lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace, stream):
     wp, wb = _ws(workspace)
-    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), tiling(tX), tiling(tW), tiling(tY), forms(form_seq), ptrs(X),
+    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), _tiling(tX), _tiling(tW), _tiling(tY), _forms(form_seq), ptrs(X),
               ptrs(W), ptrs(Y), wp, wb, _stream(stream)), what)
 
 
 def _backward(fn, what, lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad, forms_wgrad, X, W, Y, dY, dX, dW,
               workspace, stream):
     wp, wb = _ws(workspace)
-    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), tiling(tX), tiling(tW), tiling(tY), tiling(tdY),
-              _t_or(tdX, tX), forms(forms_dgrad), forms(forms_wgrad), ptrs(X), ptrs(W), ptrs(Y), ptrs(dY), ptrs(dX),
+    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), _tiling(tX), _tiling(tW), _tiling(tY), _tiling(tdY),
+              _t_or(tdX, tX), _forms(forms_dgrad), _forms(forms_wgrad), ptrs(X), ptrs(W), ptrs(Y), ptrs(dY), ptrs(dX),
               ptrs(dW), wp, wb, _stream(stream)), what)
 
 
@@ -501,8 +531,8 @@ def tt_fc_forward(lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace
 
 
 def tt_fc_forward_static(lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, stream=None):
-    _check(lib().tt_fc_forward_static(ctypes.byref(lay), batch, k, _dtype(dtype), tiling(tX), tiling(tW), tiling(tY),
-                                      forms(form_seq), ptrs(X), ptrs(W), ptrs(Y), _stream(stream)), "tt_fc_forward_static")
+    _check(lib().tt_fc_forward_static(ctypes.byref(lay), batch, k, _dtype(dtype), _tiling(tX), _tiling(tW), _tiling(tY),
+                                      _forms(form_seq), ptrs(X), ptrs(W), ptrs(Y), _stream(stream)), "tt_fc_forward_static")
 
 
 def tt_fc_backward(lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad, forms_wgrad, X, W, Y, dY, dX, dW,
@@ -515,8 +545,8 @@ def tt_fc_backward_overlapped(lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_
                               workspace=None, stream=None, aux_stream=None):
     wp, wb = _ws(workspace)
     _check(lib().tt_fc_backward_overlapped(
-        ctypes.byref(lay), batch, k, _dtype(dtype), tiling(tX), tiling(tW), tiling(tY), tiling(tdY), _t_or(tdX, tX),
-        forms(forms_dgrad), forms(forms_wgrad), ptrs(X), ptrs(W), ptrs(Y), ptrs(dY), ptrs(dX), ptrs(dW), wp, wb,
+        ctypes.byref(lay), batch, k, _dtype(dtype), _tiling(tX), _tiling(tW), _tiling(tY), _tiling(tdY), _t_or(tdX, tX),
+        _forms(forms_dgrad), _forms(forms_wgrad), ptrs(X), ptrs(W), ptrs(Y), ptrs(dY), ptrs(dX), ptrs(dW), wp, wb,
         _stream(stream), _stream(aux_stream) if aux_stream is not None else None), "tt_fc_backward_overlapped")
 
 
