@@ -314,6 +314,7 @@ __device__ __forceinline__ void run_small(const ParamsS &p, char *lds)
         constexpr bool MASK = decltype(mask)::value;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
+            if (MASK && (BF ? 16 : 8) * (s + 1) <= skip) continue; // (wave-uniform) nothing left of this step
             if constexpr (BF) {
                 bf16x8 fa[T], fb[T];
 #pragma unroll
