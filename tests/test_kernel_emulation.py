@@ -388,13 +388,18 @@ def test_convolution_steps_under_random_tilings_stay_inside_their_buffers(emu_st
 
 
 def test_assembly_loads_leave_the_wait_states_their_scalar_operands_need():
-    # A vector instruction that writes a scalar register (v_readfirstlane: the base address, M0) and a vector-memory
-    # instruction that reads it must be five wait states apart.  The compiler sees to that for its own instructions, not
-    # for loads written in assembly, so each of those has to start with s_nop 4 (five states) or more.
+    # A vector instruction that writes a scalar register (v_readfirstlane: the base address, the LDS address) and a
+    # vector-memory instruction that reads it must be five wait states apart.  The compiler sees to that for its own
+    # instructions, not for loads written in assembly, so what such a load reads (M0 and the base) has to be written by a
+    # scalar instruction of the same block: that needs no wait states, but for the one between M0 and the load.  No idle
+    # states beyond it: they would stand in front of the loads of the tile engines' main loops.
     import re
     src = open(os.path.join(ROOT, "paper_1805_04170_amd", "csrc", "tt_device.h")).read()
-    loads = re.findall(r'asm volatile\("([^"]*global_load_lds[^"]*)"', src)
-    assert len(loads) == 2
-    for text in loads:
-        m = re.match(r"s_nop (\d+)\\n\\tglobal_load_lds", text)
-        assert m and int(m.group(1)) >= 4, text
+    blocks = re.findall(r'asm volatile\("([^"]*global_load_lds[^"]*)"', src)
+    assert len(blocks) == 2
+    for text in blocks:
+        m0, second, load = text.split("\\n\\t")
+        assert re.match(r"s_mov_b32 m0, %\d+$", m0), text
+        base = re.match(r"s_mov_b64 (%\d+), %\d+$", second)      # (the wait state between M0 and the load)
+        assert base or second == "s_nop 0", text
+        assert load.startswith("global_load_lds_dwordx4 ") and load.endswith(", " + (base.group(1) if base else "off")), text
