@@ -17,12 +17,87 @@ __global__ __launch_bounds__(small::waves_of<T>() * 64, T == 1 ? 2 : 1) void gem
     small::run_small<BF, A_KC, B_KC, T, OFF>(p, lds);
 }
 
-// bf16 C = A B, both row-major as stored: the forward products.  What they store decides on which side of zero an activation
-// falls and with that the gates of the backward pass, so their sums are kept in one order whatever the split of the work:
-// fp32 fused multiply-adds, K increasing.  (With the sums in another order about one 300-wide layer in twelve, batch 100,
-// flips a gate, which moves the gradients by 1e-2.)  Bound by latency: 32 x 32 tiles, 2 x 2 results per thread, operands
-// fetched into registers four K tiles ahead.  With 64 x 64 tiles and 4 x 4
-// results 4 x (100 x 225 x 1500) took 146 us; the step of a 1500-900-300-20 chain at batch 100 went from 327 to 181 us.
+// Plain products: one 64 x 64 tile per workgroup, fp32 fused multiply-adds in the order of increasing K, any strides.  16
+// values of K per step through LDS, 4 x 4 results per thread, operands fetched into registers four steps ahead.  Bound by
+// LDS reads and the vector unit (two LDS values per four multiply-adds).
+__global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
+{
+    constexpr int T = 64, KB = 16;
+    __shared__ float As[KB][T + 1];
+    __shared__ float Bs[KB][T + 1];
+    const int tiles = p.tiles_m * p.tiles_n;
+    const int vshard = blockIdx.x / tiles, t = blockIdx.x - vshard * tiles;
+    const int m0 = (t % p.tiles_m) * T, n0 = (t / p.tiles_m) * T;
+    const int shard = vshard / p.ksplit;
+    const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
+    const int kend = kbeg + p.kchunk < p.K ? kbeg + p.kchunk : p.K;
+    const uint16_t *A = reinterpret_cast<const uint16_t *>(p.A[shard]), *B = reinterpret_cast<const uint16_t *>(p.B[shard]);
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    float acc[4][4] = {};
+    constexpr int PT = T * KB / 256, PD = 4;
+    float ra[PD][PT], rb[PD][PT];
+    // all loads of a step in flight together: clamped addresses, the out-of-range values zeroed afterwards
+    auto fetch = [&](int k0, float (&xa)[PT], float (&xb)[PT]) {
+#pragma unroll
+        for (int u = 0; u < PT; ++u) {
+            const int i = threadIdx.x + u * 256;
+            const int gka = k0 + i % KB, gm = m0 + i / KB, gkb = k0 + i / T, gn = n0 + i % T;
+            const uint32_t va = A[(int64_t)(gm < p.M ? gm : p.M - 1) * p.lda + (gka < kend ? gka : kend - 1)];
+            const uint32_t vb = B[(int64_t)(gkb < kend ? gkb : kend - 1) * p.ldb + (gn < p.N ? gn : p.N - 1)];
+            xa[u] = gm < p.M && gka < kend ? __uint_as_float(va << 16) : 0.0f;
+            xb[u] = gn < p.N && gkb < kend ? __uint_as_float(vb << 16) : 0.0f;
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < PD; ++d)
+        if (kbeg + d * KB < kend) fetch(kbeg + d * KB, ra[d], rb[d]);
+    for (int k0 = kbeg; k0 < kend; k0 += PD * KB) {
+#pragma unroll
+        for (int d = 0; d < PD; ++d) { // (unrolled: the register ring is indexed by constants)
+            const int kd = k0 + d * KB;
+            if (kd >= kend) break;
+#pragma unroll
+            for (int u = 0; u < PT; ++u) {
+                const int i = threadIdx.x + u * 256;
+                As[i % KB][i / KB] = ra[d][u];
+                Bs[i / T][i % T] = rb[d][u];
+            }
+            __syncthreads();
+            if (kd + PD * KB < kend) fetch(kd + PD * KB, ra[d], rb[d]);
+#pragma unroll
+            for (int kk = 0; kk < KB; ++kk) {
+                float a[4], b[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+            }
+            __syncthreads();
+        }
+    }
+    void *const C = p.C[vshard];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
+            if (row >= p.M || col >= p.N) continue;
+            float v = acc[i][j];
+            if (p.relu) v = v > 0.0f ? v : 0.0f;
+            if (p.out_bf16) reinterpret_cast<uint16_t *>(C)[(size_t)row * p.ldc + col] = (uint16_t)core::f32_to_bf16_bits(v);
+            else reinterpret_cast<float *>(C)[(size_t)row * p.ldc + col] = v;
+        }
+}
+
+// bf16 C = A B, both row-major as stored (the forward layout): the same multiply-adds in the same order, hence the same
+// bits, on 32 x 32 tiles.  Bound by latency: 2 x 2 results per thread, operands fetched into registers four K tiles ahead.
+// With 64 x 64 tiles 4 x (100 x 225 x 1500) took 138 us, so 53; the step of a 1500-900-300-20 chain at batch 100 went from
+// 327 to 181 us.  Why K increases here and the MFMA kernel does not take this layout: one shard product then stores the
+// same activations on every size, tile and split of the waves, and with them the ReLU gates of the backward pass.  (F3 cuts
+// and ksplit still add their partial sums per shard, and aligned sizes add in MFMA order.)  An activation next to zero that
+// falls on the other side moves that row's gradients: on one of 12 drawn inputs by 1.2e-2 of such a chain's gradients.
 constexpr int kOrdTile = 32, kOrdK = 16;
 template <bool OUT_BF16>
 __global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS p)
@@ -91,14 +166,24 @@ __global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS 
         }
 }
 
-tt_status launch_ordered(small::ParamsS &p, int count, hipStream_t s)
+// The forward layout of bf16.  64 x 64 tiles once there are about three for every two CUs, while neither side is a strip
+// that would leave half of them empty: the larger tile reads half as much LDS per multiply-add and half the operands.
+// 32 x 32 / 64 x 64 tiles, us, at K = 33 and 1023: 1023 x 1279 (320 tiles of 64 x 64) 6.9 / 8.4 and 91 / 100, 1023 x 1535 (384)
+// 7.4 / 8.4 and 107 / 101, 1023 x 1663 (416) 8.2 / 8.4 and 123 / 102, 33 x 25001 (391) 8.5 / 8.3 and 129 / 110, 1023 x 2047 (512)
+// 9.1 / 8.5 and 139 / 108; 4095 x 4093 (4096) at K = 2047 2027 / 1307.  Strips: 31 x 100001 at K = 1023 223 / 314.
+tt_status launch_forward(small::ParamsS &p, int count, hipStream_t s)
 {
-    p.tiles_m = (int32_t)(((int64_t)p.M + kOrdTile - 1) / kOrdTile);
-    p.tiles_n = (int32_t)(((int64_t)p.N + kOrdTile - 1) / kOrdTile);
-    const int64_t total = (int64_t)p.tiles_m * p.tiles_n * count * p.ksplit;
-    if (total >= (int64_t(1) << 31)) return TT_EUNSUPPORTED;
+    const int64_t outs = (int64_t)count * p.ksplit;
+    const auto tiles = [&](int64_t T) { return ((p.M + T - 1) / T) * ((p.N + T - 1) / T) * outs; };
+    const int64_t most = (int64_t(1) << 24) - 1; // workgroups of 256 threads in a launch of fewer than 2^32 threads
+    const bool large = (p.M > 32 && p.N > 32 && tiles(64) >= tuning_int("TT_FWD_T64", 400)) || tiles(kOrdTile) > most;
+    const int64_t T = large ? 64 : kOrdTile, total = tiles(T);
+    if (total > most) return TT_EUNSUPPORTED;
+    p.tiles_m = (int32_t)((p.M + T - 1) / T);
+    p.tiles_n = (int32_t)((p.N + T - 1) / T);
     const dim3 grid((uint32_t)total), block(256);
-    if (p.out_bf16) hipLaunchKernelGGL(gemm_ordered_kernel<true>, grid, block, 0, s, p);
+    if (large) hipLaunchKernelGGL(gemm_plain_kernel, grid, block, 0, s, p);
+    else if (p.out_bf16) hipLaunchKernelGGL(gemm_ordered_kernel<true>, grid, block, 0, s, p);
     else hipLaunchKernelGGL(gemm_ordered_kernel<false>, grid, block, 0, s, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
@@ -170,7 +255,7 @@ tt_status launch_gemm_small(int count, const void *const *A, const void *const *
     g.relu = relu;
     g.out_bf16 = out_dtype == TT_BF16;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (in_dtype == TT_BF16 && a_kc && !b_kc) return launch_ordered(g, count, s);
+    if (in_dtype == TT_BF16 && a_kc && !b_kc) return launch_forward(g, count, s);
     return in_dtype == TT_BF16 ? launch_small<true>(g, count, a_kc, b_kc, s) : launch_small<false>(g, count, a_kc, b_kc, s);
 }
 

@@ -94,6 +94,11 @@ def test_odd_sized_products(ta, tb, dt):
         check(n, M, N, K, ta, tb, dt, dt if i % 2 else "f32", bool(i & 1), 60 + i)
 
 
+def test_odd_sized_forward_products_of_many_tiles():
+    check(8, 511, 513, 83, 0, 0, "bf16", "bf16", True, 67)         # 64 x 64 tiles, two per CU
+    check(1, 2047, 1025, 17, 0, 0, "bf16", "f32", False, 68)
+
+
 def test_fp32_keeps_subnormal_products_and_sums():
     # results below the smallest normal fp32 number (1.2e-38): K = 64 products of 2^-70 x 2^-65
     a = torch.full((40, 64), 2.0 ** -70, dtype=torch.float32, device=DEV)

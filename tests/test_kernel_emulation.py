@@ -253,6 +253,10 @@ SHARD_CASES = [
     ((4, 256, 128, 1024, 0, 0, 1, 1, 0, 1), 8 * 256),       # one narrow column of tiles: register-staged 256 x 128
     ((3, 64, 64, 72, 0, 0, 1, 0, 1, 1), 8 * 256),           # small product, K not a multiple of the tile depth: 128 x 128 with K mask
     ((3, 50, 70, 33, 0, 1, 0, 0, 0, 1), 6 * 256),           # fp32 operands: the scalar kernel, 64 x 64 tiles
+    ((8, 511, 513, 17, 0, 0, 1, 1, 0, 1), 576 * 256),       # bf16 forward rows of odd length, two 64 x 64 tiles per CU: those
+    ((8, 33, 4097, 17, 0, 0, 1, 1, 0, 1), 520 * 256),       # ... 33 rows: still those
+    ((8, 32, 4097, 17, 0, 0, 1, 1, 0, 1), 1032 * 256),      # ... 32 rows, a strip: 32 x 32 tiles
+    ((4, 100, 225, 33, 0, 0, 1, 1, 0, 1), 128 * 256),       # ... and launches that leave CUs idle: 32 x 32 tiles
     ((2, 296, 264, 200, 1, 0, 1, 1, 0, 1), None),           # ragged tiles on every side
     ((8, 256, 512, 72, 0, 0, 1, 1, 0, 1), None),            # K the 256 x 128 engine refuses: falls through to the register-staged one
     ((4, 256, 512, 3136, 0, 0, 1, 0, 0, 4), 64 * 256),      # reduction split four ways inside one launch, sixteen partial products

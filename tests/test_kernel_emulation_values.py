@@ -206,6 +206,17 @@ def test_small_kernel_waves_and_blocks_values(lockstep_gemm, tmp_path, dt, ta, t
     check(lockstep_gemm, str(tmp_path), 2, 35, 37, 323, ta, tb, dt, "f32", False, 99, ksplit=3)
 
 
+@pytest.mark.parametrize("out_dt,relu", [("bf16", True), ("f32", False)])
+def test_forward_tiles_of_both_sizes_store_the_same_bits(lockstep_gemm, tmp_path, out_dt, relu):
+    # both add in the order of increasing K: ragged tiles, K below, at and past a step of 16 and a round of four steps
+    for i, (M, N, K) in enumerate([(65, 130, 65), (64, 64, 16), (33, 1, 1), (37, 67, 129), (63, 127, 50)]):
+        stored = []
+        for t64 in ("1000", "1"):
+            check(lockstep_gemm, str(tmp_path), 1, M, N, K, 0, 0, "bf16", out_dt, relu, 120 + i, env={"TT_FWD_T64": t64})
+            stored.append(open(os.path.join(str(tmp_path), "c0.bin"), "rb").read())
+        assert stored[0] == stored[1], (M, N, K)
+
+
 def test_random_products_values(lockstep_gemm, tmp_path):
     # seeded random shapes, layouts, types and tuning switches (sizes mostly multiples of eight, some odd): whatever
     # engine the launch code picks or falls back to has to give the product

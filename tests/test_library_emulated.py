@@ -70,6 +70,15 @@ def test_fc_layer_named_tilings(on_host, golden_loader, dt):
         on_host["fc"].run_layer(32, 64, 48, k, dt, True, tA, tW, tA, tG, tG, None, None, None, 50 + k)
 
 
+def test_products_of_more_workgroups_than_a_launch_holds_are_refused(on_host):
+    # a launch holds fewer than 2^32 threads; nothing may be launched here, so the addresses are never read
+    p = [1 << 20]
+    for M, N in [(300001, 300001), (2 ** 31 - 1, 1)]:
+        with pytest.raises(binding.TilingError) as e:
+            binding.tt_shard_gemm(p, p, p, M, N, 1, 0, 0, "bf16", "bf16")
+        assert binding.STATUS_NAMES[e.value.status] == "TT_EUNSUPPORTED"
+
+
 # ---- the GPU parity tests themselves, run on the host where their sizes allow
 
 @pytest.mark.parametrize("relu", [False, True])
