@@ -2,6 +2,7 @@
 // One launch covers all shards (Sec. 5.2 step 2 of arXiv 1805.04170).
 #include "tt_device.h"
 #include <cstdint>
+#include <type_traits>
 #include "gemm_small.h"
 #include "tt_internal.h"
 
@@ -17,11 +18,12 @@ __global__ __launch_bounds__(small::waves_of<T>() * 64, T == 1 ? 2 : 1) void gem
     small::run_small<BF, A_KC, B_KC, T, OFF>(p, lds);
 }
 
-// Plain products: one 64 x 64 tile per workgroup, fp32 fused multiply-adds in the order of increasing K, any strides.  16
+// Plain products: one 64 x 64 tile per workgroup, fp32 fused multiply-adds in the order of increasing K, any layout.  16
 // values of K per step through LDS, 4 x 4 results per thread, operands fetched into registers four steps ahead.  Bound by
 // LDS reads and the vector unit (two LDS values per four multiply-adds).
-__global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
+template <bool BF, bool A_KC, bool B_KC, bool OUT_BF16> __global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
 {
+    using E = std::conditional_t<BF, uint16_t, uint32_t>; // an element's bits
     constexpr int T = 64, KB = 16;
     __shared__ float As[KB][T + 1];
     __shared__ float Bs[KB][T + 1];
@@ -31,7 +33,7 @@ __global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
     const int shard = vshard / p.ksplit;
     const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
     const int kend = kbeg + p.kchunk < p.K ? kbeg + p.kchunk : p.K;
-    const uint16_t *A = reinterpret_cast<const uint16_t *>(p.A[shard]), *B = reinterpret_cast<const uint16_t *>(p.B[shard]);
+    const E *A = reinterpret_cast<const E *>(p.A[shard]), *B = reinterpret_cast<const E *>(p.B[shard]);
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     float acc[4][4] = {};
     constexpr int PT = T * KB / 256, PD = 4;
@@ -41,11 +43,13 @@ __global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
 #pragma unroll
         for (int u = 0; u < PT; ++u) {
             const int i = threadIdx.x + u * 256;
-            const int gka = k0 + i % KB, gm = m0 + i / KB, gkb = k0 + i / T, gn = n0 + i % T;
-            const uint32_t va = A[(int64_t)(gm < p.M ? gm : p.M - 1) * p.lda + (gka < kend ? gka : kend - 1)];
-            const uint32_t vb = B[(int64_t)(gkb < kend ? gkb : kend - 1) * p.ldb + (gn < p.N ? gn : p.N - 1)];
-            xa[u] = gm < p.M && gka < kend ? __uint_as_float(va << 16) : 0.0f;
-            xb[u] = gn < p.N && gkb < kend ? __uint_as_float(vb << 16) : 0.0f;
+            const int gm = m0 + (A_KC ? i / KB : i % T), gka = k0 + (A_KC ? i % KB : i / T);
+            const int gn = n0 + (B_KC ? i / KB : i % T), gkb = k0 + (B_KC ? i % KB : i / T);
+            const int64_t am = gm < p.M ? gm : p.M - 1, ak = gka < kend ? gka : kend - 1;
+            const int64_t bn = gn < p.N ? gn : p.N - 1, bk = gkb < kend ? gkb : kend - 1;
+            const uint32_t va = A[A_KC ? am * p.lda + ak : ak * p.lda + am], vb = B[B_KC ? bn * p.ldb + bk : bk * p.ldb + bn];
+            xa[u] = gm < p.M && gka < kend ? __uint_as_float(BF ? va << 16 : va) : 0.0f;
+            xb[u] = gn < p.N && gkb < kend ? __uint_as_float(BF ? vb << 16 : vb) : 0.0f;
         }
     };
 #pragma unroll
@@ -59,8 +63,8 @@ __global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
 #pragma unroll
             for (int u = 0; u < PT; ++u) {
                 const int i = threadIdx.x + u * 256;
-                As[i % KB][i / KB] = ra[d][u];
-                Bs[i / T][i % T] = rb[d][u];
+                As[A_KC ? i % KB : i / T][A_KC ? i / KB : i % T] = ra[d][u];
+                Bs[B_KC ? i % KB : i / T][B_KC ? i / KB : i % T] = rb[d][u];
             }
             __syncthreads();
             if (kd + PD * KB < kend) fetch(kd + PD * KB, ra[d], rb[d]);
@@ -86,7 +90,7 @@ __global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
             if (row >= p.M || col >= p.N) continue;
             float v = acc[i][j];
             if (p.relu) v = v > 0.0f ? v : 0.0f;
-            if (p.out_bf16) reinterpret_cast<uint16_t *>(C)[(size_t)row * p.ldc + col] = (uint16_t)core::f32_to_bf16_bits(v);
+            if (OUT_BF16) reinterpret_cast<uint16_t *>(C)[(size_t)row * p.ldc + col] = (uint16_t)core::f32_to_bf16_bits(v);
             else reinterpret_cast<float *>(C)[(size_t)row * p.ldc + col] = v;
         }
 }
@@ -166,6 +170,29 @@ __global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS 
         }
 }
 
+constexpr int64_t kMostGroups = (int64_t(1) << 24) - 1; // workgroups of 256 threads in a launch of fewer than 2^32 threads
+
+int64_t tiles_of(const small::ParamsS &p, int count, int64_t T) { return ((p.M + T - 1) / T) * ((p.N + T - 1) / T) * count * p.ksplit; }
+
+template <bool BF, bool A_KC, bool B_KC> tt_status launch_plain_layout(small::ParamsS &p, int count, hipStream_t s)
+{
+    const int64_t total = tiles_of(p, count, 64);
+    if (total > kMostGroups) return TT_EUNSUPPORTED;
+    p.tiles_m = (int32_t)(((int64_t)p.M + 63) / 64);
+    p.tiles_n = (int32_t)(((int64_t)p.N + 63) / 64);
+    const dim3 grid((uint32_t)total), block(256);
+    if (p.out_bf16) hipLaunchKernelGGL((gemm_plain_kernel<BF, A_KC, B_KC, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((gemm_plain_kernel<BF, A_KC, B_KC, false>), grid, block, 0, s, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+
+template <bool BF> tt_status launch_plain(small::ParamsS &p, int count, bool a_kc, bool b_kc, hipStream_t s)
+{
+    if (a_kc && b_kc) return launch_plain_layout<BF, true, true>(p, count, s);
+    if (a_kc) return launch_plain_layout<BF, true, false>(p, count, s);
+    return b_kc ? launch_plain_layout<BF, false, true>(p, count, s) : launch_plain_layout<BF, false, false>(p, count, s);
+}
+
 // The forward layout of bf16.  64 x 64 tiles once there are about three for every two CUs, while neither side is a strip
 // that would leave half of them empty: the larger tile reads half as much LDS per multiply-add and half the operands.
 // 32 x 32 / 64 x 64 tiles, us, at K = 33 and 1023: 1023 x 1279 (320 tiles of 64 x 64) 6.9 / 8.4 and 91 / 100, 1023 x 1535 (384)
@@ -173,19 +200,43 @@ __global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS 
 // 9.1 / 8.5 and 139 / 108; 4095 x 4093 (4096) at K = 2047 2027 / 1307.  Strips: 31 x 100001 at K = 1023 223 / 314.
 tt_status launch_forward(small::ParamsS &p, int count, hipStream_t s)
 {
-    const int64_t outs = (int64_t)count * p.ksplit;
-    const auto tiles = [&](int64_t T) { return ((p.M + T - 1) / T) * ((p.N + T - 1) / T) * outs; };
-    const int64_t most = (int64_t(1) << 24) - 1; // workgroups of 256 threads in a launch of fewer than 2^32 threads
-    const bool large = (p.M > 32 && p.N > 32 && tiles(64) >= tuning_int("TT_FWD_T64", 400)) || tiles(kOrdTile) > most;
-    const int64_t T = large ? 64 : kOrdTile, total = tiles(T);
-    if (total > most) return TT_EUNSUPPORTED;
-    p.tiles_m = (int32_t)((p.M + T - 1) / T);
-    p.tiles_n = (int32_t)((p.N + T - 1) / T);
+    const int64_t total = tiles_of(p, count, kOrdTile);
+    if ((p.M > 32 && p.N > 32 && tiles_of(p, count, 64) >= tuning_int("TT_FWD_T64", 400)) || total > kMostGroups)
+        return launch_plain<true>(p, count, true, false, s);
+    p.tiles_m = (int32_t)(((int64_t)p.M + kOrdTile - 1) / kOrdTile);
+    p.tiles_n = (int32_t)(((int64_t)p.N + kOrdTile - 1) / kOrdTile);
     const dim3 grid((uint32_t)total), block(256);
-    if (large) hipLaunchKernelGGL(gemm_plain_kernel, grid, block, 0, s, p);
-    else if (p.out_bf16) hipLaunchKernelGGL(gemm_ordered_kernel<true>, grid, block, 0, s, p);
+    if (p.out_bf16) hipLaunchKernelGGL(gemm_ordered_kernel<true>, grid, block, 0, s, p);
     else hipLaunchKernelGGL(gemm_ordered_kernel<false>, grid, block, 0, s, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+
+// Short K: whether the plain kernel is the faster one.  gemm_small_kernel's waves take K in chunks (64 values, fp32 32), of
+// which a short K gives them one or two, and its write-out goes through LDS once more; the longer K is, the more the matrix
+// instructions win, the sooner the more often every CU gets a tile (tiles: of 64 x 64).  Between 128 and 192 values of K (fp32
+// between 64 and 96) the chunks are not yet cut over two waves.  Plain / small kernel, us:
+//   bf16 A B^T  1023 x 1535 (384 tiles)  K 15 5.5 / 14.5, 95 12.9 / 20.1, 175 20.3 / 22.0, 223 24.7 / 17.1;  767 x 769 (156)  47 7.1 / 9.0,
+//     63 8.2 / 8.1;  257 x 255 (20)  15 4.6 / 5.9, 47 6.8 / 6.3;  8 x (511 x 513) (576)  191 28.6 / 41.6, 223 32.6 / 30.8;
+//     2047 x 4095 (2048)  63 26.4 / 37.2, 95 36.7 / 42.1, 127 47.0 / 42.6;  strips 31 x 100001 (1563)  47 19.1 / 25.3, 63 23.2 / 22.4
+//   fp32 A B  1023 x 1535  15 6.4 / 13.2, 95 13.1 / 19.9, 111 14.7 / 13.7;  767 x 769  95 10.6 / 11.7, 127 12.9 / 12.7;  257 x 255  15 4.2 / 4.9,
+//     31 5.4 / 4.9, 47 6.7 / 7.5, 111 11.4 / 6.9;  8 x (511 x 513)  159 25.6 / 30.4, 191 30.1 / 30.5;  2047 x 4095  111 44.9 / 47.4,
+//     143 54.6 / 52.6;  strips 31 x 100001  63 25.3 / 33.2, 111 38.8 / 40.1
+bool plain_is_faster(bool bf, bool a_kc, bool b_kc, int64_t M, int64_t N, int64_t K, int64_t tiles)
+{
+    const int forced = tuning_int("TT_PLAIN_K", -1);
+    if (forced >= 0) return K <= forced;
+    const bool nt = a_kc && b_kc;
+    if (M <= 32 || N <= 32) { // a strip: half of each 64 x 64 tile is empty, while the other kernel's blocks are 32 x 32
+        if (!bf) return K <= (tiles < 512 ? 16 : tiles < 1024 ? 64 : a_kc || b_kc ? 96 : 144);
+        return K <= (tiles < 256 ? 16 : nt || tiles >= 1024 ? 48 : tiles < 512 ? 16 : 32);
+    }
+    if (tiles < 128) return bf ? K <= 32 : K <= 16 || (K > 32 && K <= 48 && !nt); // (fp32 up to 32: a single chunk)
+    if (tiles < 256) return K <= (bf ? 48 : 96);
+    if (M <= 64 || N <= 64) return K <= 192; // half of the other kernel's waves have no rows or columns of their own
+    if (tiles < 512) return K <= (bf ? 176 : 96);
+    if (tiles < 1024) return K <= (bf ? 192 : 160);
+    if (tiles < 2048) return K <= 144;
+    return K <= (bf ? 96 : 128);
 }
 
 template <bool BF, int T, class OFF> tt_status launch_small_layout(const small::ParamsS &p, bool a_kc, bool b_kc, hipStream_t s)
@@ -255,8 +306,11 @@ tt_status launch_gemm_small(int count, const void *const *A, const void *const *
     g.relu = relu;
     g.out_bf16 = out_dtype == TT_BF16;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (in_dtype == TT_BF16 && a_kc && !b_kc) return launch_forward(g, count, s);
-    return in_dtype == TT_BF16 ? launch_small<true>(g, count, a_kc, b_kc, s) : launch_small<false>(g, count, a_kc, b_kc, s);
+    const bool bf = in_dtype == TT_BF16;
+    if (bf && a_kc && !b_kc) return launch_forward(g, count, s);
+    if (plain_is_faster(bf, a_kc, b_kc, M, N, ksplit > 1 ? kchunk : K, tiles_of(g, count, 64)))
+        return bf ? launch_plain<true>(g, count, a_kc, b_kc, s) : launch_plain<false>(g, count, a_kc, b_kc, s);
+    return bf ? launch_small<true>(g, count, a_kc, b_kc, s) : launch_small<false>(g, count, a_kc, b_kc, s);
 }
 
 } // namespace tt

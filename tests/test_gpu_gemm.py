@@ -94,6 +94,14 @@ def test_odd_sized_products(ta, tb, dt):
         check(n, M, N, K, ta, tb, dt, dt if i % 2 else "f32", bool(i & 1), 60 + i)
 
 
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_short_odd_sized_products(ta, tb, dt):
+    # both kernels on either side of the lines: few tiles (K = 16 and 17), a strip, tiles for every CU
+    for i, (n, M, N, K) in enumerate([(2, 65, 35, 16), (2, 65, 35, 17), (1, 33, 131, 33), (1, 5, 33001, 15), (64, 65, 67, 9), (64, 65, 67, 97), (5, 511, 513, 31)]):
+        check(n, M, N, K, ta, tb, dt, dt if i % 2 else "f32", bool(i & 1), 80 + i)
+
+
 def test_odd_sized_forward_products_of_many_tiles():
     check(8, 511, 513, 83, 0, 0, "bf16", "bf16", True, 67)         # 64 x 64 tiles, two per CU
     check(1, 2047, 1025, 17, 0, 0, "bf16", "f32", False, 68)

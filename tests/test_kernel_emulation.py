@@ -257,6 +257,10 @@ SHARD_CASES = [
     ((8, 33, 4097, 17, 0, 0, 1, 1, 0, 1), 520 * 256),       # ... 33 rows: still those
     ((8, 32, 4097, 17, 0, 0, 1, 1, 0, 1), 1032 * 256),      # ... 32 rows, a strip: 32 x 32 tiles
     ((4, 100, 225, 33, 0, 0, 1, 1, 0, 1), 128 * 256),       # ... and launches that leave CUs idle: 32 x 32 tiles
+    ((64, 65, 67, 9, 0, 1, 1, 1, 0, 1), 256 * 256),         # short K, odd rows: the plain kernel, 64 x 64 tiles, bf16 ...
+    ((64, 65, 67, 9, 1, 0, 0, 0, 1, 1), 256 * 256),         # ... and fp32
+    ((64, 65, 67, 193, 1, 0, 1, 1, 0, 1), 128 * 256),       # longer K: 64 x 64 blocks, K over two of four waves
+    ((4, 33, 129, 47, 0, 1, 0, 0, 0, 1), 24 * 128),         # few tiles, fp32: 32 x 32 blocks, two waves side by side
     ((2, 296, 264, 200, 1, 0, 1, 1, 0, 1), None),           # ragged tiles on every side
     ((8, 256, 512, 72, 0, 0, 1, 1, 0, 1), None),            # K the 256 x 128 engine refuses: falls through to the register-staged one
     ((4, 256, 512, 3136, 0, 0, 1, 0, 0, 4), 64 * 256),      # reduction split four ways inside one launch, sixteen partial products
@@ -282,6 +286,17 @@ def test_small_kernel_stays_inside_its_buffers(emu_shard_gemm, layout, bf, monke
         for M, N, K in [(1, 1, 1), (65, 129, 97), (129, 65, 9), (97, 193, 515), (63, 35, 1051), (34, 66, 64)]:
             r = run(emu_shard_gemm, (2, M, N, K) + layout + (bf, bf, 1, 1))
             assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (t2, M, N, K, r.stdout[-400:] + r.stderr[-1500:])
+
+
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("bf", [0, 1])
+@pytest.mark.parametrize("plain_k", ["0", "100000"])
+def test_short_products_stay_inside_their_buffers_on_either_kernel(emu_shard_gemm, layout, bf, plain_k, monkeypatch):
+    # K below, at and past a step of the plain kernel (16) and a chunk of the small one, ragged and single tiles
+    monkeypatch.setenv("TT_PLAIN_K", plain_k)
+    for M, N, K in [(1, 1, 1), (65, 131, 17), (129, 63, 31), (33, 65, 65), (67, 35, 16)]:
+        r = run(emu_shard_gemm, (2, M, N, K) + layout + (bf, bf, 1, 1))
+        assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (M, N, K, r.stdout[-400:] + r.stderr[-1500:])
 
 
 def test_shard_product_entry_point_rejects_what_the_library_rejects(emu_shard_gemm):

@@ -206,6 +206,16 @@ def test_small_kernel_waves_and_blocks_values(lockstep_gemm, tmp_path, dt, ta, t
     check(lockstep_gemm, str(tmp_path), 2, 35, 37, 323, ta, tb, dt, "f32", False, 99, ksplit=3)
 
 
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("plain_k", ["0", "100000"])
+def test_short_products_on_either_kernel_values(lockstep_gemm, tmp_path, dt, ta, tb, plain_k):
+    # K below, at and past a step of the plain kernel (16) and a chunk of the small one; a round of four steps and more
+    for i, (M, N, K) in enumerate([(65, 37, 17), (33, 67, 31), (1, 1, 1), (63, 129, 65), (35, 33, 16)]):
+        check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, dt, dt, bool(i & 1), 130 + i, env={"TT_PLAIN_K": plain_k})
+    check(lockstep_gemm, str(tmp_path), 2, 35, 37, 323, ta, tb, dt, "f32", False, 139, ksplit=3, env={"TT_PLAIN_K": plain_k})
+
+
 @pytest.mark.parametrize("out_dt,relu", [("bf16", True), ("f32", False)])
 def test_forward_tiles_of_both_sizes_store_the_same_bits(lockstep_gemm, tmp_path, out_dt, relu):
     # both add in the order of increasing K: ragged tiles, K below, at and past a step of 16 and a round of four steps
