@@ -256,7 +256,7 @@ template <bool BF> tt_status launch_small(small::ParamsS &p, int count, bool a_k
     // 64 x 64 blocks halve what a product reads through L2; they pay once they give every CU a workgroup (bf16, NN: 128 of
     // them, 256 x 2047 x 2047, 26 us against 21.5 with 32 x 32 blocks; 256, 1001 x 1003 x 1007, 18 against 21.6; fp32 32 against 43)
     const bool big_pitch = p.lda >= (1 << 24) || p.ldb >= (1 << 24); // a lane's offset inside a block must fit 32 bits
-    const int64_t blocks64 = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64) * outs;
+    const int64_t blocks64 = tiles_of(p, count, 64);
     const int T = !big_pitch && p.M > 32 && p.N > 32 && blocks64 >= tuning_int("TT_SMALL_T2", 256) ? 2 : 1;
     // Waves along K: as many as leave each of them two chunks (both on their way at once: a wave alone would not be done
     // sooner with one), while the output blocks alone do not give every CU eight waves.  Four waves at least: what K does
@@ -264,19 +264,19 @@ template <bool BF> tt_status launch_small(small::ParamsS &p, int count, bool a_k
     const int S = 32 * T, KU = small::chunk_k<BF>(), W = T == 1 ? small::waves_of<1>() : small::waves_of<2>();
     const int64_t chunks = ((int64_t)(p.ksplit > 1 ? p.kchunk : p.K) + KU - 1) / KU;
     p.wk = 1;
-    const int64_t blocks = T == 2 ? blocks64 : (int64_t)((p.M + 31) / 32) * ((p.N + 31) / 32) * outs;
+    const int64_t blocks = T == 2 ? blocks64 : tiles_of(p, count, 32);
     while (p.wk < W && 4 * p.wk <= chunks && blocks * p.wk < 2048) p.wk *= 2;
     p.wn = p.wk <= 2 ? 2 : 1;
     p.wm = p.wk == 1 ? 2 : 1;
     // (fewer side by side where that leaves CUs without a workgroup: the fp32 step of tiny_mlp 98.8 -> 92.6 us)
-    if ((int64_t)((p.M + p.wm * S - 1) / (p.wm * S)) * (((int64_t)p.N + p.wn * S - 1) / (p.wn * S)) * outs < 256) {
+    if ((((int64_t)p.M + p.wm * S - 1) / (p.wm * S)) * (((int64_t)p.N + p.wn * S - 1) / (p.wn * S)) * outs < 256) {
         p.wm = 1;
         p.wn = T == 1 && p.wk == 1 ? 2 : 1;
     }
     p.tiles_m = (int32_t)(((int64_t)p.M + p.wm * S - 1) / (p.wm * S));
     p.tiles_n = (int32_t)(((int64_t)p.N + p.wn * S - 1) / (p.wn * S));
     const int64_t total = (int64_t)p.tiles_m * p.tiles_n * outs;
-    if (total >= (int64_t(1) << 30)) return TT_EUNSUPPORTED;
+    if (total > kMostGroups - kXcds) return TT_EUNSUPPORTED; // (launches of more than 2048 blocks have four waves or fewer)
     p.total = (int32_t)total;
     p.per_xcd = total < 8 * kXcds ? 0 : (int32_t)((total + kXcds - 1) / kXcds); // (a handful of workgroups: any order will do)
     if (big_pitch) return launch_small_layout<BF, 1, uint64_t>(p, a_kc, b_kc, s);

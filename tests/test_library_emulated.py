@@ -73,9 +73,10 @@ def test_fc_layer_named_tilings(on_host, golden_loader, dt):
 def test_products_of_more_workgroups_than_a_launch_holds_are_refused(on_host):
     # a launch holds fewer than 2^32 threads; nothing may be launched here, so the addresses are never read
     p = [1 << 20]
-    for M, N in [(300001, 300001), (2 ** 31 - 1, 1)]:
+    for M, N, K, tb, dt in [(300001, 300001, 1, 0, "bf16"), (2 ** 31 - 1, 1, 1, 0, "bf16"), (2 ** 31 - 1, 1, 1001, 1, "bf16"),
+                            (1, 2 ** 31 - 1, 1001, 0, "f32"), (2 ** 31 - 1, 33, 9, 1, "f32")]:
         with pytest.raises(binding.TilingError) as e:
-            binding.tt_shard_gemm(p, p, p, M, N, 1, 0, 0, "bf16", "bf16")
+            binding.tt_shard_gemm(p, p, p, M, N, K, 0, tb, dt, dt)
         assert binding.STATUS_NAMES[e.value.status] == "TT_EUNSUPPORTED"
 
 
