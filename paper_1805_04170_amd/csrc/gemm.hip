@@ -2,7 +2,7 @@
 // after input conversion every device runs the same sub-operator on its own tiles).
 //
 // bf16 path: the MFMA tile engine of gemm_core.h with dense-matrix loaders (NN, NT, TN, TT all share one main loop).
-// fp32 path / shapes without 16-byte rows: MFMAs on fragments loaded straight into registers (gemm_small.hip).
+// fp32, rows without 16-byte vectors or off 16-byte boundaries, operands of 2^31 elements and more: gemm_small.hip.
 #include "tt_device.h"
 #include <cstdint>
 #include <cstdlib>
@@ -15,9 +15,7 @@
 namespace tt {
 namespace {
 
-using core::kThreads;
 using core::kXcds;
-using core::f32_to_bf16_bits;
 
 struct GemmParams {
     const void *A[kMaxShards];

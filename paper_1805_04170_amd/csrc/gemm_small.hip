@@ -1,4 +1,7 @@
-// Shard products that the MFMA tile engines do not take: fp32, or bf16 rows without 16-byte vectors (gemm_small.h).
+// Shard products that the MFMA tile engines do not take: fp32, and bf16 whose rows are not whole 16-byte vectors, whose
+// addresses are not multiples of 16 bytes, or of which one operand has 2^31 elements or more.  gemm_small_kernel
+// (gemm_small.h): matrix instructions.  gemm_plain_kernel, gemm_ordered_kernel: fused multiply-adds in the order of
+// increasing K; short K, and the forward layout of bf16.
 // One launch covers all shards (Sec. 5.2 step 2 of arXiv 1805.04170).
 #include "tt_device.h"
 #include <cstdint>
@@ -243,7 +246,10 @@ template <bool BF, int T, class OFF> tt_status launch_small_layout(const small::
 {
     const dim3 grid(p.per_xcd > 0 ? (uint32_t)p.per_xcd * kXcds : (uint32_t)p.total), block(p.wm * p.wn * p.wk * 64);
     if (a_kc && b_kc) hipLaunchKernelGGL((gemm_small_kernel<BF, true, true, T, OFF>), grid, block, 0, s, p);
-    else if (a_kc) hipLaunchKernelGGL((gemm_small_kernel<BF, true, false, T, OFF>), grid, block, 0, s, p);
+    else if (a_kc) {
+        if constexpr (BF) return TT_EINVAL; // (launch_forward's)
+        else hipLaunchKernelGGL((gemm_small_kernel<BF, true, false, T, OFF>), grid, block, 0, s, p);
+    }
     else if (b_kc) hipLaunchKernelGGL((gemm_small_kernel<BF, false, true, T, OFF>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((gemm_small_kernel<BF, false, false, T, OFF>), grid, block, 0, s, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
@@ -253,8 +259,11 @@ template <bool BF, int T, class OFF> tt_status launch_small_layout(const small::
 template <bool BF> tt_status launch_small(small::ParamsS &p, int count, bool a_kc, bool b_kc, hipStream_t s)
 {
     const int64_t outs = (int64_t)count * p.ksplit;
-    // 64 x 64 blocks halve what a product reads through L2; they pay once they give every CU a workgroup (bf16, NN: 128 of
-    // them, 256 x 2047 x 2047, 26 us against 21.5 with 32 x 32 blocks; 256, 1001 x 1003 x 1007, 18 against 21.6; fp32 32 against 43)
+    // 64 x 64 blocks halve what a product reads through L2; they pay once they give every CU a workgroup.  32 x 32 / 64 x 64
+    // blocks, us, K = 1023: bf16 A^T B 255 x 2047 (128 blocks of 64 x 64) 14.6 / 16.5, 1001 x 1007 (256) 22.8 / 16.6, 2047 x 2047
+    // (1024) 76 / 53;  fp32 A B 24.8 / 27.5, 42.8 / 31.3, 146 / 110.  (The line is not sharp: 511 x 1535, 192 blocks, 23.8 / 16.7
+    // and 41 / 29; and bf16 A B^T, whose staged rows need no more loads with the small block, stays ahead with it up to
+    // 1024 blocks: 1001 x 1007 17.7 / 18.7, 8 x (511 x 513) 38.6 / 52.3, 2047 x 2047 55 / 59, K = 2047 99 / 94.)
     const bool big_pitch = p.lda >= (1 << 24) || p.ldb >= (1 << 24); // a lane's offset inside a block must fit 32 bits
     const int64_t blocks64 = tiles_of(p, count, 64);
     const int T = !big_pitch && p.M > 32 && p.N > 32 && blocks64 >= tuning_int("TT_SMALL_T2", 256) ? 2 : 1;
