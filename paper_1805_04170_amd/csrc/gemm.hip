@@ -132,6 +132,20 @@ int pick_tile(int64_t M, int64_t N, int64_t K, int count)
     return (M > 128 && K >= 1024) ? 0 : 1;
 }
 
+// 128 x 128 tiles: whether a second K tile on its way pays.  At most one workgroup per CU: its registers are free for it.
+// At least three K tiles: with one or two the wider prologue costs 0.2-0.5 us of 5.  Full column tiles: where the last
+// one is short, one tile ahead already runs faster (fewer lanes load) and two lose 0.5-1.5 us; with A row-contiguous only
+// where rows are cut short too, up to K of about 768.  One tile ahead / two, us: 16 x (128 x 128) NN K 64 4.7 / 4.8, 320 7.8 / 7.4, 1000
+// 19.3 / 17.5, TN 320 9.7 / 9.1, 1000 24.0 / 19.0;  4 x (200 x 264) NN 264 7.7 / 8.4, 1000 16.2 / 17.7, TN 264 8.1 / 8.5;  8 x (128 x 264) TN
+// 264 8.8 / 8.5, 1000 20.9 / 17.5;  16 x (40 x 40) TN 320 7.7 / 8.0, 1000 17.5 / 17.7.
+bool two_tiles_ahead(int64_t M, int64_t N, int64_t K, int64_t outs, bool a_kc)
+{
+    const int64_t tiles_n = (N + 127) / 128;
+    if ((M + 127) / 128 * tiles_n * outs > 256 || K <= 128) return false;
+    if (N % 128 == 0) return true;
+    return !a_kc && (M % 128 == 0 || (tiles_n * 128 - N) * 16 <= N || K >= 768);
+}
+
 template <bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_mfma_tile(GemmParams &p, int count, hipStream_t s)
 {
     const int tile = pick_tile(p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, count * p.ksplit);
@@ -149,9 +163,7 @@ template <bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status l
             if (p.M <= 32) return launch_mfma_cfg<32, 128, 1, 4, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
             if (p.M <= 64) return launch_mfma_cfg<64, 128, 1, 4, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
         }
-        // at most one workgroup per CU: its registers are free for a second K tile on its way (8 x (128 x 512 x 512)
-        // 11.9 -> 10.4 us)
-        if ((int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) * count * p.ksplit <= 256)
+        if (two_tiles_ahead(p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, count * p.ksplit, A_KC))
             return launch_mfma_cfg<128, 128, 2, 2, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     }
     return launch_mfma_cfg<128, 128, 2, 2, 1, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);

@@ -5,6 +5,7 @@
 // outside the launch's LDS (address sanitizer and explicit ranges), every output byte written.
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #define TT_HOST_EMULATION 1
@@ -44,6 +45,11 @@ int main(int argc, char **argv)
     // which writes count * ksplit partial products)
     // With a directory as one more argument (lock-step build): operands are read from a<s>.bin / b<s>.bin there and the
     // results written to c<s>.bin, for the caller to compare with the oracle's.
+    // emu_shard_gemm ahead outputs M N K trans_a: how many K tiles of 64 the 128 x 128 tile keeps on their way
+    if (argc == 7 && std::strcmp(argv[1], "ahead") == 0) {
+        std::printf("%d\n", tt::two_tiles_ahead(std::atol(argv[3]), std::atol(argv[4]), std::atol(argv[5]), std::atol(argv[2]), std::atoi(argv[6]) == 0) ? 2 : 1);
+        return 0;
+    }
     if (argc != 11 && argc != 12) { std::fprintf(stderr, "usage: emu_shard_gemm count M N K trans_a trans_b in_bf16 out_bf16 relu ksplit [dir]\n"); return 64; }
     const char *dir = argc == 12 ? argv[11] : nullptr;
     emu_register_lds(tt::smem, sizeof(tt::smem));

@@ -277,6 +277,15 @@ def test_shard_product_entry_point_stays_inside_its_buffers(emu_shard_gemm, case
         assert int(r.stdout.split()[2]) == threads, r.stdout
 
 
+# outputs, M, N, K, A transposed: K tiles on their way
+@pytest.mark.parametrize("case,ahead", [((16, 128, 128, 128, 0), 1), ((16, 128, 128, 129, 0), 2), ((16, 40, 128, 192, 1), 2), ((16, 40, 40, 512, 1), 1),
+                                        ((16, 40, 40, 768, 1), 2), ((4, 200, 264, 1000, 0), 1), ((8, 128, 264, 192, 1), 2), ((8, 16, 1000, 320, 1), 2),
+                                        ((1, 512, 1000, 520, 0), 1), ((257, 128, 128, 512, 0), 1), ((256, 128, 128, 512, 0), 2)])
+def test_the_second_k_tile_on_its_way_is_taken_where_it_pays(emu_shard_gemm, case, ahead):
+    r = run(emu_shard_gemm, ("ahead",) + case)
+    assert r.returncode == 0 and int(r.stdout) == ahead
+
+
 @pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("bf", [0, 1])
 def test_small_kernel_stays_inside_its_buffers(emu_shard_gemm, layout, bf, monkeypatch):
