@@ -10,6 +10,7 @@
 // before the first one is used, where an element lies is worked out per row and column of the tile and not per element, and
 // a tensor that gives few 64 x 64 tiles is cut into 32 x 32 ones.
 #include <cstdint>
+#include <type_traits>
 #include "tt_device.h"
 #include "tt_internal.h"
 
@@ -70,7 +71,6 @@ __global__ __launch_bounds__(kFlatThreads) void flatten_kernel(const FlattenPara
     const uint32_t c0 = cc * TILE, p0 = pc * TILE;
     const uint32_t lane = threadIdx.x % TILE, grp = threadIdx.x / TILE;
     const uint32_t clast = p.channels - 1, plast = p.pixels - 1;
-
     // elements past the end are loaded from the last channel or pixel and not stored
     T v[PER];
     if (TO_MATRIX) {
@@ -82,19 +82,29 @@ __global__ __launch_bounds__(kFlatThreads) void flatten_kernel(const FlattenPara
             const uint32_t px = p0 + grp + i * STEP;
             v[i] = src[(uint64_t)(px < plast ? px : plast) * p.S.schans];
         }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) tile[grp + i * STEP][lane] = v[i];
     } else {
-        const uint32_t px = p0 + lane < plast ? p0 + lane : plast;
+        // few channels leave passes of the workgroup without one (the same passes for all its threads): these would load for
+        // nothing, each with its own search for the shard (256 x 3 x 1024: 26.6 us with them, 18.9 without)
+        const uint32_t rows = p.channels - c0, px = p0 + lane < plast ? p0 + lane : plast;
+        const auto move = [&](auto every_pass) {
+            constexpr bool ALL = decltype(every_pass)::value;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const uint32_t c = c0 + grp + i * STEP;
-            const ChanLoc e = locate_chan<false>(p.S, p.k, p.pixels, n, c < clast ? c : clast);
-            v[i] = reinterpret_cast<const T *>(p.src[e.shard])[e.base + px];
-        }
-    }
+            for (int i = 0; i < PER; ++i) {
+                if (!ALL && (uint32_t)(i * STEP) >= rows) break;
+                const uint32_t c = c0 + grp + i * STEP;
+                const ChanLoc e = locate_chan<false>(p.S, p.k, p.pixels, n, c < clast ? c : clast);
+                v[i] = reinterpret_cast<const T *>(p.src[e.shard])[e.base + px];
+            }
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        if (TO_MATRIX) tile[grp + i * STEP][lane] = v[i];
-        else tile[lane][grp + i * STEP] = v[i];
+            for (int i = 0; i < PER; ++i) {
+                if (!ALL && (uint32_t)(i * STEP) >= rows) break;
+                tile[lane][grp + i * STEP] = v[i];
+            }
+        };
+        if (rows > (uint32_t)((PER - 1) * STEP)) move(std::true_type());
+        else move(std::false_type());
     }
     __syncthreads();
     if (TO_MATRIX) {
@@ -175,12 +185,15 @@ extern "C" tt_status tt_flatten(void *const *dst, tt_tiling B, const void *const
     for (uint32_t r = 0; r < p.nrep; ++r) p.rep_ids[r] = (uint8_t)deposit(r, gb.maskX, k);
     p.channels = (uint32_t)channels;
     p.pixels = (uint32_t)pixels;
-    // 64 x 64 tiles (whole cache lines on both sides) where they give every CU four workgroups, else 32 x 32
+    // 64 x 64 tiles (whole cache lines on both sides) where they give every CU four workgroups, else 32 x 32; those also
+    // where the pixels, or on the way to images the channels, of an image fit in one (the larger tile's passes would mostly
+    // be empty).  64 x 64 / 32 x 32 tiles, us: to matrix 2048 x 64 x 4 14.2 / 9.4, 4096 x 8 x 16 8.0 / 5.4, but 8 x 1 x 65536 11.4 / 12.9
+    // and 512 x 20 x 400 12.3 / 12.5; to images 256 x 3 x 1024 18.9 / 12.5, 512 x 20 x 400 18.2 / 15.2.
     const uint64_t tiles64 = (((uint64_t)channels + 63) / 64) * (((uint64_t)pixels + 63) / 64) * (uint64_t)batch;
     const uint64_t bytes = (uint64_t)batch * channels * pixels * elem_bytes;
     ProfileScope scope(stream, TT_K_CONVERT, n, batch * pixels, channels, elem_bytes, bytes * (1u + p.nrep), 0);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    if (tiles64 >= 1024)
+    if (tiles64 >= 1024 && pixels > 32 && (to_matrix || channels > 32))
         return elem_bytes == 2 ? launch_flatten_t<uint16_t, 64>(p, batch, to_matrix != 0, s)
                                : launch_flatten_t<uint32_t, 64>(p, batch, to_matrix != 0, s);
     return elem_bytes == 2 ? launch_flatten_t<uint16_t, 32>(p, batch, to_matrix != 0, s)

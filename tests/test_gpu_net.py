@@ -94,6 +94,12 @@ def test_flatten_large_tensors_take_the_large_tiles():
     flatten_case(512, 72, 9, 7, "Rr", "CC", np.float32, 405)      # ragged in both
 
 
+def test_flatten_few_channels_or_pixels_of_many_images():
+    flatten_case(1024, 64, 2, 2, "R", "C", np.uint16, 406)        # few pixels: 32 x 32 tiles either way
+    flatten_case(512, 3, 10, 7, "", "", np.float32, 407)          # few channels: 64 x 64 to the matrix, 32 x 32 back
+    flatten_case(1024, 40, 7, 7, "RC", "RR", np.uint16, 408)      # 64 x 64 both ways, 40 channels: the last passes without one
+
+
 def test_flatten_refusals():
     x = [torch.zeros(4096, dtype=torch.int16, device=DEV)] * 4
     with pytest.raises(tt.TilingError) as e:                       # 6 channels cannot be cut twice

@@ -80,6 +80,20 @@ def test_products_of_more_workgroups_than_a_launch_holds_are_refused(on_host):
         assert binding.STATUS_NAMES[e.value.status] == "TT_EUNSUPPORTED"
 
 
+@pytest.mark.parametrize("channels,pixels,to_matrix,groups", [(64, 4, True, 2), (64, 4, False, 2), (3, 100, True, 2), (3, 100, False, 4), (33, 33, False, 1)])
+def test_flatten_takes_small_tiles_where_large_ones_would_be_mostly_empty(on_host, emulated_library, channels, pixels, to_matrix, groups):
+    # workgroups of 256 threads per image, of as many images as give 1024 tiles of 64 x 64
+    images = 1024 // -(-pixels // 64)
+    x = torch.arange(images * channels * pixels, dtype=torch.int32)
+    y = torch.empty_like(x)
+    ran = ctypes.c_ulonglong.in_dll(ctypes.CDLL(emulated_library), "g_emu_threads_run")
+    before = ran.value
+    binding.tt_flatten([y], "", [x], "", images, channels, pixels, 4, to_matrix)
+    assert ran.value - before == images * groups * 256
+    a = x.view(images, pixels, channels) if to_matrix else x.view(images, channels, pixels)
+    assert torch.equal(y.view(images, -1), a.transpose(1, 2).reshape(images, -1))
+
+
 # ---- the GPU parity tests themselves, run on the host where their sizes allow
 
 @pytest.mark.parametrize("relu", [False, True])
