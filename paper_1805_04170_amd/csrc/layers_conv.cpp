@@ -433,11 +433,11 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         int split = 1;
         {
             const int64_t tiles = ((Ks + 255) / 256) * ((rs * Cs + 127) / 128) * n; // 256 x 128 tiles of the filter gradient
-            // Worth it while the K tiles it takes out of the longest chain (64 pixels each, 1.6 us for a lone workgroup) cost
-            // more than twice the partial sums it adds (written and read once more, 4 TB/s).  32 x 14 x 14 pixels, 8 shards of
-            // 8 x 576: two sub-products 80 us, eight 26 us.
+            // Worth it while the K tiles it takes out of the longest chain (64 pixels each, 1.1-1.5 us for a lone workgroup: 64 to 8
+            // channels 1.1, 64 to 64 1.2, 16 to 256 1.4) cost half as much again as the partial sums it adds (written and read
+            // once more, 4 TB/s).  32 x 14 x 14 pixels, 8 shards of 8 x 576: two sub-products 80 us, eight 26-28 us.
             while (tiles * split < 256 && split < 8 && Ns % (2 * split) == 0 && n * 2 * split <= kMaxShards &&
-                   (double)(Ns / (2 * split)) * (double)pq / 64.0 * 1.6 > 2.0 * (double)(n * split) * (double)blk_bytes * 2.0 / 4.0e6 &&
+                   (double)(Ns / (2 * split)) * (double)pq / 64.0 * 1.2 > 1.5 * (double)(n * split) * (double)blk_bytes * 2.0 / 4.0e6 &&
                    (Ns / (2 * split)) * pq >= 256)
                 split *= 2;
         }
