@@ -264,7 +264,8 @@ template <bool BF> tt_status launch_small(small::ParamsS &p, int count, bool a_k
     // (1024) 76 / 53;  fp32 A B 24.8 / 27.5, 42.8 / 31.3, 146 / 110.  (The line is not sharp: 511 x 1535, 192 blocks, 23.8 / 16.7
     // and 41 / 29; and bf16 A B^T, whose staged rows need no more loads with the small block, stays ahead with it up to
     // 1024 blocks: 1001 x 1007 17.7 / 18.7, 8 x (511 x 513) 38.6 / 52.3, 2047 x 2047 55 / 59, K = 2047 99 / 94.)
-    const bool big_pitch = p.lda >= (1 << 24) || p.ldb >= (1 << 24); // a lane's offset inside a block must fit 32 bits
+    const int64_t pitch32 = tuning_int("TT_SMALL_PITCH", 1 << 24); // a lane's offset inside a block must fit 32 bits
+    const bool big_pitch = p.lda >= pitch32 || p.ldb >= pitch32;
     const int64_t blocks64 = tiles_of(p, count, 64);
     const int T = !big_pitch && p.M > 32 && p.N > 32 && blocks64 >= tuning_int("TT_SMALL_T2", 256) ? 2 : 1;
     // Waves along K: as many as leave each of them two chunks (both on their way at once: a wave alone would not be done

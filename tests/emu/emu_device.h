@@ -74,6 +74,7 @@ inline hipError_t hipDeviceGetAttribute(int *value, hipDeviceAttribute_t, int)
 // body or as `extern __shared__ T name[]`, which the driver then defines with the same storage class
 #define __shared__ thread_local
 inline unsigned long long g_emu_threads_run = 0;
+inline size_t g_emu_last_lds = 0; // dynamic LDS of the latest launch
 // kernels that declare `extern __shared__ T name[]`: whoever defines the array registers it here; a launch then makes
 // everything past its dynamic size inaccessible to the address sanitizer (several arrays: one name per kernel family)
 struct EmuLds { char *base; size_t cap; };
@@ -101,6 +102,7 @@ template <class F> inline void emu_launch(F &&body, dim3 grid, dim3 block, size_
         __asan_poison_memory_region(g_emu_lds[i].base + dyn_bytes, g_emu_lds[i].cap - dyn_bytes);
     }
     emu_set_lds_limit(dyn_bytes);
+    g_emu_last_lds = dyn_bytes;
     for (unsigned by = 0; by < grid.y; ++by)
         for (unsigned b = 0; b < grid.x; ++b) {
             blockIdx = {b, by, 0};

@@ -94,6 +94,6 @@ int main(int argc, char **argv)
     for (size_t s = 0; s < C.size(); ++s)
         for (size_t i = 0; i < C[s].size(); ++i)
             if (C[s][i] != 0) { std::printf("output %zu byte %zu never written\n", s, i); return 1; }
-    std::printf("ok shard_gemm: %llu threads run, %llu bytes global -> LDS\n", g_emu_threads_run, tt::dev::g_dma_bytes);
+    std::printf("ok shard_gemm: %llu threads run, %llu bytes global -> LDS, %zu bytes of LDS\n", g_emu_threads_run, tt::dev::g_dma_bytes, g_emu_last_lds);
     return 0;
 }

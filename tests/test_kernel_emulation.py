@@ -251,8 +251,8 @@ SHARD_CASES = [
     ((16, 256, 4096, 512, 0, 1, 1, 0, 0, 1), 256 * 512),    # skinny data gradient: 256 x 256 tiles loaded straight into LDS
     ((16, 256, 2048, 512, 0, 0, 1, 0, 0, 1), 128 * 512),    # skinny NN product: the persistent engine, 128 tiles
     ((4, 256, 128, 1024, 0, 0, 1, 1, 0, 1), 8 * 256),       # one narrow column of tiles: register-staged 256 x 128
-    ((3, 64, 64, 72, 0, 0, 1, 0, 1, 1), 8 * 256),           # small product, K not a multiple of the tile depth: 128 x 128 with K mask
-    ((3, 50, 70, 33, 0, 1, 0, 0, 0, 1), 6 * 256),           # fp32 operands: the scalar kernel, 64 x 64 tiles
+    ((3, 64, 64, 72, 0, 0, 1, 0, 1, 1), 8 * 256),           # small product, K not a multiple of the tile depth: 64 x 128 with K mask
+    ((3, 50, 70, 33, 0, 1, 0, 0, 0, 1), 6 * 256),           # fp32 operands, few tiles: 32 x 32 blocks, two waves side by side (12 workgroups of 128)
     ((8, 511, 513, 17, 0, 0, 1, 1, 0, 1), 576 * 256),       # bf16 forward rows of odd length, two 64 x 64 tiles per CU: those
     ((8, 33, 4097, 17, 0, 0, 1, 1, 0, 1), 520 * 256),       # ... 33 rows: still those
     ((8, 32, 4097, 17, 0, 0, 1, 1, 0, 1), 1032 * 256),      # ... 32 rows, a strip: 32 x 32 tiles
@@ -277,6 +277,16 @@ def test_shard_product_entry_point_stays_inside_its_buffers(emu_shard_gemm, case
         assert int(r.stdout.split()[2]) == threads, r.stdout
 
 
+# two buffers of (rows + 128 columns) x 64 values of K in rows of 144 bytes
+@pytest.mark.parametrize("M,ta,rows", [(1, 0, 32), (32, 0, 32), (33, 0, 64), (64, 0, 64), (65, 0, 128), (32, 1, 128), (64, 1, 128)])
+@pytest.mark.parametrize("K", [64, 328])
+def test_few_rows_take_short_tiles(emu_shard_gemm, M, ta, rows, K):
+    # (A row-contiguous has no shorter tile than 128 rows; its rows are multiples of eight)
+    r = run(emu_shard_gemm, (2, M, 1000, K, ta, 1, 1, 1, 0, 1))
+    assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), r.stdout[-400:] + r.stderr[-1500:]
+    assert int(r.stdout.split()[2]) == 16 * 256 and int(r.stdout.split()[-4]) == 2 * (rows + 128) * 144, r.stdout
+
+
 # outputs, M, N, K, A transposed: K tiles on their way
 @pytest.mark.parametrize("case,ahead", [((16, 128, 128, 128, 0), 1), ((16, 128, 128, 129, 0), 2), ((16, 40, 128, 192, 1), 2), ((16, 40, 40, 512, 1), 1),
                                         ((16, 40, 40, 768, 1), 2), ((4, 200, 264, 1000, 0), 1), ((8, 128, 264, 192, 1), 2), ((8, 16, 1000, 320, 1), 2),
@@ -290,11 +300,23 @@ def test_the_second_k_tile_on_its_way_is_taken_where_it_pays(emu_shard_gemm, cas
 @pytest.mark.parametrize("bf", [0, 1])
 def test_small_kernel_stays_inside_its_buffers(emu_shard_gemm, layout, bf, monkeypatch):
     # operands of exactly their size, odd in every dimension: 32 x 32 and 64 x 64 blocks, K below one MFMA step, K tails
+    # (bf16 in the forward layout runs on kernels of its own, which the switch does not concern)
     for t2 in ("256", "1"):
         monkeypatch.setenv("TT_SMALL_T2", t2)
         for M, N, K in [(1, 1, 1), (65, 129, 97), (129, 65, 9), (97, 193, 515), (63, 35, 1051), (34, 66, 64)]:
             r = run(emu_shard_gemm, (2, M, N, K) + layout + (bf, bf, 1, 1))
             assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (t2, M, N, K, r.stdout[-400:] + r.stderr[-1500:])
+
+
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("bf", [0, 1])
+def test_small_kernel_with_wide_offsets_stays_inside_its_buffers(emu_shard_gemm, layout, bf, monkeypatch):
+    # row pitches of 2^24 elements and more take lane offsets of 64 bits; the limit lowered to where small operands pass it
+    monkeypatch.setenv("TT_SMALL_PITCH", "1")
+    monkeypatch.setenv("TT_PLAIN_K", "0")
+    for M, N, K in [(1, 1, 1), (65, 129, 97), (34, 33, 9), (63, 35, 1051), (34, 66, 64)]:
+        r = run(emu_shard_gemm, (2, M, N, K) + layout + (bf, bf, 1, 1))
+        assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (M, N, K, r.stdout[-400:] + r.stderr[-1500:])
 
 
 @pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])

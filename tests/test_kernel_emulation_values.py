@@ -198,12 +198,22 @@ def test_generic_kernel_values(lockstep_gemm, tmp_path, ta, tb):
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_small_kernel_waves_and_blocks_values(lockstep_gemm, tmp_path, dt, ta, tb):
     # every split of the waves (K of one, two, four and eight waves, the last with a tail that is no whole MFMA step),
-    # single results, and 64 x 64 blocks with one row or column in the last one (the row pairs of bf16 operands)
+    # single results, and 64 x 64 blocks with one row or column in the last one (the row pairs of bf16 operands).  (bf16
+    # in the forward layout runs on kernels of its own.)
     for i, (M, N, K) in enumerate([(33, 47, 1051), (1, 1, 1), (40, 31, 263), (5, 67, 131)]):
         check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, dt, "f32", False, 80 + i)
     for i, (M, N, K) in enumerate([(65, 129, 97), (66, 127, 515), (129, 65, 9)]):
         check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, dt, dt, True, 90 + i, env={"TT_SMALL_T2": "1"})
     check(lockstep_gemm, str(tmp_path), 2, 35, 37, 323, ta, tb, dt, "f32", False, 99, ksplit=3)
+
+
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_small_kernel_with_wide_offsets_values(lockstep_gemm, tmp_path, dt, ta, tb):
+    # lane offsets of 64 bits (row pitches of 2^24 elements and more), on operands small enough to check: whole chunks of
+    # every wave split, tails, K below a chunk
+    for i, (M, N, K) in enumerate([(33, 47, 1051), (40, 31, 263), (65, 35, 131), (35, 33, 23), (1, 1, 1)]):
+        check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, dt, "f32", bool(i & 1), 150 + i, env={"TT_SMALL_PITCH": "1", "TT_PLAIN_K": "0"})
 
 
 @pytest.mark.parametrize("ta,tb", LAYOUTS)
