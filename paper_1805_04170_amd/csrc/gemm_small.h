@@ -8,7 +8,7 @@
 // row pitch is stored coalesced.  bf16 operands use v_mfma_f32_32x32x16_bf16, fp32 ones v_mfma_f32_32x32x2_f32 (products
 // and sums in fp32, K in a fixed order: chunks of one wave in increasing order, then waves in increasing order).
 //
-// (bf16 A B, the forward layout, and short K run on the plain kernels of gemm_small.hip instead.)
+// (bf16 A B, the forward layout, short K and most of fp32 run on the ordered kernel of gemm_small.hip instead.)
 // Measured on MI355X (before: the plain kernel of 64 x 64 tiles, K walked by one workgroup):
 //   bf16 A B^T / A^T B 256 x 2047 x 2047 202 -> 18-24 us, 4 x (101 x 225 x 1500) 140 -> 8-13 us, 4095 x 4093 x 4091 2720 ->
 //   550-600 us; fp32 256 x 2047 x 2047 204 -> 41-44 us, 4 x (32 x 128 x 256) 25.5 -> 8 us, 4095 x 4093 x 4091 2730 -> 1210-1520 us.
@@ -41,6 +41,7 @@ using core::f32x16;
 
 struct __attribute__((packed, aligned(4))) Quad32 { float f[4]; };      // 16 bytes at any 4-byte boundary
 struct __attribute__((packed, aligned(2))) Pair16 { uint32_t w; };      // 4 bytes at any 2-byte boundary
+struct __attribute__((packed, aligned(4))) Pair32 { uint32_t w[2]; };   // 8 bytes at any 4-byte boundary
 
 struct ParamsS {
     const void *A[64];

@@ -1,7 +1,7 @@
 // Shard products that the MFMA tile engines do not take: fp32, and bf16 whose rows are not whole 16-byte vectors, whose
 // addresses are not multiples of 16 bytes, or of which one operand has 2^31 elements or more.  gemm_small_kernel
-// (gemm_small.h): matrix instructions.  gemm_plain_kernel, gemm_ordered_kernel: fused multiply-adds in the order of
-// increasing K; short K, and the forward layout of bf16.
+// (gemm_small.h): K cut over the waves of a workgroup.  gemm_ordered_kernel: K walked in order; short K, most of fp32, and the
+// forward layout of bf16.
 // One launch covers all shards (Sec. 5.2 step 2 of arXiv 1805.04170).
 #include "tt_device.h"
 #include <cstdint>
@@ -21,225 +21,219 @@ __global__ __launch_bounds__(small::waves_of<T>() * 64, T == 1 ? 2 : 1) void gem
     small::run_small<BF, A_KC, B_KC, T, OFF>(p, lds);
 }
 
-// Plain products: one 64 x 64 tile per workgroup, fp32 fused multiply-adds in the order of increasing K, any layout.  16
-// values of K per step through LDS, 4 x 4 results per thread, operands fetched into registers four steps ahead.  Bound by
-// LDS reads and the vector unit (two LDS values per four multiply-adds).
-template <bool BF, bool A_KC, bool B_KC, bool OUT_BF16> __global__ __launch_bounds__(256) void gemm_plain_kernel(const small::ParamsS p)
-{
-    using E = std::conditional_t<BF, uint16_t, uint32_t>; // an element's bits
-    constexpr int T = 64, KB = 16;
-    __shared__ float As[KB][T + 1];
-    __shared__ float Bs[KB][T + 1];
-    const int tiles = p.tiles_m * p.tiles_n;
-    const int vshard = blockIdx.x / tiles, t = blockIdx.x - vshard * tiles;
-    const int m0 = (t % p.tiles_m) * T, n0 = (t / p.tiles_m) * T;
-    const int shard = vshard / p.ksplit;
-    const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
-    const int kend = kbeg + p.kchunk < p.K ? kbeg + p.kchunk : p.K;
-    const E *A = reinterpret_cast<const E *>(p.A[shard]), *B = reinterpret_cast<const E *>(p.B[shard]);
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4] = {};
-    constexpr int PT = T * KB / 256, PD = 4;
-    float ra[PD][PT], rb[PD][PT];
-    // all loads of a step in flight together: clamped addresses, the out-of-range values zeroed afterwards
-    auto fetch = [&](int k0, float (&xa)[PT], float (&xb)[PT]) {
-#pragma unroll
-        for (int u = 0; u < PT; ++u) {
-            const int i = threadIdx.x + u * 256;
-            const int gm = m0 + (A_KC ? i / KB : i % T), gka = k0 + (A_KC ? i % KB : i / T);
-            const int gn = n0 + (B_KC ? i / KB : i % T), gkb = k0 + (B_KC ? i % KB : i / T);
-            const int64_t am = gm < p.M ? gm : p.M - 1, ak = gka < kend ? gka : kend - 1;
-            const int64_t bn = gn < p.N ? gn : p.N - 1, bk = gkb < kend ? gkb : kend - 1;
-            const uint32_t va = A[A_KC ? am * p.lda + ak : ak * p.lda + am], vb = B[B_KC ? bn * p.ldb + bk : bk * p.ldb + bn];
-            xa[u] = gm < p.M && gka < kend ? __uint_as_float(BF ? va << 16 : va) : 0.0f;
-            xb[u] = gn < p.N && gkb < kend ? __uint_as_float(BF ? vb << 16 : vb) : 0.0f;
-        }
-    };
-#pragma unroll
-    for (int d = 0; d < PD; ++d)
-        if (kbeg + d * KB < kend) fetch(kbeg + d * KB, ra[d], rb[d]);
-    for (int k0 = kbeg; k0 < kend; k0 += PD * KB) {
-#pragma unroll
-        for (int d = 0; d < PD; ++d) { // (unrolled: the register ring is indexed by constants)
-            const int kd = k0 + d * KB;
-            if (kd >= kend) break;
-#pragma unroll
-            for (int u = 0; u < PT; ++u) {
-                const int i = threadIdx.x + u * 256;
-                As[A_KC ? i % KB : i / T][A_KC ? i / KB : i % T] = ra[d][u];
-                Bs[B_KC ? i % KB : i / T][B_KC ? i / KB : i % T] = rb[d][u];
-            }
-            __syncthreads();
-            if (kd + PD * KB < kend) fetch(kd + PD * KB, ra[d], rb[d]);
-#pragma unroll
-            for (int kk = 0; kk < KB; ++kk) {
-                float a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-            }
-            __syncthreads();
-        }
-    }
-    void *const C = p.C[vshard];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-            if (row >= p.M || col >= p.N) continue;
-            float v = acc[i][j];
-            if (p.relu) v = v > 0.0f ? v : 0.0f;
-            if (OUT_BF16) reinterpret_cast<uint16_t *>(C)[(size_t)row * p.ldc + col] = (uint16_t)core::f32_to_bf16_bits(v);
-            else reinterpret_cast<float *>(C)[(size_t)row * p.ldc + col] = v;
-        }
-}
+// Ordered products: every result is a chain of fp32 fused multiply-adds with K increasing, on fp32 matrix instructions (fp32
+// operands: four or eight chains, K dealt out to them in turn and added pairwise at the end, since one chain of K terms
+// rounds worse than the eight waves of gemm_small_kernel; relative error at K = 16, 128, 512, 4096 7.4e-8, 1.5e-7, 1.6e-7,
+// 4.1e-7 there, 5.6e-8, 8.8e-8, 1.5e-7, 4.1e-7 here).
+// v_mfma_f32_16x16x4_f32 and v_mfma_f32_32x32x2_f32 add their four or two products to the accumulator one after the other,
+// k increasing, each rounded like fmaf (compared bit for bit with chains of fmaf: normal, widely spread, subnormal operands;
+// a bf16 value is an fp32 value), so the bits do not depend on the tile.
+//
+// Four waves, one block of S x S results each.  S = 16 is the shorter chain: a result waits 8 cycles per value of K (the
+// instruction takes 32 for four), S = 32 32 cycles; per flop both cost the matrix unit the same, and the larger tile takes in
+// half the operands.  KB values of K per step: global -> registers four steps ahead (pairs at any boundary of an element,
+// untouched until their step, so that no load is waited for early), registers -> LDS as fp32, one barrier per step.
+// bf16 A B, us, on 64 x 64 tiles of vector multiply-adds (or 32 x 32 ones, whose loads were waited for step by step) / so:
+// 4 x (100 x 225 x 1500) 71 / 9.5, 1023^3 79 / 33, 8 x (257 x 255 x 255) 17.0 / 8.5, 4095 x 4093 x 2047 1312 / 669 (103 TFLOP/s of
+// the unit's 157).
+template <bool BF, bool KC, int S, int KB> struct OrderedSide {
+    static constexpr int T = 2 * S, KM = 64 / S;                         // rows of the tile, K per instruction
+    static constexpr int PT = T * KB / 2 / 256, W = BF ? 1 : 2;          // pairs per thread and step, words per pair
+    static constexpr int ES = BF ? 2 : 4;
+    // LDS: as stored, rows of K values or K rows of row values; the 64 values of a fragment lie in 64 banks
+    static constexpr int PITCH = KC ? KB + KM : (S == 16 ? 48 : 96);
+    static constexpr int LDS = (KC ? T : KB) * PITCH;
+    static constexpr int PER = (KC ? KB : T) / 2, STEP = 256 / PER;      // pairs along the contiguous side, lines per round of the workgroup
+    int c, line;        // this thread's pair (its first value) along the contiguous side; its first line along the other
+    int row0, rows;
+    int64_t pitch;      // bytes
+    const char *base[KC ? PT : 1];
 
-// bf16 C = A B, both row-major as stored (the forward layout): the same multiply-adds in the same order, hence the same
-// bits, on 32 x 32 tiles.  Bound by latency: 2 x 2 results per thread, operands fetched into registers four K tiles ahead.
-// With 64 x 64 tiles 4 x (100 x 225 x 1500) took 138 us, so 53; the step of a 1500-900-300-20 chain at batch 100 went from
-// 327 to 181 us.  Why K increases here and the MFMA kernel does not take this layout: one shard product then stores the
-// same activations on every size, tile and split of the waves, and with them the ReLU gates of the backward pass.  (F3 cuts
-// and ksplit still add their partial sums per shard, and aligned sizes add in MFMA order.)  An activation next to zero that
-// falls on the other side moves that row's gradients: on one of 12 drawn inputs by 1.2e-2 of such a chain's gradients.
-constexpr int kOrdTile = 32, kOrdK = 16;
-template <bool OUT_BF16>
-__global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS p)
+    __device__ __forceinline__ void init(const void *mat, int64_t ld, int r0, int n)
+    {
+        c = 2 * (threadIdx.x % PER);
+        line = threadIdx.x / PER;
+        row0 = r0;
+        rows = n;
+        pitch = ld * ES;
+        if constexpr (KC) {
+#pragma unroll
+            for (int u = 0; u < PT; ++u) {
+                const int r = row0 + line + u * STEP;
+                base[u] = reinterpret_cast<const char *>(mat) + (int64_t)(r < rows ? r : rows - 1) * pitch;
+            }
+        } else {
+            base[0] = reinterpret_cast<const char *>(mat) + (int64_t)(row0 + c < rows - 1 ? row0 + c : rows - 2) * ES;
+        }
+    }
+    // clamped addresses; what does not exist is zeroed in store().  (The contiguous side has two values at least.)
+    __device__ __forceinline__ void fetch(int k0, int kend, uint32_t (&x)[PT][W]) const
+    {
+#pragma unroll
+        for (int u = 0; u < PT; ++u) {
+            const int k = KC ? (k0 + c < kend - 1 ? k0 + c : kend - 2) : (k0 + line + u * STEP < kend ? k0 + line + u * STEP : kend - 1);
+            const char *const p = KC ? base[u] + (int64_t)k * ES : base[0] + (int64_t)k * pitch;
+            if constexpr (BF) x[u][0] = reinterpret_cast<const small::Pair16 *>(p)->w;
+            else {
+                const small::Pair32 v = *reinterpret_cast<const small::Pair32 *>(p);
+                x[u][0] = v.w[0];
+                x[u][1] = v.w[1];
+            }
+        }
+    }
+    __device__ __forceinline__ void store(int k0, int kend, const uint32_t (&x)[PT][W], float *lds) const
+    {
+        // of a pair that was moved back by one value at the end of an odd side, the second value is this thread's first
+        const int left = KC ? kend - (k0 + c) : rows - (row0 + c);
+#pragma unroll
+        for (int u = 0; u < PT; ++u) {
+            const bool line_in = KC ? row0 + line + u * STEP < rows : k0 + line + u * STEP < kend;
+            const uint32_t keep0 = line_in && left > 0 ? 0xffffffffu : 0u, keep1 = line_in && left > 1 ? 0xffffffffu : 0u;
+            const uint32_t first = BF ? x[u][0] << 16 : x[u][0], second = BF ? x[u][0] & 0xffff0000u : x[u][W - 1];
+            float *const d = lds + (line + u * STEP) * PITCH + c;
+            d[0] = __uint_as_float((left == 1 ? second : first) & keep0);
+            d[1] = __uint_as_float(second & keep1);
+        }
+    }
+    // where this lane's value of the first instruction lies (block w0 of the tile), and the distance to the next one's
+    __device__ __forceinline__ static int frag(int w0, int lane) { return KC ? (w0 + lane % S) * PITCH + lane / S : lane / S * PITCH + w0 + lane % S; }
+    static constexpr int NEXT = KC ? KM : KM * PITCH;
+};
+
+template <bool BF, bool A_KC, bool B_KC, int S, int KB> __global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS p)
 {
-    constexpr int T = kOrdTile, KB = kOrdK, PT = T * KB / 256, PD = 4;
-    __shared__ float As[2][KB][T + 2];
-    __shared__ float Bs[2][KB][T + 2];
+    using OA = OrderedSide<BF, A_KC, S, KB>;
+    using OB = OrderedSide<BF, B_KC, S, KB>;
+    constexpr int T = OA::T, KM = OA::KM, PD = 4;
+    constexpr int CHAINS = BF ? 1 : KB / KM < 8 ? 4 : S == 16 ? 8 : 4;
+    __shared__ __attribute__((aligned(16))) float As[2][OA::LDS];
+    __shared__ __attribute__((aligned(16))) float Bs[2][OB::LDS];
+    using acc_t = std::conditional_t<S == 16, core::f32x4, core::f32x16>;
     const int tiles = p.tiles_m * p.tiles_n;
     const int vshard = blockIdx.x / tiles, t = blockIdx.x - vshard * tiles;
     const int m0 = (t % p.tiles_m) * T, n0 = (t / p.tiles_m) * T;
     const int shard = vshard / p.ksplit;
     const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
     const int kend = kbeg + p.kchunk < p.K ? kbeg + p.kchunk : p.K;
-    const uint16_t *A = reinterpret_cast<const uint16_t *>(p.A[shard]), *B = reinterpret_cast<const uint16_t *>(p.B[shard]);
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[2][2] = {};
-    uint32_t ra[PD][PT], rb[PD][PT];
-    // clamped addresses, out-of-range values zeroed by AND (a load under a branch would be waited for by itself)
-    auto fetch = [&](int k0, uint32_t (&xa)[PT], uint32_t (&xb)[PT]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm0 = (wave >> 1) * S, wn0 = (wave & 1) * S;
+    OA a;
+    OB b;
+    a.init(p.A[shard], p.lda, m0, p.M);
+    b.init(p.B[shard], p.ldb, n0, p.N);
+    uint32_t ra[PD][OA::PT][OA::W], rb[PD][OB::PT][OB::W];
+    acc_t acc[CHAINS];
 #pragma unroll
-        for (int u = 0; u < PT; ++u) {
-            const int i = threadIdx.x + u * 256;
-            const int gka = k0 + i % KB, gm = m0 + i / KB, gkb = k0 + i / T, gn = n0 + i % T;
-            const uint32_t va = A[(int64_t)(gm < p.M ? gm : p.M - 1) * p.lda + (gka < kend ? gka : kend - 1)];
-            const uint32_t vb = B[(int64_t)(gkb < kend ? gkb : kend - 1) * p.ldb + (gn < p.N ? gn : p.N - 1)];
-            xa[u] = (va << 16) & (gm < p.M && gka < kend ? 0xffffffffu : 0u);
-            xb[u] = (vb << 16) & (gn < p.N && gkb < kend ? 0xffffffffu : 0u);
-        }
-    };
+    for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+        for (int e = 0; e < S * S / 64; ++e) acc[c][e] = 0.0f;
 #pragma unroll
     for (int d = 0; d < PD; ++d)
-        if (kbeg + d * KB < kend) fetch(kbeg + d * KB, ra[d], rb[d]);
+        if (kbeg + d * KB < kend) {
+            a.fetch(kbeg + d * KB, kend, ra[d]);
+            b.fetch(kbeg + d * KB, kend, rb[d]);
+        }
     for (int k0 = kbeg; k0 < kend; k0 += PD * KB) {
 #pragma unroll
-        for (int d = 0; d < PD; ++d) { // (unrolled: the register ring is indexed by constants; two LDS tiles in turn, one barrier each)
+        for (int d = 0; d < PD; ++d) { // (unrolled: the register ring is indexed by constants; two LDS tiles in turn)
             const int kd = k0 + d * KB;
             if (kd >= kend) break;
-#pragma unroll
-            for (int u = 0; u < PT; ++u) {
-                const int i = threadIdx.x + u * 256;
-                As[d & 1][i % KB][i / KB] = __uint_as_float(ra[d][u]);
-                Bs[d & 1][i / T][i % T] = __uint_as_float(rb[d][u]);
-            }
+            a.store(kd, kend, ra[d], As[d & 1]);
+            b.store(kd, kend, rb[d], Bs[d & 1]);
             __syncthreads();
-            if (kd + PD * KB < kend) fetch(kd + PD * KB, ra[d], rb[d]);
+            if (kd + PD * KB < kend) {
+                a.fetch(kd + PD * KB, kend, ra[d]);
+                b.fetch(kd + PD * KB, kend, rb[d]);
+            }
+            const float *const as = As[d & 1] + OA::frag(wm0, lane), *const bs = Bs[d & 1] + OB::frag(wn0, lane);
 #pragma unroll
-            for (int kk = 0; kk < KB; ++kk) {
-                const float a0 = As[d & 1][kk][ty * 2], a1 = As[d & 1][kk][ty * 2 + 1];
-                const float b0 = Bs[d & 1][kk][tx * 2], b1 = Bs[d & 1][kk][tx * 2 + 1];
-                acc[0][0] = fmaf(a0, b0, acc[0][0]); acc[0][1] = fmaf(a0, b1, acc[0][1]);
-                acc[1][0] = fmaf(a1, b0, acc[1][0]); acc[1][1] = fmaf(a1, b1, acc[1][1]);
+            for (int i = 0; i < KB / KM; ++i) {
+                acc_t &x = acc[i % CHAINS];
+                if constexpr (S == 16) x = __builtin_amdgcn_mfma_f32_16x16x4f32(as[i * OA::NEXT], bs[i * OB::NEXT], x, 0, 0, 0);
+                else x = __builtin_amdgcn_mfma_f32_32x32x2f32(as[i * OA::NEXT], bs[i * OB::NEXT], x, 0, 0, 0);
             }
         }
     }
+#pragma unroll
+    for (int n = CHAINS / 2; n >= 1; n /= 2)
+#pragma unroll
+        for (int c = 0; c < n; ++c) acc[c] += acc[c + n];
     void *const C = p.C[vshard];
+    const int col = n0 + wn0 + lane % S;
+    if (col >= p.N) return;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int row = m0 + ty * 2 + i, col = n0 + tx * 2 + j;
-            if (row >= p.M || col >= p.N) continue;
-            float v = acc[i][j];
-            if (p.relu) v = v > 0.0f ? v : 0.0f;
-            if (OUT_BF16) reinterpret_cast<uint16_t *>(C)[(size_t)row * p.ldc + col] = (uint16_t)core::f32_to_bf16_bits(v);
-            else reinterpret_cast<float *>(C)[(size_t)row * p.ldc + col] = v;
-        }
+    for (int e = 0; e < S * S / 64; ++e) { // a lane holds one column and rows 4 (lane / S) + e % 4 of every 256 / S
+        const int row = m0 + wm0 + (e >> 2) * 4 * KM + lane / S * 4 + (e & 3);
+        if (row >= p.M) continue;
+        float v = acc[0][e];
+        if (p.relu) v = v > 0.0f ? v : 0.0f;
+        if (p.out_bf16) reinterpret_cast<uint16_t *>(C)[(size_t)row * p.ldc + col] = (uint16_t)core::f32_to_bf16_bits(v);
+        else reinterpret_cast<float *>(C)[(size_t)row * p.ldc + col] = v;
+    }
 }
 
 constexpr int64_t kMostGroups = (int64_t(1) << 24) - 1; // workgroups of 256 threads in a launch of fewer than 2^32 threads
 
 int64_t tiles_of(const small::ParamsS &p, int count, int64_t T) { return ((p.M + T - 1) / T) * ((p.N + T - 1) / T) * count * p.ksplit; }
 
-template <bool BF, bool A_KC, bool B_KC> tt_status launch_plain_layout(small::ParamsS &p, int count, hipStream_t s)
+template <bool BF, int S, int KB> tt_status launch_ordered_tile(small::ParamsS &p, int count, bool a_kc, bool b_kc, hipStream_t s)
 {
-    const int64_t total = tiles_of(p, count, 64);
+    const int64_t total = tiles_of(p, count, 2 * S);
     if (total > kMostGroups) return TT_EUNSUPPORTED;
-    p.tiles_m = (int32_t)(((int64_t)p.M + 63) / 64);
-    p.tiles_n = (int32_t)(((int64_t)p.N + 63) / 64);
+    p.tiles_m = (int32_t)(((int64_t)p.M + 2 * S - 1) / (2 * S));
+    p.tiles_n = (int32_t)(((int64_t)p.N + 2 * S - 1) / (2 * S));
     const dim3 grid((uint32_t)total), block(256);
-    if (p.out_bf16) hipLaunchKernelGGL((gemm_plain_kernel<BF, A_KC, B_KC, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((gemm_plain_kernel<BF, A_KC, B_KC, false>), grid, block, 0, s, p);
+    if (a_kc && b_kc) hipLaunchKernelGGL((gemm_ordered_kernel<BF, true, true, S, KB>), grid, block, 0, s, p);
+    else if (a_kc) hipLaunchKernelGGL((gemm_ordered_kernel<BF, true, false, S, KB>), grid, block, 0, s, p);
+    else if (b_kc) hipLaunchKernelGGL((gemm_ordered_kernel<BF, false, true, S, KB>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((gemm_ordered_kernel<BF, false, false, S, KB>), grid, block, 0, s, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
 
-template <bool BF> tt_status launch_plain(small::ParamsS &p, int count, bool a_kc, bool b_kc, hipStream_t s)
+// 64 x 64 tiles where they fill one round of the CUs or come in more than one and a half, while neither side is a strip that
+// would leave half of them empty.  32 x 32 / 64 x 64 tiles, us, bf16 A B at K = 1023: 8 x (257 x 255) (200 tiles of 64 x 64) 26.8 / 31.7,
+// 1023 x 1023 (256) 37.4 / 32.8, 1023 x 1535 (384) 49.4 / 50.9, 1023 x 1791 (448) 56.4 / 50.5, 1023 x 2047 (512) 63.8 / 52.5,
+// 4095 x 4093 (4096) 450 / 342;  strips 20001 x 31 26.1 / 49.5, 31 x 100001 107 / 153.  One step of A B: 1023 x 1023 x 16 3.7 / 4.4.
+// Steps of 16 while K is little more than one of the longer ones, whose idle part costs more than a few more barriers; on few
+// tiles sooner, as there each step's wait shows.  Longer step / 16, us: 31 x 100001 x 7 bf16 13.9 / 7.6, K = 65 / 58 per cent of the time
+// on A^T B fp32 50001 x 9, 1023 x 1535 0.83 of it at K = 96, 0.99 at 127; 4 x (101 x 225) 1.01 and 1.16; 4 x (2047 x 4095) 0.92 at 127.
+template <bool BF> tt_status launch_ordered(small::ParamsS &p, int count, bool a_kc, bool b_kc, hipStream_t s)
 {
-    if (a_kc && b_kc) return launch_plain_layout<BF, true, true>(p, count, s);
-    if (a_kc) return launch_plain_layout<BF, true, false>(p, count, s);
-    return b_kc ? launch_plain_layout<BF, false, true>(p, count, s) : launch_plain_layout<BF, false, false>(p, count, s);
+    const int64_t tiles = tiles_of(p, count, 64);
+    const int t64 = tuning_int("TT_FWD_T64", -1); // development builds: 64 x 64 from that many tiles on
+    const int64_t K = p.ksplit > 1 ? p.kchunk : p.K;
+    const bool one_round = tiles > 224 && tiles <= 256 && !(BF && a_kc && !b_kc && K <= 32);
+    const bool large = p.M > 32 && p.N > 32 && (t64 >= 0 ? tiles >= t64 : one_round || tiles > 384);
+    const bool is_short = K <= (tiles < 512 ? 96 : 160);
+    if (large || tiles_of(p, count, 32) > kMostGroups)
+        return is_short ? launch_ordered_tile<BF, 32, 16>(p, count, a_kc, b_kc, s) : launch_ordered_tile<BF, 32, 32>(p, count, a_kc, b_kc, s);
+    return is_short ? launch_ordered_tile<BF, 16, 16>(p, count, a_kc, b_kc, s) : launch_ordered_tile<BF, 16, 64>(p, count, a_kc, b_kc, s);
 }
 
-// The forward layout of bf16.  64 x 64 tiles once there are about three for every two CUs, while neither side is a strip
-// that would leave half of them empty: the larger tile reads half as much LDS per multiply-add and half the operands.
-// 32 x 32 / 64 x 64 tiles, us, at K = 33 and 1023: 1023 x 1279 (320 tiles of 64 x 64) 6.9 / 8.4 and 91 / 100, 1023 x 1535 (384)
-// 7.4 / 8.4 and 107 / 101, 1023 x 1663 (416) 8.2 / 8.4 and 123 / 102, 33 x 25001 (391) 8.5 / 8.3 and 129 / 110, 1023 x 2047 (512)
-// 9.1 / 8.5 and 139 / 108; 4095 x 4093 (4096) at K = 2047 2027 / 1307.  Strips: 31 x 100001 at K = 1023 223 / 314.
-tt_status launch_forward(small::ParamsS &p, int count, hipStream_t s)
-{
-    const int64_t total = tiles_of(p, count, kOrdTile);
-    if ((p.M > 32 && p.N > 32 && tiles_of(p, count, 64) >= tuning_int("TT_FWD_T64", 400)) || total > kMostGroups)
-        return launch_plain<true>(p, count, true, false, s);
-    p.tiles_m = (int32_t)(((int64_t)p.M + kOrdTile - 1) / kOrdTile);
-    p.tiles_n = (int32_t)(((int64_t)p.N + kOrdTile - 1) / kOrdTile);
-    const dim3 grid((uint32_t)total), block(256);
-    if (p.out_bf16) hipLaunchKernelGGL(gemm_ordered_kernel<true>, grid, block, 0, s, p);
-    else hipLaunchKernelGGL(gemm_ordered_kernel<false>, grid, block, 0, s, p);
-    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
-}
-
-// Short K: whether the plain kernel is the faster one.  gemm_small_kernel's waves take K in chunks (64 values, fp32 32), of
-// which a short K gives them one or two, and its write-out goes through LDS once more; the longer K is, the more the matrix
-// instructions win, the sooner the more often every CU gets a tile (tiles: of 64 x 64).  Between 128 and 192 values of K (fp32
-// between 64 and 96) the chunks are not yet cut over two waves.  Plain / small kernel, us:
-//   bf16 A B^T  1023 x 1535 (384 tiles)  K 15 5.5 / 14.5, 95 12.9 / 20.1, 175 20.3 / 22.0, 223 24.7 / 17.1;  767 x 769 (156)  47 7.1 / 9.0,
-//     63 8.2 / 8.1;  257 x 255 (20)  15 4.6 / 5.9, 47 6.8 / 6.3;  8 x (511 x 513) (576)  191 28.6 / 41.6, 223 32.6 / 30.8;
-//     2047 x 4095 (2048)  63 26.4 / 37.2, 95 36.7 / 42.1, 127 47.0 / 42.6;  strips 31 x 100001 (1563)  47 19.1 / 25.3, 63 23.2 / 22.4
-//   fp32 A B  1023 x 1535  15 6.4 / 13.2, 95 13.1 / 19.9, 111 14.7 / 13.7;  767 x 769  95 10.6 / 11.7, 127 12.9 / 12.7;  257 x 255  15 4.2 / 4.9,
-//     31 5.4 / 4.9, 47 6.7 / 7.5, 111 11.4 / 6.9;  8 x (511 x 513)  159 25.6 / 30.4, 191 30.1 / 30.5;  2047 x 4095  111 44.9 / 47.4,
-//     143 54.6 / 52.6;  strips 31 x 100001  63 25.3 / 33.2, 111 38.8 / 40.1
-bool plain_is_faster(bool bf, bool a_kc, bool b_kc, int64_t M, int64_t N, int64_t K, int64_t tiles)
+// Whether the ordered kernel is the faster one.  gemm_small_kernel cuts K over waves whose chunks (64 values, fp32 32) need K to
+// be worth cutting and whose write-out goes through LDS once more; its bf16 instructions multiply eight times as fast.  So
+// bf16 crosses over at K of 200 to 500, fp32 only where K is long enough for eight waves to walk it sooner than one (few
+// tiles), or where its 64 x 64 blocks fill the CUs better.  (tiles: of 64 x 64.)  Small / ordered kernel, us:
+//   bf16 A B^T  257 x 255 (20 tiles)  K 63 6.1 / 3.2, 255 6.2 / 5.3, 319 6.7 / 6.1, 383 6.6 / 6.8;  767 x 1153 (228)  223 9.9 / 9.8, 255 9.7 / 10.6;
+//     8 x (511 x 513) (576)  127 24.0 / 14.1, 511 39.6 / 37.0, 767 46.8 / 51.9;  2047 x 4095 (2048)  159 45.3 / 33.5, 255 49.9 / 48.6, 319 54.8 / 59.3
+//   bf16 A^T B  257 x 255  95 10.0 / 3.8, 511 8.9 / 8.1, 767 10.5 / 11.1;  1023 x 1535 (384)  127 18.6 / 9.5, 191 20.5 / 12.2, 223 14.6 / 14.9;
+//     2047 x 4095  191 40.6 / 40.4, 223 43.7 / 45.7
+//   fp32 A B^T  4 x (32 x 128) (8)  1535 20.3 / 20.8;  1023 x 1023 (256)  1023 29.6 / 33.1;  2047 x 4095  1023 186 / 202;  fp32 A^T B  4 x (101 x 225) (32)
+//     1023 15.1 / 16.3;  fp32 A B  64 x (65 x 67) (256)  255 12.6 / 12.0, 511 18.1 / 20.0;  4095 x 4093 (4096) ahead up to K = 4095 (1385 / 1310)
+// (fp32 A B^T on few tiles with K a little over one chunk keeps its kernel, whose one trip to memory takes it in.)
+bool ordered_is_faster(bool bf, bool a_kc, bool b_kc, int64_t K, int64_t tiles)
 {
     const int forced = tuning_int("TT_PLAIN_K", -1);
     if (forced >= 0) return K <= forced;
-    const bool nt = a_kc && b_kc;
-    if (M <= 32 || N <= 32) { // a strip: half of each 64 x 64 tile is empty, while the other kernel's blocks are 32 x 32
-        if (!bf) return K <= (tiles < 512 ? 16 : tiles < 1024 ? 64 : a_kc || b_kc ? 96 : 144);
-        return K <= (tiles < 256 ? 16 : nt || tiles >= 1024 ? 48 : tiles < 512 ? 16 : 32);
+    const bool nt = a_kc && b_kc, tn = !a_kc && !b_kc;
+    if (!bf) {
+        if (tiles < 128 && nt && K > 32 && K <= 48) return false;
+        if (tiles <= 256) return K <= (tiles < 72 ? 768 : tiles <= 224 ? 1536 : 320);
+        return K <= (nt ? 768 : b_kc ? 1536 : 4096);
     }
-    if (tiles < 128) return bf ? K <= 32 : K <= 16 || (K > 32 && K <= 48 && !nt); // (fp32 up to 32: a single chunk)
-    if (tiles < 256) return K <= (bf ? 48 : 96);
-    if (M <= 64 || N <= 64) return K <= 192; // half of the other kernel's waves have no rows or columns of their own
-    if (tiles < 512) return K <= (bf ? 176 : 96);
-    if (tiles < 1024) return K <= (bf ? 192 : 160);
-    if (tiles < 2048) return K <= 144;
-    return K <= (bf ? 96 : 128);
+    if (tiles <= 224) return K <= (nt ? 320 : tn ? 512 : 448);
+    if (tiles <= 256) return K <= (nt ? 224 : tn ? 192 : 256);
+    return K <= (tiles < 2048 ? (nt ? 448 : tn ? 208 : 256) : (nt ? 256 : 208));
 }
 
 template <bool BF, int T, class OFF> tt_status launch_small_layout(const small::ParamsS &p, bool a_kc, bool b_kc, hipStream_t s)
@@ -247,7 +241,7 @@ template <bool BF, int T, class OFF> tt_status launch_small_layout(const small::
     const dim3 grid(p.per_xcd > 0 ? (uint32_t)p.per_xcd * kXcds : (uint32_t)p.total), block(p.wm * p.wn * p.wk * 64);
     if (a_kc && b_kc) hipLaunchKernelGGL((gemm_small_kernel<BF, true, true, T, OFF>), grid, block, 0, s, p);
     else if (a_kc) {
-        if constexpr (BF) return TT_EINVAL; // (launch_forward's)
+        if constexpr (BF) return TT_EINVAL; // (the ordered kernel's)
         else hipLaunchKernelGGL((gemm_small_kernel<BF, true, false, T, OFF>), grid, block, 0, s, p);
     }
     else if (b_kc) hipLaunchKernelGGL((gemm_small_kernel<BF, false, true, T, OFF>), grid, block, 0, s, p);
@@ -317,9 +311,20 @@ tt_status launch_gemm_small(int count, const void *const *A, const void *const *
     g.out_bf16 = out_dtype == TT_BF16;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool bf = in_dtype == TT_BF16;
-    if (bf && a_kc && !b_kc) return launch_forward(g, count, s);
-    if (plain_is_faster(bf, a_kc, b_kc, M, N, ksplit > 1 ? kchunk : K, tiles_of(g, count, 64)))
-        return bf ? launch_plain<true>(g, count, a_kc, b_kc, s) : launch_plain<false>(g, count, a_kc, b_kc, s);
+    // bf16 A B, the forward layout: K increasing on every size, so that one shard product stores the same activations whatever
+    // its size, tile and split, and with them the ReLU gates of the backward pass.  (F3 cuts and ksplit still add their partial
+    // sums per shard, and aligned sizes add in MFMA order.)  An activation next to zero that falls on the other side moves that
+    // row's gradients: on one of 12 drawn inputs by 1.2e-2 of a 1500-900-300-20 chain's gradients.
+    const bool ordered = (bf && a_kc && !b_kc) || ordered_is_faster(bf, a_kc, b_kc, ksplit > 1 ? kchunk : K, tiles_of(g, count, 64));
+    // The ordered kernel loads pairs along an operand's contiguous side.  A matrix of one row or one column is as well stored
+    // the other way round; one that is a single value has no pair.
+    if (ordered && (K > 1 || M > 1) && (K > 1 || N > 1)) {
+        if (a_kc ? K == 1 : M == 1) { a_kc = !a_kc; g.lda = a_kc ? K : M; }
+        if (b_kc ? K == 1 : N == 1) { b_kc = !b_kc; g.ldb = b_kc ? K : N; }
+        return bf ? launch_ordered<true>(g, count, a_kc, b_kc, s) : launch_ordered<false>(g, count, a_kc, b_kc, s);
+    }
+    if (K == 1 && N == 1) b_kc = true;      // (either way round: the layouts that exist below)
+    else if (K == 1 && M == 1) a_kc = false;
     return bf ? launch_small<true>(g, count, a_kc, b_kc, s) : launch_small<false>(g, count, a_kc, b_kc, s);
 }
 

@@ -107,6 +107,21 @@ def test_odd_sized_forward_products_of_many_tiles():
     check(1, 2047, 1025, 17, 0, 0, "bf16", "f32", False, 68)
 
 
+@pytest.mark.parametrize("M,N,K", [(33, 35, 1), (1, 67, 65), (65, 1, 129), (100, 225, 1500), (1023, 961, 63), (32, 100, 257)])
+def test_odd_sized_forward_products_add_in_the_order_of_k(M, N, K):
+    # bit for bit a chain of fp32 fused multiply-adds (float64 holds every sum of these operands exactly), on either tile
+    rng = np.random.default_rng(M + N + K)
+    a, b = (to_bf16_bits(rng.uniform(0.25, 2.0, s).astype(np.float32) * rng.choice([-1, 1], s).astype(np.float32)) for s in ((M, K), (K, N)))
+    af, bf = bf16_bits_to_f64(a), bf16_bits_to_f64(b)
+    want = np.zeros((M, N), np.float32)
+    for k in range(K):
+        want = (want.astype(np.float64) + af[:, k:k + 1] * bf[k:k + 1]).astype(np.float32)
+    c = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    up = [torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16) for x in (a, b)]
+    tt.tt_shard_gemm([up[0]], [up[1]], [c], M, N, K, 0, 0, "bf16", "f32")
+    assert np.array_equal(dev_to_np(c), want)
+
+
 def test_fp32_keeps_subnormal_products_and_sums():
     # results below the smallest normal fp32 number (1.2e-38): K = 64 products of 2^-70 x 2^-65
     a = torch.full((40, 64), 2.0 ** -70, dtype=torch.float32, device=DEV)

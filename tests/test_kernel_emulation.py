@@ -330,6 +330,18 @@ def test_short_products_stay_inside_their_buffers_on_either_kernel(emu_shard_gem
         assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (M, N, K, r.stdout[-400:] + r.stderr[-1500:])
 
 
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("bf", [0, 1])
+def test_ordered_kernel_stays_inside_its_buffers(emu_shard_gemm, layout, bf, monkeypatch):
+    # pairs at the end of an odd side, sides of one value, both tiles
+    monkeypatch.setenv("TT_PLAIN_K", "100000")
+    for t64 in ("1000", "1"):
+        monkeypatch.setenv("TT_FWD_T64", t64)
+        for M, N, K in [(1, 33, 5), (34, 1, 7), (33, 35, 1), (1, 1, 9), (1, 37, 1), (33, 1, 1), (65, 66, 64), (35, 33, 257), (67, 131, 321)]:
+            r = run(emu_shard_gemm, (2, M, N, K) + layout + (bf, bf, 1, 1))
+            assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (t64, M, N, K, r.stdout[-400:] + r.stderr[-1500:])
+
+
 def test_shard_product_entry_point_rejects_what_the_library_rejects(emu_shard_gemm):
     # a K split that would leave the last chunk empty (chunks are rounded up to the tile depth: two of 64 cover K = 128)
     r = run(emu_shard_gemm, (2, 64, 64, 128, 0, 0, 1, 0, 0, 3))

@@ -237,6 +237,16 @@ def test_forward_tiles_of_both_sizes_store_the_same_bits(lockstep_gemm, tmp_path
         assert stored[0] == stored[1], (M, N, K)
 
 
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("t64", ["1000", "1"])
+def test_ordered_kernel_values(lockstep_gemm, tmp_path, dt, ta, tb, t64):
+    # 32 x 32 and 64 x 64 tiles: a single row, column or value of K (operands without a pair along the side they are stored
+    # by), the last of an odd side, K at and past a step of 64 and a round of four
+    for i, (M, N, K) in enumerate([(1, 33, 5), (34, 1, 7), (33, 35, 1), (1, 1, 9), (1, 37, 1), (65, 66, 64), (35, 33, 257)]):
+        check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, dt, dt, bool(i & 1), 170 + i, env={"TT_PLAIN_K": "100000", "TT_FWD_T64": t64})
+
+
 def test_random_products_values(lockstep_gemm, tmp_path):
     # seeded random shapes, layouts, types and tuning switches (sizes mostly multiples of eight, some odd): whatever
     # engine the launch code picks or falls back to has to give the product
