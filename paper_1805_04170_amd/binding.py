@@ -1,4 +1,5 @@
-"""ctypes binding of libtensor_tiling.so: same names as include/tensor_tiling.h, argument marshalling only.
+"""Binding of libtensor_tiling.so: same names as include/tensor_tiling.h, argument marshalling only (ctypes; the calls a step
+is made of through the extension module _calls, csrc/python/calls.cpp).
 
 Shard lists are Python sequences of torch tensors (their data_ptr() is passed) or of integer device addresses.
 Tilings are strings over "RCr" (cut 0 first); form sequences are strings over "123".  A non-zero status raises
@@ -71,6 +72,7 @@ class tt_layer(ctypes.Structure):
 
 
 _lib = None
+_calls = None
 _vpp = ctypes.POINTER(ctypes.c_void_p)
 _u8p = ctypes.POINTER(ctypes.c_uint8)
 _u64p = ctypes.POINTER(ctypes.c_uint64)
@@ -78,10 +80,14 @@ _u64p = ctypes.POINTER(ctypes.c_uint64)
 
 def lib():
     """Load the HIP library.  There is no fallback: a missing library is an error."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError("libtensor_tiling.so is not built; run `python -m paper_1805_04170_amd.build`")
+        if _calls is None:
+            from . import _calls as c
+            c.converters(tiling, forms, _dtype)
+            _calls = c
         L = ctypes.CDLL(LIB_PATH)
         L.tt_strerror.restype = ctypes.c_char_p
         L.tt_strerror.argtypes = [ctypes.c_int]
@@ -146,8 +152,17 @@ def lib():
         L.tt_fc_backward_overlapped.argtypes = bwd_args + [ctypes.c_void_p]
         L.tt_profile_end.argtypes = [ctypes.POINTER(ctypes.c_int)]
         L.tt_profile_get.argtypes = [ctypes.c_int, ctypes.POINTER(tt_kernel_record)]
+        L.addresses = {n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _DIRECT}
         _lib = L
     return _lib
+
+
+# the calls that go through the extension module, which takes a function by its address
+_DIRECT = ("tt_fc_forward", "tt_conv_forward", "tt_fc_forward_static", "tt_fc_backward", "tt_conv_backward", "tt_flatten", "tt_retile")
+
+
+def _address(name):
+    return (_lib or lib()).addresses[name]
 
 
 def strerror(status):
@@ -228,12 +243,21 @@ def ptrs(shards):
     return _ptr_array(max(len(vals), 1))(*vals)
 
 
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream
+except ImportError: # a torch without it, or no torch: the public way, when a stream is asked for
+    _raw_stream = None
+
+
 def _stream(stream):
     if stream is not None:
         # a raw stream handle, or a torch.cuda.Stream
-        return ctypes.c_void_p(int(getattr(stream, "cuda_stream", stream)))
+        return int(getattr(stream, "cuda_stream", stream))
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle alone, where torch offers it (0.3 us; a Stream object around it 2.9 us)
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype(d):
@@ -451,14 +475,14 @@ def tt_graph_eval(tensors, ops, k, tilings):
 
 def tt_retile(dst, B, src, A, rows, cols, elem_bytes, k=None, stream=None):
     k = len(A) if k is None else k
-    _check(lib().tt_retile(ptrs(dst), _tiling(B), ptrs(src), _tiling(A), k, rows, cols, elem_bytes, _stream(stream)),
-           "tt_retile")
+    fn = _address("tt_retile")
+    _check(_calls.retile(fn, dst, B, src, A, k, rows, cols, elem_bytes, _stream(stream)), "tt_retile")
 
 
 def tt_flatten(dst, B, src, A, batch, channels, pixels, elem_bytes, to_matrix=True, k=None, stream=None):
     k = len(A) if k is None else k
-    _check(lib().tt_flatten(ptrs(dst), _tiling(B), ptrs(src), _tiling(A), k, batch, channels, pixels, elem_bytes,
-                            1 if to_matrix else 0, _stream(stream)), "tt_flatten")
+    fn = _address("tt_flatten")
+    _check(_calls.flatten(fn, dst, B, src, A, k, batch, channels, pixels, elem_bytes, to_matrix, _stream(stream)), "tt_flatten")
 
 
 def tt_retile_gate(dst, B, src, A, mask, Am, rows, cols, dtype, k=None, stream=None):
@@ -512,33 +536,21 @@ def tt_conv_workspace_bytes(lay, batch, k, dtype, op, tX, tW, tY, tdY=None, tdX=
                             tY, tdY, tdX, forms_a, forms_b, with_dx)
 
 
-def _forward(fn, what, lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace, stream):
-    wp, wb = _ws(workspace)
-    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), _tiling(tX), _tiling(tW), _tiling(tY), _forms(form_seq), ptrs(X),
-              ptrs(W), ptrs(Y), wp, wb, _stream(stream)), what)
-
-
-def _backward(fn, what, lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad, forms_wgrad, X, W, Y, dY, dX, dW,
-              workspace, stream):
-    wp, wb = _ws(workspace)
-    _check(fn(ctypes.byref(lay), batch, k, _dtype(dtype), _tiling(tX), _tiling(tW), _tiling(tY), _tiling(tdY),
-              _t_or(tdX, tX), _forms(forms_dgrad), _forms(forms_wgrad), ptrs(X), ptrs(W), ptrs(Y), ptrs(dY), ptrs(dX),
-              ptrs(dW), wp, wb, _stream(stream)), what)
-
-
 def tt_fc_forward(lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace=None, stream=None):
-    _forward(lib().tt_fc_forward, "tt_fc_forward", lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace, stream)
+    fn = _address("tt_fc_forward")
+    _check(_calls.forward(fn, lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace, _stream(stream)), "tt_fc_forward")
 
 
 def tt_fc_forward_static(lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, stream=None):
-    _check(lib().tt_fc_forward_static(ctypes.byref(lay), batch, k, _dtype(dtype), _tiling(tX), _tiling(tW), _tiling(tY),
-                                      _forms(form_seq), ptrs(X), ptrs(W), ptrs(Y), _stream(stream)), "tt_fc_forward_static")
+    fn = _address("tt_fc_forward_static")
+    _check(_calls.forward_static(fn, lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, _stream(stream)), "tt_fc_forward_static")
 
 
 def tt_fc_backward(lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad, forms_wgrad, X, W, Y, dY, dX, dW,
                    workspace=None, stream=None):
-    _backward(lib().tt_fc_backward, "tt_fc_backward", lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad,
-              forms_wgrad, X, W, Y, dY, dX, dW, workspace, stream)
+    fn = _address("tt_fc_backward")
+    _check(_calls.backward(fn, lay, batch, k, dtype, tX, tW, tY, tdY, tX if tdX is None else tdX, forms_dgrad, forms_wgrad, X, W, Y, dY,
+                           dX, dW, workspace, _stream(stream)), "tt_fc_backward")
 
 
 def tt_fc_backward_overlapped(lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad, forms_wgrad, X, W, Y, dY, dX, dW,
@@ -551,14 +563,15 @@ def tt_fc_backward_overlapped(lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_
 
 
 def tt_conv_forward(lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace=None, stream=None):
-    _forward(lib().tt_conv_forward, "tt_conv_forward", lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace,
-             stream)
+    fn = _address("tt_conv_forward")
+    _check(_calls.forward(fn, lay, batch, k, dtype, tX, tW, tY, form_seq, X, W, Y, workspace, _stream(stream)), "tt_conv_forward")
 
 
 def tt_conv_backward(lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad, forms_wgrad, X, W, Y, dY, dX, dW,
                      workspace=None, stream=None):
-    _backward(lib().tt_conv_backward, "tt_conv_backward", lay, batch, k, dtype, tX, tW, tY, tdY, tdX, forms_dgrad,
-              forms_wgrad, X, W, Y, dY, dX, dW, workspace, stream)
+    fn = _address("tt_conv_backward")
+    _check(_calls.backward(fn, lay, batch, k, dtype, tX, tW, tY, tdY, tX if tdX is None else tdX, forms_dgrad, forms_wgrad, X, W, Y, dY,
+                           dX, dW, workspace, _stream(stream)), "tt_conv_backward")
 
 
 # ------------------------------------------------------------- kernel timing

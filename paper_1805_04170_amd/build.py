@@ -1,10 +1,11 @@
-"""Compile the HIP/C++ sources under csrc/ into libtensor_tiling.so (gfx950 only).
+"""Compile the HIP/C++ sources under csrc/ into libtensor_tiling.so (gfx950 only) and the binding's extension module.
 
     python -m paper_1805_04170_amd.build
 """
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -12,6 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtensor_tiling.so")
+CALLS = os.path.join(PKG, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 # -packed-fp32-ops: keep the compiler from forming packed fp32 instructions (hipcc's host pass warns that it does
 # not know the feature; harmless)
@@ -35,8 +37,17 @@ def _compile(src):
     return out
 
 
+def build_calls():
+    """the binding's extension module (host code; the library's functions reach it by address)"""
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "python", "calls.cpp"), "-o", CALLS]
+    subprocess.check_call(cmd)
+    return CALLS
+
+
 def build(jobs=8):
     os.makedirs(OBJ, exist_ok=True)
+    build_calls()
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, sources()))
     cmd = ["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs

@@ -412,3 +412,27 @@ def test_the_product_build_reads_no_environment():
         pytest.skip("no nm, or the library is not built")
     syms = subprocess.run([nm, "-D", "--undefined-only", tt.binding.LIB_PATH], capture_output=True, text=True).stdout
     assert "getenv" not in syms
+
+
+def test_layer_calls_take_what_the_binding_documents(monkeypatch):
+    # nothing is launched: every call is refused, or fails before it reaches the library
+    import torch
+    monkeypatch.setattr(tt.binding, "_stream", lambda stream: 0)
+    lay, x = tt.layer("fc", "none", 8, 8), [torch.zeros(8) for _ in range(2)]
+
+    def fwd(*, X=x, Y=x, batch=5, dtype="bf16", tX="R", f="1"):
+        tt.tt_fc_forward(lay, batch, 1, dtype, tX, "r", "R", f, X, x, Y)
+
+    for ok in (dict(), dict(X=tuple(x)), dict(X=iter(x)), dict(X=[1 << 20, 2 << 20]), dict(X=[x[0], 1 << 20]), dict(dtype=tt.TT_F32),
+               dict(tX=tt.tiling("R")), dict(f=tt.binding.forms("1")), dict(f=None)):
+        with pytest.raises(tt.TilingError) as e:      # a batch of five under one row cut
+            fwd(**ok)
+        assert e.value.status == 2, ok
+    for bad, status in ((dict(X=None), 1), (dict(X=x[:1]), 1), (dict(tX="X"), 1), (dict(tX="RRRRRRR"), 1), (dict(f="4"), 2), (dict(f=""), 2)):
+        with pytest.raises(tt.TilingError) as e:
+            fwd(**bad)
+        assert e.value.status == status, bad
+    for bad, error in ((dict(dtype="bf17"), KeyError), (dict(X=[None, 1]), TypeError), (dict(X=5), TypeError), (dict(batch=4.5), TypeError),
+                       (dict(f="a"), ValueError)):
+        with pytest.raises(error):
+            fwd(**bad)
