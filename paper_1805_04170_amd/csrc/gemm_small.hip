@@ -34,7 +34,7 @@ __global__ __launch_bounds__(small::waves_of<T>() * 64, T == 1 ? 2 : 1) void gem
 // half the operands.  KB values of K per step: global -> registers four steps ahead (pairs at any boundary of an element,
 // untouched until their step, so that no load is waited for early), registers -> LDS as fp32, one barrier per step.
 // bf16 A B, us, on 64 x 64 tiles of vector multiply-adds (or 32 x 32 ones, whose loads were waited for step by step) / so:
-// 4 x (100 x 225 x 1500) 71 / 9.5, 1023^3 79 / 33, 8 x (257 x 255 x 255) 17.0 / 8.5, 4095 x 4093 x 2047 1312 / 669 (103 TFLOP/s of
+// 4 x (100 x 225 x 1500) 53 / 20, 1023^3 79 / 33, 8 x (257 x 255 x 255) 17.0 / 8.5, 4095 x 4093 x 2047 1312 / 669 (103 TFLOP/s of
 // the unit's 157).
 template <bool BF, bool KC, int S, int KB> struct OrderedSide {
     static constexpr int T = 2 * S, KM = 64 / S;                         // rows of the tile, K per instruction
