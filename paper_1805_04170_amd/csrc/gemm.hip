@@ -17,10 +17,10 @@ namespace {
 
 using core::kXcds;
 
-struct GemmParams {
-    const void *A[kMaxShards];
-    const void *B[kMaxShards];
-    void *C[kMaxShards];
+template <int NS, int NC> struct GemmParamsT { // tables of NS shards and NC outputs
+    const void *A[NS];
+    const void *B[NS];
+    void *C[NC];
     int32_t M, N, K;
     int32_t lda, ldb, ldc;
     int32_t tiles_m, tiles_n;
@@ -30,13 +30,11 @@ struct GemmParams {
     int32_t ksplit;   // each shard's K range is cut into ksplit chunks of kchunk (a multiple of 64); chunk c of shard s
     int32_t kchunk;   // writes its own output C[s * ksplit + c] (partial sums, added up by the reduction kernel)
 };
+using GemmParams = GemmParamsT<kMaxShards, kMaxShards>;
 
-template <int BM, int BN, int WM, int WN, int DEPTH, bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC>
-__global__ __launch_bounds__(WM * WN * 64, (WM * WN / 4) * (DEPTH == 0 ? (BM == 128 ? 3 : 2) : 1)) void gemm_bf16_kernel(const GemmParams p)
+template <int BM, int BN, int WM, int WN, int DEPTH, bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC, class P>
+__device__ __forceinline__ void run_bf16_tile(const P &p, int logical, uint16_t *smem)
 {
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
-    const int logical = core::logical_block(p.per_xcd, p.total);
-    if (logical < 0) return;
     const int tiles = p.tiles_m * p.tiles_n;
     const int vshard = logical / tiles;
     const int t = logical - vshard * tiles;
@@ -57,6 +55,50 @@ __global__ __launch_bounds__(WM * WN * 64, (WM * WN / 4) * (DEPTH == 0 ? (BM == 
     lb.base = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
     lb.ld = p.ldb; lb.rows = p.N; lb.K = klen;
     core::tile_product<BM, BN, WM, WN, DEPTH, KMASK, OUT_BF16, VEC>(la, lb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * BM, tn * BN, p.relu != 0, smem);
+}
+
+template <int BM, int BN, int WM, int WN, int DEPTH, bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC>
+__global__ __launch_bounds__(WM * WN * 64, (WM * WN / 4) * (DEPTH == 0 ? (BM == 128 ? 3 : 2) : 1)) void gemm_bf16_kernel(const GemmParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    const int logical = core::logical_block(p.per_xcd, p.total);
+    if (logical < 0) return;
+    run_bf16_tile<BM, BN, WM, WN, DEPTH, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, logical, smem);
+}
+
+// A B^T (DM x 128 tiles) and A^T B (128 x 128) of a backward step in one launch
+struct GemmPair {
+    GemmParamsT<8, 64> dgrad;
+    GemmParamsT<8, 8> wgrad;
+};
+template <int DM, bool KMASK, bool D_BF16> __global__ __launch_bounds__(256, 2) void gemm_bf16_pair_kernel(const GemmPair p)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    const int first = p.dgrad.per_xcd * kXcds, bid = (int)blockIdx.x; // (a multiple of the XCDs: both parts are dealt out alike)
+    if (bid < first) {
+        const int logical = core::logical_block(bid, p.dgrad.per_xcd, p.dgrad.total);
+        if (logical < 0) return;
+        constexpr int WM = DM == 128 ? 2 : 1, DEPTH = DM == 128 ? 1 : 2;
+        run_bf16_tile<DM, 128, WM, 4 / WM, DEPTH, KMASK, true, true, D_BF16, true>(p.dgrad, logical, smem);
+    } else {
+        const int logical = core::logical_block(bid - first, p.wgrad.per_xcd, p.wgrad.total);
+        if (logical < 0) return;
+        run_bf16_tile<128, 128, 2, 2, 1, KMASK, false, false, true, true>(p.wgrad, logical, smem);
+    }
+}
+template <int DM, bool KMASK, bool D_BF16> tt_status launch_bf16_pair(const GemmPair &p, hipStream_t s)
+{
+    auto kern = gemm_bf16_pair_kernel<DM, KMASK, D_BF16>;
+    constexpr size_t d = core::smem_bytes<DM, 128, DM == 128 ? 1 : 2>(), w = core::smem_bytes<128, 128, 1>(), smem = d > w ? d : w;
+    if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem) != TT_OK) return TT_EDEVICE;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)(p.dgrad.per_xcd + p.wgrad.per_xcd) * kXcds), dim3(256), smem, s, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+template <bool KMASK> tt_status launch_bf16_pair_rows(const GemmPair &p, int DM, bool d_bf16, hipStream_t s)
+{
+    if (DM == 32) return d_bf16 ? launch_bf16_pair<32, KMASK, true>(p, s) : launch_bf16_pair<32, KMASK, false>(p, s);
+    if (DM == 64) return d_bf16 ? launch_bf16_pair<64, KMASK, true>(p, s) : launch_bf16_pair<64, KMASK, false>(p, s);
+    return d_bf16 ? launch_bf16_pair<128, KMASK, true>(p, s) : launch_bf16_pair<128, KMASK, false>(p, s);
 }
 
 // second engine: operand tiles loaded straight into LDS, 256 x 256 tiles, eight waves
@@ -196,6 +238,13 @@ bool all_aligned16(const void *const *ptrs, int n)
     return true;
 }
 
+// 16-byte vectors along each operand's contiguous side, byte offsets in 31 bits
+bool mfma_takes(int count, const void *const *A, const void *const *B, int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b, int in_dtype)
+{
+    return in_dtype == TT_BF16 && K > 0 && (trans_a ? M : K) % 8 == 0 && (trans_b ? K : N) % 8 == 0 && M * K < (int64_t(1) << 31) &&
+           K * N < (int64_t(1) << 31) && all_aligned16(A, count) && all_aligned16(B, count);
+}
+
 } // namespace
 
 tt_status launch_gemm(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
@@ -219,9 +268,7 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
     // MFMA path needs 16-byte vectors along each operand's contiguous dimension
     const int64_t a_contig = trans_a ? M : K, b_contig = trans_b ? K : N;
     // (operand byte offsets are kept in 32 bits inside the kernel)
-    const bool mfma_ok = in_dtype == TT_BF16 && K > 0 && a_contig % 8 == 0 && b_contig % 8 == 0 &&
-                         M * K < (int64_t(1) << 31) && K * N < (int64_t(1) << 31) &&
-                         all_aligned16(A, count) && all_aligned16(B, count);
+    const bool mfma_ok = mfma_takes(count, A, B, M, N, K, trans_a != 0, trans_b != 0, in_dtype);
     const uint64_t in_b = in_dtype == TT_BF16 ? 2 : 4, out_b = out_dtype == TT_BF16 ? 2 : 4;
     const int kclass = !mfma_ok ? TT_K_GEMM_GENERIC
                                 : (trans_a ? (trans_b ? TT_K_GEMM_TT : TT_K_GEMM_TN) : (trans_b ? TT_K_GEMM_NT : TT_K_GEMM_NN));
@@ -289,6 +336,69 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
     }
     return launch_gemm_small(count, A, B, C, M, N, K, a_contig, b_contig, !trans_a, trans_b != 0, in_dtype, out_dtype,
                              act == TT_ACT_RELU, ksplit, kchunk, stream);
+}
+
+namespace {
+
+template <class P> void fill_pair_half(P *p, const GemmCall &c, bool dgrad, int BM, int ns, int nc)
+{
+    for (int i = 0; i < ns; ++i) {
+        p->A[i] = i < c.count ? c.A[i] : nullptr;
+        p->B[i] = i < c.count ? c.B[i] : nullptr;
+    }
+    for (int i = 0; i < nc; ++i) p->C[i] = i < c.count * c.ksplit ? c.C[i] : nullptr;
+    p->M = (int32_t)c.M; p->N = (int32_t)c.N; p->K = (int32_t)c.K;
+    p->lda = (int32_t)(dgrad ? c.K : c.M);
+    p->ldb = (int32_t)(dgrad ? c.K : c.N);
+    p->ldc = (int32_t)c.N;
+    p->tiles_m = (int32_t)((c.M + BM - 1) / BM);
+    p->tiles_n = (int32_t)((c.N + 127) / 128);
+    p->total = p->tiles_m * p->tiles_n * c.count * c.ksplit;
+    p->per_xcd = (p->total + kXcds - 1) / kXcds;
+    p->relu = 0;
+    p->ksplit = c.ksplit;
+    p->kchunk = (int32_t)(c.ksplit == 1 ? c.K : ((c.K + c.ksplit - 1) / c.ksplit + 63) / 64 * 64);
+}
+
+} // namespace
+
+tt_status launch_gemm_pair(const GemmCall &d, const GemmCall &w, void *stream)
+{
+    const GemmCall *const g[2] = {&d, &w};
+    bool mfma[2];
+    for (int i = 0; i < 2; ++i) {
+        const GemmCall &c = *g[i];
+        if (!c.A || !c.B || !c.C || c.count < 1 || c.count > 8 || c.ksplit < 1 || c.count * c.ksplit > kMaxShards) return TT_EUNSUPPORTED;
+        if (c.M < 1 || c.N < 1 || c.K < 1 || c.M >= (int64_t(1) << 31) || c.N >= (int64_t(1) << 31) || c.K >= (int64_t(1) << 31)) return TT_EUNSUPPORTED;
+        for (int s = 0; s < c.count; ++s)
+            if (!c.A[s] || !c.B[s]) return TT_EUNSUPPORTED;
+        for (int s = 0; s < c.count * c.ksplit; ++s)
+            if (!c.C[s]) return TT_EUNSUPPORTED;
+        mfma[i] = mfma_takes(c.count, c.A, c.B, c.M, c.N, c.K, i == 1, i == 0, c.in_dtype);
+    }
+    if (mfma[0] != mfma[1]) return TT_EUNSUPPORTED;
+    if (!mfma[0]) return launch_ordered_pair(d, w, stream);
+    // Results with 16-byte rows, the weight gradient in bf16 over K of at most 1024 (one K tile on its way, where a launch of its
+    // own has two), and no more than two workgroups per CU of either on the 128-column tiles of the register-staged engine: all
+    // of them are resident together.  Backward call, apart / together, us: 256 x 4096-1000 on 8 shards 29.1 / 21.3, 256 x 512-512 on
+    // one 21.7 / 12.0, 64 x 1536-776 on 4 16.4 / 9.7, 1024 x 1024-1024 on one 41.7 / 32.0, 128 x 4096-2048 on 8 (512 workgroups) 25.1 / 20.2.
+    // Past that: 256 x 4096-4096 on 8 (1024) 43 / 51; 2048 x 512-512 on 8 (weight gradients over K = 2048) 47.9 / 54.1.
+    if (w.ksplit != 1 || w.out_dtype != TT_BF16 || w.K > 1024) return TT_EUNSUPPORTED;
+    if (w.N % 8 || d.N % (d.out_dtype == TT_BF16 ? 8 : 4) || !all_aligned16(const_cast<const void *const *>(w.C), w.count) ||
+        !all_aligned16(const_cast<const void *const *>(d.C), d.count * d.ksplit))
+        return TT_EUNSUPPORTED;
+    const int DM = d.M <= 32 ? 32 : d.M <= 64 ? 64 : 128;
+    static const int most = tuning_int("TT_PAIR_TILES", 512);
+    if (((d.M + DM - 1) / DM) * ((d.N + 127) / 128) * d.count * d.ksplit > most || ((w.M + 127) / 128) * ((w.N + 127) / 128) * w.count > most)
+        return TT_EUNSUPPORTED;
+    GemmPair p;
+    fill_pair_half(&p.dgrad, d, true, DM, 8, 64);
+    fill_pair_half(&p.wgrad, w, false, 128, 8, 8);
+    if (d.ksplit > 1 && (int64_t)p.dgrad.kchunk * (d.ksplit - 1) >= d.K) return TT_EUNSUPPORTED;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    ProfileScope scope(stream, TT_K_GEMM_NT, d.count, d.M, d.N, d.K, d.bytes() + w.bytes(), d.flops() + w.flops());
+    return d.K % core::BK || w.K % core::BK ? launch_bf16_pair_rows<true>(p, DM, d.out_dtype == TT_BF16, s)
+                                            : launch_bf16_pair_rows<false>(p, DM, d.out_dtype == TT_BF16, s);
 }
 
 } // namespace tt

@@ -380,12 +380,12 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, 
 
 // XCD-aware workgroup order: hardware workgroup numbers go round-robin over the 8 XCDs; hand every XCD a contiguous
 // range of logical workgroups so tiles that share operands share an L2.  Returns -1 for padding workgroups.
-__device__ __forceinline__ int logical_block(int per_xcd, int total)
+__device__ __forceinline__ int logical_block(int bid, int per_xcd, int total)
 {
-    const int bid = blockIdx.x;
     const int logical = (bid % kXcds) * per_xcd + bid / kXcds;
     return logical < total ? logical : -1;
 }
+__device__ __forceinline__ int logical_block(int per_xcd, int total) { return logical_block((int)blockIdx.x, per_xcd, total); }
 
 // Tile order inside one shard: column tiles are taken in groups of four; inside a group the row tiles run slowest and
 // the group's columns fastest.  Workgroups that run at the same time then share a few column tiles of B and a few row

@@ -43,10 +43,10 @@ struct __attribute__((packed, aligned(4))) Quad32 { float f[4]; };      // 16 by
 struct __attribute__((packed, aligned(2))) Pair16 { uint32_t w; };      // 4 bytes at any 2-byte boundary
 struct __attribute__((packed, aligned(4))) Pair32 { uint32_t w[2]; };   // 8 bytes at any 4-byte boundary
 
-struct ParamsS {
-    const void *A[64];
-    const void *B[64];
-    void *C[64];
+template <int NS> struct ParamsT { // tables of NS shards
+    const void *A[NS];
+    const void *B[NS];
+    void *C[NS];
     int32_t M, N, K;
     int64_t lda, ldb;     // elements between rows of the stored matrices
     int32_t ldc;
@@ -56,6 +56,7 @@ struct ParamsS {
     int32_t wm, wn, wk;       // waves of a workgroup along M, N and K
     int32_t relu, out_bf16;
 };
+using ParamsS = ParamsT<64>;
 
 // T blocks of 32 per side of a wave's output; most waves a workgroup has
 template <int T> constexpr int waves_of() { return T == 1 ? 8 : 4; }

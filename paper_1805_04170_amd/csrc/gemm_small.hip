@@ -100,17 +100,21 @@ template <bool BF, bool KC, int S, int KB> struct OrderedSide {
     static constexpr int NEXT = KC ? KM : KM * PITCH;
 };
 
-template <bool BF, bool A_KC, bool B_KC, int S, int KB> __global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS p)
+template <bool BF, bool A_KC, bool B_KC, int S, int KB> constexpr int ordered_lds()
+{
+    return 2 * (OrderedSide<BF, A_KC, S, KB>::LDS + OrderedSide<BF, B_KC, S, KB>::LDS);
+}
+
+template <bool BF, bool A_KC, bool B_KC, int S, int KB, class P> __device__ __forceinline__ void run_ordered(const P &p, int block, float *lds)
 {
     using OA = OrderedSide<BF, A_KC, S, KB>;
     using OB = OrderedSide<BF, B_KC, S, KB>;
     constexpr int T = OA::T, KM = OA::KM, PD = 4;
     constexpr int CHAINS = BF ? 1 : KB / KM < 8 ? 4 : S == 16 ? 8 : 4;
-    __shared__ __attribute__((aligned(16))) float As[2][OA::LDS];
-    __shared__ __attribute__((aligned(16))) float Bs[2][OB::LDS];
+    float *const As = lds, *const Bs = lds + 2 * OA::LDS; // two tiles each
     using acc_t = std::conditional_t<S == 16, core::f32x4, core::f32x16>;
     const int tiles = p.tiles_m * p.tiles_n;
-    const int vshard = blockIdx.x / tiles, t = blockIdx.x - vshard * tiles;
+    const int vshard = block / tiles, t = block - vshard * tiles;
     const int m0 = (t % p.tiles_m) * T, n0 = (t / p.tiles_m) * T;
     const int shard = vshard / p.ksplit;
     const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
@@ -138,14 +142,14 @@ template <bool BF, bool A_KC, bool B_KC, int S, int KB> __global__ __launch_boun
         for (int d = 0; d < PD; ++d) { // (unrolled: the register ring is indexed by constants; two LDS tiles in turn)
             const int kd = k0 + d * KB;
             if (kd >= kend) break;
-            a.store(kd, kend, ra[d], As[d & 1]);
-            b.store(kd, kend, rb[d], Bs[d & 1]);
+            a.store(kd, kend, ra[d], As + (d & 1) * OA::LDS);
+            b.store(kd, kend, rb[d], Bs + (d & 1) * OB::LDS);
             __syncthreads();
             if (kd + PD * KB < kend) {
                 a.fetch(kd + PD * KB, kend, ra[d]);
                 b.fetch(kd + PD * KB, kend, rb[d]);
             }
-            const float *const as = As[d & 1] + OA::frag(wm0, lane), *const bs = Bs[d & 1] + OB::frag(wn0, lane);
+            const float *const as = As + (d & 1) * OA::LDS + OA::frag(wm0, lane), *const bs = Bs + (d & 1) * OB::LDS + OB::frag(wn0, lane);
 #pragma unroll
             for (int i = 0; i < KB / KM; ++i) {
                 acc_t &x = acc[i % CHAINS];
@@ -172,9 +176,31 @@ template <bool BF, bool A_KC, bool B_KC, int S, int KB> __global__ __launch_boun
     }
 }
 
+template <bool BF, bool A_KC, bool B_KC, int S, int KB> __global__ __launch_bounds__(256) void gemm_ordered_kernel(const small::ParamsS p)
+{
+    __shared__ __attribute__((aligned(16))) float lds[ordered_lds<BF, A_KC, B_KC, S, KB>()];
+    run_ordered<BF, A_KC, B_KC, S, KB>(p, (int)blockIdx.x, lds);
+}
+
+// A B^T and A^T B of a backward step in one launch.  Both are bound by their launch and a few trips to memory, and together
+// take what the longer one takes alone: 3.8 + 3.7, 6.9 + 3.4 and 5.6 + 3.5 us of the 68 us of kernels in the fp32 step 256-512-256-10.
+struct OrderedPair {
+    small::ParamsT<8> dgrad, wgrad;
+    int32_t first; // workgroups of the data gradient
+};
+template <bool BF, int KD, int KW> __global__ __launch_bounds__(256) void gemm_ordered_pair_kernel(const OrderedPair p)
+{
+    constexpr int D = ordered_lds<BF, true, true, 16, KD>(), W = ordered_lds<BF, false, false, 16, KW>();
+    __shared__ __attribute__((aligned(16))) float lds[D > W ? D : W];
+    const int block = (int)blockIdx.x;
+    if (block < p.first) run_ordered<BF, true, true, 16, KD>(p.dgrad, block, lds);
+    else run_ordered<BF, false, false, 16, KW>(p.wgrad, block - p.first, lds);
+}
+
 constexpr int64_t kMostGroups = (int64_t(1) << 24) - 1; // workgroups of 256 threads in a launch of fewer than 2^32 threads
 
-int64_t tiles_of(const small::ParamsS &p, int count, int64_t T) { return ((p.M + T - 1) / T) * ((p.N + T - 1) / T) * count * p.ksplit; }
+int64_t tiles_of(int64_t M, int64_t N, int64_t outs, int64_t T) { return ((M + T - 1) / T) * ((N + T - 1) / T) * outs; }
+int64_t tiles_of(const small::ParamsS &p, int count, int64_t T) { return tiles_of(p.M, p.N, (int64_t)count * p.ksplit, T); }
 
 template <bool BF, int S, int KB> tt_status launch_ordered_tile(small::ParamsS &p, int count, bool a_kc, bool b_kc, hipStream_t s)
 {
@@ -197,17 +223,24 @@ template <bool BF, int S, int KB> tt_status launch_ordered_tile(small::ParamsS &
 // Steps of 16 while K is little more than one of the longer ones, whose idle part costs more than a few more barriers; on few
 // tiles sooner, as there each step's wait shows.  Longer step / 16, us: 31 x 100001 x 7 bf16 13.9 / 7.6, K = 65 / 58 per cent of the time
 // on A^T B fp32 50001 x 9, 1023 x 1535 0.83 of it at K = 96, 0.99 at 127; 4 x (101 x 225) 1.01 and 1.16; 4 x (2047 x 4095) 0.92 at 127.
+struct OrderedTile {
+    bool large, small_step; // 64 x 64 tiles; steps of 16
+};
+OrderedTile pick_ordered(bool nn_bf16, int64_t M, int64_t N, int64_t K, int64_t outs)
+{
+    const int64_t tiles = tiles_of(M, N, outs, 64);
+    const int t64 = tuning_int("TT_FWD_T64", -1); // development builds: 64 x 64 from that many tiles on
+    const bool one_round = tiles > 224 && tiles <= 256 && !(nn_bf16 && K <= 32);
+    const bool large = (M > 32 && N > 32 && (t64 >= 0 ? tiles >= t64 : one_round || tiles > 384)) || tiles_of(M, N, outs, 32) > kMostGroups;
+    return {large, K <= (tiles < 512 ? 96 : 160)};
+}
+
 template <bool BF> tt_status launch_ordered(small::ParamsS &p, int count, bool a_kc, bool b_kc, hipStream_t s)
 {
-    const int64_t tiles = tiles_of(p, count, 64);
-    const int t64 = tuning_int("TT_FWD_T64", -1); // development builds: 64 x 64 from that many tiles on
-    const int64_t K = p.ksplit > 1 ? p.kchunk : p.K;
-    const bool one_round = tiles > 224 && tiles <= 256 && !(BF && a_kc && !b_kc && K <= 32);
-    const bool large = p.M > 32 && p.N > 32 && (t64 >= 0 ? tiles >= t64 : one_round || tiles > 384);
-    const bool is_short = K <= (tiles < 512 ? 96 : 160);
-    if (large || tiles_of(p, count, 32) > kMostGroups)
-        return is_short ? launch_ordered_tile<BF, 32, 16>(p, count, a_kc, b_kc, s) : launch_ordered_tile<BF, 32, 32>(p, count, a_kc, b_kc, s);
-    return is_short ? launch_ordered_tile<BF, 16, 16>(p, count, a_kc, b_kc, s) : launch_ordered_tile<BF, 16, 64>(p, count, a_kc, b_kc, s);
+    const OrderedTile t = pick_ordered(BF && a_kc && !b_kc, p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, (int64_t)count * p.ksplit);
+    if (t.large)
+        return t.small_step ? launch_ordered_tile<BF, 32, 16>(p, count, a_kc, b_kc, s) : launch_ordered_tile<BF, 32, 32>(p, count, a_kc, b_kc, s);
+    return t.small_step ? launch_ordered_tile<BF, 16, 16>(p, count, a_kc, b_kc, s) : launch_ordered_tile<BF, 16, 64>(p, count, a_kc, b_kc, s);
 }
 
 // Whether the ordered kernel is the faster one.  gemm_small_kernel cuts K over waves whose chunks (64 values, fp32 32) need K to
@@ -217,7 +250,7 @@ template <bool BF> tt_status launch_ordered(small::ParamsS &p, int count, bool a
 //   bf16 A B^T  257 x 255 (20 tiles)  K 63 6.1 / 3.2, 255 6.2 / 5.3, 319 6.7 / 6.1, 383 6.6 / 6.8;  767 x 1153 (228)  223 9.9 / 9.8, 255 9.7 / 10.6;
 //     8 x (511 x 513) (576)  127 24.0 / 14.1, 511 39.6 / 37.0, 767 46.8 / 51.9;  2047 x 4095 (2048)  159 45.3 / 33.5, 255 49.9 / 48.6, 319 54.8 / 59.3
 //   bf16 A^T B  257 x 255  95 10.0 / 3.8, 511 8.9 / 8.1, 767 10.5 / 11.1;  1023 x 1535 (384)  127 18.6 / 9.5, 191 20.5 / 12.2, 223 14.6 / 14.9;
-//     2047 x 4095  191 40.6 / 40.4, 223 43.7 / 45.7
+//     4 x (375 x 900) (360)  200 17.1 / 18.7;  2047 x 4095  191 40.6 / 40.4, 223 43.7 / 45.7
 //   fp32 A B^T  4 x (32 x 128) (8)  1535 20.3 / 20.8;  1023 x 1023 (256)  1023 29.6 / 33.1;  2047 x 4095  1023 186 / 202;  fp32 A^T B  4 x (101 x 225) (32)
 //     1023 15.1 / 16.3;  fp32 A B  64 x (65 x 67) (256)  255 12.6 / 12.0, 511 18.1 / 20.0;  4095 x 4093 (4096) ahead up to K = 4095 (1385 / 1310)
 // (fp32 A B^T on few tiles with K a little over one chunk keeps its kernel, whose one trip to memory takes it in.)
@@ -233,7 +266,18 @@ bool ordered_is_faster(bool bf, bool a_kc, bool b_kc, int64_t K, int64_t tiles)
     }
     if (tiles <= 224) return K <= (nt ? 320 : tn ? 512 : 448);
     if (tiles <= 256) return K <= (nt ? 224 : tn ? 192 : 256);
-    return K <= (tiles < 2048 ? (nt ? 448 : tn ? 208 : 256) : (nt ? 256 : 208));
+    return K <= (tiles < 2048 ? (nt ? 448 : tn ? 192 : 256) : (nt ? 256 : 192));
+}
+
+template <bool BF, int KD, int KW> tt_status launch_ordered_pair_steps(const OrderedPair &p, int64_t total, hipStream_t s)
+{
+    hipLaunchKernelGGL((gemm_ordered_pair_kernel<BF, KD, KW>), dim3((uint32_t)total), dim3(256), 0, s, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+template <bool BF> tt_status launch_ordered_pair_type(const OrderedPair &p, int64_t total, bool short_d, bool short_w, hipStream_t s)
+{
+    if (short_d) return short_w ? launch_ordered_pair_steps<BF, 16, 16>(p, total, s) : launch_ordered_pair_steps<BF, 16, 64>(p, total, s);
+    return short_w ? launch_ordered_pair_steps<BF, 64, 16>(p, total, s) : launch_ordered_pair_steps<BF, 64, 64>(p, total, s);
 }
 
 template <bool BF, int T, class OFF> tt_status launch_small_layout(const small::ParamsS &p, bool a_kc, bool b_kc, hipStream_t s)
@@ -326,6 +370,54 @@ tt_status launch_gemm_small(int count, const void *const *A, const void *const *
     if (K == 1 && N == 1) b_kc = true;      // (either way round: the layouts that exist below)
     else if (K == 1 && M == 1) a_kc = false;
     return bf ? launch_small<true>(g, count, a_kc, b_kc, s) : launch_small<false>(g, count, a_kc, b_kc, s);
+}
+
+// Both on the ordered kernel with 32 x 32 tiles (what is larger fills the chip by itself), up to eight shards.
+tt_status launch_ordered_pair(const GemmCall &d, const GemmCall &w, void *stream)
+{
+    const GemmCall *const g[2] = {&d, &w};
+    bool small_step[2];
+    int64_t tiles[2];
+    for (int i = 0; i < 2; ++i) {
+        const GemmCall &c = *g[i];
+        const bool bf = c.in_dtype == TT_BF16, nt = i == 0;
+        if (c.in_dtype != d.in_dtype || c.ksplit != 1 || c.count < 1 || c.count > 8) return TT_EUNSUPPORTED;
+        if (nt ? c.K < 2 : c.K < 1 || c.M < 2 || c.N < 2) return TT_EUNSUPPORTED; // pairs along the contiguous sides
+        if (!ordered_is_faster(bf, nt, nt, c.K, tiles_of(c.M, c.N, c.count, 64))) return TT_EUNSUPPORTED;
+        const OrderedTile t = pick_ordered(false, c.M, c.N, c.K, c.count);
+        if (t.large) return TT_EUNSUPPORTED;
+        small_step[i] = t.small_step;
+        tiles[i] = tiles_of(c.M, c.N, c.count, 32);
+    }
+    if (tiles[0] + tiles[1] > kMostGroups) return TT_EUNSUPPORTED;
+    OrderedPair p;
+    for (int i = 0; i < 2; ++i) {
+        const GemmCall &c = *g[i];
+        small::ParamsT<8> &q = i == 0 ? p.dgrad : p.wgrad;
+        for (int s = 0; s < 8; ++s) {
+            q.A[s] = s < c.count ? c.A[s] : nullptr;
+            q.B[s] = s < c.count ? c.B[s] : nullptr;
+            q.C[s] = s < c.count ? c.C[s] : nullptr;
+        }
+        q.M = (int32_t)c.M; q.N = (int32_t)c.N; q.K = (int32_t)c.K;
+        q.lda = i == 0 ? c.K : c.M;
+        q.ldb = i == 0 ? c.K : c.N;
+        q.ldc = (int32_t)c.N;
+        q.tiles_m = (int32_t)((c.M + 31) / 32);
+        q.tiles_n = (int32_t)((c.N + 31) / 32);
+        q.per_xcd = 0;
+        q.total = (int32_t)tiles[i];
+        q.ksplit = 1;
+        q.kchunk = (int32_t)c.K;
+        q.wm = q.wn = q.wk = 1;
+        q.relu = 0;
+        q.out_bf16 = c.out_dtype == TT_BF16;
+    }
+    p.first = (int32_t)tiles[0];
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    ProfileScope scope(stream, TT_K_GEMM_GENERIC, d.count, d.M, d.N, d.K, d.bytes() + w.bytes(), d.flops() + w.flops());
+    if (d.in_dtype == TT_BF16) return launch_ordered_pair_type<true>(p, tiles[0] + tiles[1], small_step[0], small_step[1], s);
+    return launch_ordered_pair_type<false>(p, tiles[0] + tiles[1], small_step[0], small_step[1], s);
 }
 
 } // namespace tt

@@ -154,7 +154,21 @@ tt_status backward(const FcArgs &a, Workspace &ws)
         if ((st = fk.fork(a.stream, a.aux)) != TT_OK) return st;
         wstream = a.aux;
     }
-    auto wgrad = [&]() -> tt_status {
+    // The operands and the output of a product, ready to launch
+    struct Product {
+        Sharded A, B;
+        OutputPlan op;
+        GemmCall call;
+    };
+    const auto ready = [&](Product &p, int64_t M, int64_t N, int64_t K, int ksplit) {
+        p.call = GemmCall{n, p.A.ptr, p.B.ptr, p.op.gemm_out, M, N, K, a.dtype, p.op.gemm_dtype, ksplit};
+    };
+    const auto launch = [&](const Product &p, bool dgrad_layout, void *stream) {
+        const GemmCall &c = p.call;
+        return launch_gemm(c.count, c.A, c.B, c.C, c.M, c.N, c.K, dgrad_layout ? 0 : 1, dgrad_layout ? 1 : 0, c.in_dtype, c.out_dtype,
+                           p.op.gemm_act, c.ksplit, stream);
+    };
+    const auto prepare_wgrad = [&](Product &p) -> tt_status {
         // dW = X^T G : M = n_in, K = b, N = n_out; first operand is X transposed; dW stored like W
         uint8_t f[TT_MAX_K];
         const tt_tiling tXt = transpose_tiling(a.tX, k);
@@ -165,47 +179,47 @@ tt_status backward(const FcArgs &a, Workspace &ws)
         const tt_tiling aX = transpose_tiling(aXt, k);
         int k1, k2, k3;
         form_counts(f, k, &k1, &k2, &k3);
-        Sharded Xa, Ga;
-        if ((st = prepare_operand(X, aX, k, esz, nullptr, a.dtype, ws, wstream, &Xa)) != TT_OK) return st;
-        if ((st = prepare_operand(G, aG, k, esz, gated ? nullptr : &Y, a.dtype, ws, wstream, &Ga)) != TT_OK) return st;
-        OutputPlan op;
-        if ((st = plan_output(f, a.tW, a.dW, ni, no, k, a.dtype, TT_ACT_NONE, ws, &op)) != TT_OK) return st;
-        if (!ws.dry) {
-            // X shard is (b/..) x (n_in/..) row-major = K x M: trans_a
-            st = launch_gemm(n, Xa.ptr, Ga.ptr, op.gemm_out, ni >> k1, no >> k2, b >> k3, 1, 0, a.dtype, op.gemm_dtype,
-                             op.gemm_act, 1, wstream);
-            if (st != TT_OK) return st;
-            if ((st = finish_output(op, a.tW, a.dW, ni, no, k, a.dtype, TT_ACT_NONE, wstream)) != TT_OK) return st;
-        }
+        if ((st = prepare_operand(X, aX, k, esz, nullptr, a.dtype, ws, wstream, &p.A)) != TT_OK) return st;
+        if ((st = prepare_operand(G, aG, k, esz, gated ? nullptr : &Y, a.dtype, ws, wstream, &p.B)) != TT_OK) return st;
+        if ((st = plan_output(f, a.tW, a.dW, ni, no, k, a.dtype, TT_ACT_NONE, ws, &p.op)) != TT_OK) return st;
+        ready(p, ni >> k1, no >> k2, b >> k3, 1); // X shard is (b/..) x (n_in/..) row-major = K x M: transposed
         return TT_OK;
     };
-    auto dgrad = [&]() -> tt_status {
-        if (!a.with_dx) return TT_OK;
-        Sharded Wa;
-        if ((st = prepare_operand(W, aW_d, k, esz, nullptr, a.dtype, ws, a.stream, &Wa)) != TT_OK) return st;
-        OutputPlan op;
+    const auto finish_wgrad = [&](const Product &p) { return finish_output(p.op, a.tW, a.dW, ni, no, k, a.dtype, TT_ACT_NONE, wstream); };
+    const auto prepare_dgrad = [&](Product &p) -> tt_status {
+        p.A = Ga_d;
+        if ((st = prepare_operand(W, aW_d, k, esz, nullptr, a.dtype, ws, a.stream, &p.B)) != TT_OK) return st;
         const int64_t Ms = b >> d1, Ns = ni >> d2, Ks = no >> d3;
         const int ksplit = pick_ksplit(Ms, Ns, Ks, n, a.dtype, Ks % 8 == 0, Ks % 8 == 0);
-        if ((st = plan_output(fd, a.tdX, a.dX, b, ni, k, a.dtype, TT_ACT_NONE, ws, &op, ksplit)) != TT_OK) return st;
-        if (!ws.dry) {
-            // W shard is (n_in/..) x (n_out/..) row-major = N x K: trans_b
-            st = launch_gemm(n, Ga_d.ptr, Wa.ptr, op.gemm_out, Ms, Ns, Ks, 0, 1, a.dtype, op.gemm_dtype, op.gemm_act, ksplit,
-                             a.stream);
-            if (st != TT_OK) return st;
-            if ((st = finish_output(op, a.tdX, a.dX, b, ni, k, a.dtype, TT_ACT_NONE, a.stream)) != TT_OK) return st;
-        }
+        if ((st = plan_output(fd, a.tdX, a.dX, b, ni, k, a.dtype, TT_ACT_NONE, ws, &p.op, ksplit)) != TT_OK) return st;
+        ready(p, Ms, Ns, Ks, ksplit); // W shard is (n_in/..) x (n_out/..) row-major = N x K: transposed
         return TT_OK;
     };
-    // One stream: dX product first, then the weight gradient.  Two streams: the weight gradient is enqueued first so
-    // that it is already running on the side stream while the dX product is being launched.
+    const auto finish_dgrad = [&](const Product &p) { return finish_output(p.op, a.tdX, a.dX, b, ni, k, a.dtype, TT_ACT_NONE, a.stream); };
+    // Two streams: the weight gradient is enqueued first so that it is already running on the side stream while the dX product
+    // is being launched.
+    Product pd, pw;
     if (fk.forked) {
-        if ((st = wgrad()) != TT_OK) return st;
-        if ((st = dgrad()) != TT_OK) return st;
-    } else {
-        if ((st = dgrad()) != TT_OK) return st;
-        if ((st = wgrad()) != TT_OK) return st;
+        if ((st = prepare_wgrad(pw)) != TT_OK) return st;
+        if ((st = launch(pw, false, wstream)) != TT_OK || (st = finish_wgrad(pw)) != TT_OK) return st;
+        if (a.with_dx) {
+            if ((st = prepare_dgrad(pd)) != TT_OK) return st;
+            if ((st = launch(pd, true, a.stream)) != TT_OK || (st = finish_dgrad(pd)) != TT_OK) return st;
+        }
+        return fk.join();
     }
-    return fk.join();
+    // One stream: small products together in one launch, others one after the other.
+    if (a.with_dx && (st = prepare_dgrad(pd)) != TT_OK) return st;
+    if ((st = prepare_wgrad(pw)) != TT_OK) return st;
+    if (ws.dry) return TT_OK;
+    st = a.with_dx ? launch_gemm_pair(pd.call, pw.call, a.stream) : TT_EUNSUPPORTED;
+    if (st == TT_EUNSUPPORTED) {
+        if (a.with_dx && ((st = launch(pd, true, a.stream)) != TT_OK || (st = finish_dgrad(pd)) != TT_OK)) return st;
+        if ((st = launch(pw, false, a.stream)) != TT_OK) return st;
+        return finish_wgrad(pw);
+    }
+    if (st != TT_OK || (st = finish_dgrad(pd)) != TT_OK) return st;
+    return finish_wgrad(pw);
 }
 
 bool null_in(const void *const *p, int n)

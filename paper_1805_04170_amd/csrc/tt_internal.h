@@ -130,6 +130,25 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
                       int64_t K, int trans_a, int trans_b, int in_dtype, int out_dtype, int act, int ksplit,
                       void *stream);
 
+// The products of a backward step, which do not depend on each other, in one launch: a data gradient (A B^T) and a weight
+// gradient (A^T B), neither of which fills the chip by itself.  TT_EUNSUPPORTED when no kernel takes the pair, and when one of
+// the two is better off on an engine of its own (the caller launches them one after the other).
+struct GemmCall {
+    int count;
+    const void *const *A, *const *B;
+    void *const *C;
+    int64_t M, N, K;
+    int in_dtype, out_dtype, ksplit;
+    uint64_t bytes() const // operands read once, results written once
+    {
+        const uint64_t e = in_dtype == TT_BF16 ? 2 : 4, o = out_dtype == TT_BF16 ? 2 : 4;
+        return (uint64_t)count * (e * ((uint64_t)M * K + (uint64_t)K * N) + o * (uint64_t)M * N);
+    }
+    uint64_t flops() const { return 2ull * (uint64_t)M * (uint64_t)N * (uint64_t)K * (uint64_t)count; }
+};
+tt_status launch_gemm_pair(const GemmCall &dgrad, const GemmCall &wgrad, void *stream);
+tt_status launch_ordered_pair(const GemmCall &dgrad, const GemmCall &wgrad, void *stream); // (gemm_small.hip)
+
 // Persistent software-pipelined MFMA engine (gemm3.hip); bf16 operands.  a_kc / b_kc: the operand's rows (m / n) have
 // K contiguous.  TT_EUNSUPPORTED when the shape does not meet the kernel's assumptions (the caller falls back).
 tt_status launch_gemm_v3(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,

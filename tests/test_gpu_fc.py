@@ -114,6 +114,31 @@ def _backward_once(fn, lay, b, k, dt, t, forms, Xs, Ws, Ys, dYs, ni, no, **kw):
     return dXs, dWs, ws
 
 
+def run_together(b, ni, no, k, dt, seed, **aux):
+    # small products of a backward step share a launch; the two-stream variant launches them apart: the very same bits
+    t = dict(X="R" * k, W="r" * k, Y="R" * k, dY="R" * k, dX="R" * k) if seed % 2 else dict(X="r" * k, W="C" * k, Y="C" * k, dY="C" * k, dX="r" * k)
+    lay = tt.layer("fc", "none", ni, no)
+    X, W, Y, dY = (to_store(normal_f32(seed, i, shape, s), dt) for i, shape, s in
+                   ((0, (b, ni), 1.0), (1, (ni, no), 0.05), (3, (b, no), 1.0), (2, (b, no), 1.0)))
+    Xs, Ws, Ys, dYs = (shards_to_dev(a, tt_, dt == "bf16") for a, tt_ in ((X, t["X"]), (W, t["W"]), (Y, t["Y"]), (dY, t["dY"])))
+    one = _backward_once(tt.tt_fc_backward, lay, b, k, dt, t, (None, None), Xs, Ws, Ys, dYs, ni, no)
+    two = _backward_once(tt.tt_fc_backward_overlapped, lay, b, k, dt, t, (None, None), Xs, Ws, Ys, dYs, ni, no, **aux)
+    torch.cuda.synchronize()
+    for g, r in zip(one[0] + one[1], two[0] + two[1]):
+        assert not torch.isnan(g.float()).any()
+        assert torch.equal(g, r)
+
+
+@pytest.mark.parametrize("b,ni,no", [(1, 33, 2), (33, 65, 67), (100, 301, 129), (32, 256, 128), (40, 136, 72), (96, 264, 200), (64, 520, 1000), (65, 2048, 64)])
+@pytest.mark.parametrize("dt,k", [("bf16", 0), ("f32", 0), ("bf16", 1)])
+def test_backward_products_in_one_launch_equal_two(b, ni, no, dt, k):
+    # odd sizes and fp32: the ordered kernel; sizes in 16-byte vectors: tiles of 32, 64 and 128 rows, K with and without a tail
+    if k == 1 and (no % 2 or b % 2):
+        pytest.skip("uneven cut")
+    for seed in (94, 95)[:1 + k]:
+        run_together(b, ni, no, k, dt, seed, aux_stream=torch.cuda.Stream())
+
+
 @pytest.mark.parametrize("relu", [False, True])
 def test_backward_overlapped_equals_backward(relu):
     # the two-stream variant must produce the very same bits, eagerly and as a captured graph replayed several times

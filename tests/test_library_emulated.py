@@ -265,6 +265,13 @@ def test_fc_backward_overlapped_equals_backward(on_host, monkeypatch, relu):
         assert not torch.isnan(g.float()).any()
 
 
+@pytest.mark.parametrize("b,ni,no,dt,k", [(33, 65, 67, "bf16", 0), (35, 40, 33, "f32", 0), (1, 33, 2, "bf16", 0), (32, 136, 64, "bf16", 0), (40, 264, 72, "bf16", 1),
+                                           (66, 128, 136, "bf16", 0)])
+def test_backward_products_in_one_launch_equal_two(on_host, monkeypatch, b, ni, no, dt, k):
+    monkeypatch.setattr(binding, "_stream", lambda s: s if isinstance(s, int) else 0)
+    on_host["fc"].run_together(b, ni, no, k, dt, 94, aux_stream=16)
+
+
 def test_forward_with_the_library_s_own_scratch(on_host):
     import test_zz_no_alloc as na
     na.test_static_scratch_forward_twice_second_smaller()
