@@ -83,6 +83,7 @@ struct OutputPlan {
     int gemm_dtype = TT_F32;
     int gemm_act = TT_ACT_NONE;
     int mode = 0; // 0: products write the stored shards; 1: conversion afterwards; 2: reduction afterwards
+    int parts = 0; // > 0: the products were run block by block (launch_blocks), parts results each
     int ksplit = 1; // > 1: each shard product is cut further along K into ksplit partial sums (mode 2)
     uint8_t zl[TT_MAX_K];
 };
@@ -163,18 +164,89 @@ inline int pick_ksplit(int64_t M, int64_t N, int64_t K, int count, int dtype, bo
     return s;
 }
 
+// Shards that an F3 cut makes add up into the same output block, and where they run one product each, every one of them
+// writes its whole block as an fp32 partial sum for the reduction to read again (16 x 512 x 8192 in the F3^4 layer: 268 MB).
+// How a block's K range is cut is free, so it is cut into as many runs as fill the chip, and no more (gemm_core3.h).
+// Returns the number of runs, or 0 where a product per shard is no slower.  The estimate, in microseconds with all CUs at
+// work: 2.0 per K tile of a 256 x 256 tile, 9 to write its fp32 results (5 in bf16), 5.5 TB/s for the reduction (4 TB/s
+// for the copy into the stored tiling that one bf16 result needs).
+inline int pick_runs(int64_t M, int64_t N, int64_t K, int nblk, int nred, int k)
+{
+    if (nred < 2 || K % 64 || N % 8) return 0;
+    const int forced = tuning_int("TT_RUNS", 0); // development builds only
+    if (forced) return forced <= nred && (forced << k) <= kMaxShards ? forced : 0;
+    if (M <= 128 || N <= 128) return 0;
+    const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256) * nblk;
+    if (tiles * nred < 200) return 0; // (too few 256 x 256 tiles: such launches run on other engines, launch_gemm)
+    const int64_t all = K / 64 * nred, cus = 256;
+    const double blk = 4.0 * (double)M * (double)N * nblk;
+    const auto us = [&](int64_t parts) {
+        const double rounds = (double)((tiles * parts + cus - 1) / cus), len = (double)((all + parts - 1) / parts);
+        return parts == 1 ? rounds * (len * 2.0 + 5.0) + blk / 4.0e6 : rounds * (len * 2.0 + 9.0) + blk * (double)parts / 5.5e6;
+    };
+    int best = 0;
+    double best_us = 0.95 * us(nred);
+    for (int parts = 1; parts <= nred && (parts << k) <= kMaxShards; ++parts)
+        if (us(parts) < best_us) { best = parts; best_us = us(parts); }
+    return best;
+}
+
+// The products of a planned output (mode 2, no split inside shards) block by block, where that is the faster way and the
+// engine takes them; TT_EUNSUPPORTED otherwise.  The partial sums go into the buffers planned for the shards' (there are
+// no fewer of those).
+inline tt_status launch_blocks(OutputPlan *op, int k, const void *const *A, const void *const *B, int64_t M, int64_t N, int64_t K,
+                               int trans_a, int trans_b, int dtype, int act, void *stream)
+{
+    if (op->mode != 2 || op->ksplit != 1 || dtype != TT_BF16) return TT_EUNSUPPORTED;
+    uint32_t red = 0;
+    for (int j = 0; j < k; ++j)
+        if (op->zl[j] == kRed) red |= 1u << (k - 1 - j);
+    const uint32_t keep = ((1u << k) - 1u) & ~red;
+    int kred = 0;
+    for (int j = 0; j < k; ++j) kred += (red >> j) & 1;
+    const int nred = 1 << kred, nblk = 1 << (k - kred);
+    const int parts = pick_runs(M, N, K, nblk, nred, k);
+    if (!parts) return TT_EUNSUPPORTED;
+    const void *a[kMaxShards], *b[kMaxShards];
+    void *out[kMaxShards];
+    for (int blk = 0; blk < nblk; ++blk) {
+        for (int q = 0; q < nred; ++q) {
+            const uint32_t s = deposit((uint32_t)blk, keep, k) | deposit((uint32_t)q, red, k);
+            a[blk * nred + q] = A[s];
+            b[blk * nred + q] = B[s];
+        }
+        for (int c = 0; c < parts; ++c) out[blk * parts + c] = op->gemm_out[blk * parts + c];
+    }
+    const int out_dtype = parts == 1 ? TT_BF16 : TT_F32;
+    const tt_status st = launch_gemm_runs(nblk, nred, parts, a, b, out, M, N, K, trans_a, trans_b, out_dtype, parts == 1 ? act : TT_ACT_NONE, stream);
+    if (st != TT_OK) return st;
+    op->parts = parts;
+    op->gemm_dtype = out_dtype;
+    // where the output kernels look: a single result stands for every shard of its block, partial sum c of a block at its
+    // shard with zero bits at the F3 cuts
+    for (int i = 0; i < kMaxShards; ++i) op->gemm_out[i] = nullptr;
+    for (int blk = 0; blk < nblk; ++blk) {
+        const uint32_t s0 = deposit((uint32_t)blk, keep, k);
+        if (parts == 1)
+            for (int q = 0; q < nred; ++q) op->gemm_out[s0 | deposit((uint32_t)q, red, k)] = out[blk];
+        else
+            for (int c = 0; c < parts; ++c) op->gemm_out[(int)s0 * parts + c] = out[blk * parts + c];
+    }
+    return TT_OK;
+}
+
 inline tt_status finish_output(const OutputPlan &op, const tt_tiling &tZ, void *const *Z, int64_t rows, int64_t cols, int k,
                                int dtype, int act, void *stream)
 {
     if (op.mode == 0) return TT_OK;
-    if (op.mode == 1) {
+    if (op.mode == 1 || op.parts == 1) {
         tt_tiling az;
-        for (int j = 0; j < k; ++j) az.cut[j] = op.zl[j];
+        for (int j = 0; j < k; ++j) az.cut[j] = op.zl[j] == kRed ? (uint8_t)TT_REP : op.zl[j];
         return launch_convert(Z, tZ.cut, const_cast<const void *const *>(op.gemm_out), az.cut, nullptr, nullptr, k, rows,
                               cols, dtype == TT_BF16 ? 2 : 4, 0, false, stream);
     }
     return launch_reduce(Z, tZ.cut, dtype, reinterpret_cast<const float *const *>(op.gemm_out), op.zl, k, rows, cols, act,
-                         op.ksplit, stream);
+                         op.parts ? op.parts : op.ksplit, stream, op.parts > 0);
 }
 
 inline bool forms_feasible(const uint8_t *forms, int k, int64_t M, int64_t N, int64_t K)

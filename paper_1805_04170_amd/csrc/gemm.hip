@@ -338,6 +338,24 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
                              act == TT_ACT_RELU, ksplit, kchunk, stream);
 }
 
+tt_status launch_gemm_runs(int nblk, int nred, int parts, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
+                           int64_t K, int trans_a, int trans_b, int out_dtype, int act, void *stream)
+{
+    if (!A || !B || !C || nblk < 1 || nred < 1 || parts < 1 || nblk * nred > kMaxShards || nblk * parts > kMaxShards) return TT_EUNSUPPORTED;
+    if (M < 1 || N < 1 || K < 1 || M >= (int64_t(1) << 31) || N >= (int64_t(1) << 31) || K >= (int64_t(1) << 31)) return TT_EUNSUPPORTED;
+    for (int i = 0; i < nblk * nred; ++i)
+        if (!A[i] || !B[i]) return TT_EUNSUPPORTED;
+    for (int i = 0; i < nblk * parts; ++i)
+        if (!C[i]) return TT_EUNSUPPORTED;
+    if (!mfma_takes(nblk * nred, A, B, M, N, K, trans_a != 0, trans_b != 0, TT_BF16)) return TT_EUNSUPPORTED;
+    if (N % (out_dtype == TT_BF16 ? 8 : 4) || !all_aligned16(const_cast<const void *const *>(C), nblk * parts)) return TT_EUNSUPPORTED;
+    ProfileScope scope(stream, trans_a ? TT_K_GEMM_TN : trans_b ? TT_K_GEMM_NT : TT_K_GEMM_NN, nblk * nred, M, N, K,
+                       2ull * nblk * nred * ((uint64_t)M * K + (uint64_t)K * N) + (out_dtype == TT_BF16 ? 2ull : 4ull) * nblk * parts * (uint64_t)M * N,
+                       2ull * (uint64_t)M * (uint64_t)N * (uint64_t)K * (uint64_t)(nblk * nred));
+    return launch_gemm_v3_runs(nblk, nred, parts, A, B, C, M, N, K, trans_a ? M : K, trans_b ? K : N, N, !trans_a, trans_b != 0, out_dtype,
+                               act == TT_ACT_RELU, stream);
+}
+
 namespace {
 
 template <class P> void fill_pair_half(P *p, const GemmCall &c, bool dgrad, int BM, int ns, int nc)

@@ -15,11 +15,11 @@
 namespace tt {
 namespace {
 
-template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV>
+template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV, bool RUNS = false>
 __global__ __launch_bounds__(core3::kThreads3, 2) void gemm_bf16_v3_kernel(const core3::Params3 p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem3[];
-    core3::run_tiles<BK, NS, A_KC, B_KC, OUT_BF16, STAGED, ILV>(p, smem3);
+    core3::run_tiles<BK, NS, A_KC, B_KC, OUT_BF16, STAGED, ILV, RUNS>(p, smem3);
 }
 
 // 256 x 128 tiles, four waves, two workgroups per CU (gemm_core4.h); one tile per workgroup
@@ -114,10 +114,10 @@ int cu_count()
     return n;
 }
 
-template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV = false>
+template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV = false, bool RUNS = false>
 tt_status launch_cfg(core3::Params3 &p, hipStream_t s)
 {
-    auto kern = gemm_bf16_v3_kernel<BK, NS, A_KC, B_KC, OUT_BF16, STAGED, ILV>;
+    auto kern = gemm_bf16_v3_kernel<BK, NS, A_KC, B_KC, OUT_BF16, STAGED, ILV, RUNS>;
     constexpr size_t smem = core3::smem_bytes3<BK, NS, STAGED>();
     if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem) != TT_OK) return TT_EDEVICE;
     hipLaunchKernelGGL(kern, dim3((uint32_t)p.wg_per_xcd * core::kXcds), dim3(core3::kThreads3), smem, s, p);
@@ -143,6 +143,13 @@ template <bool A_KC, bool B_KC> tt_status launch_layout(core3::Params3 &p, int o
         if (!bf && ilv) return vec ? launch_cfg<64, 2, A_KC, B_KC, false, true, true>(p, s) : launch_cfg<64, 2, A_KC, B_KC, false, false, true>(p, s);
     if (!bf && vec) return launch_cfg<64, 2, A_KC, B_KC, false, true>(p, s); // fp32 partial sums with 16-byte rows: staged too
     return bf ? launch_cfg<64, 2, A_KC, B_KC, true, false>(p, s) : launch_cfg<64, 2, A_KC, B_KC, false, false>(p, s);
+}
+
+// over runs of K tiles; loads between the k-steps as above
+template <bool A_KC, bool B_KC> tt_status launch_runs(core3::Params3 &p, int out_dtype, hipStream_t s)
+{
+    if (out_dtype == TT_BF16) return launch_cfg<64, 2, A_KC, B_KC, true, true, true, true>(p, s);
+    return launch_cfg<64, 2, A_KC, B_KC, false, true, A_KC && !B_KC, true>(p, s);
 }
 
 } // namespace
@@ -226,6 +233,20 @@ tt_status launch_gemm_v3(int count, const void *const *A, const void *const *B, 
     if (a_kc && !b_kc) return launch_layout<true, false>(p, out_dtype, vec, s);
     if (!a_kc && !b_kc) return launch_layout<false, false>(p, out_dtype, vec, s);
     return launch_layout<false, true>(p, out_dtype, vec, s);
+}
+
+// Rows of C of 16-byte vectors; NN, NT and TN (what the layers launch)
+tt_status launch_gemm_v3_runs(int nblk, int nred, int parts, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
+                              int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc, bool b_kc, int out_dtype, int relu, void *stream)
+{
+    core3::Params3 p;
+    const tt_status st = fill_params3_runs(&p, cu_count(), nblk, nred, parts, A, B, C, M, N, K, lda, ldb, ldc, a_kc, b_kc, relu);
+    if (st != TT_OK) return st;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (a_kc && b_kc) return launch_runs<true, true>(p, out_dtype, s);
+    if (a_kc) return launch_runs<true, false>(p, out_dtype, s);
+    if (!b_kc) return launch_runs<false, false>(p, out_dtype, s);
+    return TT_EUNSUPPORTED;
 }
 
 } // namespace tt

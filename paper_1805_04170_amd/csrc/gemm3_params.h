@@ -40,6 +40,32 @@ inline tt_status fill_params3(core3::Params3 *p, int tile_m, int tile_n, int k_t
     p->relu = relu;
     p->ksplit = ksplit;
     p->kchunk = (int32_t)(ksplit > 1 ? kchunk : K);
+    p->nred = p->parts = 1;
+    return TT_OK;
+}
+
+// Persistent engine over runs of K tiles (RUNS in gemm_core3.h): nblk output blocks of nred shards each (A, B: a block's
+// shards one after the other), `parts` runs and results per block.
+inline tt_status fill_params3_runs(core3::Params3 *p, int cus, int nblk, int nred, int parts, const void *const *A, const void *const *B,
+                                   void *const *C, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc,
+                                   bool b_kc, int relu)
+{
+    if (nblk < 1 || nred < 1 || nblk > 64 || nred > 64 || parts < 1 || parts > 64 || nblk * nred > 64 || nblk * parts > 64) return TT_EUNSUPPORTED;
+    void *first[64]; // (fill_params3 reads one result per shard)
+    for (int i = 0; i < 64; ++i) first[i] = i < nblk * parts ? C[i] : nullptr;
+    const tt_status st = fill_params3(p, core3::BM3, core3::BN3, 64, cus, nblk * nred, A, B, first, M, N, K, lda, ldb, ldc, a_kc, b_kc, relu, 1, K);
+    if (st != TT_OK) return st;
+    const int64_t all = K / 64 * nred; // every run has at least one K tile; products of run and tile numbers fit 32 bits
+    if (all < parts || all > (int64_t(1) << 24)) return TT_EUNSUPPORTED;
+    for (int i = 0; i < 64; ++i) p->C[i] = first[i];
+    const int64_t total = (int64_t)p->tiles_m * p->tiles_n * nblk * parts;
+    if (total >= (int64_t(1) << 30)) return TT_EUNSUPPORTED;
+    p->total = (int32_t)total;
+    p->per_xcd = (int32_t)((total + core::kXcds - 1) / core::kXcds);
+    const int per_xcd_cus = cus / core::kXcds > 0 ? cus / core::kXcds : 1;
+    p->wg_per_xcd = per_xcd_cus < p->per_xcd ? per_xcd_cus : p->per_xcd;
+    p->nred = nred;
+    p->parts = parts;
     return TT_OK;
 }
 

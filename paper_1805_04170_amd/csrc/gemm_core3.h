@@ -100,6 +100,7 @@ struct Params3 {
     int32_t total;       // tiles_m * tiles_n * count * ksplit
     int32_t relu;
     int32_t ksplit, kchunk;
+    int32_t nred, parts; // RUNS (below): shards per output block, runs their K tiles are cut into
 };
 
 // position of one output tile
@@ -108,7 +109,11 @@ struct TilePos {
 };
 
 // j-th output tile of this workgroup; false when the list is exhausted
-__device__ __forceinline__ bool tile_of(const Params3 &p, int j, TilePos *t)
+//   RUNS = false: one item per shard (and K chunk of it).
+//   RUNS = true: shards blk * nred .. + nred - 1 add up into output block blk.  Their K tiles, one shard's after the
+//   other's, are cut into `parts` runs of equal length (to a tile) that need not end where a shard does; run c of block b
+//   writes C[b * parts + c].
+template <bool RUNS = false> __device__ __forceinline__ bool tile_of(const Params3 &p, int j, TilePos *t)
 {
     const int bid = blockIdx.x;
     const int li = bid / core::kXcds + j * p.wg_per_xcd;
@@ -121,6 +126,15 @@ __device__ __forceinline__ bool tile_of(const Params3 &p, int j, TilePos *t)
     core::grouped_tile(r, p.tiles_m, p.tiles_n, &tm, &tn);
     t->m0 = tm * BM3;
     t->n0 = tn * BN3;
+    if constexpr (RUNS) {
+        const int seg = p.K / 64, all = seg * p.nred; // K tiles of a shard, of a block
+        const int blk = t->vshard / p.parts, part = t->vshard - blk * p.parts;
+        const int first = part * all / p.parts, end = (part + 1) * all / p.parts, q = first / seg;
+        t->shard = blk * p.nred + q;
+        t->kbeg = (first - q * seg) * 64;
+        t->klen = (end - first) * 64;
+        return true;
+    }
     t->shard = t->vshard / p.ksplit;
     t->kbeg = (t->vshard - t->shard * p.ksplit) * p.kchunk;
     t->klen = p.K - t->kbeg < p.kchunk ? p.K - t->kbeg : p.kchunk;
@@ -130,12 +144,14 @@ __device__ __forceinline__ bool tile_of(const Params3 &p, int j, TilePos *t)
 // Stream of operand tiles of one operand over the whole work list of the workgroup.
 //   KC = true : operand rows (m for A, n for B) have K contiguous (leading dimension ld = K extent of the matrix)
 //   KC = false: K rows of the matrix are contiguous over the operand's rows (ld = row extent)
-template <int BK, bool KC, bool IS_A> struct Feeder {
+template <int BK, bool KC, bool IS_A, bool RUNS = false> struct Feeder {
+    static_assert(!RUNS || BK == 64, "runs are counted in K tiles of 64");
     static constexpr int NL = loads_per_op<BK>();
     uint32_t voff[NL];  // lane part of the address of this thread's chunks
     const char *base;   // wave-uniform part: start of the current K tile
     uint32_t kstep;     // bytes from one K tile to the next
     int kt, nk, j;      // K tile inside the output tile, their number, ordinal of the output tile
+    int left, shard;    // RUNS: K tiles of the current shard from the current one on, the shard
     bool live;
 
     __device__ __forceinline__ void bind(const Params3 &p, const TilePos &t)
@@ -172,13 +188,17 @@ template <int BK, bool KC, bool IS_A> struct Feeder {
         }
         kt = 0;
         nk = t.klen / BK;
+        if constexpr (RUNS) {
+            left = (p.K - t.kbeg) / BK;
+            shard = t.shard;
+        }
     }
 
     __device__ __forceinline__ void start(const Params3 &p)
     {
         TilePos t;
         j = 0;
-        live = tile_of(p, 0, &t);
+        live = tile_of<RUNS>(p, 0, &t);
         if (live) bind(p, t);
     }
 
@@ -205,10 +225,16 @@ template <int BK, bool KC, bool IS_A> struct Feeder {
         if (kt + 1 < nk) {
             ++kt;
             base += kstep;
+            if constexpr (RUNS)
+                if (--left == 0) { // the run goes on in the next shard: same rows, same pitch, another matrix
+                    ++shard;
+                    base = reinterpret_cast<const char *>(IS_A ? p.A[shard] : p.B[shard]);
+                    left = p.K / BK;
+                }
             return;
         }
         TilePos t;
-        if (tile_of(p, j + 1, &t)) {
+        if (tile_of<RUNS>(p, j + 1, &t)) {
             ++j;
             bind(p, t);
         } else {
@@ -237,7 +263,7 @@ template <int BK, bool KC> __device__ __forceinline__ bf16x8 read_frag3(const ch
     }
 }
 
-template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV>
+template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV, bool RUNS = false>
 __device__ __forceinline__ void run_tiles(const Params3 &p, char *smem)
 {
     static_assert(NS >= 2 && (BK == 32 || BK == 64), "ring shape");
@@ -251,13 +277,13 @@ __device__ __forceinline__ void run_tiles(const Params3 &p, char *smem)
     const int wm0 = (wave / WN) * (TM * 32), wn0 = (wave % WN) * (TN * 32);
     const uint32_t lds0 = dev::lds_addr(smem);
 
-    Feeder<BK, A_KC, true> fa;
-    Feeder<BK, B_KC, false> fb;
+    Feeder<BK, A_KC, true, RUNS> fa;
+    Feeder<BK, B_KC, false, RUNS> fb;
     fa.start(p);
     fb.start(p);
     TilePos cur;
     int jc = 0;
-    if (!tile_of(p, 0, &cur)) return; // no work for this workgroup (uniform)
+    if (!tile_of<RUNS>(p, 0, &cur)) return; // no work for this workgroup (uniform)
 
     int is = 0; // stage the next loads go to
 #pragma unroll
@@ -388,7 +414,7 @@ __device__ __forceinline__ void run_tiles(const Params3 &p, char *smem)
         }
 
         ++jc;
-        if (!tile_of(p, jc, &cur)) break;
+        if (!tile_of<RUNS>(p, jc, &cur)) break;
     }
     // the re-fetches issued past the end of the list must have landed before the workgroup gives up its LDS
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));

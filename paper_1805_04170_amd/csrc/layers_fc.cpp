@@ -102,8 +102,9 @@ tt_status forward(const FcArgs &a, Workspace &ws)
     const int ksplit = pick_ksplit(Ms, Ns, Ks, n, a.dtype, Ks % 8 == 0, Ns % 8 == 0);
     if ((st = plan_output(forms, a.tY, a.Yout, M, N, k, a.dtype, a.layer->act, ws, &op, ksplit)) != TT_OK) return st;
     if (ws.dry) return TT_OK;
-    st = launch_gemm(n, Xa.ptr, Wa.ptr, op.gemm_out, Ms, Ns, Ks, 0, 0, a.dtype, op.gemm_dtype, op.gemm_act, ksplit,
-                     a.stream);
+    st = launch_blocks(&op, k, Xa.ptr, Wa.ptr, Ms, Ns, Ks, 0, 0, a.dtype, a.layer->act, a.stream);
+    if (st == TT_EUNSUPPORTED)
+        st = launch_gemm(n, Xa.ptr, Wa.ptr, op.gemm_out, Ms, Ns, Ks, 0, 0, a.dtype, op.gemm_dtype, op.gemm_act, ksplit, a.stream);
     if (st != TT_OK) return st;
     return finish_output(op, a.tY, a.Yout, M, N, k, a.dtype, a.layer->act, a.stream);
 }
@@ -163,8 +164,10 @@ tt_status backward(const FcArgs &a, Workspace &ws)
     const auto ready = [&](Product &p, int64_t M, int64_t N, int64_t K, int ksplit) {
         p.call = GemmCall{n, p.A.ptr, p.B.ptr, p.op.gemm_out, M, N, K, a.dtype, p.op.gemm_dtype, ksplit};
     };
-    const auto launch = [&](const Product &p, bool dgrad_layout, void *stream) {
+    const auto launch = [&](Product &p, bool dgrad_layout, void *stream) {
         const GemmCall &c = p.call;
+        const tt_status s = launch_blocks(&p.op, k, c.A, c.B, c.M, c.N, c.K, dgrad_layout ? 0 : 1, dgrad_layout ? 1 : 0, c.in_dtype, TT_ACT_NONE, stream);
+        if (s != TT_EUNSUPPORTED) return s;
         return launch_gemm(c.count, c.A, c.B, c.C, c.M, c.N, c.K, dgrad_layout ? 0 : 1, dgrad_layout ? 1 : 0, c.in_dtype, c.out_dtype,
                            p.op.gemm_act, c.ksplit, stream);
     };

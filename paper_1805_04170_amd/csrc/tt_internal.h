@@ -155,6 +155,14 @@ tt_status launch_gemm_v3(int count, const void *const *A, const void *const *B, 
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc, bool b_kc, int out_dtype, int relu,
                          bool vec, int ksplit, int64_t kchunk, void *stream);
 
+// The same engine over output blocks that nred shards each add up into: their K tiles are cut into `parts` runs (gemm_core3.h),
+// run c of block b writes C[b * parts + c].  A, B: a block's shards one after the other.
+tt_status launch_gemm_v3_runs(int nblk, int nred, int parts, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
+                              int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc, bool b_kc, int out_dtype, int relu, void *stream);
+// (gemm.hip) bf16 operands; TT_EUNSUPPORTED where that engine does not take them
+tt_status launch_gemm_runs(int nblk, int nred, int parts, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
+                           int64_t K, int trans_a, int trans_b, int out_dtype, int act, void *stream);
+
 // Same contract for the 256 x 128 engine with two workgroups per CU (gemm_core4.h); K a multiple of 32.
 tt_status launch_gemm_v5(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int relu, void *stream);

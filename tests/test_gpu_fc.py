@@ -105,6 +105,24 @@ def test_three_cuts_ragged_width_and_skip_dx():
     run_layer(64, 1000, 40, 3, "bf16", True, "rCr", "CRC", "CrC", "CrC", "RCR", "232", "323", "212", 82)
 
 
+def run_blocks(b, ni, no, k, forms, relu, seed):
+    # every form sequence once per product, under stored tilings that need the result in another grid and in replicas
+    run_layer(b, ni, no, k, "bf16", relu, "C" * k, "R" * k, "r" * (k - 1) + "C", "C" * k, "R" + "r" * (k - 1), *forms, seed)
+
+
+# What the shards of an F3 cut add up into is run block by block, K cut into as many runs as fill the chip: two and three runs
+# for four shards (the three end inside shards), one (no partial sums, ragged tiles), two blocks of two runs, data and weight gradient
+@pytest.mark.parametrize("b,ni,no,k,forms,relu", [
+    (264, 512, 16384, 2, ("33", None, None), True),
+    (264, 1024, 10744, 2, ("33", None, None), False),
+    (520, 128, 17928, 1, ("3", None, None), True),
+    (264, 1024, 32768, 3, ("323", None, None), False),
+    (264, 10744, 1024, 2, (None, "33", None), True),
+    (1024, 264, 10744, 2, (None, None, "33"), False)])
+def test_shards_of_one_block_run_as_one_product(b, ni, no, k, forms, relu):
+    run_blocks(b, ni, no, k, forms, relu, 97)
+
+
 def _backward_once(fn, lay, b, k, dt, t, forms, Xs, Ws, Ys, dYs, ni, no, **kw):
     dXs = alloc_shards(b, ni, t["dX"], tdtype(dt), fill=float("nan"))
     dWs = alloc_shards(ni, no, t["W"], tdtype(dt), fill=float("nan"))

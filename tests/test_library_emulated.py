@@ -272,6 +272,17 @@ def test_backward_products_in_one_launch_equal_two(on_host, monkeypatch, b, ni, 
     on_host["fc"].run_together(b, ni, no, k, dt, 94, aux_stream=16)
 
 
+@pytest.mark.parametrize("runs", [1, 2, 3, 4])
+@pytest.mark.parametrize("k,forms", [(2, "33"), (3, "323")])
+def test_shards_of_one_block_run_as_one_product(on_host, monkeypatch, runs, k, forms):
+    # (four shards of two K tiles in three runs: one starts inside the third shard; 264: ragged tiles)
+    monkeypatch.setenv("TT_RUNS", str(runs))
+    cut = 1 << forms.count("3")
+    on_host["fc"].run_blocks(64 if k == 3 else 72, 128 * cut, 272, k, (forms, None, None), True, 97)
+    on_host["fc"].run_blocks(264, 64, 64 * cut, k, (None, forms, None), False, 98)
+    on_host["fc"].run_blocks(64 * cut, 264, 80, k, (None, None, forms), False, 99)
+
+
 def test_forward_with_the_library_s_own_scratch(on_host):
     import test_zz_no_alloc as na
     na.test_static_scratch_forward_twice_second_smaller()
