@@ -358,30 +358,35 @@ __global__ __launch_bounds__(WN * 128, WN / 2) void conv_wgrad_split_kernel(cons
 
 // The same product on the engine that loads tiles straight into LDS (gemm_core2.h): both operands are stored with the
 // pixels as the slow dimension, so their tiles go into LDS as they lie in memory and the fragments come out through LDS
-// transpose reads; no register transposes and no LDS store instructions.  256 x 256 tiles, eight waves, one workgroup per CU.
-struct SegDenseRC2 {
+// transpose reads; no register transposes and no LDS store instructions.  BM x 256 tiles, eight waves.
+// TAIL: a shard's pixels are no whole number of K tiles; what lies past them in its last tile is read as zeros.
+template <bool TAIL> struct SegDenseRC2 {
     static constexpr bool KC = false;
     Segment seg;
-    int ld, rows;
+    int ld, rows, pixels;
     template <int ROWS> __device__ __forceinline__ void issue(int row0, int k0, char *lds) const
     {
-        static_assert(ROWS == 256, "tile side");
+        constexpr int CPR = ROWS / 8, KR = core2::kThreads2 / CPR; // chunks per k-row, k-rows that the threads cover at once
         int kshift;
         const char *base = seg.locate(k0, &kshift);
         const int tid = threadIdx.x, wave = tid >> 6;
-        const int kr = tid >> 5, pc = tid & 31; // chunk tid + 512 i: k-row kr + 16 i, position pc (see core2::issue_tile)
+        const int kr = tid / CPR, pc = tid % CPR; // chunk tid + 512 i: k-row kr + KR i, position pc (see core2::issue_tile)
         int r0 = row0 + ((pc ^ ((kr & 3) << 1)) << 3);
         r0 = r0 < rows ? r0 : rows - 8; // rows past the end only feed C rows that are never stored
-        const char *a = base + ((size_t)(k0 + kshift + kr) * (size_t)ld + (size_t)r0) * 2;
+        const int px = k0 + kshift + kr;
+        const char *a = base + ((size_t)px * (size_t)ld + (size_t)r0) * 2;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            core2::load_chunk_to_lds(a + (size_t)i * 16 * (size_t)ld * 2, lds + (size_t)(wave * 64 + i * core2::kThreads2) * 16);
+        for (int i = 0; i < ROWS * core::BK / 8 / core2::kThreads2; ++i) {
+            const void *c = a + (size_t)i * KR * (size_t)ld * 2;
+            if (TAIL && px + i * KR >= pixels) c = core2::g_zero_chunk;
+            core2::load_chunk_to_lds(c, lds + (size_t)(wave * 64 + i * core2::kThreads2) * 16);
+        }
     }
 };
 
 struct PixelStep { int dn, dp, dq; }; // a run of pixels as whole images, whole rows and columns
 
-struct SegGatherRC2 {
+template <bool TAIL> struct SegGatherRC2 {
     static constexpr bool KC = false;
     Segment seg;
     int H, W, P, Q, S, pad, Cs, rows, Ns;
@@ -410,21 +415,21 @@ struct SegGatherRC2 {
         r0 = r0 < rows ? r0 : rows - 8;
         const int tap = r0 / Cs, c0 = r0 - tap * Cs;
         const int fr = tap / S, dy = fr - pad, dx = tap - fr * S - pad;
-        if (k0 == 0) {
-            const int kl = kshift + kr; // pixel inside the shard
+        if (k0 == 0 || (TAIL && k0 + kshift == 0)) { // (with a tail the next shard does not start where this one ends)
+            const int kl = k0 + kshift + kr; // pixel inside the shard
             n_ = kl / (P * Q);
             const int rem = kl - n_ * (P * Q);
             p_ = rem / Q;
             q_ = rem - p_ * Q;
         } else {
             step(s64, P, Q, n_, p_, q_);
-            n_ -= n_ >= Ns ? Ns : 0; // the run went on into the next shard
+            if (!TAIL) n_ -= n_ >= Ns ? Ns : 0; // the run went on into the next shard
         }
         int n = n_, p = p_, q = q_;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int iy = p + dy, ix = q + dx;
-            const bool ok = iy >= 0 && iy < H && ix >= 0 && ix < W;
+            const bool ok = iy >= 0 && iy < H && ix >= 0 && ix < W && (!TAIL || n < Ns);
             const char *a = base + ((size_t)((n * H + iy) * W + ix) * (size_t)Cs + (size_t)c0) * 2;
             core2::load_chunk_to_lds(ok ? (const void *)a : (const void *)core2::g_zero_chunk,
                                      lds + (size_t)(wave * 64 + i * core2::kThreads2) * 16);
@@ -443,7 +448,8 @@ __device__ __forceinline__ PixelStep pixel_step(int d, int P, int Q)
     return s;
 }
 
-__global__ __launch_bounds__(core2::kThreads2, 2) void conv_wgrad_split2_kernel(const WgradSplitParams w)
+template <int BM, bool TAIL> // (BM = 64: two workgroups fit a CU's LDS)
+__global__ __launch_bounds__(core2::kThreads2, BM == 64 ? 4 : 2) void conv_wgrad_split2_kernel(const WgradSplitParams w)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     const ConvParams &p = w.c;
@@ -452,21 +458,21 @@ __global__ __launch_bounds__(core2::kThreads2, 2) void conv_wgrad_split2_kernel(
     const int tiles = p.tiles_m * p.tiles_n;
     const int bp = logical / tiles, r = logical - bp * tiles;
     const int blk = bp / w.sp.parts, part = bp - blk * w.sp.parts;
-    const int n0 = (r % p.tiles_n) * 256, m0 = (r / p.tiles_n) * 256;
+    const int n0 = (r % p.tiles_n) * 256, m0 = (r / p.tiles_n) * BM;
     const int G = w.sp.nred * w.sp.ktps;
     const int g0 = (int)((int64_t)part * G / w.sp.parts), g1 = (int)((int64_t)(part + 1) * G / w.sp.parts);
     const int K = (g1 - g0) * core::BK;
     const ConvGeom &g = p.g;
-    SegDenseRC2 la;
+    SegDenseRC2<TAIL> la;
     la.seg.bind(w.c.A, w.sp.red_ids, w.sp.blk_ids[blk], w.sp.nred, w.sp.ktps, g0);
-    la.ld = g.Ks; la.rows = p.M;
-    SegGatherRC2 lb;
+    la.ld = g.Ks; la.rows = p.M; la.pixels = p.K;
+    SegGatherRC2<TAIL> lb;
     lb.seg.bind(w.c.B, w.sp.red_ids, w.sp.blk_ids[blk], w.sp.nred, w.sp.ktps, g0);
     lb.H = g.H; lb.W = g.W; lb.P = g.P; lb.Q = g.Q; lb.S = g.S; lb.pad = g.pad; lb.Cs = g.Cs; lb.rows = p.N; lb.Ns = g.Ns;
     lb.s16 = pixel_step(16, g.P, g.Q);
     lb.s64 = pixel_step(64, g.P, g.Q);
     lb.n_ = lb.p_ = lb.q_ = 0;
-    core2::tile_product2<false, true>(la, lb, p.C[bp], p.ldc, p.M, p.N, K, m0, n0, false, reinterpret_cast<char *>(smem));
+    core2::tile_product2<false, true, BM>(la, lb, p.C[bp], p.ldc, p.M, p.N, K, m0, n0, false, reinterpret_cast<char *>(smem));
 }
 
 // Filters [Ks][R][S][Cs] -> [Cs][R][S][Ks] with the taps reversed: with these the gradient w.r.t. the input IS a forward
@@ -682,6 +688,15 @@ template <bool OUT_BF16> tt_status launch_wgrad(ConvParams &p, int count, hipStr
                  : launch(conv_wgrad_kernel<128, 128, 2, 2, false, OUT_BF16>, sm, p, 128, 128, 256, count, s);
 }
 
+template <int BM, bool TAIL> tt_status launch_split2(const WgradSplitParams &w, hipStream_t s)
+{
+    auto kern = conv_wgrad_split2_kernel<BM, TAIL>;
+    constexpr size_t sm = core2::smem_bytes2<BM>();
+    if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), sm) != TT_OK) return TT_EDEVICE;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)w.c.per_xcd * kXcds), dim3(core2::kThreads2), sm, s, w);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+
 bool aligned16(const void *const *ptrs, int n)
 {
     for (int i = 0; i < n; ++i)
@@ -803,25 +818,27 @@ tt_status launch_conv(int op, int count, const void *const *A, const void *const
 // Weight-gradient products of all output blocks with each block's pixel range cut into `parts` partial sums (see
 // SplitGeom).  A, B: dY and X shards by shard id (2^k entries); C: nblk * parts fp32 buffers of Ks x (R*S*Cs), buffer
 // blk * parts + part.  blk_ids / red_ids: id bits of block b / of a block's q-th shard.  Ns images per shard; the pixels
-// of a shard must be a multiple of 64 (TT_EUNSUPPORTED otherwise: the caller takes the per-shard path).
+// of a shard are counted in K tiles of 64, the last one short where they do not divide (not on engine 1).
 tt_status launch_conv_wgrad_split(int k, int nblk, int nred, const uint8_t *blk_ids, const uint8_t *red_ids, int parts,
                                   const void *const *A, const void *const *B, void *const *C, int64_t Ns, int64_t Cs,
                                   int64_t Ks, int64_t H, int64_t W, int64_t R, int64_t S, int64_t pad, int engine,
                                   void *stream)
 {
-    if (engine != 1 && engine != 2) return TT_EINVAL;
+    if (engine < 1 || engine > 4) return TT_EINVAL;
+    const int tile_m = engine <= 2 ? 256 : engine == 3 ? 128 : 64;
     if (!A || !B || !C || !blk_ids || !red_ids || !valid_k(k) || nblk < 1 || nred < 1 || nblk * nred != (1 << k)) return TT_EINVAL;
     if (parts < 1 || nblk * parts > kMaxShards) return TT_EINVAL;
     if (Ns <= 0 || Cs <= 0 || Ks <= 0 || H <= 0 || W <= 0 || R <= 0 || S <= 0 || pad < 0) return TT_EINVAL;
     const int64_t P = H + 2 * pad - R + 1, Q = W + 2 * pad - S + 1;
     if (P <= 0 || Q <= 0) return TT_EINVAL;
-    if (Cs % 8 || Ks % 8 || R * S > 32 || Ks <= 128) return TT_EUNSUPPORTED;
+    if (Cs % 8 || Ks % 8 || R * S > 32) return TT_EUNSUPPORTED;
     const int64_t lim = int64_t(1) << 30, pixels = Ns * P * Q;
     if (Ns * H * W * Cs >= lim || pixels * Ks >= lim || Ks * R * S * Cs >= lim) return TT_EUNSUPPORTED;
-    if (pixels % core::BK || (int64_t)nred * (pixels / core::BK) < parts) return TT_EUNSUPPORTED;
+    const int64_t ktps = (pixels + core::BK - 1) / core::BK;
+    if ((engine == 1 && pixels % core::BK) || (int64_t)nred * ktps < parts) return TT_EUNSUPPORTED;
     {
         // shards one work item can touch: its K tiles, rounded up to whole shards, plus one for a start inside a shard
-        const int64_t ktps = pixels / core::BK, len = (nred * ktps + parts - 1) / parts;
+        const int64_t len = (nred * ktps + parts - 1) / parts;
         if ((len + ktps - 1) / ktps + 1 > kSegs && nred > kSegs) return TT_EUNSUPPORTED;
     }
     const int n = 1 << k;
@@ -843,23 +860,24 @@ tt_status launch_conv_wgrad_split(int k, int nblk, int nred, const uint8_t *blk_
     p.members = 1;
     p.member_cols = 0;
     p.M = (int32_t)Ks; p.N = (int32_t)(R * S * Cs); p.K = (int32_t)pixels; p.ldc = p.N;
-    w.sp.parts = parts; w.sp.nred = nred; w.sp.ktps = (int32_t)(pixels / core::BK);
+    w.sp.parts = parts; w.sp.nred = nred; w.sp.ktps = (int32_t)ktps;
     const uint64_t x_b = (uint64_t)(Ns * H * W * Cs) * 2, y_b = (uint64_t)(pixels * Ks) * 2, w_b = (uint64_t)(Ks * R * S * Cs) * 4;
     ProfileScope scope(stream, TT_K_CONV_WGRAD, n, p.M, p.N, p.K, (x_b + y_b) * (uint64_t)n + w_b * (uint64_t)(nblk * parts),
                        2ull * (uint64_t)p.M * (uint64_t)p.N * (uint64_t)p.K * (uint64_t)n);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     // engine 1: register-staged, 256 x 128 tiles, four waves, two workgroups per CU (the tile the per-shard weight
-    // gradient uses); engine 2: straight into LDS, 256 x 256 tiles, eight waves, one workgroup per CU
-    p.tiles_m = (p.M + 255) / 256;
-    p.tiles_n = (p.N + (engine == 2 ? 255 : 127)) / (engine == 2 ? 256 : 128);
+    // gradient uses); engines 2, 3, 4: straight into LDS, 256 / 128 / 64 x 256 tiles, eight waves
+    p.tiles_m = (p.M + tile_m - 1) / tile_m;
+    p.tiles_n = (p.N + (engine >= 2 ? 255 : 127)) / (engine >= 2 ? 256 : 128);
     const int64_t total = (int64_t)p.tiles_m * p.tiles_n * nblk * parts;
     if (total >= (int64_t(1) << 30)) return TT_EUNSUPPORTED;
     p.total = (int32_t)total;
     p.per_xcd = (int32_t)((total + kXcds - 1) / kXcds);
-    if (engine == 2) {
-        auto kern = conv_wgrad_split2_kernel;
-        if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), core2::kSmemBytes) != TT_OK) return TT_EDEVICE;
-        hipLaunchKernelGGL(kern, dim3((uint32_t)p.per_xcd * kXcds), dim3(core2::kThreads2), core2::kSmemBytes, s, w);
+    if (engine >= 2) {
+        const bool tail = pixels % core::BK != 0;
+        if (tile_m == 256) return tail ? launch_split2<256, true>(w, s) : launch_split2<256, false>(w, s);
+        if (tile_m == 128) return tail ? launch_split2<128, true>(w, s) : launch_split2<128, false>(w, s);
+        return tail ? launch_split2<64, true>(w, s) : launch_split2<64, false>(w, s);
     } else {
         auto kern = conv_wgrad_split_kernel<256, 128, 2, 2>;
         constexpr size_t sm = core::smem_bytes<256, 128>();

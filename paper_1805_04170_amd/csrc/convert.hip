@@ -421,7 +421,7 @@ tt_status launch_reduce(void *const *dst, const uint8_t *Bl, int out_dtype, cons
                         const uint8_t *zl, int k, int64_t rows, int64_t cols, int act, int ksplit, void *stream, bool per_block)
 {
     // in-shard splits come in powers of two (the launch code that cuts K makes no others); per-block partial sums in any number
-    if (ksplit < 1 || (!per_block && (ksplit & (ksplit - 1)) != 0) || (ksplit << k) > kMaxShards) return TT_EINVAL;
+    if (ksplit < 1 || ksplit > kMaxShards || (!per_block && ((ksplit & (ksplit - 1)) != 0 || (ksplit << k) > kMaxShards))) return TT_EINVAL;
     if (!dst || !partials || !valid_k(k) || rows < 0 || cols < 0) return TT_EINVAL;
     if (rows == 0 || cols == 0) return TT_OK;
     if (out_dtype != TT_F32 && out_dtype != TT_BF16) return TT_EINVAL;
@@ -432,24 +432,24 @@ tt_status launch_reduce(void *const *dst, const uint8_t *Bl, int out_dtype, cons
     const int n = 1 << k;
     for (int s = 0; s < n; ++s)
         if (!dst[s]) return TT_EINVAL;
-    // per_block: only the table entries of shard ids with zero bits at the kRed cuts are used
-    for (int s = 0; s < n; ++s)
-        for (int c = 0; c < ksplit; ++c)
-            if (!(per_block && ((uint32_t)s & Z.maskX)) && !partials[s * ksplit + c]) return TT_EINVAL;
+    const int n_tab = (per_block ? n >> Z.kX : n) * ksplit; // partial buffers
+    if (n_tab > kMaxShards) return TT_EINVAL;
+    for (int s = 0; s < n_tab; ++s)
+        if (!partials[s]) return TT_EINVAL;
     int64_t piece_rows = Z.srows < B.srows ? Z.srows : B.srows;
     int64_t piece_cols = Z.scols < B.scols ? Z.scols : B.scols;
     const size_t out_b = out_dtype == TT_BF16 ? 2 : 4;
     int ev = 4;
     bool parts_aligned = true;
-    for (int s = 0; s < n * ksplit; ++s)
-        if (!(per_block && ((uint32_t)(s / ksplit) & Z.maskX)) && reinterpret_cast<uintptr_t>(partials[s]) % 16) parts_aligned = false;
+    for (int s = 0; s < n_tab; ++s)
+        if (reinterpret_cast<uintptr_t>(partials[s]) % 16) parts_aligned = false;
     if (piece_cols % 4 || !parts_aligned ||
         !aligned_all(const_cast<const void *const *>(dst), n, 4 * out_b))
         ev = 1;
 
     ReduceParams p;
     for (int s = 0; s < kMaxShards; ++s) {
-        p.part[s] = (s < n * ksplit && !(per_block && ((uint32_t)(s / ksplit) & Z.maskX))) ? partials[s] : nullptr;
+        p.part[s] = s < n_tab ? partials[s] : nullptr;
         p.dst[s] = s < n ? dst[s] : nullptr;
         p.rep_ids[s] = 0;
         p.red_ids[s] = 0;
@@ -459,6 +459,11 @@ tt_status launch_reduce(void *const *dst, const uint8_t *Bl, int out_dtype, cons
     p.k = (uint32_t)k;
     p.nrep = 1u << B.kX;
     p.nred = per_block ? 1u : 1u << Z.kX;
+    if (per_block) { // the kernel looks a block up by its number: the masks without the kRed cuts' bits
+        const uint32_t kept = (uint32_t)(n - 1) & ~Z.maskX;
+        p.Z.maskR = extract(Z.maskR, kept, k);
+        p.Z.maskC = extract(Z.maskC, kept, k);
+    }
     p.ksplit = (uint32_t)ksplit;
     p.relu = act == TT_ACT_RELU;
     for (uint32_t r = 0; r < p.nrep; ++r) p.rep_ids[r] = (uint8_t)deposit(r, B.maskX, k);

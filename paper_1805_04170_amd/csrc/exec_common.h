@@ -170,11 +170,11 @@ inline int pick_ksplit(int64_t M, int64_t N, int64_t K, int count, int dtype, bo
 // Returns the number of runs, or 0 where a product per shard is no slower.  The estimate, in microseconds with all CUs at
 // work: 2.0 per K tile of a 256 x 256 tile, 9 to write its fp32 results (5 in bf16), 5.5 TB/s for the reduction (4 TB/s
 // for the copy into the stored tiling that one bf16 result needs).
-inline int pick_runs(int64_t M, int64_t N, int64_t K, int nblk, int nred, int k)
+inline int pick_runs(int64_t M, int64_t N, int64_t K, int nblk, int nred)
 {
     if (nred < 2 || K % 64 || N % 8) return 0;
     const int forced = tuning_int("TT_RUNS", 0); // development builds only
-    if (forced) return forced <= nred && (forced << k) <= kMaxShards ? forced : 0;
+    if (forced) return forced <= nred ? forced : 0;
     if (M <= 128 || N <= 128) return 0;
     const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256) * nblk;
     if (tiles * nred < 200) return 0; // (too few 256 x 256 tiles: such launches run on other engines, launch_gemm)
@@ -186,7 +186,7 @@ inline int pick_runs(int64_t M, int64_t N, int64_t K, int nblk, int nred, int k)
     };
     int best = 0;
     double best_us = 0.95 * us(nred);
-    for (int parts = 1; parts <= nred && (parts << k) <= kMaxShards; ++parts)
+    for (int parts = 1; parts <= nred; ++parts) // (as many result buffers as are planned)
         if (us(parts) < best_us) { best = parts; best_us = us(parts); }
     return best;
 }
@@ -205,7 +205,7 @@ inline tt_status launch_blocks(OutputPlan *op, int k, const void *const *A, cons
     int kred = 0;
     for (int j = 0; j < k; ++j) kred += (red >> j) & 1;
     const int nred = 1 << kred, nblk = 1 << (k - kred);
-    const int parts = pick_runs(M, N, K, nblk, nred, k);
+    const int parts = pick_runs(M, N, K, nblk, nred);
     if (!parts) return TT_EUNSUPPORTED;
     const void *a[kMaxShards], *b[kMaxShards];
     void *out[kMaxShards];
@@ -222,15 +222,13 @@ inline tt_status launch_blocks(OutputPlan *op, int k, const void *const *A, cons
     if (st != TT_OK) return st;
     op->parts = parts;
     op->gemm_dtype = out_dtype;
-    // where the output kernels look: a single result stands for every shard of its block, partial sum c of a block at its
-    // shard with zero bits at the F3 cuts
+    // where the output kernels look: a single result stands for every shard of its block, partial sum c of block b at b * parts + c
     for (int i = 0; i < kMaxShards; ++i) op->gemm_out[i] = nullptr;
     for (int blk = 0; blk < nblk; ++blk) {
-        const uint32_t s0 = deposit((uint32_t)blk, keep, k);
         if (parts == 1)
-            for (int q = 0; q < nred; ++q) op->gemm_out[s0 | deposit((uint32_t)q, red, k)] = out[blk];
+            for (int q = 0; q < nred; ++q) op->gemm_out[deposit((uint32_t)blk, keep, k) | deposit((uint32_t)q, red, k)] = out[blk];
         else
-            for (int c = 0; c < parts; ++c) op->gemm_out[(int)s0 * parts + c] = out[blk * parts + c];
+            for (int c = 0; c < parts; ++c) op->gemm_out[blk * parts + c] = out[blk * parts + c];
     }
     return TT_OK;
 }

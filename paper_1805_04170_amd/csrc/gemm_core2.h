@@ -111,15 +111,24 @@ template <int ROWS, bool KC> __device__ __forceinline__ bf16x8 read_frag(const c
     }
 }
 
-// C tile (m0, n0) of C = A B; 512 threads; smem: kSmemBytes, 16-byte aligned.
-template <bool OUT_BF16, bool VEC_STORE, class LA, class LB>
+// LDS of a product on BM x 256 tiles: two stages, or the strips of the write-out
+template <int BM> constexpr size_t smem_bytes2()
+{
+    constexpr size_t stages = 2 * (size_t)(BM + BN2) * BK * 2, strips = 8 * 32 * (64 + 4) * sizeof(float);
+    return stages > strips ? stages : strips;
+}
+static_assert(smem_bytes2<BM2>() == kSmemBytes, "the dense kernels' size");
+
+// C tile (m0, n0) of C = A B; 512 threads; smem: smem_bytes2<BM>(), 16-byte aligned.
+// BM = 128 or 64: products with few rows, whose 256-row tile would take in and multiply rows that do not exist.
+template <bool OUT_BF16, bool VEC_STORE, int BM = BM2, class LA, class LB>
 __device__ __forceinline__ void tile_product2(const LA &la, const LB &lb, void *Cv, int ldc, int M, int N, int K, int m0,
                                               int n0, bool relu, char *smem)
 {
-    constexpr int TM = 4, TN = 2, WN = 4; // 2 x 4 waves, 128 x 64 per wave
+    constexpr int TM = BM / 64, TN = 2, WN = 4; // 2 x 4 waves, BM / 2 x 64 per wave
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (wave / WN) * (TM * 32), wn0 = (wave % WN) * (TN * 32);
-    constexpr int A_BYTES = BM2 * BK * 2;
+    constexpr int A_BYTES = BM * BK * 2, STAGE = (BM + BN2) * BK * 2;
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -130,15 +139,15 @@ __device__ __forceinline__ void tile_product2(const LA &la, const LB &lb, void *
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
     const int nk = (K + BK - 1) / BK;
-    la.template issue<BM2>(m0, 0, smem);
+    la.template issue<BM>(m0, 0, smem);
     lb.template issue<BN2>(n0, 0, smem + A_BYTES);
 
     for (int kt = 0; kt < nk; ++kt) {
-        char *cur = smem + (kt & 1) * kStageBytes, *nxt = smem + ((kt & 1) ^ 1) * kStageBytes;
+        char *cur = smem + (kt & 1) * STAGE, *nxt = smem + ((kt & 1) ^ 1) * STAGE;
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's chunks of tile kt have landed
         __syncthreads();                     // everyone's have; and everyone is done reading the other stage
         if (kt + 1 < nk) {
-            la.template issue<BM2>(m0, (kt + 1) * BK, nxt);
+            la.template issue<BM>(m0, (kt + 1) * BK, nxt);
             lb.template issue<BN2>(n0, (kt + 1) * BK, nxt + A_BYTES);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -147,7 +156,7 @@ __device__ __forceinline__ void tile_product2(const LA &la, const LB &lb, void *
         for (int ks = 0; ks < BK / 16; ++ks) {
             bf16x8 af[TM], bf[TN];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = read_frag<BM2, LA::KC>(cur, wm0 + i * 32, ks, lane);
+            for (int i = 0; i < TM; ++i) af[i] = read_frag<BM, LA::KC>(cur, wm0 + i * 32, ks, lane);
 #pragma unroll
             for (int j = 0; j < TN; ++j) bf[j] = read_frag<BN2, LB::KC>(cur + A_BYTES, wn0 + j * 32, ks, lane);
 #pragma unroll
@@ -181,7 +190,7 @@ __device__ __forceinline__ void tile_product2(const LA &la, const LB &lb, void *
     } else {
         constexpr int SW = TN * 32, SLD = SW + 4;
         float *strip = reinterpret_cast<float *>(smem) + wave * (32 * SLD);
-        static_assert(8 * 32 * SLD * sizeof(float) <= kSmemBytes, "strip staging fits");
+        static_assert(8 * 32 * SLD * sizeof(float) <= smem_bytes2<BM>(), "strip staging fits");
         constexpr int EPV = OUT_BF16 ? 8 : 4, VPR = SW / EPV, RPI = 64 / VPR;
         const int vr = lane / VPR, vc = (lane % VPR) * EPV;
 #pragma unroll

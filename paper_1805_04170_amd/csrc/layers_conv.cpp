@@ -69,29 +69,34 @@ tt_status filter_view(Sharded *s, const void *const *ptrs, const tt_tiling &t, i
 }
 
 // Number of partial sums per filter block, and the tile engine, for the weight gradient with an evenly cut reduction
-// range; parts = 0 when that path does not apply.  The work items (output tiles times partial sums) run in rounds of as
-// many as the chip holds; a round takes as long as one item's K tiles; every partial sum is written and read once more by
-// the reduction.  Times in microseconds from measured rates on MI355X with the chip full: engine 1 (256 x 128 tiles, 512
-// resident) 3.9 us per K tile, engine 2 (256 x 256 tiles, 256 resident) 2.6 us; partial sums at 4 TB/s.
+// range.  The work items (output tiles times partial sums) run in rounds of as many as the chip holds; a round takes as long
+// as one item's K tiles; every partial sum is written and read once more by the reduction.  Times in microseconds from
+// measured rates on MI355X with the chip full: engine 1 (256 x 128 tiles, 512 resident) 3.9 us per K tile, engine 2 (256 x 256,
+// 256 resident) 2.6 us, engines 3 and 4 (128 and 64 x 256, 256 and 512 resident) 1.9 and 2.4; 4 us to start and write an item;
+// partial sums at 4 TB/s.  What it replaced where a shard's pixels are no multiple of 64 or it has at most 128 output channels,
+// one workgroup per tile and shard (batch-split group of images): 96 x 34 x 46 pixels, 128 to 384 channels, 8 shards 493 -> 266 us;
+// 24 x 35 x 41, 384 to 64, 8 shards 97 -> 38; 14 x 42 x 35, 80 to 96, 1x1 filters, 2 shards 209 -> 23; 32 x 14 x 14, 64 to 64, 8 shards 29 -> 24.
 struct WgradChoice { int parts, engine; };
-WgradChoice pick_wgrad_parts(int k, int nblk, int nred, int64_t ktps, int64_t Ks, int64_t ncols, size_t blk_bytes)
+WgradChoice pick_wgrad_parts(int nblk, int nred, int64_t pixels, int64_t Ks, int64_t ncols, size_t blk_bytes)
 {
-    const int64_t total_kt = (int64_t)nred * ktps;
-    const int max_parts = kMaxShards >> k;
+    static const struct { int64_t tile_m, tile_n, resident; double kt_us; } engines[4] = {
+        {256, 128, 512, 3.9}, {256, 256, 256, 2.6}, {128, 256, 256, 1.9}, {64, 256, 512, 2.4}};
+    const int64_t ktps = (pixels + 63) / 64, total_kt = (int64_t)nred * ktps;
+    const int max_parts = kMaxShards / nblk;
     WgradChoice best{0, 1};
     double best_us = 0.0;
     const int forced = tuning_int("TT_WGRAD_PARTS", 0), forced_engine = tuning_int("TT_WGRAD_ENGINE", 0); // development builds only
-    for (int engine = 1; engine <= 2; ++engine) {
+    for (int engine = 1; engine <= 4; ++engine) {
         if (forced_engine && engine != forced_engine) continue;
-        const int64_t tile_n = engine == 2 ? 256 : 128, resident = engine == 2 ? 256 : 512;
-        const double kt_us = engine == 2 ? 2.6 : 3.9;
-        const int64_t tiles = ((Ks + 255) / 256) * ((ncols + tile_n - 1) / tile_n);
+        if (engine == 1 && pixels % 64) continue;
+        const auto &e = engines[engine - 1];
+        const int64_t tiles = ((Ks + e.tile_m - 1) / e.tile_m) * ((ncols + e.tile_n - 1) / e.tile_n);
         for (int parts = 1; parts <= max_parts && parts <= total_kt; ++parts) {
             const int64_t len = (total_kt + parts - 1) / parts;
             if (nred > 4 && (len + ktps - 1) / ktps + 1 > 4) continue; // an item may touch at most four shards
             if (parts == forced) return WgradChoice{parts, engine};
-            const int64_t rounds = (nblk * tiles * parts + resident - 1) / resident;
-            const double us = (double)rounds * (double)len * kt_us + (double)nblk * parts * (double)blk_bytes * 2.0 / 4.0e6;
+            const int64_t rounds = (nblk * tiles * parts + e.resident - 1) / e.resident;
+            const double us = (double)rounds * ((double)len * e.kt_us + 4.0) + (double)nblk * parts * (double)blk_bytes * 2.0 / 4.0e6;
             if (best.parts == 0 || us < best_us) { best = WgradChoice{parts, engine}; best_us = us; }
         }
     }
@@ -334,7 +339,7 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
             const int64_t Cm = m1 ? d.C : d.C >> k1, Km = m2 ? d.K : d.K >> k2, Ns = d.N >> k3; // per product
             const int64_t lim = int64_t(1) << 30; // the evenly cut product's own limits (32-bit offsets, 16-byte chunks, tap masks)
             const bool fits = Cm % 8 == 0 && Km % 8 == 0 && Km > 128 && rs <= 32 && Ns * hw * Cm < lim && Ns * pq * Km < lim &&
-                              Km * rs * Cm < lim && (Ns * pq) % 64 == 0;
+                              Km * rs * Cm < lim && Ns * pq >= 8;
             uint32_t mask_m = 0;
             uint8_t zr[TT_MAX_K], zp[TT_MAX_K]; // letters for the reduction (k cuts) and for the product (the cuts kept)
             tt_tiling aGm = aG, aXm = transpose_tiling(aXt, k);
@@ -353,7 +358,7 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
             if ((m1 || m2) && fits && make_grid(zp, kp, rows_w, d.C, &gp) && make_grid(zr, k, rows_w, d.C, &gr)) {
                 const int nred = 1 << gp.kX, nblk = (1 << kp) >> gp.kX;
                 const size_t blk_bytes = (size_t)gp.srows * (size_t)gp.scols * 4;
-                const WgradChoice choice = pick_wgrad_parts(k, nblk, nred, Ns * pq / 64, Km, rs * Cm, blk_bytes);
+                const WgradChoice choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes);
                 if (choice.parts > 0) {
                     if ((st = prepare_operand(X, aXm, k, esz, nullptr, a.dtype, ws, a.stream, &Xa)) != TT_OK) return st;
                     if ((st = prepare_operand(G, aGm, k, esz, gated ? nullptr : &Y, a.dtype, ws, a.stream, &Ga)) != TT_OK) return st;
@@ -368,8 +373,7 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
                     for (int b = 0; b < nblk; ++b)
                         for (int c = 0; c < parts; ++c) {
                             sums[b * parts + c] = ws.take(blk_bytes);
-                            // block b among the k cuts: its id in the product's numbering, spread over the cuts that were kept
-                            table[deposit((uint32_t)blk_ids[b], mask_keep, k) * parts + c] = static_cast<const float *>(sums[b * parts + c]);
+                            table[b * parts + c] = static_cast<const float *>(sums[b * parts + c]);
                         }
                     if (ws.overflow) return TT_EWORKSPACE;
                     if (ws.dry) return TT_OK;
@@ -397,14 +401,15 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         const int64_t Ns = d.N >> k3, Cs = d.C >> k1, Ks = d.K >> k2;
         // First choice: the pixels of all shards that add up into one filter block form one reduction range, cut into
         // `parts` equal runs (pick_wgrad_parts; conv.hip says why that is free).  The partial sums then belong to a block,
-        // not to a shard: buffer c of block b sits at table entry (b's shard id with zero F3 bits) * parts + c, which is
-        // where the reduction kernel looks for it.
+        // not to a shard: the reduction kernel looks for buffer c of block b at table entry b * parts + c.
         Grid gz;
         if (!make_grid(zl, k, d.K * rs, d.C, &gz)) return TT_EINFEASIBLE;
         const int nred = 1 << gz.kX, nblk = n >> gz.kX;
         const size_t blk_bytes = (size_t)gz.srows * (size_t)gz.scols * 4;
-        const WgradChoice choice = bf16 && (Ns * pq) % 64 == 0 && Ks > 128 ? pick_wgrad_parts(k, nblk, nred, Ns * pq / 64, Ks, rs * Cs, blk_bytes)
-                                                                     : WgradChoice{0, 1};
+        const int64_t lim = int64_t(1) << 30; // (the launcher's own conditions)
+        const bool even = bf16 && Cs % 8 == 0 && Ks % 8 == 0 && rs <= 32 && Ns * hw * Cs < lim && Ns * pq * Ks < lim && Ks * rs * Cs < lim &&
+                          Ns * pq >= 8;
+        const WgradChoice choice = even ? pick_wgrad_parts(nblk, nred, Ns * pq, Ks, rs * Cs, blk_bytes) : WgradChoice{0, 1};
         const int parts = choice.parts;
         if (parts > 0 && !(parts == 1 && nred == 1)) {
             uint8_t blk_ids[kMaxShards], red_ids[kMaxShards];
@@ -417,7 +422,7 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
             for (int b = 0; b < nblk; ++b)
                 for (int c = 0; c < parts; ++c) {
                     sums[b * parts + c] = ws.take(blk_bytes);
-                    table[blk_ids[b] * parts + c] = static_cast<const float *>(sums[b * parts + c]);
+                    table[b * parts + c] = static_cast<const float *>(sums[b * parts + c]);
                 }
             if (ws.overflow) return TT_EWORKSPACE;
             if (ws.dry) return TT_OK;

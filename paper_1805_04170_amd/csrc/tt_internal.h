@@ -121,7 +121,8 @@ tt_status launch_convert(void *const *dst, const uint8_t *B, const void *const *
                          void *stream);
 // ksplit > 1: every shard comes as ksplit partial buffers (partials[s * ksplit + c]) that are summed as well.
 // per_block: the partial sums of an output block are not held shard by shard but as ksplit buffers per block (any
-// ksplit >= 1), partials[b * ksplit + c] with b the block's shard id with zero bits at the kRed cuts.
+// ksplit >= 1, at most kMaxShards buffers in all), partials[b * ksplit + c] with b the block's number: its shards' id bits at
+// the cuts that are not kRed, closed up.
 tt_status launch_reduce(void *const *dst, const uint8_t *B, int out_dtype, const float *const *partials,
                         const uint8_t *zletters /* R, C or kRed per cut */, int k, int64_t rows, int64_t cols, int act,
                         int ksplit, void *stream, bool per_block = false);
@@ -206,7 +207,7 @@ tt_status launch_conv_fused(int op, int groups, int members, const void *const *
 tt_status launch_conv_wgrad_split(int k, int nblk, int nred, const uint8_t *blk_ids, const uint8_t *red_ids, int parts,
                                   const void *const *A, const void *const *B, void *const *C, int64_t Ns, int64_t Cs,
                                   int64_t Ks, int64_t H, int64_t W, int64_t R, int64_t S, int64_t pad,
-                                  int engine /* 1: 256 x 128 tiles, two workgroups per CU; 2: 256 x 256, straight into LDS */,
+                                  int engine /* 1: 256 x 128 tiles, two workgroups per CU; 2, 3, 4: straight into LDS, 256, 128, 64 x 256 */,
                                   void *stream);
 
 // ---- optional kernel timing (profile.cpp).  A scope object brackets one launch with two events when the calling

@@ -138,6 +138,15 @@ def test_weight_gradient_with_the_reduction_range_cut_evenly():
     run_conv(16, 16, 264, 4, 4, 1, 1, 0, 1, False, "R", "r", "R", "R", "R", "1", "1", "3", 143)                    # 1x1 filters, 16 pixels per image, two row tiles
 
 
+@pytest.mark.parametrize("K", [8, 72, 136, 264])
+def test_weight_gradient_of_pixels_that_end_inside_a_tile(K):
+    # shards of 105, 35, 297 and 9 pixels, the last K tile of each short; 64-, 128- and 256-row tiles, the last of each with 8 rows
+    run_conv(12, 16, K, 7, 5, 3, 3, 1, 2, True, "RR", "rr", "RR", "RR", "RR", "11", "11", "33", 190)    # runs over four shards
+    run_conv(8, 40, K, 7, 5, 3, 3, 1, 3, False, "RRR", "rrr", "RRR", "RRR", "RRR", "111", "111", "333", 191)  # over eight
+    run_conv(6, 16, 2 * K, 9, 11, 1, 1, 0, 2, True, "rR", "CR", "CR", "Rr", "RC", "23", "13", "32", 192)  # two blocks, 1x1 filters
+    run_conv(2, 8, K, 3, 3, 3, 3, 1, 1, False, "R", "r", "R", "R", "R", "1", "1", "3", 193)
+
+
 def test_shards_that_share_their_left_operand_run_as_one_product():
     # 64 or 128 columns per shard and the left operand replicated over the cuts that split them: forward and data gradient
     # run one product per group of shards, every wave writing into its own shard's result

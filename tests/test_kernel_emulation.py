@@ -218,6 +218,11 @@ CONV_CASES = [
     (3, 8, 1, 8, 264, 8, 8, 3, 3, 1, 3, 8, 2),
     (3, 2, 64, 8, 136, 7, 5, 5, 3, 2, 3, 2, 2),        # 7 x 5 images, 5 x 3 filter, padding 2: 49 output pixels per image
     (3, 2, 64, 8, 136, 7, 5, 5, 3, 2, 3, 2, 1),
+    (3, 4, 3, 16, 136, 7, 5, 3, 3, 1, 5, 4, 2),        # 105 pixels per shard: the last K tile of every shard is short, runs go on behind it
+    (3, 4, 3, 16, 136, 7, 5, 3, 3, 1, 3, 2, 3),        # 128-row tiles, two of them, the second with 8 rows
+    (3, 2, 1, 8, 8, 3, 3, 3, 3, 1, 1, 2, 4),           # 64-row tiles with 8 rows, 9 pixels per shard
+    (3, 4, 64, 40, 72, 4, 4, 1, 1, 0, 7, 2, 4),        # whole K tiles, two 64-row tiles
+    (3, 1, 14, 40, 48, 42, 35, 1, 1, 0, 61, 1, 4),     # 61 runs
 ]
 
 

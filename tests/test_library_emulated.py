@@ -150,6 +150,14 @@ def test_conv_weight_gradient_every_number_of_partial_sums(on_host, monkeypatch,
     on_host["conv"].run_conv(12, 16, 272, 8, 8, 3, 3, 1, 3, True, "RRC", "rrR", "RRr", "RRC", "RRr", "112", "113", "332", 150 + parts)
 
 
+@pytest.mark.parametrize("engine", [0, 2, 3, 4])
+def test_conv_weight_gradient_of_pixels_that_end_inside_a_tile(on_host, monkeypatch, engine):
+    monkeypatch.setenv("TT_WGRAD_ENGINE", str(engine))   # 0: the library's own choice
+    on_host["conv"].test_weight_gradient_of_pixels_that_end_inside_a_tile(136)
+    monkeypatch.setenv("TT_WGRAD_PARTS", "2")            # eight shards of one K tile: a run touches too many of them, others go through
+    on_host["conv"].test_weight_gradient_of_pixels_that_end_inside_a_tile(72)
+
+
 def test_conv_shards_that_share_their_left_operand(on_host):
     on_host["conv"].test_shards_that_share_their_left_operand_run_as_one_product()
 
