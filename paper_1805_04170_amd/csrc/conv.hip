@@ -213,6 +213,87 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN / 4) void conv_gather_a_kerne
     }
 }
 
+// The gathered operand of a forward product for the engine that loads tiles straight into LDS (gemm_core2.h).  A thread's
+// chunks of a tile differ in the row only, so the tap and the channel they read are one pair per thread and tile, moved on
+// by 64 values of K from tile to tile; rows whose tap lies outside the image, and K past the end, read a chunk of zeros.
+template <int ROWS> struct GatherKC2 {
+    static constexpr bool KC = true;
+    static constexpr int NI = ROWS * core::BK / 8 / core2::kThreads2, RI = core2::kThreads2 / 8; // chunks per thread, rows between them
+    const char *base;
+    int IW, S, Ch, K, kc;
+    int dtap, dc;         // 64 values of K as taps and channels
+    mutable int tap, c;   // of the K tile issued last
+    int32_t pix[NI];      // element offset of the source pixel at tap 0, may be negative
+    uint32_t inside[NI];  // bit t: tap t reads inside the image
+    __device__ __forceinline__ void init(const ConvGeom &g, const void *src, int rows, int K_, int row0)
+    {
+        const int tid = threadIdx.x;
+        base = reinterpret_cast<const char *>(src);
+        IW = g.W; S = g.S; Ch = g.Cs; K = K_;
+        kc = ((tid & 7) ^ ((tid >> 4) & 7)) << 3; // (see core2::issue_tile; the row's part of it is the same in all chunks)
+        dtap = core::BK / Ch;
+        dc = core::BK - dtap * Ch;
+        tap = kc / Ch;
+        c = kc - tap * Ch;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            int row = row0 + (tid >> 3) + RI * i;
+            row = row < rows ? row : rows - 1; // rows past the end only feed C rows that are never stored
+            const int n = row / (g.P * g.Q), rem = row - n * (g.P * g.Q);
+            const int y = rem / g.Q - g.pad, x = rem - (rem / g.Q) * g.Q - g.pad;
+            pix[i] = ((n * g.H + y) * g.W + x) * g.Cs;
+            uint32_t m = 0;
+            for (int r = 0; r < g.R; ++r)
+                for (int s = 0; s < g.S; ++s)
+                    if (y + r >= 0 && y + r < g.H && x + s >= 0 && x + s < g.W) m |= 1u << (r * g.S + s);
+            inside[i] = m;
+        }
+    }
+    template <int ROWS_> __device__ __forceinline__ void issue(int, int k0, char *lds) const
+    {
+        static_assert(ROWS_ == ROWS, "tile side");
+        if (k0 > 0) { // tiles are issued in order
+            c += dc;
+            const int carry = c >= Ch;
+            c -= carry ? Ch : 0;
+            tap += dtap + carry;
+        }
+        const int r = tap / S, s = tap - r * S;
+        const int32_t delta = (r * IW + s) * Ch + c;
+        const uint32_t bit = k0 + kc < K ? 1u << (tap & 31) : 0u;
+        const int wave = threadIdx.x >> 6;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const char *a = base + (ptrdiff_t)(pix[i] + delta) * 2;
+            core2::load_chunk_to_lds(inside[i] & bit ? (const void *)a : (const void *)core2::g_zero_chunk,
+                                     lds + (size_t)(wave * 64 + i * core2::kThreads2) * 16);
+        }
+    }
+};
+
+// Forward products on BM x 256 tiles of that engine (a wave owns 64 columns, so a member's block holds all of them: see above).
+template <int BM, bool OUT_BF16> __global__ __launch_bounds__(core2::kThreads2, 2) void conv_gather_a2_kernel(const ConvParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    TileId t;
+    if (!tile_of<BM, 256>(p, &t)) return;
+    GatherKC2<BM> la;
+    la.init(p.g, p.A[t.shard], p.M, p.K, t.m0);
+    core2::DenseKC2 lb;
+    lb.base = reinterpret_cast<const char *>(p.B[t.shard * p.members]);
+    lb.ld = p.K; lb.rows = p.N; lb.K = p.K;
+    void *Cw = p.C[t.shard];
+    int ldc = p.ldc;
+    if (p.members > 1) {
+        const int col0 = t.n0 + ((threadIdx.x >> 6) % 4) * 64;
+        int m = col0 / p.member_cols;
+        m = m < p.members ? m : p.members - 1; // columns past N are never stored
+        Cw = reinterpret_cast<char *>(p.C[t.shard * p.members + m]) - (ptrdiff_t)m * p.member_cols * (OUT_BF16 ? 2 : 4);
+        ldc = p.member_cols;
+    }
+    core2::tile_product2<OUT_BF16, true, BM>(la, lb, Cw, ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, reinterpret_cast<char *>(smem));
+}
+
 template <int BM, int BN, int WN, int DEPTH, bool KMASK, bool OUT_BF16>
 __global__ __launch_bounds__(WN * 128, WN / 2) void conv_wgrad_kernel(const ConvParams p)
 {
@@ -644,6 +725,11 @@ template <int OP, bool OUT_BF16, bool ONE_TAP> tt_status launch_gather_a_t(ConvP
         return kmask ? launch(conv_gather_a_kernel<256, 64, 1, 2, true, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 256, 64, 256, count, s)
                      : launch(conv_gather_a_kernel<256, 64, 1, 2, false, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 256, 64, 256, count, s);
     }
+    // Both operands K-contiguous: straight into LDS instead of through registers (VGG-16 conv4, 50176 x 512 x 4608, as the planner
+    // cuts it 313 -> 291 us, its data gradient 301 -> 289; shorter K, 1728 and 1152, equal within 2 %)
+    if constexpr (OP == 0)
+    if ((tile == 2 && tuning_int("TT_CONV_TILE", -1) < 0) || tuning_int("TT_CONV_TILE", -1) == 3)
+        return launch(conv_gather_a2_kernel<256, OUT_BF16>, core2::smem_bytes2<256>(), p, 256, 256, core2::kThreads2, count, s);
     if (tile == 2) {
         constexpr size_t sm = core::smem_bytes<256, 256>();
         return kmask ? launch(conv_gather_a_kernel<256, 256, 4, 1, true, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s)

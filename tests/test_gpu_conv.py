@@ -147,6 +147,16 @@ def test_weight_gradient_of_pixels_that_end_inside_a_tile(K):
     run_conv(2, 8, K, 3, 3, 3, 3, 1, 1, False, "R", "r", "R", "R", "R", "1", "1", "3", 193)
 
 
+def run_straight_into_lds(images, C, R):
+    # K of 72 (eight channels per tap, a short last K tile), of whole K tiles, one tap of 72, and taps that end inside a K tile
+    run_conv(images, C, 136, 15, 17, R, R, R // 2, 1, True, "R", "r", "R", "R", "R", "1", "1", "3", 195)
+
+
+@pytest.mark.parametrize("C,R", [(8, 3), (64, 3), (72, 1), (136, 3)])
+def test_forward_tiles_loaded_straight_into_lds(C, R):
+    run_straight_into_lds(130, C, R)    # 130 tiles of 256 x 256, short ones among them
+
+
 def test_shards_that_share_their_left_operand_run_as_one_product():
     # 64 or 128 columns per shard and the left operand replicated over the cuts that split them: forward and data gradient
     # run one product per group of shards, every wave writing into its own shard's result

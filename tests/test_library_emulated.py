@@ -158,6 +158,14 @@ def test_conv_weight_gradient_of_pixels_that_end_inside_a_tile(on_host, monkeypa
     on_host["conv"].test_weight_gradient_of_pixels_that_end_inside_a_tile(72)
 
 
+@pytest.mark.parametrize("C,R", [(8, 3), (64, 3), (72, 1), (136, 3)])
+def test_conv_forward_tiles_loaded_straight_into_lds(on_host, monkeypatch, C, R):
+    monkeypatch.setenv("TT_CONV_TILE", "3")
+    on_host["conv"].run_straight_into_lds(4, C, R)
+    if C == 8:      # members of a group side by side
+        on_host["conv"].run_conv(4, 64, 256, 5, 7, 3, 3, 1, 1, False, "r", "C", "C", "C", "r", "2", "3", "2", 181)
+
+
 def test_conv_shards_that_share_their_left_operand(on_host):
     on_host["conv"].test_shards_that_share_their_left_operand_run_as_one_product()
 
