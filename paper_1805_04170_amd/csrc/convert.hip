@@ -185,9 +185,15 @@ template <> struct FVec<1> { using type = float; };
 
 // CHUNK partial buffers are read per round with all loads in flight together (a last round may be shorter: the count
 // need not be a multiple of CHUNK); lanes past the end of a piece read a clamped in-range address and store nothing.
-template <int EV, bool OUT_BF16, int U, int CHUNK>
+// WS = 4: small results of many partial sums (filter gradients, products cut along K), bound by the trips to memory one
+// after the other and by too few workgroups: the four waves of a workgroup add a quarter of the partial sums each for the
+// same 64 vectors, and the first adds their sums.
+template <int EV, bool OUT_BF16, int U, int CHUNK, int WS = 1>
 __global__ __launch_bounds__(kThreads) void reduce_kernel(const ReduceParams p)
 {
+    static_assert(WS == 1 || (WS == 4 && U == 1 && kThreads == 256), "a wave per quarter, one vector per lane");
+    const uint32_t part_wave = WS == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane_id = WS == 1 ? threadIdx.x : threadIdx.x & 63u;
     using FV = typename FVec<EV>::type;
     uint32_t bid = blockIdx.x;
     uint32_t tile = bid % p.tiles_per_piece;
@@ -202,7 +208,7 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(const ReduceParams p)
     PieceLoc sz = locate(p.Z, p.k, row0, col0, 0u);
     uint64_t dbase = (uint64_t)(pr * p.piece_rows) * p.B.scols_v + pc * p.piece_cv;
 
-    uint32_t idx = tile * (kThreads * U) + threadIdx.x;
+    uint32_t idx = tile * (kThreads / WS * U) + lane_id;
     uint32_t row = idx / p.piece_cv, cv = idx - row * p.piece_cv;
 
     float acc[U][EV];
@@ -221,8 +227,10 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(const ReduceParams p)
         if (cv >= p.piece_cv) { cv -= p.piece_cv; ++row; }
     }
     // partial sums are added in increasing partial number: a fixed order, independent of the launch shape
-    const uint32_t total = p.nred * p.ksplit;
-    for (uint32_t q0 = 0; q0 < total; q0 += CHUNK) {
+    const uint32_t all = p.nred * p.ksplit;
+    const uint32_t total = WS == 1 ? all : (part_wave + 1) * all / WS; // (of this wave: from `first` on, at least one)
+    const uint32_t first = part_wave * all / WS;
+    for (uint32_t q0 = first; q0 < total; q0 += CHUNK) {
         FV v[CHUNK][U];
 #pragma unroll
         for (int j = 0; j < CHUNK; ++j) {
@@ -242,6 +250,18 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(const ReduceParams p)
                     acc[u][0] += v[j][u];
                 }
             }
+    }
+    if constexpr (WS > 1) {
+        __shared__ float sums[WS - 1][EV][64];
+        if (part_wave > 0)
+#pragma unroll
+            for (int e = 0; e < EV; ++e) sums[part_wave - 1][e][lane_id] = acc[0][e];
+        __syncthreads();
+        if (part_wave > 0) return;
+#pragma unroll
+        for (int w = 0; w < WS - 1; ++w)
+#pragma unroll
+            for (int e = 0; e < EV; ++e) acc[0][e] += sums[w][e][lane_id];
     }
     if (p.relu) {
 #pragma unroll
@@ -417,6 +437,14 @@ template <int EV, bool OUT_BF16> static tt_status launch_reduce_e(const ReducePa
     return launch_reduce_u<EV, OUT_BF16, 1>(p, blocks, s);
 }
 
+template <int EV, bool OUT_BF16> static tt_status launch_reduce_waves(const ReduceParams &p, uint32_t blocks, hipStream_t s)
+{
+    if (p.nred * p.ksplit >= 32) hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 8, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
+    else if (p.nred * p.ksplit >= 16) hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 4, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
+    else hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 2, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+
 tt_status launch_reduce(void *const *dst, const uint8_t *Bl, int out_dtype, const float *const *partials,
                         const uint8_t *zl, int k, int64_t rows, int64_t cols, int act, int ksplit, void *stream, bool per_block)
 {
@@ -485,7 +513,10 @@ tt_status launch_reduce(void *const *dst, const uint8_t *Bl, int out_dtype, cons
     p.pieces_c = (uint32_t)(B.scols / piece_cols);
     p.pieces = (uint32_t)((B.srows / piece_rows) * (B.scols / piece_cols));
     p.piece_vecs = (uint32_t)piece_vecs;
-    const uint32_t per_tile = (uint32_t)(kThreads * unroll);
+    // A quarter of the partial sums per wave below 64 K vectors: 7936 vectors of 57 partial sums 15.0 -> 5.5 us, 1536 of 48 8.8 -> 4.9,
+    // 53184 of 8 7.5 -> 6.1, 1024 of 32 9.2 -> 5.4; 64000 of 16 as before (7.9 / 8.1), 121856 of 8 slower (7.8 / 10.1).
+    const bool by_waves = unroll == 1 && unique_vecs < (uint64_t)1 << 16 && n_part >= 8;
+    const uint32_t per_tile = by_waves ? kThreads / 4 : (uint32_t)(kThreads * unroll);
     p.tiles_per_piece = (uint32_t)((piece_vecs + per_tile - 1) / per_tile);
     p.step_rows = (uint32_t)(kThreads / piece_cv);
     p.step_cv = (uint32_t)(kThreads % piece_cv);
@@ -494,6 +525,10 @@ tt_status launch_reduce(void *const *dst, const uint8_t *Bl, int out_dtype, cons
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const uint64_t elems = (uint64_t)rows * (uint64_t)cols;
     ProfileScope scope(stream, TT_K_REDUCE, n, rows, cols, (int64_t)out_b, elems * 4u * p.nred * p.ksplit + elems * out_b * p.nrep, 0);
+    if (by_waves) {
+        if (ev == 4) return out_dtype == TT_BF16 ? launch_reduce_waves<4, true>(p, (uint32_t)blocks, s) : launch_reduce_waves<4, false>(p, (uint32_t)blocks, s);
+        return out_dtype == TT_BF16 ? launch_reduce_waves<1, true>(p, (uint32_t)blocks, s) : launch_reduce_waves<1, false>(p, (uint32_t)blocks, s);
+    }
     if (ev == 4) return out_dtype == TT_BF16 ? launch_reduce_e<4, true>(p, (uint32_t)blocks, unroll, s)
                                               : launch_reduce_e<4, false>(p, (uint32_t)blocks, unroll, s);
     return out_dtype == TT_BF16 ? launch_reduce_e<1, true>(p, (uint32_t)blocks, unroll, s)

@@ -73,7 +73,7 @@ tt_status filter_view(Sharded *s, const void *const *ptrs, const tt_tiling &t, i
 // as one item's K tiles; every partial sum is written and read once more by the reduction.  Times in microseconds from
 // measured rates on MI355X with the chip full: engine 1 (256 x 128 tiles, 512 resident) 3.9 us per K tile, engine 2 (256 x 256,
 // 256 resident) 2.6 us, engines 3 and 4 (128 and 64 x 256, 256 and 512 resident) 1.9 and 2.4; 4 us to start and write an item;
-// partial sums at 4 TB/s.  What it replaced where a shard's pixels are no multiple of 64 or it has at most 128 output channels,
+// partial sums at 4 TB/s, at 8 while they stay in the caches.  What it replaced where a shard's pixels are no multiple of 64 or it has at most 128 output channels,
 // one workgroup per tile and shard (batch-split group of images): 96 x 34 x 46 pixels, 128 to 384 channels, 8 shards 493 -> 266 us;
 // 24 x 35 x 41, 384 to 64, 8 shards 97 -> 38; 14 x 42 x 35, 80 to 96, 1x1 filters, 2 shards 209 -> 23; 32 x 14 x 14, 64 to 64, 8 shards 29 -> 24.
 struct WgradChoice { int parts, engine; };
@@ -95,8 +95,10 @@ WgradChoice pick_wgrad_parts(int nblk, int nred, int64_t pixels, int64_t Ks, int
             const int64_t len = (total_kt + parts - 1) / parts;
             if (nred > 4 && (len + ktps - 1) / ktps + 1 > 4) continue; // an item may touch at most four shards
             if (parts == forced) return WgradChoice{parts, engine};
-            const int64_t rounds = (nblk * tiles * parts + e.resident - 1) / e.resident;
-            const double us = (double)rounds * ((double)len * e.kt_us + 4.0) + (double)nblk * parts * (double)blk_bytes * 2.0 / 4.0e6;
+            const int64_t items = nblk * tiles * parts, rounds = (items + e.resident - 1) / e.resident;
+            const double kt_us = engine == 4 && items <= 256 ? 1.5 : e.kt_us; // (one workgroup per CU)
+            const double sums = (double)nblk * parts * (double)blk_bytes;
+            const double us = (double)rounds * ((double)len * kt_us + 4.0) + sums * 2.0 / (sums <= 32e6 ? 8.0e6 : 4.0e6);
             if (best.parts == 0 || us < best_us) { best = WgradChoice{parts, engine}; best_us = us; }
         }
     }

@@ -166,6 +166,22 @@ def test_reduce_against_oracle(forms, B, out, relu):
         assert np.all(np.abs(gf - w) <= tol + 1e-30), (forms, B, s)
 
 
+@pytest.mark.parametrize("forms,B,rows,cols", [("333", "RrC", 8, 128), ("3333", "rCrr", 4, 260), ("333333", "rrrrRC", 4, 250),
+                                               ("33233", "CrrrR", 2, 512), ("33133", "rRCrr", 16, 50), ("333", "rrr", 1, 1)])
+def test_reduce_of_many_partial_sums(forms, B, rows, cols):
+    # 8, 16 and 64 partial sums, a quarter of them per wave; 64 vectors of a piece and one more, single elements, two blocks
+    rng = np.random.default_rng(len(forms) + cols)
+    k1, k2 = forms.count("1"), forms.count("2")
+    parts = [rng.standard_normal((rows >> k1, cols >> k2)).astype(np.float32) for _ in range(1 << len(forms))]
+    want = ex.reduce_to([p.astype(np.float64) for p in parts], forms, B, rows, cols, True)
+    mag = ex.assemble([np.abs(p).astype(np.float64) for p in parts], forms, rows, cols)
+    dst = alloc_shards(rows, cols, B, torch.float32)
+    tt.tt_reduce(dst, B, "f32", [np_to_dev(p) for p in parts], forms, rows, cols, tt.TT_ACT_RELU)
+    torch.cuda.synchronize()
+    for s, (d, w) in enumerate(zip(dst, want)):     # each of at most 64 additions rounds by 2^-24 of at most the sum of |partials|
+        assert np.all(np.abs(dev_to_np(d).astype(np.float64) - w) <= 64 * 2.0 ** -24 * mag[tl.shard_slices(rows, cols, B, s)] + 1e-30)
+
+
 def test_reduce_ragged_columns_scalar_path():
     rng = np.random.default_rng(21)
     rows, cols = 32, 250            # 125-wide blocks: no 16-byte vectors
