@@ -77,12 +77,22 @@ tt_status filter_view(Sharded *s, const void *const *ptrs, const tt_tiling &t, i
 // one workgroup per tile and shard (batch-split group of images): 96 x 34 x 46 pixels, 128 to 384 channels, 8 shards 493 -> 266 us;
 // 24 x 35 x 41, 384 to 64, 8 shards 97 -> 38; 14 x 42 x 35, 80 to 96, 1x1 filters, 2 shards 209 -> 23; 32 x 14 x 14, 64 to 64, 8 shards 29 -> 24.
 struct WgradChoice { int parts, engine; };
-WgradChoice pick_wgrad_parts(int nblk, int nred, int64_t pixels, int64_t Ks, int64_t ncols, size_t blk_bytes)
+// most: runs per block that the workspace has room for (a smaller one than tt_conv_workspace_bytes asks for takes fewer runs)
+int runs_that_fit(const Workspace &ws, int nblk, size_t blk_bytes)
+{
+    const int most = kMaxShards / nblk;
+    if (ws.dry) return most;
+    const size_t used = align_up(ws.used, 256), each = align_up(blk_bytes, 256) * (size_t)nblk;
+    // (the last buffer need not be rounded up)
+    const size_t fit = ws.cap <= used ? 0 : (ws.cap - used + align_up(blk_bytes, 256) - blk_bytes) / each;
+    return fit < (size_t)most ? (int)fit : most;
+}
+WgradChoice pick_wgrad_parts(int nblk, int nred, int64_t pixels, int64_t Ks, int64_t ncols, size_t blk_bytes, int most)
 {
     static const struct { int64_t tile_m, tile_n, resident; double kt_us; } engines[4] = {
         {256, 128, 512, 3.9}, {256, 256, 256, 2.6}, {128, 256, 256, 1.9}, {64, 256, 512, 2.4}};
     const int64_t ktps = (pixels + 63) / 64, total_kt = (int64_t)nred * ktps;
-    const int max_parts = kMaxShards / nblk;
+    const int max_parts = most;
     WgradChoice best{0, 1};
     double best_us = 0.0;
     const int forced = tuning_int("TT_WGRAD_PARTS", 0), forced_engine = tuning_int("TT_WGRAD_ENGINE", 0); // development builds only
@@ -360,10 +370,12 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
             if ((m1 || m2) && fits && make_grid(zp, kp, rows_w, d.C, &gp) && make_grid(zr, k, rows_w, d.C, &gr)) {
                 const int nred = 1 << gp.kX, nblk = (1 << kp) >> gp.kX;
                 const size_t blk_bytes = (size_t)gp.srows * (size_t)gp.scols * 4;
-                const WgradChoice choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes);
+                WgradChoice choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes, kMaxShards / nblk);
                 if (choice.parts > 0) {
                     if ((st = prepare_operand(X, aXm, k, esz, nullptr, a.dtype, ws, a.stream, &Xa)) != TT_OK) return st;
                     if ((st = prepare_operand(G, aGm, k, esz, gated ? nullptr : &Y, a.dtype, ws, a.stream, &Ga)) != TT_OK) return st;
+                    choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes, runs_that_fit(ws, nblk, blk_bytes));
+                    if (choice.parts == 0) return TT_EWORKSPACE;
                     const int parts = choice.parts;
                     uint8_t blk_ids[kMaxShards], red_ids[kMaxShards];
                     const uint32_t mask_blk = ((1u << kp) - 1u) & ~gp.maskX;
@@ -411,7 +423,8 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         const int64_t lim = int64_t(1) << 30; // (the launcher's own conditions)
         const bool even = bf16 && Cs % 8 == 0 && Ks % 8 == 0 && rs <= 32 && Ns * hw * Cs < lim && Ns * pq * Ks < lim && Ks * rs * Cs < lim &&
                           Ns * pq >= 8;
-        const WgradChoice choice = even ? pick_wgrad_parts(nblk, nred, Ns * pq, Ks, rs * Cs, blk_bytes) : WgradChoice{0, 1};
+        const WgradChoice choice = even ? pick_wgrad_parts(nblk, nred, Ns * pq, Ks, rs * Cs, blk_bytes, runs_that_fit(ws, nblk, blk_bytes))
+                                        : WgradChoice{0, 1};
         const int parts = choice.parts;
         if (parts > 0 && !(parts == 1 && nred == 1)) {
             uint8_t blk_ids[kMaxShards], red_ids[kMaxShards];

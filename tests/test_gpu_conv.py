@@ -147,6 +147,29 @@ def test_weight_gradient_of_pixels_that_end_inside_a_tile(K):
     run_conv(2, 8, K, 3, 3, 3, 3, 1, 1, False, "R", "r", "R", "R", "R", "1", "1", "3", 193)
 
 
+def test_weight_gradient_in_a_smaller_workspace_takes_fewer_runs():
+    # 12 images of 7 x 5 pixels on four shards: the runs that fit, down to one; less than one partial sum is refused
+    lay = tt.layer("conv", "none", 16, 72, H=7, W=5, R=3, S=3, pad=1)
+    X, dY = (to_bf16_bits(normal_f32(196, i, (12, c, 7, 5), 1.0)) for i, c in ((0, 16), (2, 72)))
+    Xs, dYs = up(act_matrix(X), "RR"), up(act_matrix(dY), "RR")
+    Ws_ = up(filt_matrix(to_bf16_bits(normal_f32(196, 1, (72, 16, 3, 3), 0.05))), "rr")
+    nb = tt.tt_conv_workspace_bytes(lay, 12, 2, "bf16", tt.TT_OP_DGRAD, "RR", "rr", "RR", "RR", "RR", "11", "33", False)
+    one = 72 * 9 * 16 * 4
+    assert nb > one
+    for nbytes in (nb, one, one - 256):
+        dWs = alloc_shards(72 * 9, 16, "rr", torch.bfloat16, fill=float("nan"))
+        args = (lay, 12, 2, "bf16", "RR", "rr", "RR", "RR", "RR", "11", "33", Xs, Ws_, dYs, dYs, None, dWs, ws(nbytes))
+        if nbytes < one:
+            with pytest.raises(tt.TilingError):
+                tt.tt_conv_backward(*args)
+            continue
+        tt.tt_conv_backward(*args)
+        torch.cuda.synchronize()
+        got = filt_from_matrix(bf16_bits_to_f64(tl.untile(shards_to_np(dWs), "rr", 72 * 9, 16)), 72, 16, 3, 3)
+        Xf, G = bf16_bits_to_f64(X), bf16_bits_to_f64(dY)
+        close(got, ly.conv_wgrad(Xf, G, 1, 3, 3), ly.conv_wgrad(np.abs(Xf), np.abs(G), 1, 3, 3), ("wgrad", nbytes), 1e-2)
+
+
 def run_straight_into_lds(images, C, R):
     # K of 72 (eight channels per tap, a short last K tile), of whole K tiles, one tap of 72, and taps that end inside a K tile
     run_conv(images, C, 136, 15, 17, R, R, R // 2, 1, True, "R", "r", "R", "R", "R", "1", "1", "3", 195)

@@ -158,6 +158,10 @@ def test_conv_weight_gradient_of_pixels_that_end_inside_a_tile(on_host, monkeypa
     on_host["conv"].test_weight_gradient_of_pixels_that_end_inside_a_tile(72)
 
 
+def test_conv_weight_gradient_in_a_smaller_workspace(on_host):
+    on_host["conv"].test_weight_gradient_in_a_smaller_workspace_takes_fewer_runs()
+
+
 @pytest.mark.parametrize("C,R", [(8, 3), (64, 3), (72, 1), (136, 3)])
 def test_conv_forward_tiles_loaded_straight_into_lds(on_host, monkeypatch, C, R):
     monkeypatch.setenv("TT_CONV_TILE", "3")
