@@ -728,8 +728,9 @@ template <int OP, bool OUT_BF16, bool ONE_TAP> tt_status launch_gather_a_t(ConvP
     // Both operands K-contiguous: straight into LDS instead of through registers (VGG-16 conv4, 50176 x 512 x 4608, as the planner
     // cuts it 313 -> 291 us, its data gradient 301 -> 289; shorter K, 1728 and 1152, equal within 2 %)
     if constexpr (OP == 0)
-    if ((tile == 2 && tuning_int("TT_CONV_TILE", -1) < 0) || tuning_int("TT_CONV_TILE", -1) == 3)
+    if (tile == 2 || tuning_int("TT_CONV_TILE", -1) == 3)
         return launch(conv_gather_a2_kernel<256, OUT_BF16>, core2::smem_bytes2<256>(), p, 256, 256, core2::kThreads2, count, s);
+    if constexpr (OP == 1)
     if (tile == 2) {
         constexpr size_t sm = core::smem_bytes<256, 256>();
         return kmask ? launch(conv_gather_a_kernel<256, 256, 4, 1, true, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s)
