@@ -186,12 +186,13 @@ template <> struct FVec<1> { using type = float; };
 // CHUNK partial buffers are read per round with all loads in flight together (a last round may be shorter: the count
 // need not be a multiple of CHUNK); lanes past the end of a piece read a clamped in-range address and store nothing.
 // WS = 4: small results of many partial sums (filter gradients, products cut along K), bound by the trips to memory one
-// after the other and by too few workgroups: the four waves of a workgroup add a quarter of the partial sums each for the
-// same 64 vectors, and the first adds their sums.
+// after the other and by too few workgroups: the four waves of a workgroup fetch up to CHUNK partial sums each of the same
+// 64 vectors, all of them in flight together, and lay them out in LDS, where every thread adds one value's.  Either way the
+// partial sums of a value are added one after the other in increasing number, so the bits do not depend on the size.
 template <int EV, bool OUT_BF16, int U, int CHUNK, int WS = 1>
 __global__ __launch_bounds__(kThreads) void reduce_kernel(const ReduceParams p)
 {
-    static_assert(WS == 1 || (WS == 4 && U == 1 && kThreads == 256), "a wave per quarter, one vector per lane");
+    static_assert(WS == 1 || (WS == 4 && U == 1 && kThreads == 256 && EV * 64 <= kThreads), "CHUNK partial sums per wave, one vector per lane");
     const uint32_t part_wave = WS == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane_id = WS == 1 ? threadIdx.x : threadIdx.x & 63u;
     using FV = typename FVec<EV>::type;
@@ -227,41 +228,51 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(const ReduceParams p)
         if (cv >= p.piece_cv) { cv -= p.piece_cv; ++row; }
     }
     // partial sums are added in increasing partial number: a fixed order, independent of the launch shape
-    const uint32_t all = p.nred * p.ksplit;
-    const uint32_t total = WS == 1 ? all : (part_wave + 1) * all / WS; // (of this wave: from `first` on, at least one)
-    const uint32_t first = part_wave * all / WS;
-    for (uint32_t q0 = first; q0 < total; q0 += CHUNK) {
-        FV v[CHUNK][U];
+    const uint32_t total = p.nred * p.ksplit;
+    const auto partial = [&](uint32_t qq) { // buffer of partial sum qq of this piece
+        const uint32_t q = qq / p.ksplit, c = qq - q * p.ksplit;
+        return reinterpret_cast<const FV *>(p.part[(sz.shard | p.red_ids[q]) * p.ksplit + c]);
+    };
+    if constexpr (WS == 1) {
+        for (uint32_t q0 = 0; q0 < total; q0 += CHUNK) {
+            FV v[CHUNK][U];
 #pragma unroll
-        for (int j = 0; j < CHUNK; ++j) {
-            const uint32_t qq = q0 + j < total ? q0 + j : total - 1, q = qq / p.ksplit, c = qq - q * p.ksplit;
-            const FV *src = reinterpret_cast<const FV *>(p.part[(sz.shard | p.red_ids[q]) * p.ksplit + c]);
+            for (int j = 0; j < CHUNK; ++j) {
+                const FV *src = partial(q0 + j < total ? q0 + j : total - 1);
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[j][u] = __builtin_nontemporal_load(src + soff[u]);
-        }
-#pragma unroll
-        for (int j = 0; j < CHUNK; ++j)
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (q0 + j >= total) continue; // short last round (wave-uniform): the re-read buffer is not added again
-                if constexpr (EV == 4) {
-                    acc[u][0] += v[j][u].x; acc[u][1] += v[j][u].y; acc[u][2] += v[j][u].z; acc[u][3] += v[j][u].w;
-                } else {
-                    acc[u][0] += v[j][u];
-                }
+                for (int u = 0; u < U; ++u) v[j][u] = __builtin_nontemporal_load(src + soff[u]);
             }
-    }
-    if constexpr (WS > 1) {
-        __shared__ float sums[WS - 1][EV][64];
-        if (part_wave > 0)
 #pragma unroll
-            for (int e = 0; e < EV; ++e) sums[part_wave - 1][e][lane_id] = acc[0][e];
+            for (int j = 0; j < CHUNK; ++j)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (q0 + j >= total) continue; // short last round (wave-uniform): the re-read buffer is not added again
+                    if constexpr (EV == 4) {
+                        acc[u][0] += v[j][u].x; acc[u][1] += v[j][u].y; acc[u][2] += v[j][u].z; acc[u][3] += v[j][u].w;
+                    } else {
+                        acc[u][0] += v[j][u];
+                    }
+                }
+        }
+    } else {
+        __shared__ __attribute__((aligned(16))) float held[WS * CHUNK][64 * EV]; // total <= WS * CHUNK
+        FV v[CHUNK];
+        const uint32_t q0 = part_wave * CHUNK;
+#pragma unroll
+        for (int j = 0; j < CHUNK; ++j) v[j] = __builtin_nontemporal_load(partial(q0 + j < total ? q0 + j : total - 1) + soff[0]);
+#pragma unroll
+        for (int j = 0; j < CHUNK; ++j) *reinterpret_cast<FV *>(&held[q0 + j][lane_id * EV]) = v[j];
+        __syncthreads();
+        if (threadIdx.x < 64 * EV) {
+            float sum = 0.0f;
+#pragma unroll 8
+            for (uint32_t q = 0; q < total; ++q) sum += held[q][threadIdx.x];
+            held[0][threadIdx.x] = sum; // (nobody else reads this column)
+        }
         __syncthreads();
         if (part_wave > 0) return;
 #pragma unroll
-        for (int w = 0; w < WS - 1; ++w)
-#pragma unroll
-            for (int e = 0; e < EV; ++e) acc[0][e] += sums[w][e][lane_id];
+        for (int e = 0; e < EV; ++e) acc[0][e] = held[0][lane_id * EV + e];
     }
     if (p.relu) {
 #pragma unroll
@@ -437,10 +448,14 @@ template <int EV, bool OUT_BF16> static tt_status launch_reduce_e(const ReducePa
     return launch_reduce_u<EV, OUT_BF16, 1>(p, blocks, s);
 }
 
+// (as many partial sums per wave as a quarter of them; there are 64 at most)
 template <int EV, bool OUT_BF16> static tt_status launch_reduce_waves(const ReduceParams &p, uint32_t blocks, hipStream_t s)
 {
-    if (p.nred * p.ksplit >= 32) hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 8, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
-    else if (p.nred * p.ksplit >= 16) hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 4, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
+    static_assert(kMaxShards <= 4 * 16, "the largest chunk takes them all");
+    const uint32_t total = p.nred * p.ksplit;
+    if (total > 32) hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 16, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
+    else if (total > 16) hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 8, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
+    else if (total > 8) hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 4, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
     else hipLaunchKernelGGL((reduce_kernel<EV, OUT_BF16, 1, 2, 4>), dim3(blocks), dim3(kThreads), 0, s, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }

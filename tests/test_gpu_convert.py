@@ -182,6 +182,46 @@ def test_reduce_of_many_partial_sums(forms, B, rows, cols):
         assert np.all(np.abs(dev_to_np(d).astype(np.float64) - w) <= 64 * 2.0 ** -24 * mag[tl.shard_slices(rows, cols, B, s)] + 1e-30)
 
 
+def run_reduce_in_order(forms, B, rows, cols, out="f32", off=0):
+    # bit for bit the partial sums added one after the other in fp32, whatever the size of the result and the vectors it is read in
+    rng = np.random.default_rng(len(forms) + rows + cols)
+    k, cuts = len(forms), [j for j, f in enumerate(forms) if f == "3"]
+    k1, k2 = forms.count("1"), forms.count("2")
+    parts = [rng.standard_normal((rows >> k1, cols >> k2)).astype(np.float32) for _ in range(1 << k)]
+    want = np.zeros((rows, cols), np.float32)
+    for s in range(1 << k):     # increasing shard number is increasing partial number inside every block
+        rb = cb = 0
+        for j, f in enumerate(forms):
+            bit = (s >> (k - 1 - j)) & 1
+            rb, cb = (2 * rb + bit, cb) if f == "1" else (rb, 2 * cb + bit) if f == "2" else (rb, cb)
+        r, c = rows >> k1, cols >> k2
+        want[rb * r:(rb + 1) * r, cb * c:(cb + 1) * c] += parts[s]
+    assert len(cuts) >= 2
+    want = (torch.from_numpy(want).to(torch.bfloat16) if out == "bf16" else torch.from_numpy(want)).float().numpy()
+    dst = alloc_shards(rows, cols, B, torch.bfloat16 if out == "bf16" else torch.float32)
+    held = [torch.empty(p.size + off, dtype=torch.float32, device=DEV)[off:].view(p.shape) for p in parts]
+    for h, q in zip(held, parts):
+        h.copy_(torch.from_numpy(q))
+    tt.tt_reduce(dst, B, out, held, forms, rows, cols)
+    torch.cuda.synchronize()
+    for s, d in enumerate(dst):
+        assert np.array_equal(d.float().cpu().numpy(), want[tl.shard_slices(rows, cols, B, s)]), (forms, B, s)
+
+
+# 4, 8, 16, 32 and 64 partial sums; vectors of four, single values (odd widths, addresses that are no multiple of 16); 64 vectors
+# of a piece, one more and one fewer; blocks
+REDUCE_IN_ORDER = [("33", "rr", 8, 128, "f32", 0), ("333", "rrr", 8, 32, "f32", 0), ("333", "RrC", 8, 130, "bf16", 0), ("3333", "rCrr", 4, 260, "f32", 0),
+                   ("33333", "rrRrr", 6, 252, "f32", 1), ("333333", "rrrrRC", 4, 250, "bf16", 0), ("333333", "rrrrrr", 1, 256, "f32", 0),
+                   ("33233", "CrrrR", 2, 512, "bf16", 0), ("31333", "rRCrr", 16, 52, "f32", 0), ("333", "rrr", 1, 1, "f32", 0)]
+
+
+@pytest.mark.parametrize("case", REDUCE_IN_ORDER + [
+    ("333", "rrr", 255, 1024, "f32", 0), ("333", "rrr", 256, 1024, "f32", 0), ("333333", "rrrrrr", 128, 2044, "f32", 0),   # either side of 65536 vectors
+    ("333", "RrR", 256, 255, "f32", 0), ("3333", "rrrr", 258, 255, "bf16", 0)])
+def test_reduce_adds_in_increasing_partial_number(case):
+    run_reduce_in_order(*case)
+
+
 def test_reduce_ragged_columns_scalar_path():
     rng = np.random.default_rng(21)
     rows, cols = 32, 250            # 125-wide blocks: no 16-byte vectors

@@ -205,6 +205,8 @@ def test_reduce(on_host):
     c.test_reduce_ragged_columns_scalar_path()
     for case in (("333", "RrC", 8, 128), ("333333", "rrrrRC", 4, 250), ("33233", "CrrrR", 2, 512), ("333", "rrr", 1, 1)):
         c.test_reduce_of_many_partial_sums(*case)
+    for case in c.REDUCE_IN_ORDER:
+        c.run_reduce_in_order(*case)
     for forms, B, out, relu in [("3", "r", "f32", False), ("33", "RR", "bf16", True), ("13", "CR", "f32", True), ("32", "rC", "bf16", False),
                                 ("333", "RRR", "bf16", False), ("231", "rCr", "f32", False), ("3333", "RRCC", "f32", False)]:
         c.test_reduce_against_oracle(forms, B, out, relu)
