@@ -21,10 +21,11 @@ __global__ __launch_bounds__(small::waves_of<T>() * 64, T == 1 ? 2 : 1) void gem
     small::run_small<BF, A_KC, B_KC, T, OFF>(p, lds);
 }
 
-// Ordered products: every result is a chain of fp32 fused multiply-adds with K increasing, on fp32 matrix instructions (fp32
-// operands: four or eight chains, K dealt out to them in turn and added pairwise at the end, since one chain of K terms
-// rounds worse than the eight waves of gemm_small_kernel; relative error at K = 16, 128, 512, 4096 7.4e-8, 1.5e-7, 1.6e-7,
-// 4.1e-7 there, 5.6e-8, 8.8e-8, 1.5e-7, 4.1e-7 here).
+// Ordered products: every result is a chain of fp32 fused multiply-adds with K increasing, on fp32 matrix instructions.  Only
+// bf16 A B, the forward layout, is one chain; elsewhere K is dealt out to four or eight chains in turn that are added pairwise
+// at the end, since one chain of K terms rounds worse than the waves of gemm_small_kernel.  Relative error of fp32 results, there / here:
+// fp32 K = 17, 129, 511, 1023 7.6e-8 / 5.6e-8, 1.5e-7 / 8.8e-8, 1.6e-7 / 1.5e-7, 2.1e-7 / 2.1e-7; bf16 A B^T and A^T B K = 33, 129, 255, 511 3.0e-8 /
+// 3.0e-8, 6.0e-8 / 4.9e-8, 6.6e-8 / 5.8e-8, 7.2e-8 / 6.9e-8 (as one chain 3.6e-8, 7.3e-8, 1.1e-7, 1.6e-7).
 // v_mfma_f32_16x16x4_f32 and v_mfma_f32_32x32x2_f32 add their four or two products to the accumulator one after the other,
 // k increasing, each rounded like fmaf (compared bit for bit with chains of fmaf: normal, widely spread, subnormal operands;
 // a bf16 value is an fp32 value), so the bits do not depend on the tile.
@@ -110,7 +111,8 @@ template <bool BF, bool A_KC, bool B_KC, int S, int KB, class P> __device__ __fo
     using OA = OrderedSide<BF, A_KC, S, KB>;
     using OB = OrderedSide<BF, B_KC, S, KB>;
     constexpr int T = OA::T, KM = OA::KM, PD = 4;
-    constexpr int CHAINS = BF ? 1 : KB / KM < 8 ? 4 : S == 16 ? 8 : 4;
+    constexpr bool ONE_CHAIN = BF && A_KC && !B_KC;
+    constexpr int CHAINS = ONE_CHAIN ? 1 : KB / KM < 8 ? 4 : S == 16 ? 8 : 4;
     float *const As = lds, *const Bs = lds + 2 * OA::LDS; // two tiles each
     using acc_t = std::conditional_t<S == 16, core::f32x4, core::f32x16>;
     const int tiles = p.tiles_m * p.tiles_n;

@@ -122,6 +122,35 @@ def test_odd_sized_forward_products_add_in_the_order_of_k(M, N, K):
     assert np.array_equal(dev_to_np(c), want)
 
 
+def run_error_against_one_chain(ta, tb, M, N, K, dt):
+    # fp32 results of odd-sized products that need not keep the order of K are cut into four chains of additions or more.  The error
+    # of a chain of n additions grows at least as the square root of n (0.5 of a single chain's for four; 0.6 here, as the first
+    # additions of bf16 products are exact), and joining eight chains adds three levels of additions that round by 2.5e-8 of
+    # the result each (uniform rounding: 2^-24 / sqrt(3), 0.72 of it on average over the mantissa): 4.3e-8 together.
+    rng = np.random.default_rng(K + ta + 2 * tb)
+    a, b = (rng.standard_normal(s).astype(np.float32) for s in ((M, K), (K, N)))
+    if dt == "bf16":
+        a, b = (bf16_bits_to_f64(to_bf16_bits(x)).astype(np.float32) for x in (a, b))
+    one = np.zeros((M, N), np.float32)
+    for k in range(K):      # fused: the product of two fp32 values is exact in float64, and the sum is rounded to fp32 next to correctly
+        one = (one.astype(np.float64) + a[:, k:k + 1].astype(np.float64) * b[k:k + 1]).astype(np.float32)
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    c = torch.empty((M, N), dtype=torch.float32, device=DEV)
+    up = [torch.from_numpy(np.ascontiguousarray(x)).to(torch.bfloat16 if dt == "bf16" else torch.float32).to(DEV) for x in (a.T if ta else a, b.T if tb else b)]
+    tt.tt_shard_gemm([up[0]], [up[1]], [c], M, N, K, ta, tb, dt, "f32")
+    got = np.linalg.norm(dev_to_np(c).astype(np.float64) - want)
+    bound = np.hypot(0.6 * np.linalg.norm(one.astype(np.float64) - want), 4.3e-8 * np.linalg.norm(want))
+    assert bound < 0.9 * np.linalg.norm(one.astype(np.float64) - want)      # (a single chain would not pass)
+    assert got <= bound, (ta, tb, M, N, K, dt)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("M,N,K", [(101, 225, 129), (257, 255, 255), (257, 255, 447), (1023, 961, 159), (1281, 1279, 191)])
+def test_odd_sized_products_are_not_one_chain_of_additions(ta, tb, dt, M, N, K):
+    run_error_against_one_chain(ta, tb, M, N, K, dt)
+
+
 def test_fp32_keeps_subnormal_products_and_sums():
     # results below the smallest normal fp32 number (1.2e-38): K = 64 products of 2^-70 x 2^-65
     a = torch.full((40, 64), 2.0 ** -70, dtype=torch.float32, device=DEV)

@@ -117,6 +117,12 @@ def test_fc_tiny_mlp_planned_and_recursive(on_host):
     on_host["fc"].test_config_tiny_mlp_fp32_planned_and_recursive()
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (1, 1)])
+def test_odd_sized_products_are_not_one_chain_of_additions(on_host, ta, tb):
+    for dt, K in (("bf16", 129), ("bf16", 255), ("f32", 255)):
+        on_host["gemm"].run_error_against_one_chain(ta, tb, 33, 35, K, dt)
+
+
 def test_conv_single_shard_and_one_cut(on_host):
     on_host["conv"].test_single_shard_and_one_cut()
 
