@@ -77,15 +77,22 @@ tt_status filter_view(Sharded *s, const void *const *ptrs, const tt_tiling &t, i
 // one workgroup per tile and shard (batch-split group of images): 96 x 34 x 46 pixels, 128 to 384 channels, 8 shards 493 -> 266 us;
 // 24 x 35 x 41, 384 to 64, 8 shards 97 -> 38; 14 x 42 x 35, 80 to 96, 1x1 filters, 2 shards 209 -> 23; 32 x 14 x 14, 64 to 64, 8 shards 29 -> 24.
 struct WgradChoice { int parts, engine; };
-// most: runs per block that the workspace has room for (a smaller one than tt_conv_workspace_bytes asks for takes fewer runs)
-int runs_that_fit(const Workspace &ws, int nblk, size_t blk_bytes)
+// runs per block that a workspace has room for (a smaller one than tt_conv_workspace_bytes asks for takes fewer runs)
+int runs_that_fit(const Workspace &ws, size_t taken, int nblk, size_t blk_bytes)
 {
     const int most = kMaxShards / nblk;
     if (ws.dry) return most;
-    const size_t used = align_up(ws.used, 256), each = align_up(blk_bytes, 256) * (size_t)nblk;
+    const size_t used = align_up(taken, 256), each = align_up(blk_bytes, 256) * (size_t)nblk;
     // (the last buffer need not be rounded up)
     const size_t fit = ws.cap <= used ? 0 : (ws.cap - used + align_up(blk_bytes, 256) - blk_bytes) / each;
     return fit < (size_t)most ? (int)fit : most;
+}
+// Whether the product reads its operands at 16-byte addresses (a query knows no stored address)
+bool aligned_operands(const Sharded &x, const Sharded &g, int n)
+{
+    for (int s = 0; s < n; ++s)
+        if ((reinterpret_cast<uintptr_t>(x.ptr[s]) | reinterpret_cast<uintptr_t>(g.ptr[s])) & 15) return false;
+    return true;
 }
 WgradChoice pick_wgrad_parts(int nblk, int nred, int64_t pixels, int64_t Ks, int64_t ncols, size_t blk_bytes, int most)
 {
@@ -336,6 +343,7 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         int k1, k2, k3;
         form_counts(f, k, &k1, &k2, &k3);
         Sharded Xa, Ga;
+        size_t other = 0; // what a query finds for the first of two ways that the call may go
         const int64_t rows_w = d.K * rs; // the filter storage matrix is (K*R*S) x C
         // Channels cut so far that a shard keeps at most 128 of them leave every shard a sliver of the product: 64 rows of
         // dY^T against the whole gathered X where the output channels are cut (F2), or the whole dY^T against 64 gathered
@@ -349,9 +357,13 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         if (bf16 && tuning_int("TT_WGRAD_MERGE", 1) != 0) {
             const bool m1 = k1 > 0 && (d.C >> k1) <= 128 && d.C > 128, m2 = k2 > 0 && (d.K >> k2) <= 128 && d.K > 128;
             const int64_t Cm = m1 ? d.C : d.C >> k1, Km = m2 ? d.K : d.K >> k2, Ns = d.N >> k3; // per product
+            // Shards of whole K tiles run this way or not at all.  Others have a product per shard to fall back on: for channels of a
+            // shard that are no multiple of 8 (refused there), for workspaces of no more than that one needs (X or dY whole takes up
+            // more room) and for operands stored at addresses that only a copy brings to 16 bytes; a query covers both ways.
+            const bool only = (Ns * pq) % 64 == 0;
             const int64_t lim = int64_t(1) << 30; // the evenly cut product's own limits (32-bit offsets, 16-byte chunks, tap masks)
             const bool fits = Cm % 8 == 0 && Km % 8 == 0 && Km > 128 && rs <= 32 && Ns * hw * Cm < lim && Ns * pq * Km < lim &&
-                              Km * rs * Cm < lim && Ns * pq >= 8;
+                              Km * rs * Cm < lim && Ns * pq >= 8 && (only || ((d.C >> k1) % 8 == 0 && (d.K >> k2) % 8 == 0));
             uint32_t mask_m = 0;
             uint8_t zr[TT_MAX_K], zp[TT_MAX_K]; // letters for the reduction (k cuts) and for the product (the cuts kept)
             tt_tiling aGm = aG, aXm = transpose_tiling(aXt, k);
@@ -371,11 +383,26 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
                 const int nred = 1 << gp.kX, nblk = (1 << kp) >> gp.kX;
                 const size_t blk_bytes = (size_t)gp.srows * (size_t)gp.scols * 4;
                 WgradChoice choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes, kMaxShards / nblk);
-                if (choice.parts > 0) {
+                bool taken = choice.parts > 0;
+                if (taken) { // tried out before anything is launched
+                    Workspace probe = ws;
+                    probe.dry = true;
+                    if ((st = prepare_operand(X, aXm, k, esz, nullptr, a.dtype, probe, a.stream, &Xa)) != TT_OK) return st;
+                    if ((st = prepare_operand(G, aGm, k, esz, gated ? nullptr : &Y, a.dtype, probe, a.stream, &Ga)) != TT_OK) return st;
+                    if (ws.dry) {
+                        for (int i = 0; i < nblk * choice.parts; ++i) probe.take(blk_bytes);
+                        other = probe.used;
+                        if (only) { ws.used = other; return TT_OK; }
+                        taken = false;
+                    } else {
+                        choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes, runs_that_fit(ws, probe.used, nblk, blk_bytes));
+                        if (only && choice.parts == 0) return TT_EWORKSPACE;
+                        taken = only || (choice.parts > 0 && aligned_operands(Xa, Ga, n));
+                    }
+                }
+                if (taken) {
                     if ((st = prepare_operand(X, aXm, k, esz, nullptr, a.dtype, ws, a.stream, &Xa)) != TT_OK) return st;
                     if ((st = prepare_operand(G, aGm, k, esz, gated ? nullptr : &Y, a.dtype, ws, a.stream, &Ga)) != TT_OK) return st;
-                    choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes, runs_that_fit(ws, nblk, blk_bytes));
-                    if (choice.parts == 0) return TT_EWORKSPACE;
                     const int parts = choice.parts;
                     uint8_t blk_ids[kMaxShards], red_ids[kMaxShards];
                     const uint32_t mask_blk = ((1u << kp) - 1u) & ~gp.maskX;
@@ -390,7 +417,6 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
                             table[b * parts + c] = static_cast<const float *>(sums[b * parts + c]);
                         }
                     if (ws.overflow) return TT_EWORKSPACE;
-                    if (ws.dry) return TT_OK;
                     const void *Gp[kMaxShards], *Xp[kMaxShards];
                     for (int s = 0; s < (1 << kp); ++s) {
                         const uint32_t sid = deposit((uint32_t)s, mask_keep, k);
@@ -423,7 +449,7 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         const int64_t lim = int64_t(1) << 30; // (the launcher's own conditions)
         const bool even = bf16 && Cs % 8 == 0 && Ks % 8 == 0 && rs <= 32 && Ns * hw * Cs < lim && Ns * pq * Ks < lim && Ks * rs * Cs < lim &&
                           Ns * pq >= 8;
-        const WgradChoice choice = even ? pick_wgrad_parts(nblk, nred, Ns * pq, Ks, rs * Cs, blk_bytes, runs_that_fit(ws, nblk, blk_bytes))
+        const WgradChoice choice = even ? pick_wgrad_parts(nblk, nred, Ns * pq, Ks, rs * Cs, blk_bytes, runs_that_fit(ws, ws.used, nblk, blk_bytes))
                                         : WgradChoice{0, 1};
         const int parts = choice.parts;
         if (parts > 0 && !(parts == 1 && nred == 1)) {
@@ -440,7 +466,10 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
                     table[b * parts + c] = static_cast<const float *>(sums[b * parts + c]);
                 }
             if (ws.overflow) return TT_EWORKSPACE;
-            if (ws.dry) return TT_OK;
+            if (ws.dry) {
+                if (ws.used < other) ws.used = other;
+                return TT_OK;
+            }
             st = launch_conv_wgrad_split(k, nblk, nred, blk_ids, red_ids, parts, Ga.ptr, Xa.ptr, sums, Ns, Cs, Ks, d.H, d.W, d.R,
                                          d.S, d.pad, choice.engine, a.stream);
             if (st != TT_OK) return st; // (the shapes were checked above with the launcher's own conditions)
@@ -463,6 +492,7 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         }
         OutputPlan op;
         if ((st = plan_output_letters(zl, tWs, a.dW, d.K * rs, d.C, k, a.dtype, TT_ACT_NONE, ws, &op, split)) != TT_OK) return st;
+        if (ws.dry && ws.used < other) ws.used = other;
         if (!ws.dry) {
             const void *Gs[kMaxShards], *Xs[kMaxShards];
             const int64_t Nsub = Ns / split;

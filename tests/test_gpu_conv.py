@@ -170,6 +170,40 @@ def test_weight_gradient_in_a_smaller_workspace_takes_fewer_runs():
         close(got, ly.conv_wgrad(Xf, G, 1, 3, 3), ly.conv_wgrad(np.abs(Xf), np.abs(G), 1, 3, 3), ("wgrad", nbytes), 1e-2)
 
 
+def run_wgrad_in(nbytes, N, C, K, H, W, R, pad, t, form, seed, off=0):
+    # the filter gradient alone, in a workspace of nbytes (None: what the library asks for), X at `off` elements from an aligned address
+    tX, tW, tY, tdY = t
+    k = len(tX)
+    lay = tt.layer("conv", "none", C, K, H=H, W=W, R=R, S=R, pad=pad)
+    P, Q = H + 2 * pad - R + 1, W + 2 * pad - R + 1
+    X, dY = to_bf16_bits(normal_f32(seed, 0, (N, C, H, W), 1.0)), to_bf16_bits(normal_f32(seed, 2, (N, K, P, Q), 1.0))
+    tWs = ex.transpose_tiling(tW)
+    Xs = []
+    for s in up(act_matrix(X), tX):
+        Xs.append(torch.empty(s.numel() + 8, dtype=s.dtype, device=DEV)[off:off + s.numel()].view(s.shape))
+        Xs[-1].copy_(s)
+    Ws_, dYs = up(filt_matrix(to_bf16_bits(normal_f32(seed, 1, (K, C, R, R), 0.05))), tWs), up(act_matrix(dY), tdY)
+    asked = tt.tt_conv_workspace_bytes(lay, N, k, "bf16", tt.TT_OP_DGRAD, tX, tW, tY, tdY, tX, None, form, False)
+    dWs = alloc_shards(K * R * R, C, tWs, torch.bfloat16, fill=float("nan"))
+    tt.tt_conv_backward(lay, N, k, "bf16", tX, tW, tY, tdY, tX, None, form, Xs, Ws_, dYs, dYs, None, dWs, ws(asked if nbytes is None else nbytes))
+    torch.cuda.synchronize()
+    got = filt_from_matrix(bf16_bits_to_f64(tl.untile(shards_to_np(dWs), tWs, K * R * R, C)), K, C, R, R)
+    Xf, G = bf16_bits_to_f64(X), bf16_bits_to_f64(dY)
+    close(got, ly.conv_wgrad(Xf, G, pad, R, R), ly.conv_wgrad(np.abs(Xf), np.abs(G), pad, R, R), ("wgrad", t, form, nbytes, off))
+    return asked
+
+
+def test_weight_gradient_where_shards_cannot_run_as_one_product():
+    # few channels per shard, pixels that are no multiple of 64: run as one product over all channels where the workspace has room
+    # for it and what it reads in place is aligned, and shard by shard otherwise
+    t = ("C", "r", "C", "C")
+    assert run_wgrad_in(None, 10, 16, 192, 8, 23, 3, 1, t, "2", 197) > 280064
+    run_wgrad_in(280064, 10, 16, 192, 8, 23, 3, 1, t, "2", 197)     # X whole, and nothing for partial sums
+    for off in (0, 2, 4):
+        run_wgrad_in(None, 6, 144, 192, 5, 7, 3, 1, ("r", "r", "r", "r"), "1", 198, off)   # X is read as stored
+        run_wgrad_in(None, 6, 144, 192, 5, 7, 3, 1, ("r", "R", "r", "r"), "1", 199, off)
+
+
 def run_straight_into_lds(images, C, R):
     # K of 72 (eight channels per tap, a short last K tile), of whole K tiles, one tap of 72, and taps that end inside a K tile
     run_conv(images, C, 136, 15, 17, R, R, R // 2, 1, True, "R", "r", "R", "R", "R", "1", "1", "3", 195)

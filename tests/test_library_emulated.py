@@ -168,6 +168,22 @@ def test_conv_weight_gradient_in_a_smaller_workspace(on_host):
     on_host["conv"].test_weight_gradient_in_a_smaller_workspace_takes_fewer_runs()
 
 
+def test_conv_weight_gradient_where_shards_cannot_run_as_one_product(on_host, monkeypatch):
+    c = on_host["conv"]
+    c.test_weight_gradient_where_shards_cannot_run_as_one_product()
+    for case in ((6, 16, 144, 5, 7, 3, 1, ("R", "C", "r", "R"), "2"), (4, 16, 192, 3, 9, 1, 0, ("rR", "rC", "CR", "rC"), "32"),
+                 (8, 144, 176, 5, 5, 3, 1, ("Rr", "rr", "RC", "Cr"), "12")):
+        monkeypatch.setenv("TT_WGRAD_MERGE", "0")
+        monkeypatch.setenv("TT_WGRAD_PARTS", "1")       # (what a product per shard asks for)
+        alone = c.run_wgrad_in(None, *case, 200)
+        monkeypatch.delenv("TT_WGRAD_MERGE")
+        monkeypatch.delenv("TT_WGRAD_PARTS")
+        c.run_wgrad_in(alone, *case, 200)
+    with pytest.raises(binding.TilingError) as e:       # twelve channels per shard
+        c.run_wgrad_in(None, 6, 16, 132, 5, 7, 1, 0, ("R", "C", "r", "R"), "2", 201)
+    assert binding.STATUS_NAMES[e.value.status] == "TT_EUNSUPPORTED"
+
+
 @pytest.mark.parametrize("C,R", [(8, 3), (64, 3), (72, 1), (136, 3)])
 def test_conv_forward_tiles_loaded_straight_into_lds(on_host, monkeypatch, C, R):
     monkeypatch.setenv("TT_CONV_TILE", "3")
