@@ -253,7 +253,9 @@ tt_status tt_shard_gemm(int count, const void *const *A, const void *const *B, v
  * the temporary outputs to the stored output tiling.  forms: k entries per product, or NULL = the first
  * minimiser of the product's communication cost (as tt_plan_eval reports it).
  * dtype: TT_BF16 (bf16 storage, fp32 accumulate; partial sums fp32) or TT_F32.
- * workspace: device memory, 256-byte aligned, at least tt_*_workspace_bytes(...) bytes; may be NULL if 0. */
+ * workspace: device memory, 256-byte aligned, at least tt_*_workspace_bytes(...) bytes; may be NULL if 0.
+ * Buffers that a call writes (results, gradients, workspace) must not overlap any other buffer given to it.  One exception:
+ * tt_fc_backward and tt_conv_backward may store dW in the place of W, whose last reader is the data gradient. */
 
 /* Exact workspace need of tt_fc_forward (op = TT_OP_FWD; tdY, tdX, forms_b ignored) or of tt_fc_backward
  * (op = TT_OP_DGRAD; forms_a = forms_dgrad, forms_b = forms_wgrad; with_dx = 0 if dX will be NULL) for the same
@@ -293,7 +295,7 @@ tt_status tt_fc_backward(const tt_layer *layer, int64_t batch, int k, int dtype,
  * earlier work and stream wait for the weight gradient before it returns, so callers keep ordering everything on
  * stream alone (and may capture stream into a HIP graph: aux_stream joins and leaves the capture inside the call).
  * Both streams must have default priority.  aux_stream NULL or equal to stream: same as tt_fc_backward.
- * The workspace need is that of tt_fc_backward (the two products never share scratch inside one call). */
+ * The workspace need is that of tt_fc_backward (the two products never share scratch inside one call).  dW may not overlap W here. */
 tt_status tt_fc_backward_overlapped(const tt_layer *layer, int64_t batch, int k, int dtype, tt_tiling tX, tt_tiling tW,
                                     tt_tiling tY, tt_tiling tdY, tt_tiling tdX, const uint8_t *forms_dgrad,
                                     const uint8_t *forms_wgrad, const void *const *X, const void *const *W,

@@ -378,6 +378,36 @@ template <class P> void fill_pair_half(P *p, const GemmCall &c, bool dgrad, int 
     p->kchunk = (int32_t)(c.ksplit == 1 ? c.K : ((c.K + c.ksplit - 1) / c.ksplit + 63) / 64 * 64);
 }
 
+// Whether a result of one product lies over an operand of the other (a weight gradient stored in the place of the weights), or over
+// a result: such products run one after the other.
+bool in_each_other_s_way(const GemmCall &d, const GemmCall &w)
+{
+    const auto meet = [](const void *const *p, int np, uint64_t pb, const void *const *q, int nq, uint64_t qb) {
+        for (int i = 0; i < np; ++i) {
+            const uintptr_t a = reinterpret_cast<uintptr_t>(p[i]);
+            for (int j = 0; j < nq; ++j) {
+                const uintptr_t b = reinterpret_cast<uintptr_t>(q[j]);
+                if (a < b + qb && b < a + pb) return true;
+            }
+        }
+        return false;
+    };
+    const auto elem = [](int dtype) { return dtype == TT_BF16 ? uint64_t(2) : uint64_t(4); };
+    const GemmCall *const g[2] = {&d, &w};
+    uint64_t a[2], b[2], c[2];
+    const void *const *out[2];
+    for (int i = 0; i < 2; ++i) {
+        a[i] = elem(g[i]->in_dtype) * (uint64_t)g[i]->M * (uint64_t)g[i]->K;
+        b[i] = elem(g[i]->in_dtype) * (uint64_t)g[i]->K * (uint64_t)g[i]->N;
+        c[i] = elem(g[i]->out_dtype) * (uint64_t)g[i]->M * (uint64_t)g[i]->N;
+        out[i] = const_cast<const void *const *>(g[i]->C);
+    }
+    const int outs[2] = {d.count * d.ksplit, w.count * w.ksplit};
+    for (int i = 0; i < 2; ++i)
+        if (meet(out[i], outs[i], c[i], g[1 - i]->A, g[1 - i]->count, a[1 - i]) || meet(out[i], outs[i], c[i], g[1 - i]->B, g[1 - i]->count, b[1 - i])) return true;
+    return meet(out[0], outs[0], c[0], out[1], outs[1], c[1]);
+}
+
 } // namespace
 
 tt_status launch_gemm_pair(const GemmCall &d, const GemmCall &w, void *stream)
@@ -394,12 +424,13 @@ tt_status launch_gemm_pair(const GemmCall &d, const GemmCall &w, void *stream)
             if (!c.C[s]) return TT_EUNSUPPORTED;
         mfma[i] = mfma_takes(c.count, c.A, c.B, c.M, c.N, c.K, i == 1, i == 0, c.in_dtype);
     }
-    if (mfma[0] != mfma[1]) return TT_EUNSUPPORTED;
+    if (mfma[0] != mfma[1] || in_each_other_s_way(d, w)) return TT_EUNSUPPORTED;
     if (!mfma[0]) return launch_ordered_pair(d, w, stream);
     // Results with 16-byte rows, the weight gradient in bf16 over K of at most 1024 (one K tile on its way, where a launch of its
-    // own has two), and no more than two workgroups per CU of either on the 128-column tiles of the register-staged engine: all
-    // of them are resident together.  Backward call, apart / together, us: 256 x 4096-1000 on 8 shards 29.1 / 21.3, 256 x 512-512 on
-    // one 21.7 / 12.0, 64 x 1536-776 on 4 16.4 / 9.7, 1024 x 1024-1024 on one 41.7 / 32.0, 128 x 4096-2048 on 8 (512 workgroups) 25.1 / 20.2.
+    // own has two), and no more than two workgroups per CU of either on the 128-column tiles of the register-staged engine.
+    // Backward call, apart / together, us: 256 x 4096-1000 on 8 shards 29.1 / 21.3, 256 x 512-512 on one 21.7 / 12.0, 64 x 1536-776 on 4
+    // 16.4 / 9.7, 1024 x 1024-1024 on one 41.7 / 32.0, 128 x 4096-2048 on 8 (512 workgroups) 25.1 / 20.2.  (Two fit a CU: at the limit
+    // the launch takes two rounds.)
     // Past that: 256 x 4096-4096 on 8 (1024) 43 / 51; 2048 x 512-512 on 8 (weight gradients over K = 2048) 47.9 / 54.1.
     if (w.ksplit != 1 || w.out_dtype != TT_BF16 || w.K > 1024) return TT_EUNSUPPORTED;
     if (w.N % 8 || d.N % (d.out_dtype == TT_BF16 ? 8 : 4) || !all_aligned16(const_cast<const void *const *>(w.C), w.count) ||

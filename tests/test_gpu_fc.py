@@ -157,6 +157,33 @@ def test_backward_products_in_one_launch_equal_two(b, ni, no, dt, k):
         run_together(b, ni, no, k, dt, seed, aux_stream=torch.cuda.Stream())
 
 
+def run_weight_gradient_over_the_weights(b, ni, no, k, dt, t, seed):
+    # dW in W's own buffers: the data gradient has read W by then, so the two products may not share a launch
+    lay = tt.layer("fc", "none", ni, no)
+    X, W, dY = (to_store(normal_f32(seed, i, shape, s), dt) for i, shape, s in ((0, (b, ni), 1.0), (1, (ni, no), 0.05), (2, (b, no), 1.0)))
+    Xs, Ws, dYs = (shards_to_dev(a, t[n], dt == "bf16") for a, n in ((X, "X"), (W, "W"), (dY, "dY")))
+    want = _backward_once(tt.tt_fc_backward, lay, b, k, dt, t, (None, None), Xs, Ws, dYs, dYs, ni, no)
+    torch.cuda.synchronize()
+    dXs = alloc_shards(b, ni, t["dX"], tdtype(dt), fill=float("nan"))
+    nb = tt.tt_fc_workspace_bytes(lay, b, k, dt, tt.TT_OP_DGRAD, t["X"], t["W"], t["Y"], t["dY"], t["dX"])
+    tt.tt_profile_begin()
+    tt.tt_fc_backward(lay, b, k, dt, t["X"], t["W"], t["Y"], t["dY"], t["dX"], None, None, Xs, Ws, dYs, dYs, dXs, Ws, workspace(nb))
+    products = [r for r in tt.tt_profile_end() if r["kernel"].startswith("gemm")]
+    assert len(products) == 2, products
+    for g, r in zip(dXs + Ws, want[0] + want[1]):
+        assert torch.equal(g, r)
+
+
+# tiles of the MFMA engine, the ordered kernel; one shard, weights in two column blocks, weights cut the other way for the data gradient
+IN_PLACE = [(40, 136, 72, 0, "bf16", "r"), (33, 65, 67, 0, "bf16", "r"), (35, 40, 33, 0, "f32", "r"), (40, 264, 72, 1, "bf16", "C"), (34, 66, 34, 1, "f32", "C")]
+
+
+@pytest.mark.parametrize("b,ni,no,k,dt,w", IN_PLACE)
+def test_weight_gradient_may_take_the_place_of_the_weights(b, ni, no, k, dt, w):
+    t = dict(X="r" * k, W=w * k, Y="C" * k, dY="C" * k, dX="r" * k)
+    run_weight_gradient_over_the_weights(b, ni, no, k, dt, t, 96)
+
+
 @pytest.mark.parametrize("relu", [False, True])
 def test_backward_overlapped_equals_backward(relu):
     # the two-stream variant must produce the very same bits, eagerly and as a captured graph replayed several times

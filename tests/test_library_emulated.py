@@ -318,6 +318,11 @@ def test_backward_products_in_one_launch_equal_two(on_host, monkeypatch, b, ni, 
     on_host["fc"].run_together(b, ni, no, k, dt, 94, aux_stream=16)
 
 
+def test_weight_gradient_may_take_the_place_of_the_weights(on_host):
+    for case in on_host["fc"].IN_PLACE:
+        on_host["fc"].test_weight_gradient_may_take_the_place_of_the_weights(*case)
+
+
 @pytest.mark.parametrize("runs", [1, 2, 3, 4])
 @pytest.mark.parametrize("k,forms", [(2, "33"), (3, "323")])
 def test_shards_of_one_block_run_as_one_product(on_host, monkeypatch, runs, k, forms):
