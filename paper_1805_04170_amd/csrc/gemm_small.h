@@ -288,7 +288,7 @@ __device__ __forceinline__ void run_small(const ParamsS &p, char *lds)
     const int m_wg = (t % p.tiles_m) * (p.wm * S), n_wg = (t / p.tiles_m) * (wn * S);
     const int shard = vshard / p.ksplit;
     const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
-    const int kend = kbeg + p.kchunk < p.K ? kbeg + p.kchunk : p.K;
+    const int kend = p.kchunk < p.K - kbeg ? kbeg + p.kchunk : p.K;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int my_k = wave % wk, blk = wave / wk;

@@ -68,11 +68,12 @@ template <bool BF, bool KC, int S, int KB> struct OrderedSide {
         }
     }
     // clamped addresses; what does not exist is zeroed in store().  (The contiguous side has two values at least.)
-    __device__ __forceinline__ void fetch(int k0, int kend, uint32_t (&x)[PT][W]) const
+    // Values of K are counted unsigned: a step's end lies up to a round of steps past K, which may be 2^31 - 1.
+    __device__ __forceinline__ void fetch(uint32_t k0, uint32_t kend, uint32_t (&x)[PT][W]) const
     {
 #pragma unroll
         for (int u = 0; u < PT; ++u) {
-            const int k = KC ? (k0 + c < kend - 1 ? k0 + c : kend - 2) : (k0 + line + u * STEP < kend ? k0 + line + u * STEP : kend - 1);
+            const uint32_t k = KC ? (k0 + c < kend - 1 ? k0 + c : kend - 2) : (k0 + line + u * STEP < kend ? k0 + line + u * STEP : kend - 1);
             const char *const p = KC ? base[u] + (int64_t)k * ES : base[0] + (int64_t)k * pitch;
             if constexpr (BF) x[u][0] = reinterpret_cast<const small::Pair16 *>(p)->w;
             else {
@@ -82,10 +83,10 @@ template <bool BF, bool KC, int S, int KB> struct OrderedSide {
             }
         }
     }
-    __device__ __forceinline__ void store(int k0, int kend, const uint32_t (&x)[PT][W], float *lds) const
+    __device__ __forceinline__ void store(uint32_t k0, uint32_t kend, const uint32_t (&x)[PT][W], float *lds) const
     {
         // of a pair that was moved back by one value at the end of an odd side, the second value is this thread's first
-        const int left = KC ? kend - (k0 + c) : rows - (row0 + c);
+        const int left = KC ? (int)(kend - (k0 + c)) : rows - (row0 + c);
 #pragma unroll
         for (int u = 0; u < PT; ++u) {
             const bool line_in = KC ? row0 + line + u * STEP < rows : k0 + line + u * STEP < kend;
@@ -119,8 +120,8 @@ template <bool BF, bool A_KC, bool B_KC, int S, int KB, class P> __device__ __fo
     const int vshard = block / tiles, t = block - vshard * tiles;
     const int m0 = (t % p.tiles_m) * T, n0 = (t / p.tiles_m) * T;
     const int shard = vshard / p.ksplit;
-    const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
-    const int kend = kbeg + p.kchunk < p.K ? kbeg + p.kchunk : p.K;
+    const uint32_t kbeg = (uint32_t)(vshard - shard * p.ksplit) * (uint32_t)p.kchunk;
+    const uint32_t kend = kbeg + (uint32_t)p.kchunk < (uint32_t)p.K ? kbeg + (uint32_t)p.kchunk : (uint32_t)p.K;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (wave >> 1) * S, wn0 = (wave & 1) * S;
     OA a;
@@ -139,10 +140,10 @@ template <bool BF, bool A_KC, bool B_KC, int S, int KB, class P> __device__ __fo
             a.fetch(kbeg + d * KB, kend, ra[d]);
             b.fetch(kbeg + d * KB, kend, rb[d]);
         }
-    for (int k0 = kbeg; k0 < kend; k0 += PD * KB) {
+    for (uint32_t k0 = kbeg; k0 < kend; k0 += PD * KB) {
 #pragma unroll
         for (int d = 0; d < PD; ++d) { // (unrolled: the register ring is indexed by constants; two LDS tiles in turn)
-            const int kd = k0 + d * KB;
+            const uint32_t kd = k0 + d * KB;
             if (kd >= kend) break;
             a.store(kd, kend, ra[d], As + (d & 1) * OA::LDS);
             b.store(kd, kend, rb[d], Bs + (d & 1) * OB::LDS);

@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <sys/mman.h>
 #include <vector>
 
 #define TT_HOST_EMULATION 1
@@ -38,6 +39,64 @@ static bool read_file(const char *dir, const char *name, int s, std::vector<char
     return got == into.size() && at_end;
 }
 
+// The last chunk of a 2 x 2 product with K = 2^31 - 2 on the ordered kernel: of operands of 2^32 values only what that chunk
+// may read can be read at all.
+struct HugeOperand {
+    char *base;
+    size_t bytes;
+    HugeOperand(bool k_contiguous, size_t es, size_t K, size_t kbeg) : bytes(2 * K * es)
+    {
+        base = static_cast<char *>(mmap(nullptr, bytes, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
+        if (base == MAP_FAILED) { std::perror("mmap"); std::exit(66); }
+        for (size_t r = 0; r < (k_contiguous ? 2 : 1); ++r) { // (whole pages)
+            const size_t lo = (k_contiguous ? (r * K + kbeg) * es : 2 * kbeg * es) & ~size_t(4095);
+            const size_t hi = ((k_contiguous ? (r + 1) * K * es : bytes) + 4095) & ~size_t(4095);
+            if (mprotect(base + lo, hi - lo, PROT_READ) != 0) { std::perror("mprotect"); std::exit(66); }
+        }
+    }
+    ~HugeOperand() { munmap(base, bytes); }
+};
+struct OneResult {
+    float c[4];
+    void *operator[](int) const { return const_cast<float *>(c); }
+};
+struct LastChunk { // (what small::ParamsT has, with the one result buffer that this chunk writes)
+    const void *A[1], *B[1];
+    OneResult C;
+    int32_t M, N, K;
+    int64_t lda, ldb;
+    int32_t ldc, tiles_m, tiles_n, ksplit, kchunk, relu, out_bf16;
+};
+template <bool BF, bool A_KC, bool B_KC, int S, int KB> static void run_last_chunk()
+{
+    const size_t K = 0x7ffffffe, kchunk = 662, chunks = K / kchunk, es = BF ? 2 : 4;
+    static_assert(K % kchunk == 0, "chunks that end where K does");
+    HugeOperand a(A_KC, es, K, K - kchunk), b(B_KC, es, K, K - kchunk);
+    LastChunk p;
+    std::memset(&p, 0, sizeof(p));
+    p.A[0] = a.base; p.B[0] = b.base;
+    for (float &v : p.C.c) v = 1.0f;
+    p.M = p.N = p.ldc = 2;
+    p.K = (int32_t)K;
+    p.lda = A_KC ? (int64_t)K : 2; p.ldb = B_KC ? (int64_t)K : 2;
+    p.tiles_m = p.tiles_n = 1;
+    p.ksplit = (int32_t)chunks;
+    p.kchunk = (int32_t)kchunk;
+    static float lds[tt::ordered_lds<BF, A_KC, B_KC, S, KB>()];
+    for (unsigned t = 0; t < 256; ++t) {
+        threadIdx = {t, 0, 0};
+        tt::run_ordered<BF, A_KC, B_KC, S, KB>(p, (int)chunks - 1, lds);
+    }
+    for (float v : p.C.c) if (v != 0.0f) { std::printf("a result of zeros is not zero\n"); std::exit(1); }
+}
+template <bool BF, bool A_KC, bool B_KC> static void run_last_chunks()
+{
+    run_last_chunk<BF, A_KC, B_KC, 16, 16>();
+    run_last_chunk<BF, A_KC, B_KC, 16, 64>();
+    run_last_chunk<BF, A_KC, B_KC, 32, 16>();
+    run_last_chunk<BF, A_KC, B_KC, 32, 32>();
+}
+
 int main(int argc, char **argv)
 {
     // emu_shard_gemm count M N K trans_a trans_b in_bf16 out_bf16 relu ksplit
@@ -48,6 +107,13 @@ int main(int argc, char **argv)
     // emu_shard_gemm ahead outputs M N K trans_a: how many K tiles of 64 the 128 x 128 tile keeps on their way
     if (argc == 7 && std::strcmp(argv[1], "ahead") == 0) {
         std::printf("%d\n", tt::two_tiles_ahead(std::atol(argv[3]), std::atol(argv[4]), std::atol(argv[5]), std::atol(argv[2]), std::atoi(argv[6]) == 0) ? 2 : 1);
+        return 0;
+    }
+    // emu_shard_gemm last_chunk
+    if (argc == 2 && std::strcmp(argv[1], "last_chunk") == 0) {
+        run_last_chunks<true, true, true>(); run_last_chunks<true, true, false>(); run_last_chunks<true, false, true>(); run_last_chunks<true, false, false>();
+        run_last_chunks<false, true, true>(); run_last_chunks<false, true, false>(); run_last_chunks<false, false, true>(); run_last_chunks<false, false, false>();
+        std::printf("ok last_chunk\n");
         return 0;
     }
     if (argc != 11 && argc != 12) { std::fprintf(stderr, "usage: emu_shard_gemm count M N K trans_a trans_b in_bf16 out_bf16 relu ksplit [dir]\n"); return 64; }

@@ -347,6 +347,12 @@ def test_ordered_kernel_stays_inside_its_buffers(emu_shard_gemm, layout, bf, mon
             assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (t64, M, N, K, r.stdout[-400:] + r.stderr[-1500:])
 
 
+def test_ordered_kernel_ends_its_walk_at_the_largest_k(emu_shard_gemm):
+    # K = 2^31 - 2: the step past the end does not fit a signed 32-bit integer
+    r = run(emu_shard_gemm, ("last_chunk",))
+    assert r.returncode == 0 and r.stdout.startswith("ok last_chunk"), r.stdout[-400:] + r.stderr[-1500:]
+
+
 def test_shard_product_entry_point_rejects_what_the_library_rejects(emu_shard_gemm):
     # a K split that would leave the last chunk empty (chunks are rounded up to the tile depth: two of 64 cover K = 128)
     r = run(emu_shard_gemm, (2, 64, 64, 128, 0, 0, 1, 0, 0, 3))
