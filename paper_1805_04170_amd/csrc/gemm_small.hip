@@ -365,7 +365,7 @@ tt_status launch_gemm_small(int count, const void *const *A, const void *const *
     const bool ordered = (bf && a_kc && !b_kc) || ordered_is_faster(bf, a_kc, b_kc, ksplit > 1 ? kchunk : K, tiles_of(g, count, 64));
     // The ordered kernel loads pairs along an operand's contiguous side.  A matrix of one row or one column is as well stored
     // the other way round; one that is a single value has no pair.
-    if (ordered && (K > 1 || M > 1) && (K > 1 || N > 1)) {
+    if (ordered && (K == 0 || ((K > 1 || M > 1) && (K > 1 || N > 1)))) { // (K = 0: nothing is loaded, zeros are stored)
         if (a_kc ? K == 1 : M == 1) { a_kc = !a_kc; g.lda = a_kc ? K : M; }
         if (b_kc ? K == 1 : N == 1) { b_kc = !b_kc; g.ldb = b_kc ? K : N; }
         return bf ? launch_ordered<true>(g, count, a_kc, b_kc, s) : launch_ordered<false>(g, count, a_kc, b_kc, s);

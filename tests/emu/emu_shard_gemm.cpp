@@ -137,7 +137,9 @@ int main(int argc, char **argv)
         A[s].assign((size_t)M * K * ib, 0);
         B[s].assign((size_t)K * N * ib, 0);
         if (dir && (!read_file(dir, "a", s, A[s]) || !read_file(dir, "b", s, B[s]))) { std::fprintf(stderr, "cannot read operand %d\n", s); return 65; }
-        Ap.push_back(A[s].data()); Bp.push_back(B[s].data());
+        // (operands of no elements: an address behind which nothing can be read)
+        alignas(16) static char none[16];
+        Ap.push_back(K ? A[s].data() : none + 16); Bp.push_back(K ? B[s].data() : none + 16);
         tt::dev::g_readable[tt::dev::g_n_readable++] = {A[s].data(), A[s].data() + A[s].size()};
         tt::dev::g_readable[tt::dev::g_n_readable++] = {B[s].data(), B[s].data() + B[s].size()};
     }

@@ -1,6 +1,8 @@
 """Parity of the shard-product kernels with the fp64 oracle.
 bf16 inputs / fp32 accumulate: |gpu - oracle| <= 1e-2 * (|A| |B|)_ij  (+ half an ulp of a bf16 store);
 fp32: <= 1e-5 * (|A| |B|)_ij."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -120,6 +122,17 @@ def test_odd_sized_forward_products_add_in_the_order_of_k(M, N, K):
     up = [torch.from_numpy(x.view(np.int16)).to(DEV).view(torch.bfloat16) for x in (a, b)]
     tt.tt_shard_gemm([up[0]], [up[1]], [c], M, N, K, 0, 0, "bf16", "f32")
     assert np.array_equal(dev_to_np(c), want)
+
+
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+def test_products_without_terms_are_zero(ta, tb):
+    # K = 0: operands of no elements (their addresses are not read), results of zeros
+    for M, N, dt, out, count in itertools.product((1, 33), (1, 33), ("bf16", "f32"), ("bf16", "f32"), (1, 3)):
+        a = [torch.ones(64, dtype=torch.bfloat16 if dt == "bf16" else torch.float32, device=DEV) for _ in range(count)]
+        c = [torch.full((M, N), float("nan"), dtype=torch.bfloat16 if out == "bf16" else torch.float32, device=DEV) for _ in range(count)]
+        tt.tt_shard_gemm(a, a, c, M, N, 0, ta, tb, dt, out)
+        for x in c:
+            assert torch.equal(x.cpu(), torch.zeros((M, N), dtype=x.dtype)), (M, N, dt, out)
 
 
 def run_error_against_one_chain(ta, tb, M, N, K, dt):

@@ -353,6 +353,14 @@ def test_ordered_kernel_ends_its_walk_at_the_largest_k(emu_shard_gemm):
     assert r.returncode == 0 and r.stdout.startswith("ok last_chunk"), r.stdout[-400:] + r.stderr[-1500:]
 
 
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_products_without_terms_read_nothing(emu_shard_gemm, layout):
+    for bf in (0, 1):
+        for M, N in [(1, 1), (1, 33), (33, 1), (33, 35), (1, 300), (64, 64)]:
+            r = run(emu_shard_gemm, (2, M, N, 0) + layout + (bf, bf, 0, 1))
+            assert r.returncode == 0 and r.stdout.startswith("ok shard_gemm"), (bf, M, N, r.stdout[-400:] + r.stderr[-1500:])
+
+
 def test_shard_product_entry_point_rejects_what_the_library_rejects(emu_shard_gemm):
     # a K split that would leave the last chunk empty (chunks are rounded up to the tile depth: two of 64 cover K = 128)
     r = run(emu_shard_gemm, (2, 64, 64, 128, 0, 0, 1, 0, 0, 3))

@@ -117,6 +117,11 @@ def test_fc_tiny_mlp_planned_and_recursive(on_host):
     on_host["fc"].test_config_tiny_mlp_fp32_planned_and_recursive()
 
 
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_products_without_terms_are_zero(on_host, ta, tb):
+    on_host["gemm"].test_products_without_terms_are_zero(ta, tb)
+
+
 @pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (1, 1)])
 def test_odd_sized_products_are_not_one_chain_of_additions(on_host, ta, tb):
     for dt, K in (("bf16", 129), ("bf16", 255), ("f32", 255)):
