@@ -86,7 +86,7 @@ def lib():
             raise ImportError("libtensor_tiling.so is not built; run `python -m paper_1805_04170_amd.build`")
         if _calls is None:
             from . import _calls as c
-            c.converters(tiling, forms, _dtype)
+            c.converters(tiling, _padded_forms, _dtype)
             _calls = c
         L = ctypes.CDLL(LIB_PATH)
         L.tt_strerror.restype = ctypes.c_char_p
@@ -211,14 +211,21 @@ def forms(f):
     return (ctypes.c_uint8 * max(len(f), 1))(*[int(ch) - 1 for ch in f])
 
 
-@functools.lru_cache(maxsize=4096)
-def _forms_of(f):
-    return forms(f)
+def _padded_forms(f):
+    """forms(f) in an array of TT_MAX_K entries: the library reads k of them, and what was not given is no form"""
+    a = forms(f)
+    if a is None:
+        return None
+    n = len(f)
+    return (ctypes.c_uint8 * max(n, TT_MAX_K))(*a[:n], *[255] * (TT_MAX_K - n))
+
+
+_forms_of = functools.lru_cache(maxsize=4096)(_padded_forms)
 
 
 def _forms(f):
-    """forms(f) for a call (the library only reads it): the array of a string is made once"""
-    return _forms_of(f) if type(f) is str else forms(f)
+    """forms for a call (the library only reads them): the array of a string is made once"""
+    return _forms_of(f) if type(f) is str else _padded_forms(f)
 
 
 def layer(kind="fc", act="none", n_in=0, n_out=0, H=0, W=0, R=0, S=0, pad=0):
@@ -366,7 +373,7 @@ def tt_product_cross_elems(M, K, N, tX, tY, tZ, form_seq, mult=(1, 1, 1), k=None
     """Returns [X conversion, Y conversion, output conversion / reduction] in elements."""
     k = len(form_seq) if k is None else k
     out = (ctypes.c_uint64 * 3)()
-    _check(lib().tt_product_cross_elems(M, K, N, tiling(tX), tiling(tY), tiling(tZ), forms(form_seq), k, mult[0], mult[1],
+    _check(lib().tt_product_cross_elems(M, K, N, tiling(tX), tiling(tY), tiling(tZ), _forms(form_seq), k, mult[0], mult[1],
                                         mult[2], out), "tt_product_cross_elems")
     return [out[0], out[1], out[2]]
 
@@ -378,6 +385,7 @@ def tt_fc_chain_cross_elems(layers, batch, k, x, g, w, layer_forms):
     ga = (tt_tiling * (L + 1))(*[tiling(t) for t in g])
     wa = (tt_tiling * L)(*[tiling(t) for t in w])
     flat = [int(ch) - 1 for lf in layer_forms for f in lf for ch in f]
+    flat += [255] * (3 * L * k - len(flat))    # (sequences shorter than k: no form)
     fo = (ctypes.c_uint8 * max(len(flat), 1))(*flat)
     out = ctypes.c_uint64()
     _check(lib().tt_fc_chain_cross_elems(_layers(layers), L, batch, k, xa, ga, wa, fo, ctypes.byref(out)),

@@ -118,7 +118,7 @@ struct Args {
             if (j == PyUnicode_GET_LENGTH(o)) return buf;
         }
         PyObject *x = converted(g_forms, o);
-        return x ? static_cast<const uint8_t *>(bytes_of(x, 1)) : nullptr;
+        return x ? static_cast<const uint8_t *>(bytes_of(x, TT_MAX_K)) : nullptr; // (the converter fills up short sequences)
     }
     int dtype()
     {

@@ -436,3 +436,25 @@ def test_layer_calls_take_what_the_binding_documents(monkeypatch):
                        (dict(f="a"), ValueError)):
         with pytest.raises(error):
             fwd(**bad)
+
+
+def test_form_sequences_shorter_than_the_cuts_are_refused(monkeypatch):
+    # nothing past the end of what was given is read, whatever it was given as (nothing is launched: every call is refused)
+    import torch
+    monkeypatch.setattr(tt.binding, "_stream", lambda stream: 0)
+    lay, x = tt.layer("fc", "none", 8, 8), [torch.zeros(8) for _ in range(4)]
+    t = ("RR", "rr", "RR")
+    for short in ("1", "", [1], (1,), [], b"", [1, 9]):
+        for call in (lambda: tt.tt_fc_forward(lay, 8, 2, "bf16", *t, short, x, x, x),
+                     lambda: tt.tt_fc_forward_static(lay, 8, 2, "bf16", *t, short, x, x, x),
+                     lambda: tt.tt_fc_backward(lay, 8, 2, "bf16", *t, "RR", "RR", short, "11", x, x, x, x, x, x),
+                     lambda: tt.tt_fc_backward(lay, 8, 2, "bf16", *t, "RR", "RR", "11", short, x, x, x, x, None, x),
+                     lambda: tt.tt_fc_backward_overlapped(lay, 8, 2, "bf16", *t, "RR", "RR", short, "11", x, x, x, x, x, x),
+                     lambda: tt.tt_fc_workspace_bytes(lay, 8, 2, "bf16", tt.TT_OP_FWD, *t, forms_a=short),
+                     lambda: tt.tt_product_cross_elems(8, 8, 8, *t, short, k=2),
+                     lambda: tt.tt_fc_chain_cross_elems([lay], 8, 2, ["RR", "RR"], ["RR", "RR"], ["rr"], [["11", "11", short]]),
+                     lambda: tt.tt_reduce(x, "rr", "f32", x, short, 8, 8, k=2)):
+            with pytest.raises(tt.TilingError) as e:
+                call()
+            assert e.value.status in (1, 2), short
+    assert tt.tt_product_cross_elems(8, 8, 8, *t, "11") == tt.tt_product_cross_elems(8, 8, 8, *t, [1, 1])
