@@ -349,9 +349,6 @@ tt_status launch_gemm_runs(int nblk, int nred, int parts, const void *const *A, 
         if (!C[i]) return TT_EUNSUPPORTED;
     if (!mfma_takes(nblk * nred, A, B, M, N, K, trans_a != 0, trans_b != 0, TT_BF16)) return TT_EUNSUPPORTED;
     if (N % (out_dtype == TT_BF16 ? 8 : 4) || !all_aligned16(const_cast<const void *const *>(C), nblk * parts)) return TT_EUNSUPPORTED;
-    ProfileScope scope(stream, trans_a ? TT_K_GEMM_TN : trans_b ? TT_K_GEMM_NT : TT_K_GEMM_NN, nblk * nred, M, N, K,
-                       2ull * nblk * nred * ((uint64_t)M * K + (uint64_t)K * N) + (out_dtype == TT_BF16 ? 2ull : 4ull) * nblk * parts * (uint64_t)M * N,
-                       2ull * (uint64_t)M * (uint64_t)N * (uint64_t)K * (uint64_t)(nblk * nred));
     return launch_gemm_v3_runs(nblk, nred, parts, A, B, C, M, N, K, trans_a ? M : K, trans_b ? K : N, N, !trans_a, trans_b != 0, out_dtype,
                                act == TT_ACT_RELU, stream);
 }
@@ -445,7 +442,7 @@ tt_status launch_gemm_pair(const GemmCall &d, const GemmCall &w, void *stream)
     fill_pair_half(&p.wgrad, w, false, 128, 8, 8);
     if (d.ksplit > 1 && (int64_t)p.dgrad.kchunk * (d.ksplit - 1) >= d.K) return TT_EUNSUPPORTED;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    ProfileScope scope(stream, TT_K_GEMM_NT, d.count, d.M, d.N, d.K, d.bytes() + w.bytes(), d.flops() + w.flops());
+    ProfileScope scope(stream, TT_K_GEMM_PAIR, d.count, d.M, d.N, d.K, d.bytes() + w.bytes(), d.flops() + w.flops());
     return d.K % core::BK || w.K % core::BK ? launch_bf16_pair_rows<true>(p, DM, d.out_dtype == TT_BF16, s)
                                             : launch_bf16_pair_rows<false>(p, DM, d.out_dtype == TT_BF16, s);
 }

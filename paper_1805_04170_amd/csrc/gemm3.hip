@@ -242,11 +242,15 @@ tt_status launch_gemm_v3_runs(int nblk, int nred, int parts, const void *const *
     core3::Params3 p;
     const tt_status st = fill_params3_runs(&p, cu_count(), nblk, nred, parts, A, B, C, M, N, K, lda, ldb, ldc, a_kc, b_kc, relu);
     if (st != TT_OK) return st;
+    if (!a_kc && b_kc) return TT_EUNSUPPORTED;
+    // (recorded only once the launch is certain: a refused product is launched, and recorded, shard by shard)
+    ProfileScope scope(stream, !a_kc ? TT_K_GEMM_TN : b_kc ? TT_K_GEMM_NT : TT_K_GEMM_NN, nblk * nred, M, N, K,
+                       2ull * nblk * nred * ((uint64_t)M * K + (uint64_t)K * N) + (out_dtype == TT_BF16 ? 2ull : 4ull) * nblk * parts * (uint64_t)M * N,
+                       2ull * (uint64_t)M * (uint64_t)N * (uint64_t)K * (uint64_t)(nblk * nred));
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (a_kc && b_kc) return launch_runs<true, true>(p, out_dtype, s);
     if (a_kc) return launch_runs<true, false>(p, out_dtype, s);
-    if (!b_kc) return launch_runs<false, false>(p, out_dtype, s);
-    return TT_EUNSUPPORTED;
+    return launch_runs<false, false>(p, out_dtype, s);
 }
 
 } // namespace tt

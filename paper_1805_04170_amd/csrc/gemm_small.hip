@@ -418,7 +418,7 @@ tt_status launch_ordered_pair(const GemmCall &d, const GemmCall &w, void *stream
     }
     p.first = (int32_t)tiles[0];
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    ProfileScope scope(stream, TT_K_GEMM_GENERIC, d.count, d.M, d.N, d.K, d.bytes() + w.bytes(), d.flops() + w.flops());
+    ProfileScope scope(stream, TT_K_GEMM_PAIR, d.count, d.M, d.N, d.K, d.bytes() + w.bytes(), d.flops() + w.flops());
     if (d.in_dtype == TT_BF16) return launch_ordered_pair_type<true>(p, tiles[0] + tiles[1], small_step[0], small_step[1], s);
     return launch_ordered_pair_type<false>(p, tiles[0] + tiles[1], small_step[0], small_step[1], s);
 }

@@ -174,8 +174,32 @@ def run_weight_gradient_over_the_weights(b, ni, no, k, dt, t, seed):
         assert torch.equal(g, r)
 
 
+def run_records_of_a_backward_pass(b, ni, no, dt):
+    # the records of a call add up to its two products, and only a shared launch is recorded as a pair
+    lay, t = tt.layer("fc", "none", ni, no), dict(X="", W="", Y="", dY="", dX="")
+    X, W, dY = (shards_to_dev(to_store(normal_f32(98, i, shape, 0.1), dt), "", dt == "bf16") for i, shape in ((0, (b, ni)), (1, (ni, no)), (2, (b, no))))
+    e = 2 if dt == "bf16" else 4
+    for fn in (tt.tt_fc_backward, tt.tt_fc_backward_overlapped):
+        tt.tt_profile_begin()
+        _backward_once(fn, lay, b, 0, dt, t, (None, None), X, W, dY, dY, ni, no, **({} if fn is tt.tt_fc_backward else dict(aux_stream=aux_stream())))
+        r = [r for r in tt.tt_profile_end() if r["kernel"].startswith("gemm")]
+        assert sum(x["flops"] for x in r) == 2 * 2 * b * ni * no
+        assert sum(x["bytes"] for x in r) == e * 2 * (b * ni + ni * no + b * no)
+        assert [x["kernel"] for x in r] == ["gemm_pair"] if fn is tt.tt_fc_backward else len(r) == 2 and "gemm_pair" not in [x["kernel"] for x in r]
+        assert sorted([(x["d0"], x["d1"], x["d2"]) for x in r]) == sorted([(b, ni, no), (ni, no, b)][:len(r)])
+
+
+def aux_stream():
+    return torch.cuda.Stream()
+
+
+@pytest.mark.parametrize("b,ni,no,dt", [(40, 136, 72, "bf16"), (33, 65, 67, "bf16"), (35, 40, 65, "f32")])
+def test_records_of_a_backward_pass(b, ni, no, dt):
+    run_records_of_a_backward_pass(b, ni, no, dt)
+
+
 # tiles of the MFMA engine, the ordered kernel; one shard, weights in two column blocks, weights cut the other way for the data gradient
-IN_PLACE = [(40, 136, 72, 0, "bf16", "r"), (33, 65, 67, 0, "bf16", "r"), (35, 40, 33, 0, "f32", "r"), (40, 264, 72, 1, "bf16", "C"), (34, 66, 34, 1, "f32", "C")]
+IN_PLACE = [(40, 136, 72, 0, "bf16", "r"), (33, 65, 67, 0, "bf16", "r"), (35, 40, 65, 0, "f32", "r"), (40, 264, 72, 1, "bf16", "C"), (34, 66, 34, 1, "f32", "C")]
 
 
 @pytest.mark.parametrize("b,ni,no,k,dt,w", IN_PLACE)

@@ -323,6 +323,13 @@ def test_backward_products_in_one_launch_equal_two(on_host, monkeypatch, b, ni, 
     on_host["fc"].run_together(b, ni, no, k, dt, 94, aux_stream=16)
 
 
+@pytest.mark.parametrize("b,ni,no,dt", [(40, 136, 72, "bf16"), (33, 65, 67, "bf16"), (35, 40, 65, "f32")])
+def test_records_of_a_backward_pass(on_host, monkeypatch, b, ni, no, dt):
+    monkeypatch.setattr(binding, "_stream", lambda s: s if isinstance(s, int) else 0)
+    monkeypatch.setattr(on_host["fc"], "aux_stream", lambda: 16)
+    on_host["fc"].run_records_of_a_backward_pass(b, ni, no, dt)
+
+
 def test_weight_gradient_may_take_the_place_of_the_weights(on_host):
     for case in on_host["fc"].IN_PLACE:
         on_host["fc"].test_weight_gradient_may_take_the_place_of_the_weights(*case)
