@@ -80,14 +80,10 @@ _u64p = ctypes.POINTER(ctypes.c_uint64)
 
 def lib():
     """Load the HIP library.  There is no fallback: a missing library is an error."""
-    global _lib, _calls
+    global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError("libtensor_tiling.so is not built; run `python -m paper_1805_04170_amd.build`")
-        if _calls is None:
-            from . import _calls as c
-            c.converters(tiling, _padded_forms, _dtype)
-            _calls = c
         L = ctypes.CDLL(LIB_PATH)
         L.tt_strerror.restype = ctypes.c_char_p
         L.tt_strerror.argtypes = [ctypes.c_int]
@@ -162,6 +158,11 @@ _DIRECT = ("tt_fc_forward", "tt_conv_forward", "tt_fc_forward_static", "tt_fc_ba
 
 
 def _address(name):
+    global _calls
+    if _calls is None:      # (the planner and the other ctypes calls do without it)
+        from . import _calls as c
+        c.converters(tiling, _padded_forms, _dtype)
+        _calls = c
     return (_lib or lib()).addresses[name]
 
 

@@ -47,11 +47,11 @@ def build_calls():
 
 def build(jobs=8):
     os.makedirs(OBJ, exist_ok=True)
-    build_calls()
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         objs = list(ex.map(_compile, sources()))
     cmd = ["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     subprocess.check_call(cmd)
+    build_calls()       # last: it needs Python's headers, the library does not
     return LIB
 
 

@@ -458,3 +458,21 @@ def test_form_sequences_shorter_than_the_cuts_are_refused(monkeypatch):
                 call()
             assert e.value.status in (1, 2), short
     assert tt.tt_product_cross_elems(8, 8, 8, *t, "11") == tt.tt_product_cross_elems(8, 8, 8, *t, [1, 1])
+
+
+def test_the_library_is_built_before_the_binding_s_module(monkeypatch):
+    # the C library knows nothing of Python: where the extension module cannot be compiled (no headers), it is still linked
+    import subprocess as sp
+    from paper_1805_04170_amd import build as b
+    ran = []
+
+    def check_call(cmd, *a, **kw):
+        ran.append(cmd)
+        if any("calls.cpp" in str(x) for x in cmd):
+            raise sp.CalledProcessError(1, cmd)
+
+    monkeypatch.setattr(b, "_compile", lambda src: src + ".o")
+    monkeypatch.setattr(b.subprocess, "check_call", check_call)
+    with pytest.raises(sp.CalledProcessError):
+        b.build()
+    assert any("-shared" in c and b.LIB in c for c in ran)
