@@ -528,9 +528,11 @@ tt_status launch_reduce(void *const *dst, const uint8_t *Bl, int out_dtype, cons
     p.pieces_c = (uint32_t)(B.scols / piece_cols);
     p.pieces = (uint32_t)((B.srows / piece_rows) * (B.scols / piece_cols));
     p.piece_vecs = (uint32_t)piece_vecs;
-    // A quarter of the partial sums per wave below 64 K vectors: 7936 vectors of 57 partial sums 15.0 -> 5.5 us, 1536 of 48 8.8 -> 4.9,
-    // 53184 of 8 7.5 -> 6.1, 1024 of 32 9.2 -> 5.4; 64000 of 16 as before (7.9 / 8.1), 121856 of 8 slower (7.8 / 10.1).
-    const bool by_waves = unroll == 1 && unique_vecs < (uint64_t)1 << 16 && n_part >= 8;
+    // A quarter of the partial sums per wave below 64 K vectors, and up to 2048 vectors per partial sum: past that a workgroup for every
+    // 64 vectors is a second round of them, while one for every 256 still has its loads in flight.  Whole / quarters, us, captured
+    // loops: 7936 vectors of 64 10.2 / 5.6, 1024 of 32 6.6 / 4.3, 16384 of 8 3.7 / 3.4, 20480 of 8 3.7 / 3.8, 53184 of 8 4.1 / 5.7, 32768 of 16
+    // 5.3 / 4.6, 57344 of 16 4.9 / 6.2, 55296 of 32 9.7 / 8.8, 65024 of 64 17.5 / 16.7.
+    const bool by_waves = unroll == 1 && n_part >= 8 && unique_vecs < (uint64_t)1 << 16 && unique_vecs <= 2048ull * n_part;
     const uint32_t per_tile = by_waves ? kThreads / 4 : (uint32_t)(kThreads * unroll);
     p.tiles_per_piece = (uint32_t)((piece_vecs + per_tile - 1) / per_tile);
     p.step_rows = (uint32_t)(kThreads / piece_cv);

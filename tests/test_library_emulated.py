@@ -94,6 +94,19 @@ def test_flatten_takes_small_tiles_where_large_ones_would_be_mostly_empty(on_hos
     assert torch.equal(y.view(images, -1), a.transpose(1, 2).reshape(images, -1))
 
 
+@pytest.mark.parametrize("vectors,partials,by_waves", [(16384, 8, True), (16388, 8, False), (2048, 4, False)])
+def test_reductions_are_cut_over_waves_while_they_leave_the_chip_idle(on_host, emulated_library, vectors, partials, by_waves):
+    # workgroups of 256 threads, for 64 vectors each or for 256
+    k = partials.bit_length() - 1
+    parts = [torch.ones(1, 4 * vectors) for _ in range(partials)]
+    out = torch.empty(1, 4 * vectors)
+    ran = ctypes.c_ulonglong.in_dll(ctypes.CDLL(emulated_library), "g_emu_threads_run")
+    before = ran.value
+    binding.tt_reduce([out] * partials, "r" * k, "f32", parts, "3" * k, 1, 4 * vectors)
+    assert ran.value - before == -(-vectors // (64 if by_waves else 256)) * 256
+    assert torch.equal(out, torch.full_like(out, partials))
+
+
 # ---- the GPU parity tests themselves, run on the host where their sizes allow
 
 @pytest.mark.parametrize("relu", [False, True])
