@@ -240,7 +240,7 @@ def _ptr_array(n):
 
 
 def ptrs(shards):
-    """sequence of tensors / addresses -> void*[]; None -> NULL"""
+    """sequence of tensors / addresses -> void*[], NULL from its end up to as many shards as there can be; None -> NULL"""
     if shards is None:
         return None
     shards = list(shards)
@@ -248,7 +248,7 @@ def ptrs(shards):
         vals = [s.data_ptr() for s in shards]
     except AttributeError:
         vals = [(s.data_ptr() if hasattr(s, "data_ptr") else int(s)) for s in shards]
-    return _ptr_array(max(len(vals), 1))(*vals)
+    return _ptr_array(max(len(vals), 1 << TT_MAX_K))(*vals)
 
 
 try:

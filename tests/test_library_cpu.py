@@ -476,3 +476,20 @@ def test_the_library_is_built_before_the_binding_s_module(monkeypatch):
     with pytest.raises(sp.CalledProcessError):
         b.build()
     assert any("-shared" in c and b.LIB in c for c in ran)
+
+
+def test_shard_lists_shorter_than_the_shards_are_refused(monkeypatch):
+    # entries that were not given are NULL addresses, in every call (nothing is launched: every call is refused)
+    import torch
+    monkeypatch.setattr(tt.binding, "_stream", lambda stream: 0)
+    lay, x = tt.layer("fc", "none", 8, 8), [torch.zeros(64) for _ in range(4)]
+    few = x[:1]
+    for call in (lambda: tt.tt_shard_gemm(few, x, x, 8, 8, 8), lambda: tt.tt_shard_gemm(x, few, x, 8, 8, 8), lambda: tt.tt_reduce(x, "rr", "f32", few, "33", 8, 8),
+                 lambda: tt.tt_reduce(few, "rr", "f32", x, "33", 8, 8), lambda: tt.tt_retile_gate(x, "RR", few, "RR", x, "RR", 8, 8, "f32"),
+                 lambda: tt.tt_retile_gate(x, "RR", x, "CC", few, "RR", 8, 8, "f32"), lambda: tt.tt_retile_gate(few, "RR", x, "CC", x, "RR", 8, 8, "f32"),
+                 lambda: tt.tt_fc_backward_overlapped(lay, 8, 2, "bf16", "RR", "rr", "RR", "RR", "RR", "11", "33", x, few, x, x, x, x),
+                 lambda: tt.tt_fc_backward(lay, 8, 2, "bf16", "RR", "rr", "RR", "RR", "RR", "11", "33", x, few, x, x, x, x)):
+        with pytest.raises(tt.TilingError) as e:
+            call()
+        assert e.value.status == 1
+    assert list(tt.binding.ptrs(few)[1:]) == [None] * 63 and tt.binding.ptrs(None) is None
