@@ -167,7 +167,11 @@ inline int pick_ksplit(int64_t M, int64_t N, int64_t K, int count, int dtype, bo
 // Shards that an F3 cut makes add up into the same output block, and where they run one product each, every one of them
 // writes its whole block as an fp32 partial sum for the reduction to read again (16 x 512 x 8192 in the F3^4 layer: 268 MB).
 // How a block's K range is cut is free, so it is cut into as many runs as fill the chip, and no more (gemm_core3.h).
-// 16 shards of 512 x 8192 x 512: product 105 -> 72 us, reduction 49 -> 16 (4 runs, one item of 32 K tiles per CU).
+// 16 shards of 512 x 8192 x 512: product 105 -> 72 us, reduction 49 -> 16 (4 runs, one item of 32 K tiles per CU).  Forward calls, a
+// product per shard / runs, us: 256 x 8192 x 8192 on 16 shards 94 / 71, 2048 x 8192-2048 on 8 120 / 95, 2048 x 8192-8192 on 4 324 / 259, 520 x
+// 8192-8192 on 4 137 / 122, 520 x 4096-12288 on 4 127 / 114; next to the line 264 x 16384-4096 on 4 85 / 84, 512 x 16384-8192 on 8 in two
+// blocks 150 / 153.  Sums of more values of K are held in fp32 than before; of the stored bf16 results 3 in 10000 instead of 2 are not
+// the rounded exact value, and their error against 64 bits agrees to seven digits (1.6586029e-3 at 512 x 8192-8192 on 16).
 // Returns the number of runs, or 0 where a product per shard is no slower.  The estimate, in microseconds with all CUs at
 // work: 2.0 per K tile of a 256 x 256 tile, 9 to write its fp32 results (5 in bf16), 5.5 TB/s for the reduction (4 TB/s
 // for the copy into the stored tiling that one bf16 result needs).

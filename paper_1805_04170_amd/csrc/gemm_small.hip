@@ -250,10 +250,11 @@ template <bool BF> tt_status launch_ordered(small::ParamsS &p, int count, bool a
 // be worth cutting and whose write-out goes through LDS once more; its bf16 instructions multiply eight times as fast.  So
 // bf16 crosses over at K of 200 to 500, fp32 only where K is long enough for eight waves to walk it sooner than one (few
 // tiles), or where its 64 x 64 blocks fill the CUs better.  (tiles: of 64 x 64.)  Small / ordered kernel, us:
-//   bf16 A B^T  257 x 255 (20 tiles)  K 63 6.1 / 3.2, 255 6.2 / 5.3, 319 6.7 / 6.1, 383 6.6 / 6.8;  767 x 1153 (228)  223 9.9 / 9.8, 255 9.7 / 10.6;
-//     8 x (511 x 513) (576)  127 24.0 / 14.1, 511 39.6 / 37.0, 767 46.8 / 51.9;  2047 x 4095 (2048)  159 45.3 / 33.5, 255 49.9 / 48.6, 319 54.8 / 59.3
-//   bf16 A^T B  257 x 255  95 10.0 / 3.8, 511 8.9 / 8.1, 767 10.5 / 11.1;  1023 x 1535 (384)  127 18.6 / 9.5, 191 20.5 / 12.2, 223 14.6 / 14.9;
-//     4 x (375 x 900) (360)  200 17.1 / 18.7;  2047 x 4095  191 40.6 / 40.4, 223 43.7 / 45.7
+//   bf16 A B^T  257 x 255 (20 tiles)  K 63 6.1 / 3.8, 255 6.2 / 5.5, 319 6.7 / 6.2, 383 6.7 / 7.0;  511 x 767 (96)  319 8.4 / 7.8, 383 8.4 / 8.8;
+//     767 x 1153 (228)  223 9.9 / 10.0, 255 9.9 / 10.8;  1023 x 1535 (384)  319 19.1 / 17.5, 447 21.2 / 21.7;  8 x (511 x 513) (576)  447 38.9 / 33.3, 511
+//     40.2 / 37.5;  2047 x 4095 (2048)  159 45.1 / 38.7, 223 49.0 / 46.7, 255 49.6 / 52.4;  4 x (2047 x 4095) (8192)  191 173 / 152, 255 189 / 192
+//   bf16 A^T B  257 x 255  255 9.4 / 5.6, 511 9.1 / 8.5;  511 x 767  447 14.5 / 10.1, 511 10.9 / 11.0;  767 x 1153  191 14.0 / 9.2;  1023 x 1535  191
+//     20.5 / 12.8, 223 14.7 / 15.6;  2047 x 4095  159 39.6 / 37.2, 191 40.3 / 41.3, 223 43.3 / 46.5;  4 x (2047 x 4095)  191 153 / 152
 //   fp32 A B^T  4 x (32 x 128) (8)  1535 20.3 / 20.8;  1023 x 1023 (256)  1023 29.6 / 33.1;  2047 x 4095  1023 186 / 202;  fp32 A^T B  4 x (101 x 225) (32)
 //     1023 15.1 / 16.3;  fp32 A B  64 x (65 x 67) (256)  255 12.6 / 12.0, 511 18.1 / 20.0;  4095 x 4093 (4096) ahead up to K = 4095 (1385 / 1310)
 // (fp32 A B^T on few tiles with K a little over one chunk keeps its kernel, whose one trip to memory takes it in.)
@@ -269,7 +270,7 @@ bool ordered_is_faster(bool bf, bool a_kc, bool b_kc, int64_t K, int64_t tiles)
     }
     if (tiles <= 224) return K <= (nt ? 320 : tn ? 512 : 448);
     if (tiles <= 256) return K <= (nt ? 224 : tn ? 192 : 256);
-    return K <= (tiles < 2048 ? (nt ? 448 : tn ? 192 : 256) : (nt ? 256 : 192));
+    return K <= (tiles < 2048 ? (nt ? 448 : tn ? 192 : 256) : (nt ? 224 : 192));
 }
 
 template <bool BF, int KD, int KW> tt_status launch_ordered_pair_steps(const OrderedPair &p, int64_t total, hipStream_t s)
