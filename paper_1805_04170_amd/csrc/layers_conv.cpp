@@ -357,13 +357,9 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
         if (bf16 && tuning_int("TT_WGRAD_MERGE", 1) != 0) {
             const bool m1 = k1 > 0 && (d.C >> k1) <= 128 && d.C > 128, m2 = k2 > 0 && (d.K >> k2) <= 128 && d.K > 128;
             const int64_t Cm = m1 ? d.C : d.C >> k1, Km = m2 ? d.K : d.K >> k2, Ns = d.N >> k3; // per product
-            // Shards of whole K tiles run this way or not at all.  Others have a product per shard to fall back on: for channels of a
-            // shard that are no multiple of 8 (refused there), for workspaces of no more than that one needs (X or dY whole takes up
-            // more room) and for operands stored at addresses that only a copy brings to 16 bytes; a query covers both ways.
-            const bool only = (Ns * pq) % 64 == 0;
             const int64_t lim = int64_t(1) << 30; // the evenly cut product's own limits (32-bit offsets, 16-byte chunks, tap masks)
             const bool fits = Cm % 8 == 0 && Km % 8 == 0 && Km > 128 && rs <= 32 && Ns * hw * Cm < lim && Ns * pq * Km < lim &&
-                              Km * rs * Cm < lim && Ns * pq >= 8 && (only || ((d.C >> k1) % 8 == 0 && (d.K >> k2) % 8 == 0));
+                              Km * rs * Cm < lim && Ns * pq >= 8;
             uint32_t mask_m = 0;
             uint8_t zr[TT_MAX_K], zp[TT_MAX_K]; // letters for the reduction (k cuts) and for the product (the cuts kept)
             tt_tiling aGm = aG, aXm = transpose_tiling(aXt, k);
@@ -383,7 +379,13 @@ tt_status backward(const ConvArgs &a, const Dims &d, Workspace &ws)
                 const int nred = 1 << gp.kX, nblk = (1 << kp) >> gp.kX;
                 const size_t blk_bytes = (size_t)gp.srows * (size_t)gp.scols * 4;
                 WgradChoice choice = pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes, kMaxShards / nblk);
-                bool taken = choice.parts > 0;
+                // Shards of whole K tiles run this way or not at all, unless so many of them add up into a block that as few partial
+                // sums as one per shard's share of the tables are not enough.  Others have a product per shard to fall back on: for
+                // channels of a shard that are no multiple of 8 (refused there), for workspaces of no more than that one needs (X or
+                // dY whole takes up more room) and for operands stored at addresses that only a copy brings to 16 bytes; a query
+                // covers both ways.
+                const bool only = (Ns * pq) % 64 == 0 && pick_wgrad_parts(nblk, nred, Ns * pq, Km, rs * Cm, blk_bytes, kMaxShards >> k).parts > 0;
+                bool taken = choice.parts > 0 && (only || ((d.C >> k1) % 8 == 0 && (d.K >> k2) % 8 == 0));
                 if (taken) { // tried out before anything is launched
                     Workspace probe = ws;
                     probe.dry = true;

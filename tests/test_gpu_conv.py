@@ -204,6 +204,15 @@ def test_weight_gradient_where_shards_cannot_run_as_one_product():
         run_wgrad_in(None, 6, 144, 192, 5, 7, 3, 1, ("r", "R", "r", "r"), "1", 199, off)
 
 
+def test_weight_gradient_of_whole_k_tiles_that_many_shards_add_up():
+    # eight shards add up into a block and 32 leave room for two partial sums per shard: once a product per shard
+    t = ("RRRrr", "rrrrr", "RRRrr", "RRRCC")
+    assert run_wgrad_in(None, 8, 16, 160, 8, 8, 1, 0, t, "33322", 202) > 81920
+    run_wgrad_in(81920, 8, 16, 160, 8, 8, 1, 0, t, "33322", 202)    # dY whole, and nothing for its partial sums
+    for off in (0, 2, 4):       # X is read as stored by the one product, and copied for a product per shard
+        run_wgrad_in(None, 8, 160, 192, 8, 8, 1, 0, ("RRRrr", "rrrrr", "RRRrr", "RRRrr"), "33311", 203, off)
+
+
 def run_straight_into_lds(images, C, R):
     # K of 72 (eight channels per tap, a short last K tile), of whole K tiles, one tap of 72, and taps that end inside a K tile
     run_conv(images, C, 136, 15, 17, R, R, R // 2, 1, True, "R", "r", "R", "R", "R", "1", "1", "3", 195)

@@ -189,6 +189,7 @@ def test_conv_weight_gradient_in_a_smaller_workspace(on_host):
 def test_conv_weight_gradient_where_shards_cannot_run_as_one_product(on_host, monkeypatch):
     c = on_host["conv"]
     c.test_weight_gradient_where_shards_cannot_run_as_one_product()
+    c.test_weight_gradient_of_whole_k_tiles_that_many_shards_add_up()
     for case in ((6, 16, 144, 5, 7, 3, 1, ("R", "C", "r", "R"), "2"), (4, 16, 192, 3, 9, 1, 0, ("rR", "rC", "CR", "rC"), "32"),
                  (8, 144, 176, 5, 5, 3, 1, ("Rr", "rr", "RC", "Cr"), "12")):
         monkeypatch.setenv("TT_WGRAD_MERGE", "0")
