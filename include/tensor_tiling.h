@@ -308,8 +308,9 @@ tt_status tt_fc_backward_overlapped(const tt_layer *layer, int64_t batch, int k,
  * channel counts per shard multiples of 8 and R * S <= 32 (else TT_EUNSUPPORTED).  dtype TT_F32: plain kernels that
  * follow the definition term by term, any channel count.  Arguments, ownership and errors as for tt_fc_*.
  * Workspace of tt_conv_backward: tt_conv_workspace_bytes asks for one fp32 partial sum of the filter gradient per run that its
- * reduction is cut into, up to 64 of them.  A smaller workspace is taken as long as the call can run in it in some way (fewer
- * runs, or a product per shard); where dW's sums are cut, and with that its last bits, then depend on ws_bytes. */
+ * reduction is cut into, up to 64 of them.  A smaller workspace is taken where the call has a way to run in it (fewer runs, or
+ * a product per shard; not both ways exist for every shape) and refused with TT_EWORKSPACE otherwise; where dW's sums are cut,
+ * and with that its last bits, then depend on ws_bytes. */
 tt_status tt_conv_workspace_bytes(const tt_layer *layer, int64_t batch, int k, int dtype, int op, tt_tiling tX,
                                   tt_tiling tW, tt_tiling tY, tt_tiling tdY, tt_tiling tdX, const uint8_t *forms_a,
                                   const uint8_t *forms_b, int with_dx, size_t *bytes);
