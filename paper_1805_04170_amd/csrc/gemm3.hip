@@ -15,11 +15,11 @@
 namespace tt {
 namespace {
 
-template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV, bool RUNS = false>
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool SPREAD, bool RUNS>
 __global__ __launch_bounds__(core3::kThreads3, 2) void gemm_bf16_v3_kernel(const core3::Params3 p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem3[];
-    core3::run_tiles<BK, NS, A_KC, B_KC, OUT_BF16, STAGED, ILV, RUNS>(p, smem3);
+    core3::run_tiles<64, 2, A_KC, B_KC, OUT_BF16, STAGED, SPREAD, RUNS>(p, smem3);
 }
 
 // 256 x 128 tiles, four waves, two workgroups per CU (gemm_core4.h); one tile per workgroup
@@ -114,11 +114,11 @@ int cu_count()
     return n;
 }
 
-template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool ILV = false, bool RUNS = false>
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool SPREAD, bool RUNS = false>
 tt_status launch_cfg(core3::Params3 &p, hipStream_t s)
 {
-    auto kern = gemm_bf16_v3_kernel<BK, NS, A_KC, B_KC, OUT_BF16, STAGED, ILV, RUNS>;
-    constexpr size_t smem = core3::smem_bytes3<BK, NS, STAGED>();
+    auto kern = gemm_bf16_v3_kernel<A_KC, B_KC, OUT_BF16, STAGED, SPREAD, RUNS>;
+    constexpr size_t smem = core3::smem_bytes3<64, 2, STAGED>();
     if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem) != TT_OK) return TT_EDEVICE;
     hipLaunchKernelGGL(kern, dim3((uint32_t)p.wg_per_xcd * core::kXcds), dim3(core3::kThreads3), smem, s, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
@@ -126,30 +126,18 @@ tt_status launch_cfg(core3::Params3 &p, hipStream_t s)
 
 template <bool A_KC, bool B_KC> tt_status launch_layout(core3::Params3 &p, int out_dtype, bool vec, hipStream_t s)
 {
-    // results with 16-byte rows: staged epilogue (ring + 18 KB).  Odd pitches store element-wise from registers.  Ring: two stages of 64 (TT_V3_RING=324: four stages of 32; tuning aid).
-    const int ring = tuning_int("TT_V3_RING", 642);
     const bool bf = out_dtype == TT_BF16;
-    if (ring == 324) {
-        if (bf && vec) return launch_cfg<32, 4, A_KC, B_KC, true, true>(p, s);
-        return bf ? launch_cfg<32, 4, A_KC, B_KC, true, false>(p, s) : launch_cfg<32, 4, A_KC, B_KC, false, false>(p, s);
-    }
-    // short K loops (the weight gradients at batch 256): loads issued between the k-steps, see run_tiles
-    // Loads issued between the k-steps (see run_tiles) measured faster for the products with bf16 results (the weight
-    // gradients: short K loops) ...  (TT_V3_ILV=0: never; tuning aid.)
-    const bool ilv = tuning_int("TT_V3_ILV", 1) != 0;
-    if (bf && vec) return ilv ? launch_cfg<64, 2, A_KC, B_KC, true, true, true>(p, s) : launch_cfg<64, 2, A_KC, B_KC, true, true>(p, s);
-    // ... and, among the products that write fp32 partial sums, for the NN layout (B read with LDS transpose reads)
-    if constexpr (A_KC && !B_KC)
-        if (!bf && ilv) return vec ? launch_cfg<64, 2, A_KC, B_KC, false, true, true>(p, s) : launch_cfg<64, 2, A_KC, B_KC, false, false, true>(p, s);
-    if (!bf && vec) return launch_cfg<64, 2, A_KC, B_KC, false, true>(p, s); // fp32 partial sums with 16-byte rows: staged too
-    return bf ? launch_cfg<64, 2, A_KC, B_KC, true, false>(p, s) : launch_cfg<64, 2, A_KC, B_KC, false, false>(p, s);
+    constexpr bool SPREAD = !A_KC && !B_KC;
+    if (vec) return bf ? launch_cfg<A_KC, B_KC, true, true, SPREAD>(p, s) : launch_cfg<A_KC, B_KC, false, true, SPREAD>(p, s);
+    return bf ? launch_cfg<A_KC, B_KC, true, false, SPREAD>(p, s) : launch_cfg<A_KC, B_KC, false, false, SPREAD>(p, s);
 }
 
-// over runs of K tiles; loads between the k-steps as above
+// over runs of K tiles
 template <bool A_KC, bool B_KC> tt_status launch_runs(core3::Params3 &p, int out_dtype, hipStream_t s)
 {
-    if (out_dtype == TT_BF16) return launch_cfg<64, 2, A_KC, B_KC, true, true, true, true>(p, s);
-    return launch_cfg<64, 2, A_KC, B_KC, false, true, A_KC && !B_KC, true>(p, s);
+    constexpr bool SPREAD = !A_KC && !B_KC;
+    if (out_dtype == TT_BF16) return launch_cfg<A_KC, B_KC, true, true, SPREAD, true>(p, s);
+    return launch_cfg<A_KC, B_KC, false, true, SPREAD, true>(p, s);
 }
 
 } // namespace

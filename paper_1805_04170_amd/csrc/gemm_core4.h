@@ -31,6 +31,46 @@ using core::f32x16;
 using core::u32x4;
 using core2::s16x4;
 
+// fp32 staging strip of one wave: 8 rows x 64 columns, padded (fits in the bf16 strip's place)
+constexpr int kEpiRowsF = 8, kEpiLdF = 64 + 4;
+
+// Write-out of a wave's 128 x 64 fp32 accumulator tile (4 x 2 blocks of 32 x 32; a lane holds column lane % 32 and rows
+// 8 g + 4 (lane / 32) + e % 4, g = e / 4, of each block) through a wave-private strip of kEpiRowsF x kEpiLdF floats: eight
+// rows at a time are turned round in LDS and leave as 16-byte vectors, 16 lanes per 256-byte row segment, four rows per
+// store instruction (stored straight from the accumulators a row segment takes 32 four-byte stores of a half wave: four
+// times the store instructions, and measured 15-30 % slower on the products that write large fp32 partial sums).
+// N must be a multiple of 4 and C 16-byte aligned.  (row0, col0): the wave tile's origin in C.
+__device__ __forceinline__ void store_wave_tile_f32(f32x16 (&acc)[4][2], float *strip, float *C, int ldc, int row0, int col0, int M,
+                                                    int N, bool relu, int lane)
+{
+    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int ee = 0; ee < 4; ++ee) {
+                    float v = acc[i][j][4 * g + ee];
+                    if (relu) v = fmaxf(v, 0.0f);
+                    strip[(row_l + ee) * kEpiLdF + j * 32 + col_l] = v;
+                }
+            // wave-private data and LDS operations of a wave execute in order: only the compiler needs a fence
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const int idx = lane + 64 * v, lrow = idx >> 4, vc = (idx & 15) * 4;
+                const int row = row0 + i * 32 + 8 * g + lrow, col = col0 + vc;
+                const core::f32x4 o = *reinterpret_cast<const core::f32x4 *>(strip + lrow * kEpiLdF + vc);
+                if (row < M && col < N) // N is a multiple of 4 on this path: a vector is all in or all out
+                    __builtin_nontemporal_store(o, reinterpret_cast<core::f32x4 *>(C + (size_t)row * ldc + col));
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+}
+
+
 constexpr int kThreads4 = 256;
 constexpr int BM4 = 256, BN4 = 128, BK4 = 32, NS4 = 3;
 constexpr int kABytes = BM4 * BK4 * 2, kBBytes = BN4 * BK4 * 2, kStage4 = kABytes + kBBytes; // 16 KB + 8 KB
@@ -106,9 +146,9 @@ __device__ __forceinline__ void write_tile4(f32x16 (&acc)[4][2], void *Cv, int l
     // ---- epilogue.  A lane holds column (lane & 31) and rows 8*(e/4) + 4*(lane/32) + e%4 of each 32 x 32 block.
     const int col_l = lane & 31, row_l = (lane >> 5) * 4;
     if constexpr (STAGED && !OUT_BF16) {
-        static_assert(4 * core3::kEpiRowsF * core3::kEpiLdF * 4 <= kSmem4, "strips fit in the ring");
-        float *strip = reinterpret_cast<float *>(smem) + wave * (core3::kEpiRowsF * core3::kEpiLdF);
-        core3::store_wave_tile_f32(acc, strip, reinterpret_cast<float *>(Cv), ldc, m0 + wm0, n0 + wn0, M, N, relu, lane);
+        static_assert(4 * kEpiRowsF * kEpiLdF * 4 <= kSmem4, "strips fit in the ring");
+        float *strip = reinterpret_cast<float *>(smem) + wave * (kEpiRowsF * kEpiLdF);
+        store_wave_tile_f32(acc, strip, reinterpret_cast<float *>(Cv), ldc, m0 + wm0, n0 + wn0, M, N, relu, lane);
     } else if constexpr (!STAGED) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)

@@ -6,7 +6,7 @@
 //     instruction together, so code may read what another lane of the same wave wrote before such a point);
 //   - v_mfma_f32_32x32x16_bf16: D = C + A B over the wave's registers in the instruction's lane layout
 //     (A: row lane % 32, k = 8 (lane / 32) + 0..7; B: column lane % 32, the same k; C, D: column lane % 32, row
-//     8 (r / 4) + 4 (lane / 32) + r % 4 for register r), products and sums in double, rounded once to fp32;
+//     8 (r / 4) + 4 (lane / 32) + r % 4 for register r), products and sums in double, rounded once to fp32; other shapes below;
 //   - ds_read_b64_tr_b16: in every group of 16 lanes, element e of lane i comes from lane 4 e + i / 4, element i % 4
 //     (the 4 x 16 block of 16-bit values the group addressed, transposed).
 // Global -> LDS loads land late: a lane's loads stay pending, in order, until a wait count of that lane lets them
@@ -146,6 +146,31 @@ template <class AB, class C> inline C mfma_32x32x16_bf16(AB a, AB b, C c)
     return c;
 }
 
+// v_mfma_f32_16x16x32_bf16: A: row lane % 16, k = 8 (lane / 16) + 0..7; B: column lane % 16, the same k; C, D: column
+// lane % 16, row 4 (lane / 16) + r for register r; products and sums in double, rounded once to fp32
+template <class AB, class C> inline C mfma_16x16x32_bf16(AB a, AB b, C c)
+{
+    static_assert(sizeof(AB) == 16 && sizeof(C) == 16, "operand registers of v_mfma_f32_16x16x32_bf16");
+    WaveState &w = my_wave();
+    const int l = lane();
+    std::memcpy(w.a[l], &a, 16);
+    std::memcpy(w.b[l], &b, 16);
+    std::memcpy(w.c[l], &c, 16);
+    wave_collective(6, [](WaveState &v) {
+        if (v.live != kWave) die("MFMA in a wave with ended lanes");
+        for (int ln = 0; ln < kWave; ++ln)
+            for (int r = 0; r < 4; ++r) {
+                const int i = 4 * (ln / 16) + r, j = ln % 16;
+                double s = v.c[ln][r];
+                for (int k = 0; k < 32; ++k)
+                    s += (double)bf16_bits_to_float(v.a[i + 16 * (k / 8)][k % 8]) * (double)bf16_bits_to_float(v.b[j + 16 * (k / 8)][k % 8]);
+                v.c[ln][r] = (float)s;
+            }
+    });
+    std::memcpy(&c, w.c[l], 16);
+    return c;
+}
+
 // v_mfma_f32_32x32x2_f32: A: row lane % 32, k = lane / 32; B: column lane % 32, the same k; C, D as above; two fp32 fused
 // multiply-adds per result, k in increasing order
 template <class C> inline C mfma_32x32x2_f32(float a, float b, C c)
@@ -265,5 +290,6 @@ inline void __syncthreads() { emu::block_barrier(); }
 #define __builtin_amdgcn_s_waitcnt(x) emu::wait_counts(x)
 #define __builtin_amdgcn_wave_barrier() emu::wave_sync()
 #define __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, x, y, z) emu::mfma_32x32x16_bf16(a, b, c)
+#define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) emu::mfma_16x16x32_bf16(a, b, c)
 #define __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, x, y, z) emu::mfma_32x32x2_f32(a, b, c)
 #define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) emu::mfma_16x16x4_f32(a, b, c)
