@@ -294,9 +294,8 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
         // Engine choice (TT_GEMM_ENGINE=1: the two older engines only, =3 / =4: that engine wherever it applies; tuning aid):
         //  - launches with too few 256 x 256 tiles to occupy the chip (the hidden-layer products at batch 256): the
         //    256 x 128 engine with two workgroups per CU, which doubles the number of workgroups;
-        //  - large launches with more than one row of tiles: the persistent pipelined engine;
-        //  - of the skinny batch-256 products of the wide layers (one row of tiles, bound by the weight stream) the NN
-        //    layout measured 6 % faster on the persistent engine, the others equal or faster on the direct-to-LDS engine.
+        //  - larger launches: the persistent pipelined engine where K is a multiple of 64 (16 x (256 x 4096 x 640) A^T B 26.9 -> 25.1 us
+        //    against the direct-to-LDS engine, A B^T over K = 512 28.3 -> 28.0), else the direct-to-LDS engine.
         const int engine = tuning_int("TT_GEMM_ENGINE", 0);
         const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256) * count * ksplit;
         //  - weight-gradient shaped products (both operands stored with K as the slow dimension, K = 128, 256 or 512, a bf16
@@ -308,14 +307,16 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
             const tt_status st = launch_gemm_v5(count, A, B, C, M, N, K, a_contig, b_contig, N, act == TT_ACT_RELU, stream);
             if (st != TT_EUNSUPPORTED) return st;
         }
-        //  - of those, the products A B^T with both operands K-contiguous (the data gradients) that give between half a
-        //    tile and one 256 x 128 tile per CU: the same tile with K tiles of 64, which fetches whole 128-byte lines of the
-        //    streamed weights (gemm_core6.h says what that is worth: 74 -> 66 us for the first VGG-16 data gradient; with
-        //    more tiles than CUs, with fewer than half as many, and for the NN layout it measured equal or slower)
+        //  - of those, launches of at most one 256 x 128 tile per CU and a K that is long enough for a start that fetches three stages
+        //    of 48 KB: the same tile with K tiles of 64 and one workgroup per CU (gemm_core6.h).  gemm_core4.h / gemm_core6.h, eight
+        //    shards of 256 rows, us: A B^T to 4096 columns K 256 9.2 / 9.6, 512 13.2 / 12.4, 1024 27.7 / 21.8, 2048 52.5 / 43.3 (1024
+        //    columns 7.4 / 8.3, 10.7 / 10.5, 16.5 / 15.2, 28.4 / 24.5); A B 11.2 / 12.0, 15.1 / 15.3, 28.4 / 23.3, 51.5 / 40.4; A^T B to
+        //    2048 columns, K 2048 38.9 / 33.9, 8 x (512 x 512 x 1024) 16.6 / 17.3; 288 tiles of K 1024 A B^T 30.3 / 31.3
+        const int64_t kc = ksplit > 1 ? kchunk : K;
         const int64_t tiles128 = ((M + 255) / 256) * ((N + 127) / 128) * count * ksplit;
-        if (a_kc && (engine == 6 || (engine == 0 && b_kc && big_tiles < 200 && M > 128 && N >= 256 && tiles128 >= 128 &&
-                                     tiles128 <= 256 && (ksplit > 1 ? kchunk : K) >= 256))) {
-            const tt_status st = launch_gemm_v6(count, A, B, C, M, N, K, a_contig, b_contig, N, b_kc, out_dtype, act == TT_ACT_RELU,
+        if (engine == 6 || (engine == 0 && big_tiles < 200 && M > 128 && N >= 256 && tiles128 <= 256 &&
+                                                   kc >= (!a_kc ? 2048 : b_kc ? 512 : 1024))) {
+            const tt_status st = launch_gemm_v6(count, A, B, C, M, N, K, a_contig, b_contig, N, a_kc, b_kc, out_dtype, act == TT_ACT_RELU,
                                                 vec, ksplit, kchunk, stream);
             if (st != TT_EUNSUPPORTED) return st;
         }
@@ -324,7 +325,7 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
                                                 act == TT_ACT_RELU, vec, ksplit, kchunk, stream);
             if (st != TT_EUNSUPPORTED) return st;
         }
-        if (engine != 1 && engine != 4 && (engine == 3 || M > 256 || (a_kc && !b_kc)) && pick_tile(M, N, ksplit > 1 ? kchunk : K, count * ksplit) == 5) {
+        if (engine != 1 && engine != 4 && pick_tile(M, N, ksplit > 1 ? kchunk : K, count * ksplit) == 5) {
             const tt_status st = launch_gemm_v3(count, A, B, C, M, N, K, a_contig, b_contig, N, a_kc, b_kc, out_dtype,
                                                 act == TT_ACT_RELU, vec, ksplit, kchunk, stream);
             if (st != TT_EUNSUPPORTED) return st;

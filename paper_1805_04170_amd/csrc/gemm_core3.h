@@ -200,7 +200,7 @@ template <bool KC, bool IS_A, bool RUNS = false> struct Feeder {
 };
 
 constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-constexpr int kWaitAll = 7 << 4; // vmcnt(0) and lgkmcnt(0)
+constexpr int waitcnt_vm_lds(int n) { return waitcnt_vm(n) & ~(15 << 8); } // ... and lgkmcnt(0)
 
 // SPREAD: loads over the whole second k-step of an item instead of its second half
 template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool SPREAD, bool RUNS = false>
@@ -243,7 +243,7 @@ __device__ __forceinline__ void run_tiles(const Params3 &p, char *smem)
             const char *At = smem + cs * kStage3;
             mma::k_step<0, false>(acc, f0, f1, ra, rb, At, At + kOpBytes3, 1, [](int) {});
             // this wave has read the item and its chunks of the next one have landed; then everyone's
-            __builtin_amdgcn_s_waitcnt(kWaitAll);
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm_lds(0));
             __syncthreads();
             const uint32_t lds_free = lds0 + (uint32_t)cs * kStage3;
             cs ^= 1;

@@ -10,65 +10,23 @@
 //   - K tiles of 32; a stage is 16 KB of A and 8 KB of B; three stages (72 KB) fetched global -> LDS with
 //     global_load_lds_dwordx4 two tiles ahead (inline assembly, see gemm_core2.h for why);
 //   - LDS layouts: K-contiguous operands as [row][4 chunks of 8 k], chunk position p of row r holds k-chunk
-//     p ^ ((r >> 2) & 3); row-contiguous operands as [k][ROWS / 8 chunks of 8 rows], swizzled and read with LDS
+//     p ^ (-(r >> 2) & 3) (LDS serves a 16-byte read of lanes 0-3, 12-15 and 20-27 together: p ^ ((r >> 2) & 3) conflicts, 307
+//     instead of 466 GB/s); row-contiguous operands as [k][ROWS / 8 chunks of 8 rows], swizzled and read with LDS
 //     transpose reads as in gemm_core2.h;
+//   - fragments, k-steps and write-out of gemm_mma.h, a K tile being one k-step.  8 x (256 x 4608 x 1024) A B^T, 288 tiles:
+//     32.9 -> 30.3 us (31.3 on gemm_core6.h); where tiles leave CUs empty gemm_core6.h is the faster one;
 //   - K must be a multiple of 32; a workgroup computes one tile and ends (the other resident workgroup and the next
-//     one queued cover its start-up and wind-down);
-//   - epilogue: bf16 results with 16-byte rows are turned around in a wave-private strip of the (drained) ring, 16 rows
-//     at a time; everything else is stored element-wise from the accumulators.
+//     one queued cover its start-up and wind-down).
 #pragma once
 #include <cstdint>
 #include "tt_device.h"
 #include "gemm_core.h"
 #include "gemm_core2.h"
 #include "gemm_core3.h"
+#include "gemm_mma.h"
 
 namespace tt {
 namespace core4 {
-
-using core::bf16x8;
-using core::f32x16;
-using core::u32x4;
-using core2::s16x4;
-
-// fp32 staging strip of one wave: 8 rows x 64 columns, padded (fits in the bf16 strip's place)
-constexpr int kEpiRowsF = 8, kEpiLdF = 64 + 4;
-
-// Write-out of a wave's 128 x 64 fp32 accumulator tile (4 x 2 blocks of 32 x 32; a lane holds column lane % 32 and rows
-// 8 g + 4 (lane / 32) + e % 4, g = e / 4, of each block) through a wave-private strip of kEpiRowsF x kEpiLdF floats: eight
-// rows at a time are turned round in LDS and leave as 16-byte vectors, 16 lanes per 256-byte row segment, four rows per
-// store instruction (stored straight from the accumulators a row segment takes 32 four-byte stores of a half wave: four
-// times the store instructions, and measured 15-30 % slower on the products that write large fp32 partial sums).
-// N must be a multiple of 4 and C 16-byte aligned.  (row0, col0): the wave tile's origin in C.
-__device__ __forceinline__ void store_wave_tile_f32(f32x16 (&acc)[4][2], float *strip, float *C, int ldc, int row0, int col0, int M,
-                                                    int N, bool relu, int lane)
-{
-    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int ee = 0; ee < 4; ++ee) {
-                    float v = acc[i][j][4 * g + ee];
-                    if (relu) v = fmaxf(v, 0.0f);
-                    strip[(row_l + ee) * kEpiLdF + j * 32 + col_l] = v;
-                }
-            // wave-private data and LDS operations of a wave execute in order: only the compiler needs a fence
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int v = 0; v < 2; ++v) {
-                const int idx = lane + 64 * v, lrow = idx >> 4, vc = (idx & 15) * 4;
-                const int row = row0 + i * 32 + 8 * g + lrow, col = col0 + vc;
-                const core::f32x4 o = *reinterpret_cast<const core::f32x4 *>(strip + lrow * kEpiLdF + vc);
-                if (row < M && col < N) // N is a multiple of 4 on this path: a vector is all in or all out
-                    __builtin_nontemporal_store(o, reinterpret_cast<core::f32x4 *>(C + (size_t)row * ldc + col));
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-}
 
 
 constexpr int kThreads4 = 256;
@@ -78,6 +36,16 @@ constexpr size_t kSmem4 = (size_t)NS4 * kStage4;                                
 constexpr int kLoadsA = kABytes / 16 / kThreads4, kLoadsB = kBBytes / 16 / kThreads4;        // 4 and 2 per thread
 
 // lane offsets of this thread's 16-byte chunks of one operand tile (ROWS x 32), see the layouts above
+__device__ __forceinline__ uint64_t uniform64(const char *p)
+{
+    // wave-uniform by construction; say so, or an "s" operand may be handed a vector register pair (readfirstlane
+    // returns a signed int: go through uint32_t so the low half is not sign-extended)
+    const uint64_t b64 = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b64);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
+    return ((uint64_t)hi << 32) | (uint64_t)lo;
+}
+
 template <int ROWS, bool KC> __device__ __forceinline__ void chunk_offsets(int row0, int rows, int ld, uint32_t *voff)
 {
     const int tid = threadIdx.x;
@@ -85,7 +53,7 @@ template <int ROWS, bool KC> __device__ __forceinline__ void chunk_offsets(int r
     if constexpr (KC) {
         // chunk c = tid + 256 i: row c / 4 = tid / 4 + 64 i, position c % 4
         const int rl = tid >> 2;
-        const int kc = (tid & 3) ^ ((rl >> 2) & 3);
+        const int kc = (tid & 3) ^ (-(rl >> 2) & 3);
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             int r = row0 + rl + 64 * i;
@@ -105,176 +73,77 @@ template <int ROWS, bool KC> __device__ __forceinline__ void chunk_offsets(int r
     }
 }
 
-template <int NL> __device__ __forceinline__ void issue_chunks(const char *base, const uint32_t *voff, uint32_t lds)
-{
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the base is wave-uniform by construction; say so, or the "s" operand may be handed a vector register pair
-    // (readfirstlane returns a signed int: go through uint32_t so the low half is not sign-extended)
-    const uint64_t b64 = reinterpret_cast<uint64_t>(base);
-    const uint32_t b_lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b64);
-    const uint32_t b_hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
-    const uint64_t sbase = ((uint64_t)b_hi << 32) | (uint64_t)b_lo;
-#pragma unroll
-    for (int i = 0; i < NL; ++i) {
-        const uint32_t dst = lds + (wave * 64u + (uint32_t)i * kThreads4) * 16u;
-        dev::lds_dma16(voff[i], sbase, dst);
-    }
-}
-
-// fragment (32 rows x 16 k) of an operand stage: rows rbase .. rbase+31 of the tile, k-step ks (0 or 1)
-template <int ROWS, bool KC> __device__ __forceinline__ bf16x8 read_frag4(const char *lds, int rbase, int ks, int lane)
-{
-    if constexpr (KC) {
-        const int r = rbase + (lane & 31), q = ks * 2 + (lane >> 5);
-        return *reinterpret_cast<const bf16x8 *>(lds + r * 64 + ((q ^ ((r >> 2) & 3)) << 4));
-    } else {
-        return core2::read_frag<ROWS, false>(lds, rbase, ks, lane);
-    }
-}
-
-// Write-out of a workgroup's 256 x 128 accumulator tile (four waves as 2 x 2, 128 x 64 per wave: the wave tile of this
-// engine and of gemm_core6.h).  The ring must be drained and idle: STAGED turns the results round in a wave-private
-// strip at the start of smem (at least 4 * 16 * 72 * 2 bytes; bf16 16 rows at a time, fp32 8) so that they leave as
-// 16-byte vectors of whole row segments; without it they are stored element by element.
-template <bool OUT_BF16, bool STAGED>
-__device__ __forceinline__ void write_tile4(f32x16 (&acc)[4][2], void *Cv, int ldc, int M, int N, int m0, int n0, bool relu,
-                                            char *smem)
-{
-    constexpr int TM = 4, TN = 2, WN = 2;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm0 = (wave / WN) * (TM * 32), wn0 = (wave % WN) * (TN * 32);
-    // ---- epilogue.  A lane holds column (lane & 31) and rows 8*(e/4) + 4*(lane/32) + e%4 of each 32 x 32 block.
-    const int col_l = lane & 31, row_l = (lane >> 5) * 4;
-    if constexpr (STAGED && !OUT_BF16) {
-        static_assert(4 * kEpiRowsF * kEpiLdF * 4 <= kSmem4, "strips fit in the ring");
-        float *strip = reinterpret_cast<float *>(smem) + wave * (kEpiRowsF * kEpiLdF);
-        store_wave_tile_f32(acc, strip, reinterpret_cast<float *>(Cv), ldc, m0 + wm0, n0 + wn0, M, N, relu, lane);
-    } else if constexpr (!STAGED) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int col = n0 + wn0 + j * 32 + col_l;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = m0 + wm0 + i * 32 + 8 * (e >> 2) + row_l + (e & 3);
-                    float v = acc[i][j][e];
-                    if (relu) v = fmaxf(v, 0.0f);
-                    if (row < M && col < N) {
-                        if constexpr (OUT_BF16)
-                            reinterpret_cast<uint16_t *>(Cv)[(size_t)row * ldc + col] = (uint16_t)core::f32_to_bf16_bits(v);
-                        else
-                            __builtin_nontemporal_store(v, reinterpret_cast<float *>(Cv) + (size_t)row * ldc + col);
-                    }
-                }
-            }
-    } else {
-        constexpr int ER = 16, ELD = 64 + 8; // strip of one wave: 16 rows x 64 columns of bf16, padded
-        static_assert(4 * ER * ELD * 2 <= kSmem4, "strips fit in the ring");
-        uint16_t *strip = reinterpret_cast<uint16_t *>(smem) + wave * (ER * ELD);
-        uint16_t *Cs = reinterpret_cast<uint16_t *>(Cv);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int eg = 0; eg < 2; ++eg)
-#pragma unroll
-                        for (int ee = 0; ee < 4; ee += 2) {
-                            float v0 = acc[i][j][(2 * h + eg) * 4 + ee], v1 = acc[i][j][(2 * h + eg) * 4 + ee + 1];
-                            if (relu) { v0 = fmaxf(v0, 0.0f); v1 = fmaxf(v1, 0.0f); }
-                            const uint32_t pk = core::pack_bf16x2(v0, v1);
-                            uint16_t *d = strip + (8 * eg + row_l + ee) * ELD + j * 32 + col_l;
-                            d[0] = (uint16_t)(pk & 0xffffu);
-                            d[ELD] = (uint16_t)(pk >> 16);
-                        }
-                // Wave-private data: LDS operations of one wave execute in order, so the reads below see the writes above and the
-                // next strip's writes cannot overtake them; no wait is needed, only a fence for the compiler's scheduler.
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int v = 0; v < 2; ++v) {
-                    const int idx = lane + 64 * v, lrow = idx >> 3, vc = (idx & 7) * 8;
-                    const int row = m0 + wm0 + i * 32 + 16 * h + lrow, col = n0 + wn0 + vc;
-                    const u32x4 o = *reinterpret_cast<const u32x4 *>(strip + lrow * ELD + vc);
-                    if (row < M && col < N) // N is a multiple of 8 on this path: a vector is all in or all out
-                        __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(Cs + (size_t)row * ldc + col));
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-    }
-}
-
-// C tile (m0, n0) of C = A B over K = klen (a multiple of 32) starting at the operands' k = 0 as given by abase / bbase.
-// 256 threads; smem: kSmem4 bytes, 16-byte aligned.  STAGED: bf16 result, 16-byte stores legal.
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED>
 __device__ __forceinline__ void tile_product4(const char *abase, int lda, const char *bbase, int ldb, void *Cv, int ldc, int M,
                                               int N, int klen, int m0, int n0, bool relu, char *smem)
 {
-    constexpr int TM = 4, TN = 2, WN = 2; // 2 x 2 waves, 128 x 64 per wave
-    constexpr int D = NS4 - 1;
-    constexpr int W = (D - 1) * (kLoadsA + kLoadsB); // loads that may still be in flight at the top of an item
+    constexpr int TM = 8, TN = 4, WN = 2; // 2 x 2 waves, 128 x 64 per wave
+    constexpr int LPS = kLoadsA + kLoadsB;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm0 = (wave / WN) * (TM * 32), wn0 = (wave % WN) * (TN * 32);
+    const int wm0 = (wave / WN) * (TM * 16), wn0 = (wave % WN) * (TN * 16);
     const uint32_t lds0 = dev::lds_addr(smem);
 
     uint32_t voa[kLoadsA], vob[kLoadsB];
     chunk_offsets<BM4, A_KC>(m0, M, lda, voa);
     chunk_offsets<BN4, B_KC>(n0, N, ldb, vob);
-    const uint32_t astep = A_KC ? BK4 * 2u : (uint32_t)BK4 * (uint32_t)lda * 2u;
-    const uint32_t bstep = B_KC ? BK4 * 2u : (uint32_t)BK4 * (uint32_t)ldb * 2u;
+    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024u;
+    const uint64_t astep = A_KC ? BK4 * 2u : (uint64_t)BK4 * (uint64_t)lda * 2u, bstep = B_KC ? BK4 * 2u : (uint64_t)BK4 * (uint64_t)ldb * 2u;
     const int nk = klen / BK4;
 
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    // Every item issues the same number of loads so that the wait count stays constant: past the end of K the last
-    // tile is fetched again into a stage nobody reads any more.
-    int it_issue = 0, is = 0;
-    auto issue = [&]() {
-        const int kt = it_issue < nk ? it_issue : nk - 1;
-        issue_chunks<kLoadsA>(abase + (size_t)kt * astep, voa, lds0 + (uint32_t)is * kStage4);
-        issue_chunks<kLoadsB>(bbase + (size_t)kt * bstep, vob, lds0 + (uint32_t)is * kStage4 + kABytes);
-        ++it_issue;
-        is = is + 1 == NS4 ? 0 : is + 1;
+    // K tile to ask for next; past the end the last one is fetched again, so that the wait counts stay the same
+    uint64_t ab = uniform64(abase), bb = uniform64(bbase);
+    int left = nk - 1;
+    auto issue_one = [&](int i, uint32_t stage) {
+        if (i < kLoadsA) dev::lds_dma16(voa[i], ab, stage + wave_lds + (uint32_t)i * (kThreads4 * 16u));
+        else dev::lds_dma16(vob[i - kLoadsA], bb, stage + kABytes + wave_lds + (uint32_t)(i - kLoadsA) * (kThreads4 * 16u));
+    };
+    auto advance = [&]() {
+        if (left > 0) {
+            ab += astep;
+            bb += bstep;
+        }
+        --left;
     };
 #pragma unroll
-    for (int s = 0; s < D; ++s) issue();
+    for (int st = 0; st < NS4; ++st) {
+#pragma unroll
+        for (int i = 0; i < LPS; ++i) issue_one(i, lds0 + (uint32_t)st * kStage4);
+        advance();
+    }
+
+    mma::Reader<BM4, A_KC, TM, BK4> ra;
+    mma::Reader<BN4, B_KC, TN, BK4> rb;
+    ra.init(wm0, lane);
+    rb.init(wn0, lane);
+    mma::Frags<TM, TN> f0, f1;
+    core::f32x4 acc[TM][TN];
+    mma::clear(acc);
+    __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm((NS4 - 1) * LPS)); // this wave's chunks of the first tiles have landed
+    __syncthreads();                                                // everyone's have
+    mma::read_frags(f0, ra, rb, smem, smem + kABytes, 0);
 
     int cs = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(W)); // this wave's chunks of the item have landed
-        __syncthreads();                                  // everyone's have; everyone has finished reading the previous item
-        issue();                                          // into the stage of the previous item
-        const char *As = smem + cs * kStage4, *Bs = As + kABytes;
+    // multiplies the fragments cur of K tile kt, reads those of the next tile and asks for the one that takes this one's stage
+    auto item = [&](const mma::Frags<TM, TN> &cur, mma::Frags<TM, TN> &nxt) {
+        // this wave has read its fragments and its chunks of the next tile have landed; then everyone's
+        __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm_lds((NS4 - 2) * LPS));
+        __syncthreads();
+        const uint32_t lds_free = lds0 + (uint32_t)cs * kStage4;
         cs = cs + 1 == NS4 ? 0 : cs + 1;
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_iglp_opt(1);
-#pragma unroll
-        for (int ks = 0; ks < BK4 / 16; ++ks) {
-            bf16x8 af[TM], bf[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = read_frag4<BM4, A_KC>(As, wm0 + i * 32, ks, lane);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bf[j] = read_frag4<BN4, B_KC>(Bs, wn0 + j * 32, ks, lane);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        const char *nA = smem + cs * kStage4;
+        mma::k_step<LPS, true>(acc, cur, nxt, ra, rb, nA, nA + kABytes, 0, [&](int i) { issue_one(i, lds_free); });
+        advance();
+    };
+    int kt = 0;
+    for (; kt + 1 < nk; kt += 2) {
+        item(f0, f1);
+        item(f1, f0);
     }
+    if (kt < nk) item(f0, f1);
     // the re-fetches issued past the end have landed and every wave is done with the ring: it can be reused / given up
-    __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(0));
+    __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm_lds(0));
     __syncthreads();
-    write_tile4<OUT_BF16, STAGED>(acc, Cv, ldc, M, N, m0, n0, relu, smem);
+    mma::store_block<OUT_BF16, STAGED>(acc, smem + wave * mma::kStripBytes, Cv, ldc, m0 + wm0, n0 + wn0, M, N, relu, lane);
 }
 
 } // namespace core4

@@ -27,16 +27,17 @@ using core::u32x4;
 
 // Fragments (16 rows x 32 k, 8 values of K per lane) of an operand tile of ROWS rows and 64 k in LDS; layouts as in gemm_core2.h.
 // T: 16-row blocks of a wave, from row w0 on (a multiple of 16 T, of 64 where T is 4 or more).
-template <int ROWS, bool KC, int T> struct Reader {
+// BK = 32: one k-step; rows of 64 bytes, chunk position p of row r holds k-chunk p ^ (-(r >> 2) & 3).
+template <int ROWS, bool KC, int T, int BK = 64> struct Reader {
     static constexpr bool kc = KC;
-    static constexpr int NOFF = KC ? 2 : T < 4 ? T : 4;
+    static constexpr int NOFF = KC ? BK / 32 : T < 4 ? T : 4;
     uint32_t off[NOFF]; // the lane's part of the address; the rest are constants
     __device__ __forceinline__ void init(int w0, int lane)
     {
         const int r = lane & 15, q = lane >> 4;
         if constexpr (KC) {
-            off[0] = (uint32_t)((w0 + r) * 128 + ((q ^ ((r >> 1) & 7)) << 4));
-            off[1] = off[0] ^ 64u; // k-step 1: chunks 4 to 7
+            off[0] = (uint32_t)((w0 + r) * (2 * BK) + ((q ^ (BK == 64 ? (r >> 1) & 7 : -(r >> 2) & 3)) << 4));
+            if constexpr (BK == 64) off[1] = off[0] ^ 64u; // k-step 1: chunks 4 to 7
         } else {
             const int k = q * 8 + (r >> 2), c = (w0 >> 3) + ((r & 3) >> 1);
 #pragma unroll
@@ -47,7 +48,7 @@ template <int ROWS, bool KC, int T> struct Reader {
     __device__ __forceinline__ bf16x8 read(const char *tile, int ks, int i) const
     {
         if constexpr (KC) {
-            return *reinterpret_cast<const bf16x8 *>(tile + off[ks] + i * 2048);
+            return *reinterpret_cast<const bf16x8 *>(tile + off[ks] + i * (32 * BK));
         } else {
             union { dev::s16x4 h[2]; bf16x8 v; } u;
 #pragma unroll

@@ -173,7 +173,7 @@ tt_status launch_gemm_v4(int count, const void *const *A, const void *const *B, 
 // The same tile with K tiles of 64 and one workgroup per CU for products whose left operand has K contiguous
 // (gemm_core6.h); K and a K chunk multiples of 64.
 tt_status launch_gemm_v6(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
-                         int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool b_kc, int out_dtype, int relu, bool vec,
+                         int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc, bool b_kc, int out_dtype, int relu, bool vec,
                          int ksplit, int64_t kchunk, void *stream);
 
 // fp32, or bf16 rows without 16-byte vectors (gemm_small.h); any sizes.
