@@ -216,29 +216,36 @@ __global__ __launch_bounds__(WM * WN * 64, WM * WN / 4) void conv_gather_a_kerne
 // The gathered operand of a forward product for the engine that loads tiles straight into LDS (gemm_core2.h).  A thread's
 // chunks of a tile differ in the row only, so the tap and the channel they read are one pair per thread and tile, moved on
 // by 64 values of K from tile to tile; rows whose tap lies outside the image, and K past the end, read a chunk of zeros.
-template <int ROWS> struct GatherKC2 {
+struct GatherKC2 {
     static constexpr bool KC = true;
-    static constexpr int NI = ROWS * core::BK / 8 / core2::kThreads2, RI = core2::kThreads2 / 8; // chunks per thread, rows between them
     const char *base;
-    int IW, S, Ch, K, kc;
-    int dtap, dc;         // 64 values of K as taps and channels
-    mutable int tap, c;   // of the K tile issued last
-    int32_t pix[NI];      // element offset of the source pixel at tap 0, may be negative
-    uint32_t inside[NI];  // bit t: tap t reads inside the image
-    __device__ __forceinline__ void init(const ConvGeom &g, const void *src, int rows, int K_, int row0)
+    ConvGeom g;
+    int M, K;
+    int kc, dtap, dc;     // this lane's k inside a K tile; 64 values of K as taps and channels
+    int k, tap, c;        // of this lane's chunks of the current K tile
+    int32_t pix[4];       // element offset of the source pixel at tap 0, may be negative
+    uint32_t inside[4];   // bit t: tap t reads inside the image
+    int32_t delta;        // of the current tile: what its tap and channel add to pix
+    uint32_t bit;         // ... its tap's bit, 0 past the end of K
+    __device__ __forceinline__ void locate()
+    {
+        const int r = tap / g.S, s = tap - r * g.S;
+        delta = (r * g.W + s) * g.Cs + c;
+        bit = k + kc < K ? 1u << (tap & 31) : 0u;
+    }
+    template <int ROWS> __device__ __forceinline__ void begin(int row0)
     {
         const int tid = threadIdx.x;
-        base = reinterpret_cast<const char *>(src);
-        IW = g.W; S = g.S; Ch = g.Cs; K = K_;
-        kc = ((tid & 7) ^ ((tid >> 4) & 7)) << 3; // (see core2::issue_tile; the row's part of it is the same in all chunks)
-        dtap = core::BK / Ch;
-        dc = core::BK - dtap * Ch;
-        tap = kc / Ch;
-        c = kc - tap * Ch;
+        kc = ((tid & 7) ^ ((tid >> 4) & 7)) << 3; // (the row's part of the swizzle is the same in all chunks)
+        dtap = core::BK / g.Cs;
+        dc = core::BK - dtap * g.Cs;
+        tap = kc / g.Cs;
+        c = kc - tap * g.Cs;
+        k = 0;
 #pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            int row = row0 + (tid >> 3) + RI * i;
-            row = row < rows ? row : rows - 1; // rows past the end only feed C rows that are never stored
+        for (int i = 0; i < core2::loads2<ROWS>(); ++i) {
+            int row = row0 + (tid >> 3) + 64 * i;
+            row = row < M ? row : M - 1; // rows past the end only feed C rows that are never stored
             const int n = row / (g.P * g.Q), rem = row - n * (g.P * g.Q);
             const int y = rem / g.Q - g.pad, x = rem - (rem / g.Q) * g.Q - g.pad;
             pix[i] = ((n * g.H + y) * g.W + x) * g.Cs;
@@ -248,26 +255,22 @@ template <int ROWS> struct GatherKC2 {
                     if (y + r >= 0 && y + r < g.H && x + s >= 0 && x + s < g.W) m |= 1u << (r * g.S + s);
             inside[i] = m;
         }
+        locate();
     }
-    template <int ROWS_> __device__ __forceinline__ void issue(int, int k0, char *lds) const
+    template <int ROWS> __device__ __forceinline__ void next()
     {
-        static_assert(ROWS_ == ROWS, "tile side");
-        if (k0 > 0) { // tiles are issued in order
-            c += dc;
-            const int carry = c >= Ch;
-            c -= carry ? Ch : 0;
-            tap += dtap + carry;
-        }
-        const int r = tap / S, s = tap - r * S;
-        const int32_t delta = (r * IW + s) * Ch + c;
-        const uint32_t bit = k0 + kc < K ? 1u << (tap & 31) : 0u;
-        const int wave = threadIdx.x >> 6;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const char *a = base + (ptrdiff_t)(pix[i] + delta) * 2;
-            core2::load_chunk_to_lds(inside[i] & bit ? (const void *)a : (const void *)core2::g_zero_chunk,
-                                     lds + (size_t)(wave * 64 + i * core2::kThreads2) * 16);
-        }
+        k += core::BK;
+        c += dc;
+        const int carry = c >= g.Cs;
+        c -= carry ? g.Cs : 0;
+        tap += dtap + carry;
+        locate();
+    }
+    template <int ROWS> __device__ __forceinline__ void issue(int i, uint32_t lds) const
+    {
+        if (!core2::mine2<ROWS>(i)) return;
+        const char *a = base + (ptrdiff_t)(pix[i] + delta) * 2;
+        dev::lds_dma16(inside[i] & bit ? (const void *)a : (const void *)core2::g_zero_chunk, core2::chunk_lds2(lds, i));
     }
 };
 
@@ -277,8 +280,9 @@ template <int BM, bool OUT_BF16> __global__ __launch_bounds__(core2::kThreads2, 
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     TileId t;
     if (!tile_of<BM, 256>(p, &t)) return;
-    GatherKC2<BM> la;
-    la.init(p.g, p.A[t.shard], p.M, p.K, t.m0);
+    GatherKC2 la;
+    la.base = reinterpret_cast<const char *>(p.A[t.shard]);
+    la.g = p.g; la.M = p.M; la.K = p.K;
     core2::DenseKC2 lb;
     lb.base = reinterpret_cast<const char *>(p.B[t.shard * p.members]);
     lb.ld = p.K; lb.rows = p.N; lb.K = p.K;
@@ -445,23 +449,37 @@ template <bool TAIL> struct SegDenseRC2 {
     static constexpr bool KC = false;
     Segment seg;
     int ld, rows, pixels;
-    template <int ROWS> __device__ __forceinline__ void issue(int row0, int k0, char *lds) const
+    uint32_t voff;      // this lane's first chunk, bytes from the current tile's first pixel
+    int k0, px;         // current tile: k, its first pixel inside the shard
+    const char *base;   // ... the shard's buffer
+    __device__ __forceinline__ void locate()
     {
-        constexpr int CPR = ROWS / 8, KR = core2::kThreads2 / CPR; // chunks per k-row, k-rows that the threads cover at once
         int kshift;
-        const char *base = seg.locate(k0, &kshift);
-        const int tid = threadIdx.x, wave = tid >> 6;
-        const int kr = tid / CPR, pc = tid % CPR; // chunk tid + 512 i: k-row kr + KR i, position pc (see core2::issue_tile)
+        base = seg.locate(k0, &kshift);
+        px = k0 + kshift;
+    }
+    template <int ROWS> __device__ __forceinline__ void begin(int row0)
+    {
+        constexpr int CPR = ROWS / 8; // chunks per k-row
+        const int kr = threadIdx.x / CPR, pc = threadIdx.x % CPR;
         int r0 = row0 + ((pc ^ ((kr & 3) << 1)) << 3);
         r0 = r0 < rows ? r0 : rows - 8; // rows past the end only feed C rows that are never stored
-        const int px = k0 + kshift + kr;
-        const char *a = base + ((size_t)px * (size_t)ld + (size_t)r0) * 2;
-#pragma unroll
-        for (int i = 0; i < ROWS * core::BK / 8 / core2::kThreads2; ++i) {
-            const void *c = a + (size_t)i * KR * (size_t)ld * 2;
-            if (TAIL && px + i * KR >= pixels) c = core2::g_zero_chunk;
-            core2::load_chunk_to_lds(c, lds + (size_t)(wave * 64 + i * core2::kThreads2) * 16);
-        }
+        voff = ((uint32_t)kr * (uint32_t)ld + (uint32_t)r0) * 2u;
+        k0 = 0;
+        locate();
+    }
+    template <int ROWS> __device__ __forceinline__ void next()
+    {
+        k0 += core::BK;
+        locate();
+    }
+    template <int ROWS> __device__ __forceinline__ void issue(int i, uint32_t lds) const
+    {
+        constexpr int CPR = ROWS / 8, KR = core2::kThreads2 / CPR; // k-rows that the threads cover at once
+        const char *b = base + (size_t)(px + i * KR) * (size_t)ld * 2;
+        if (!TAIL || px + core::BK <= pixels) dev::lds_dma16(voff, core2::uniform64(b), core2::chunk_lds2(lds, i));
+        else dev::lds_dma16(px + i * KR + (int)(threadIdx.x / CPR) < pixels ? (const void *)(b + voff) : (const void *)core2::g_zero_chunk,
+                            core2::chunk_lds2(lds, i));
     }
 };
 
@@ -472,9 +490,11 @@ template <bool TAIL> struct SegGatherRC2 {
     Segment seg;
     int H, W, P, Q, S, pad, Cs, rows, Ns;
     PixelStep s16, s64;
-    // position (image, row, column) of this thread's first pixel of the K tile it last issued; the tiles of a work item
-    // are issued in order, each 64 pixels after the one before
-    mutable int n_, p_, q_;
+    int dy, dx, c0;     // this lane's tap and channel
+    int k0;
+    const char *base;   // the current tile's shard
+    int n_, p_, q_;     // position (image, row, column) of this lane's first pixel of the current tile
+    mutable int n, p, q; // ... of its next chunk: a tile's chunks are issued in order, 16 pixels apart
     __device__ __forceinline__ static void step(const PixelStep &d, int P, int Q, int &n, int &p, int &q)
     {
         q += d.dq;
@@ -485,37 +505,48 @@ template <bool TAIL> struct SegGatherRC2 {
         p -= cp ? P : 0;
         n += d.dn + cp;
     }
-    template <int ROWS> __device__ __forceinline__ void issue(int row0, int k0, char *lds) const
+    __device__ __forceinline__ void place(int kl) // kl: pixel inside the shard
+    {
+        n_ = kl / (P * Q);
+        const int rem = kl - n_ * (P * Q);
+        p_ = rem / Q;
+        q_ = rem - p_ * Q;
+    }
+    template <int ROWS> __device__ __forceinline__ void begin(int row0)
     {
         static_assert(ROWS == 256, "tile side");
-        int kshift;
-        const char *base = seg.locate(k0, &kshift);
-        const int tid = threadIdx.x, wave = tid >> 6;
-        const int kr = tid >> 5, pc = tid & 31;
+        const int kr = threadIdx.x >> 5, pc = threadIdx.x & 31;
         int r0 = row0 + ((pc ^ ((kr & 3) << 1)) << 3);
         r0 = r0 < rows ? r0 : rows - 8;
-        const int tap = r0 / Cs, c0 = r0 - tap * Cs;
-        const int fr = tap / S, dy = fr - pad, dx = tap - fr * S - pad;
-        if (k0 == 0 || (TAIL && k0 + kshift == 0)) { // (with a tail the next shard does not start where this one ends)
-            const int kl = k0 + kshift + kr; // pixel inside the shard
-            n_ = kl / (P * Q);
-            const int rem = kl - n_ * (P * Q);
-            p_ = rem / Q;
-            q_ = rem - p_ * Q;
+        const int tap = r0 / Cs, fr = tap / S;
+        c0 = r0 - tap * Cs;
+        dy = fr - pad;
+        dx = tap - fr * S - pad;
+        k0 = 0;
+        int kshift;
+        base = seg.locate(0, &kshift);
+        place(kshift + kr);
+    }
+    template <int ROWS> __device__ __forceinline__ void next() // each tile 64 pixels after the one before
+    {
+        k0 += core::BK;
+        int kshift;
+        base = seg.locate(k0, &kshift);
+        if (TAIL && k0 + kshift == 0) { // (with a tail the next shard does not start where this one ends)
+            place((int)(threadIdx.x >> 5));
         } else {
             step(s64, P, Q, n_, p_, q_);
             if (!TAIL) n_ -= n_ >= Ns ? Ns : 0; // the run went on into the next shard
         }
-        int n = n_, p = p_, q = q_;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int iy = p + dy, ix = q + dx;
-            const bool ok = iy >= 0 && iy < H && ix >= 0 && ix < W && (!TAIL || n < Ns);
-            const char *a = base + ((size_t)((n * H + iy) * W + ix) * (size_t)Cs + (size_t)c0) * 2;
-            core2::load_chunk_to_lds(ok ? (const void *)a : (const void *)core2::g_zero_chunk,
-                                     lds + (size_t)(wave * 64 + i * core2::kThreads2) * 16);
-            step(s16, P, Q, n, p, q);
-        }
+    }
+    template <int ROWS> __device__ __forceinline__ void issue(int i, uint32_t lds) const
+    {
+        if (i == 0) { n = n_; p = p_; q = q_; }
+        const int iy = p + dy, ix = q + dx;
+        const bool ok = iy >= 0 && iy < H && ix >= 0 && ix < W && (!TAIL || n < Ns);
+        const char *a = base + ((size_t)((n * H + iy) * W + ix) * (size_t)Cs + (size_t)c0) * 2;
+        dev::lds_dma16(ok ? (const void *)a : (const void *)core2::g_zero_chunk, core2::chunk_lds2(lds, i));
+        step(s16, P, Q, n, p, q);
     }
 };
 
@@ -552,7 +583,6 @@ __global__ __launch_bounds__(core2::kThreads2, BM == 64 ? 4 : 2) void conv_wgrad
     lb.H = g.H; lb.W = g.W; lb.P = g.P; lb.Q = g.Q; lb.S = g.S; lb.pad = g.pad; lb.Cs = g.Cs; lb.rows = p.N; lb.Ns = g.Ns;
     lb.s16 = pixel_step(16, g.P, g.Q);
     lb.s64 = pixel_step(64, g.P, g.Q);
-    lb.n_ = lb.p_ = lb.q_ = 0;
     core2::tile_product2<false, true, BM>(la, lb, p.C[bp], p.ldc, p.M, p.N, K, m0, n0, false, reinterpret_cast<char *>(smem));
 }
 
@@ -706,6 +736,25 @@ int conv_tile(int64_t M, int64_t N, int count)
     return M > 128 ? 0 : 1;
 }
 
+// Rows of a 256-column tile of the engine that loads tiles straight into LDS: 256, 224 or 192, whichever gets by with the least
+// of rounds over the CUs times rows of a tile, a tile's right operand and write-out counted as 64 rows.  Forward product on 256 /
+// 224 / 192 rows, us: conv4 as the planner cuts it 234 / 212 / 285 (392, 448, 524 tiles), cut along the batch 222 / 205 / 270; 32 images
+// of 56 x 56, 256 to 256 channels, not cut 121 / 110 / 143; 96 of 34 x 46, 128 to 384, 8 shards 165 / 178 / 183; 48 of 30 x 30, 512 to
+// 256, 1 x 1 filters, 2 shards 19.0 / 18.7 / 18.1.
+int gather_rows(int64_t M, int64_t N, int count)
+{
+    const int forced = tuning_int("TT_CONV_ROWS", 0);
+    if (forced) return forced;
+    int best = 256;
+    int64_t least = INT64_MAX;
+    for (int rows = 256; rows >= 192; rows -= 32) {
+        const int64_t tiles = (M + rows - 1) / rows * ((N + 255) / 256) * count;
+        const int64_t cost = (tiles + 255) / 256 * (rows + 64);
+        if (cost < least) { least = cost; best = rows; }
+    }
+    return best;
+}
+
 template <int OP, bool OUT_BF16, bool ONE_TAP> tt_status launch_gather_a_t(ConvParams &p, int count, hipStream_t s)
 {
     const bool kmask = p.K % core::BK != 0;
@@ -726,10 +775,14 @@ template <int OP, bool OUT_BF16, bool ONE_TAP> tt_status launch_gather_a_t(ConvP
                      : launch(conv_gather_a_kernel<256, 64, 1, 2, false, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 256, 64, 256, count, s);
     }
     // Both operands K-contiguous: straight into LDS instead of through registers (VGG-16 conv4, 50176 x 512 x 4608, as the planner
-    // cuts it 313 -> 291 us, its data gradient 301 -> 289; shorter K, 1728 and 1152, equal within 2 %)
+    // cuts it 313 us through registers, 291 with 32 x 32 x 16 MFMAs, 230 now; under the profiler)
     if constexpr (OP == 0)
-    if (tile == 2 || tuning_int("TT_CONV_TILE", -1) == 3)
+    if (tile == 2 || tuning_int("TT_CONV_TILE", -1) == 3) {
+        const int rows = gather_rows(p.M, p.N, count);
+        if (rows == 192) return launch(conv_gather_a2_kernel<192, OUT_BF16>, core2::smem_bytes2<192>(), p, 192, 256, core2::kThreads2, count, s);
+        if (rows == 224) return launch(conv_gather_a2_kernel<224, OUT_BF16>, core2::smem_bytes2<224>(), p, 224, 256, core2::kThreads2, count, s);
         return launch(conv_gather_a2_kernel<256, OUT_BF16>, core2::smem_bytes2<256>(), p, 256, 256, core2::kThreads2, count, s);
+    }
     if constexpr (OP == 1)
     if (tile == 2) {
         constexpr size_t sm = core::smem_bytes<256, 256>();

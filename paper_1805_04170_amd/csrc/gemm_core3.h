@@ -199,8 +199,8 @@ template <bool KC, bool IS_A, bool RUNS = false> struct Feeder {
     }
 };
 
-constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-constexpr int waitcnt_vm_lds(int n) { return waitcnt_vm(n) & ~(15 << 8); } // ... and lgkmcnt(0)
+using mma::waitcnt_vm;
+using mma::waitcnt_vm_lds;
 
 // SPREAD: loads over the whole second k-step of an item instead of its second half
 template <int BK, int NS, bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool SPREAD, bool RUNS = false>

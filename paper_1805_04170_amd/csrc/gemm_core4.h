@@ -36,15 +36,7 @@ constexpr size_t kSmem4 = (size_t)NS4 * kStage4;                                
 constexpr int kLoadsA = kABytes / 16 / kThreads4, kLoadsB = kBBytes / 16 / kThreads4;        // 4 and 2 per thread
 
 // lane offsets of this thread's 16-byte chunks of one operand tile (ROWS x 32), see the layouts above
-__device__ __forceinline__ uint64_t uniform64(const char *p)
-{
-    // wave-uniform by construction; say so, or an "s" operand may be handed a vector register pair (readfirstlane
-    // returns a signed int: go through uint32_t so the low half is not sign-extended)
-    const uint64_t b64 = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b64);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
-    return ((uint64_t)hi << 32) | (uint64_t)lo;
-}
+using core2::uniform64;
 
 template <int ROWS, bool KC> __device__ __forceinline__ void chunk_offsets(int row0, int rows, int ld, uint32_t *voff)
 {

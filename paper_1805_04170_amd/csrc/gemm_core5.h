@@ -7,7 +7,7 @@
 // stores of the previous tile and queue behind them in the CU's memory pipeline; multiplication and write-out of a CU then
 // take turns instead of overlapping.  Here K is so short that one operand stays in registers for its whole length:
 //   - a workgroup of four waves owns a PANEL of 256 rows of C (64 per wave).  Each wave keeps its 64 x K slice of A^T in
-//     registers (2 x K/16 MFMA fragments, 128 VGPRs at K = 256), loaded once per panel through LDS with transpose reads;
+//     registers (4 x K/32 MFMA fragments, 128 VGPRs at K = 256), loaded once per panel through LDS with transpose reads;
 //   - the workgroup then walks UNITS of 64 columns of C.  A unit needs one B tile (K x 64, 32 KB at K = 256), fetched
 //     global -> LDS one unit ahead into a two-stage ring: every load a unit needs is issued BEFORE the previous unit's
 //     stores, so nothing a unit waits for queues behind stores, and the stores of unit u drain while unit u + 1 multiplies;
@@ -19,8 +19,10 @@
 //     changes, barriers and epilogues;
 //   - K = 512 (weight gradients at a per-shard batch of 512: compute-bound, 4 K flops per result element) runs the same
 //     way with ONE workgroup per CU: the panel takes 256 registers per lane and the two B stages 128 KB.  What it buys
-//     there is LDS traffic: only B goes through LDS (two fragment reads per four products instead of six per eight),
+//     there is LDS traffic: only B goes through LDS (a fragment read per four products instead of three per eight),
 //     where the tile engines that read both operands through LDS transpose reads are bound by LDS;
+//   - 16 x 16 x 32 MFMAs, a B fragment of the k-step ahead in front of every four (gemm_mma.h says why): 16 x (2048 x 2048 x 512) 71 -> 67
+//     us, 8 x (1152 x 4096 x 256) 26; the first VGG-16 weight gradient, bound by its 205 MB of stores, 59 either way;
 //   - the grid is persistent: each workgroup takes a contiguous run of units (shard-major, panel, column tile).
 //
 // LDS layouts (XOR-swizzled by the choice of which global chunk a lane fetches, as in gemm_core2.h):
@@ -35,14 +37,14 @@
 #include "gemm_core.h"
 #include "gemm_core2.h"
 #include "gemm_core3.h"
+#include "gemm_mma.h"
 
 namespace tt {
 namespace core5 {
 
 using core::bf16x8;
-using core::f32x16;
+using core::f32x4;
 using core::u32x4;
-using core2::s16x4;
 
 constexpr int kThreads5 = 256;
 constexpr int PM5 = 256; // rows of C per panel (64 per wave)
@@ -65,31 +67,23 @@ struct Params5 {
     int32_t relu;
 };
 
-// B fragment (32 columns x 16 k) of a stage: columns cbase .. cbase + 31 of the unit, k-step ks
+// B fragment (16 columns x 32 k) of a stage: columns cbase .. cbase + 15 of the unit, k-step ks
 __device__ __forceinline__ bf16x8 read_frag_b5(const char *lds, int cbase, int ks, int lane)
 {
-    const int g16 = lane >> 4, j = lane & 15;
-    const int n0 = cbase + (g16 & 1) * 16 + 4 * (j & 3); // first of this lane's 4 addressed columns
+    const int q = lane >> 4, j = lane & 15;
+    const int n0 = cbase + 4 * (j & 3); // first of this lane's 4 addressed columns
     const int c = n0 >> 3, byte = (n0 & 7) * 2;
-    union { s16x4 h[2]; bf16x8 v; } u;
+    union { dev::s16x4 h[2]; bf16x8 v; } u;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const int k = ks * 16 + (g16 >> 1) * 8 + h * 4 + (j >> 2);
+        const int k = ks * 32 + q * 8 + h * 4 + (j >> 2);
         const char *a = lds + k * (NT5 * 2) + ((c ^ (((k >> 1) & 1) << 1)) << 4) + byte;
         u.h[h] = dev::lds_read_tr16_b64(a);
     }
     return u.v;
 }
 
-__device__ __forceinline__ uint64_t uniform64(const char *p)
-{
-    // wave-uniform by construction; say so, or an "s" operand may be handed a vector register pair (readfirstlane
-    // returns a signed int: go through uint32_t so the low half is not sign-extended)
-    const uint64_t b64 = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b64);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b64 >> 32));
-    return ((uint64_t)hi << 32) | (uint64_t)lo;
-}
+using core2::uniform64;
 
 // KT = K / 16 (8, 16 or 32).  NTS: non-temporal stores.  256 threads; smem: smem_bytes5<KT>() bytes, 16-byte aligned.
 template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Params5 &p, char *smem)
@@ -119,16 +113,15 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
     const int a_chunk = (int)(apc ^ ((akl & 3u) << 1));
 
     // Result strip of the wave: 32 rows of 128 bytes.  The products are formed as (B tile) x (A panel)^T, so a lane
-    // holds row (lane & 31) of a 32 x 32 block of C and, per register group g, the four consecutive columns
-    // 8 g + 4 (lane / 32) + 0..3: eight bytes, written with one LDS store.  Row r keeps its 16-byte piece c at position
-    // c ^ ((r >> 1) & 7) and, for r >= 16, the two halves of a piece exchanged: the 32 rows written together then fall
-    // into 32 different bank pairs, and the 16-byte reads of the row-contiguous write-out stay conflict-free.
+    // holds row (lane & 15) of a 16 x 16 block of C and its four consecutive columns 4 (lane / 16) + 0..3: eight bytes,
+    // written with one LDS store.  Row r keeps its 16-byte piece c at position c ^ ((r >> 1) & 7): the 16 rows written
+    // together then fall into different banks, and the 16-byte reads of the row-contiguous write-out stay conflict-free.
     char *strip = smem + 2 * STB + wave * (kEpiRows5 * NT5 * 2);
-    const int srow = lane & 31;
-    char *swr = strip + srow * (NT5 * 2) + ((((lane >> 5) ^ (srow >> 4)) & 1) << 3);
+    const int srow = lane & 15, squad = lane >> 4;
+    char *swr = strip + srow * (NT5 * 2) + ((squad & 1) << 3);
     const int sswz = (srow >> 1) & 7;
     // write-out: lane l takes piece l % 8 of strip row l / 8 + 8 v (v = 0..3); (row >> 1) & 7 = ((l >> 4) + 4 v) & 7, so
-    // the swizzled position is that of v = 0 with bit 2 flipped for odd v; rows 16.. have their halves exchanged
+    // the swizzled position is that of v = 0 with bit 2 flipped for odd v
     const char *srd[2];
     srd[0] = strip + (lane >> 3) * (NT5 * 2) + (((lane & 7) ^ ((lane >> 4) & 7)) << 4);
     srd[1] = strip + (lane >> 3) * (NT5 * 2) + (((lane & 7) ^ ((lane >> 4) & 7) ^ 4) << 4);
@@ -146,7 +139,10 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
         // ---- the panel's slice of A^T into registers, half of K at a time through the (idle) B stages
         __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(0));
         __syncthreads(); // nobody still reads a stage
-        bf16x8 af[2][KT];
+        constexpr int KS = KT / 2; // k-steps of 32
+        bf16x8 af[4][KS];
+        mma::Reader<PM5, false, 4> ra;
+        ra.init(wm0, lane);
         {
             int col = m0 + a_chunk * 8;
             col = col < M ? col : M - 8; // columns past M only feed rows of C that are never stored
@@ -162,9 +158,9 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
                 __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(0));
                 __syncthreads();
 #pragma unroll
-                for (int ks = 0; ks < KT / 2; ++ks)
+                for (int ks = 0; ks < KS / 2; ++ks)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) af[i][c * (KT / 2) + ks] = core2::read_frag<256, false>(smem, wm0 + i * 32, ks, lane);
+                    for (int i = 0; i < 4; ++i) af[i][c * (KS / 2) + ks] = ra.read(smem, ks, i);
                 __syncthreads(); // everyone has its fragments before the staging area is overwritten
             }
         }
@@ -192,38 +188,30 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
             const char *Bs = smem + cs * STB;
             cs ^= 1;
 
-            f32x16 acc[2][2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+            f32x4 acc[4][4];
+            mma::clear(acc);
             // the B fragments are requested LOOK k-steps before the products that use them are issued: under load the LDS
-            // latency of the transpose reads is longer than the four products of one step (with one workgroup per CU,
-            // K = 512, no other wave of the SIMD fills the gap: four steps ahead there, two otherwise)
-            constexpr int LOOK = KT > 16 ? 4 : 2;
-            bf16x8 bq[LOOK + 1][2];
+            // latency of the transpose reads is long (with one workgroup per CU, K = 512, no other wave of the SIMD fills
+            // the gap: two steps ahead there, one otherwise)
+            constexpr int LOOK = KT > 16 ? 2 : 1;
+            bf16x8 bq[LOOK + 1][4];
 #pragma unroll
-            for (int a = 0; a < LOOK; ++a) {
-                bq[a][0] = read_frag_b5(Bs, 0, a, lane);
-                bq[a][1] = read_frag_b5(Bs, 32, a, lane);
-            }
+            for (int a = 0; a < LOOK; ++a)
 #pragma unroll
-            for (int ks = 0; ks < KT; ++ks) {
-                const bf16x8 b0 = bq[ks % (LOOK + 1)][0], b1 = bq[ks % (LOOK + 1)][1];
-                if (ks + LOOK < KT) {
-                    bq[(ks + LOOK) % (LOOK + 1)][0] = read_frag_b5(Bs, 0, ks + LOOK, lane);
-                    bq[(ks + LOOK) % (LOOK + 1)][1] = read_frag_b5(Bs, 32, ks + LOOK, lane);
+                for (int j = 0; j < 4; ++j) bq[a][j] = read_frag_b5(Bs, 16 * j, a, lane);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { // one of the fragments ahead in front of every four products
+                    if (ks + LOOK < KS) bq[(ks + LOOK) % (LOOK + 1)][i] = read_frag_b5(Bs, 16 * i, ks + LOOK, lane);
+                    __builtin_amdgcn_sched_barrier(0); // (left alone, the scheduler starts the next step's products early and waits for these reads)
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) { // operands exchanged: the accumulators hold blocks of C^T (see the strip above)
+                        const int j = i & 1 ? 3 - jj : jj;
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[ks % (LOOK + 1)][j], af[i][ks], acc[i][j], 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0); // (left alone, the scheduler starts the next step's products early and waits for these reads)
-                // operands exchanged: the accumulators hold blocks of C^T (see the strip above)
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b0, af[0][ks], acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1, af[0][ks], acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b0, af[1][ks], acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1, af[1][ks], acc[1][1], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
 
             // ---- epilogue: 32 rows of the wave's 64 at a time through its strip, then out as 16-byte pieces of whole
             // 128-byte rows (8 lanes per row, 8 rows per store instruction)
@@ -231,13 +219,13 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        float v0 = acc[i][j][4 * g], v1 = acc[i][j][4 * g + 1], v2 = acc[i][j][4 * g + 2], v3 = acc[i][j][4 * g + 3];
-                        v0 = fmaxf(v0, floor_v); v1 = fmaxf(v1, floor_v); v2 = fmaxf(v2, floor_v); v3 = fmaxf(v3, floor_v);
-                        const core::u32x2 pk = {core::pack_bf16x2(v0, v1), core::pack_bf16x2(v2, v3)};
-                        *reinterpret_cast<core::u32x2 *>(swr + (((4 * j + g) ^ sswz) << 4)) = pk;
+                    for (int j = 0; j < 4; ++j) {
+                        const f32x4 v = acc[2 * i + h][j];
+                        const core::u32x2 pk = {core::pack_bf16x2(fmaxf(v[0], floor_v), fmaxf(v[1], floor_v)),
+                                                core::pack_bf16x2(fmaxf(v[2], floor_v), fmaxf(v[3], floor_v))};
+                        *reinterpret_cast<core::u32x2 *>(swr + 16 * h * (NT5 * 2) + (((2 * j + (squad >> 1)) ^ sswz) << 4)) = pk;
                     }
                 // wave-private data and LDS operations of a wave execute in order: only the compiler needs a fence
                 __builtin_amdgcn_wave_barrier();
@@ -247,7 +235,7 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int row0 = m0 + wm0 + i * 32 + 8 * v; // wave-uniform: first of the 8 rows this instruction stores
-                    const u32x4 o = v >= 2 ? u32x4{t[v][2], t[v][3], t[v][0], t[v][1]} : t[v];
+                    const u32x4 o = t[v];
                     char *dst = reinterpret_cast<char *>(Cs) + ((size_t)row0 * ldc + n0) * 2 + st_off;
                     if (full) dev::store16<NTS>(dst, o);
                     else if (row0 + (lane >> 3) < M) dev::store16<NTS>(dst, o);

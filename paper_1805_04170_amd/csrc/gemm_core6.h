@@ -86,7 +86,7 @@ __device__ __forceinline__ void tile_product6(const char *abase, int lda, const 
     const int nk = klen / BK6;
 
     // K tile to ask for next; past the end the last one is fetched again, so that the wait counts stay the same
-    uint64_t ab = core4::uniform64(abase), bb = core4::uniform64(bbase);
+    uint64_t ab = core2::uniform64(abase), bb = core2::uniform64(bbase);
     int left = nk - 1;
     auto issue_one = [&](int i, uint32_t stage) {
         if (i < kLoadsA6) dev::lds_dma16(voa[i], ab, stage + wave_lds + (uint32_t)i * (kThreads6 * 16u));

@@ -25,6 +25,10 @@ using core::f32x4;
 using core::u32x2;
 using core::u32x4;
 
+// operands of s_waitcnt: at most n vector-memory operations outstanding (_lds: and no LDS operation)
+constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+constexpr int waitcnt_vm_lds(int n) { return waitcnt_vm(n) & ~(15 << 8); }
+
 // Fragments (16 rows x 32 k, 8 values of K per lane) of an operand tile of ROWS rows and 64 k in LDS; layouts as in gemm_core2.h.
 // T: 16-row blocks of a wave, from row w0 on (a multiple of 16 T, of 64 where T is 4 or more).
 // BK = 32: one k-step; rows of 64 bytes, chunk position p of row r holds k-chunk p ^ (-(r >> 2) & 3).

@@ -223,6 +223,15 @@ def test_conv_fp32(on_host):
     on_host["conv"].test_fp32_convolutions()
 
 
+@pytest.mark.parametrize("rows", [192, 224, 256])
+@pytest.mark.parametrize("C,K", [(8, 24), (64, 264)])
+def test_conv_forward_on_tiles_of_every_height(on_host, monkeypatch, rows, C, K):
+    # 324 pixels end inside the second row of tiles, K = 72 inside a K tile, 24 and 264 columns inside a tile
+    monkeypatch.setenv("TT_CONV_TILE", "3")
+    monkeypatch.setenv("TT_CONV_ROWS", str(rows))
+    on_host["conv"].run_conv(4, C, K, 9, 9, 3, 3, 1, 0, True, "", "", "", "", "", None, None, None, 61 + rows, with_dx=False)
+
+
 def test_conv_refusals(on_host):
     on_host["conv"].test_refusals()
 
