@@ -213,11 +213,10 @@ template <bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status l
 
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_mfma_kmask(GemmParams &p, int count, hipStream_t s)
 {
-    // Where the eight-wave 256 x 256 tile is chosen, the engine that loads tiles straight into LDS measured faster for
-    // every layout but NN (A K-contiguous, B row-contiguous), which stays on the register-staged engine.
+    // Where the eight-wave 256 x 256 tile is chosen, the engine that loads tiles straight into LDS is the faster one (through
+    // registers / into LDS, us: A B 2048 x 8200 x 4104 260 / 210, 4 x (1000 x 4000 x 1000) 42 / 35)
     const int tile = pick_tile(p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, count * p.ksplit);
-    const bool nn = A_KC && !B_KC;
-    if ((tile == 8 || (tile == 5 && !nn && tuning_int("TT_GEMM_TILE", -1) < 0)) && p.M >= 8 && p.N >= 8)
+    if ((tile == 8 || (tile == 5 && tuning_int("TT_GEMM_TILE", -1) < 0)) && p.M >= 8 && p.N >= 8)
         return launch_v2<A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     return p.K % core::BK ? launch_mfma_tile<true, A_KC, B_KC, OUT_BF16, VEC>(p, count, s)
                           : launch_mfma_tile<false, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
@@ -298,12 +297,15 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
         //    against the direct-to-LDS engine, A B^T over K = 512 28.3 -> 28.0), else the direct-to-LDS engine.
         const int engine = tuning_int("TT_GEMM_ENGINE", 0);
         const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256) * count * ksplit;
-        //  - weight-gradient shaped products (both operands stored with K as the slow dimension, K = 128, 256 or 512, a bf16
+        //  - weight-gradient shaped products (both operands stored with K as the slow dimension, K up to 256 or 512, a bf16
         //    result large enough to give every resident workgroup at least two 256 x 64 units; measured down to the second
         //    VGG-16 weight gradient, 8 x 1024 x 2048 x 256: 16 us against 20 us on the persistent engine): the engine that
-        //    keeps the left operand's panel in registers and is bound by writing the result (gemm_core5.h)
+        //    keeps the left operand's panel in registers and is bound by writing the result (gemm_core5.h).  Any K up to 256 runs
+        //    on the next of 64, 128 and 256, between 256 and 512 the padding costs more than it saves.  Here / 256 x 128 tiles / the
+        //    larger ones, us: 6936 x 7456 K 219 38 / 44 / 57, K 300 66 / 51 / 62, K 480 69 / 60 / 82; 13504 x 4288 K 72 31 / 32 / 41;
+        //    9072 x 11856 K 40 86 / 103 / 91; 8 x (1568 x 4096) K 192 38 / 35 / 44
         if ((engine == 5 || engine == 0) && !a_kc && !b_kc && ksplit == 1 && out_dtype == TT_BF16 && vec && in_dtype == TT_BF16 &&
-            (engine == 5 || ((M + 255) / 256) * (N / 64) * count >= 2 * 512)) {
+            (engine == 5 || (((M + 255) / 256) * ((N + 63) / 64) * count >= 2 * 512 && (K <= 256 || K == 512)))) {
             const tt_status st = launch_gemm_v5(count, A, B, C, M, N, K, a_contig, b_contig, N, act == TT_ACT_RELU, stream);
             if (st != TT_EUNSUPPORTED) return st;
         }
@@ -320,7 +322,15 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
                                                 vec, ksplit, kchunk, stream);
             if (st != TT_EUNSUPPORTED) return st;
         }
-        if (engine == 4 || (engine == 0 && big_tiles < 200 && M > 128 && N >= 256)) {
+        //  - 256 x 128 tiles, two workgroups per CU, otherwise; K that is no multiple of 32 from 128 on (8 x (300 x 4000 x 200) A B through
+        //    registers 14.4, here 11.6; K 104 6.2 / 7.7).  Of the larger launches those whose K the persistent engine does not take and
+        //    that are short enough for the second workgroup to be worth the narrower tile.  Direct-to-LDS engine / here, us: A^T B 6936 x
+        //    7456 K 529 84 / 67, 1001 128 / 114, 1529 178 / 163, 9072 x 11856 K 40 90 / 102; 8 x (500 x 8000) A B K 200 28.7 / 24.1, 520 45.8 / 44.0,
+        //    1032 73.9 / 90.4; A B^T K 200 28.9 / 26.8, 520 44.8 / 49.8
+        const bool narrow = big_tiles < 200 ? K % 32 == 0 || kc >= 128
+                                            : K % 64 != 0 ? kc >= 64 && kc <= (!a_kc && !b_kc ? 2048 : a_kc && !b_kc ? 640 : 256)
+                                                          : !a_kc && !b_kc && kc > 256 && kc < 512;
+        if (engine == 4 || (engine == 0 && narrow && M > 128 && N >= 256)) {
             const tt_status st = launch_gemm_v4(count, A, B, C, M, N, K, a_contig, b_contig, N, a_kc, b_kc, out_dtype,
                                                 act == TT_ACT_RELU, vec, ksplit, kchunk, stream);
             if (st != TT_EUNSUPPORTED) return st;

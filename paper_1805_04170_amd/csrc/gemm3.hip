@@ -23,7 +23,7 @@ __global__ __launch_bounds__(core3::kThreads3, 2) void gemm_bf16_v3_kernel(const
 }
 
 // 256 x 128 tiles, four waves, two workgroups per CU (gemm_core4.h); one tile per workgroup
-template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED>
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL>
 __global__ __launch_bounds__(core4::kThreads4, 2) void gemm_bf16_v4_kernel(const core3::Params3 p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem4[];
@@ -39,16 +39,21 @@ __global__ __launch_bounds__(core4::kThreads4, 2) void gemm_bf16_v4_kernel(const
     const int klen = p.K - kbeg < p.kchunk ? p.K - kbeg : p.kchunk;
     const char *abase = reinterpret_cast<const char *>(p.A[shard]) + (size_t)kbeg * (A_KC ? 2 : 2 * (size_t)p.lda);
     const char *bbase = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
-    core4::tile_product4<A_KC, B_KC, OUT_BF16, STAGED>(abase, p.lda, bbase, p.ldb, p.C[vshard], p.ldc, p.M, p.N, klen,
+    core4::tile_product4<A_KC, B_KC, OUT_BF16, STAGED, TAIL>(abase, p.lda, bbase, p.ldb, p.C[vshard], p.ldc, p.M, p.N, klen,
                                                        tm * core4::BM4, tn * core4::BN4, p.relu != 0, smem4);
+}
+
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL> tt_status launch_tail4(core3::Params3 &p, hipStream_t s)
+{
+    auto kern = gemm_bf16_v4_kernel<A_KC, B_KC, OUT_BF16, STAGED, TAIL>;
+    if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), core4::kSmem4) != TT_OK) return TT_EDEVICE;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)p.per_xcd * core::kXcds), dim3(core4::kThreads4), core4::kSmem4, s, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
 
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED> tt_status launch_cfg4(core3::Params3 &p, hipStream_t s)
 {
-    auto kern = gemm_bf16_v4_kernel<A_KC, B_KC, OUT_BF16, STAGED>;
-    if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), core4::kSmem4) != TT_OK) return TT_EDEVICE;
-    hipLaunchKernelGGL(kern, dim3((uint32_t)p.per_xcd * core::kXcds), dim3(core4::kThreads4), core4::kSmem4, s, p);
-    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+    return p.K % core4::BK4 ? launch_tail4<A_KC, B_KC, OUT_BF16, STAGED, true>(p, s) : launch_tail4<A_KC, B_KC, OUT_BF16, STAGED, false>(p, s);
 }
 
 template <bool A_KC, bool B_KC> tt_status launch_layout4(core3::Params3 &p, int out_dtype, bool vec, hipStream_t s)
@@ -59,7 +64,7 @@ template <bool A_KC, bool B_KC> tt_status launch_layout4(core3::Params3 &p, int 
 }
 
 // 256 x 128 tiles, K tiles of 64, one workgroup per CU (gemm_core6.h); one tile per workgroup
-template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED>
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL>
 __global__ __launch_bounds__(core6::kThreads6, 2) void gemm_bf16_v6_kernel(const core3::Params3 p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem4[];
@@ -75,16 +80,21 @@ __global__ __launch_bounds__(core6::kThreads6, 2) void gemm_bf16_v6_kernel(const
     const int klen = p.K - kbeg < p.kchunk ? p.K - kbeg : p.kchunk;
     const char *abase = reinterpret_cast<const char *>(p.A[shard]) + (size_t)kbeg * (A_KC ? 2 : 2 * (size_t)p.lda);
     const char *bbase = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
-    core6::tile_product6<A_KC, B_KC, OUT_BF16, STAGED>(abase, p.lda, bbase, p.ldb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * core6::BM6,
+    core6::tile_product6<A_KC, B_KC, OUT_BF16, STAGED, TAIL>(abase, p.lda, bbase, p.ldb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * core6::BM6,
                                                        tn * core6::BN6, p.relu != 0, smem4);
+}
+
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL> tt_status launch_tail6(core3::Params3 &p, hipStream_t s)
+{
+    auto kern = gemm_bf16_v6_kernel<A_KC, B_KC, OUT_BF16, STAGED, TAIL>;
+    if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), core6::kSmem6) != TT_OK) return TT_EDEVICE;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)p.per_xcd * core::kXcds), dim3(core6::kThreads6), core6::kSmem6, s, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
 
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED> tt_status launch_cfg6(core3::Params3 &p, hipStream_t s)
 {
-    auto kern = gemm_bf16_v6_kernel<A_KC, B_KC, OUT_BF16, STAGED>;
-    if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), core6::kSmem6) != TT_OK) return TT_EDEVICE;
-    hipLaunchKernelGGL(kern, dim3((uint32_t)p.per_xcd * core::kXcds), dim3(core6::kThreads6), core6::kSmem6, s, p);
-    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+    return p.K % core6::BK6 ? launch_tail6<A_KC, B_KC, OUT_BF16, STAGED, true>(p, s) : launch_tail6<A_KC, B_KC, OUT_BF16, STAGED, false>(p, s);
 }
 
 template <bool A_KC, bool B_KC> tt_status launch_layout6(core3::Params3 &p, int out_dtype, bool vec, hipStream_t s)
@@ -94,20 +104,27 @@ template <bool A_KC, bool B_KC> tt_status launch_layout6(core3::Params3 &p, int 
     return bf ? launch_cfg6<A_KC, B_KC, true, false>(p, s) : launch_cfg6<A_KC, B_KC, false, false>(p, s);
 }
 
-// short-K products with the left operand's panel held in registers (gemm_core5.h); two workgroups per CU
-template <int KT, bool NTS> __global__ __launch_bounds__(core5::kThreads5, KT <= 16 ? 2 : 1) void gemm_bf16_v5_kernel(const core5::Params5 p)
+// short-K products with the left operand's panel held in registers (gemm_core5.h); two workgroups per CU, one for KT = 32
+template <int KT, bool NTS, bool TAIL> __global__ __launch_bounds__(core5::kThreads5, KT <= 16 ? 2 : 1) void gemm_bf16_v5_kernel(const core5::Params5 p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem3[];
-    core5::run_panels<KT, NTS>(p, smem3);
+    core5::run_panels<KT, NTS, TAIL>(p, smem3);
 }
 
-template <int KT, bool NTS> tt_status launch_cfg5(core5::Params5 &p, hipStream_t s)
+template <int KT, bool NTS, bool TAIL> tt_status launch_tail5(core5::Params5 &p, hipStream_t s)
 {
-    auto kern = gemm_bf16_v5_kernel<KT, NTS>;
+    auto kern = gemm_bf16_v5_kernel<KT, NTS, TAIL>;
     constexpr size_t smem = core5::smem_bytes5<KT>();
     if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem) != TT_OK) return TT_EDEVICE;
     hipLaunchKernelGGL(kern, dim3((uint32_t)p.grid), dim3(core5::kThreads5), smem, s, p);
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+
+template <int KT> tt_status launch_cfg5(core5::Params5 &p, hipStream_t s)
+{
+    // (rows that begin inside a 64-byte piece: see mma::store_block)
+    if (p.ldc % 32 == 0) return p.K == KT * 16 ? launch_tail5<KT, true, false>(p, s) : launch_tail5<KT, true, true>(p, s);
+    return p.K == KT * 16 ? launch_tail5<KT, false, false>(p, s) : launch_tail5<KT, false, true>(p, s);
 }
 
 int cu_count()
@@ -149,12 +166,12 @@ template <bool A_KC, bool B_KC> tt_status launch_runs(core3::Params3 &p, int out
 
 } // namespace
 
-// C_s = A_s^T B_s, A_s stored K x M, B_s stored K x N, K = 128, 256 or 512, bf16 result with 16-byte rows.
+// C_s = A_s^T B_s, A_s stored K x M, B_s stored K x N, K up to 512, bf16 result with 16-byte rows.
 // TT_EUNSUPPORTED when the engine does not take the product.
 tt_status launch_gemm_v5(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int relu, void *stream)
 {
-    if ((K != 128 && K != 256 && K != 512) || N < core5::NT5 || N % core5::NT5 || M < 8 || M % 8 || count < 1 || count > 64)
+    if (K < 1 || K > 512 || N < 8 || N % 8 || M < 8 || M % 8 || count < 1 || count > 64)
         return TT_EUNSUPPORTED;
     if (lda % 8 || ldb % 8 || ldc % 8 || lda < M || ldb < N || ldc < N) return TT_EUNSUPPORTED; // 16-byte chunks and rows
     if (K * lda >= (int64_t(1) << 30) || K * ldb >= (int64_t(1) << 30)) return TT_EUNSUPPORTED; // 32-bit byte offsets
@@ -164,10 +181,10 @@ tt_status launch_gemm_v5(int count, const void *const *A, const void *const *B, 
         p.B[i] = i < count ? B[i] : nullptr;
         p.C[i] = i < count ? C[i] : nullptr;
     }
-    p.M = (int32_t)M; p.N = (int32_t)N;
+    p.M = (int32_t)M; p.N = (int32_t)N; p.K = (int32_t)K;
     p.lda = (int32_t)lda; p.ldb = (int32_t)ldb; p.ldc = (int32_t)ldc;
     p.panels = (int32_t)((M + core5::PM5 - 1) / core5::PM5);
-    p.ntiles = (int32_t)(N / core5::NT5);
+    p.ntiles = (int32_t)((N + core5::NT5 - 1) / core5::NT5);
     const int64_t total = (int64_t)count * p.panels * p.ntiles;
     if (total >= (int64_t(1) << 30)) return TT_EUNSUPPORTED;
     p.total = (int32_t)total;
@@ -175,10 +192,9 @@ tt_status launch_gemm_v5(int count, const void *const *A, const void *const *B, 
     p.grid = (int32_t)(total < resident ? total : resident);
     p.relu = relu;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const bool nts = tuning_int("TT_V5_NT", 1) != 0;
-    if (K == 512) return nts ? launch_cfg5<32, true>(p, s) : launch_cfg5<32, false>(p, s);
-    if (K == 256) return nts ? launch_cfg5<16, true>(p, s) : launch_cfg5<16, false>(p, s);
-    return nts ? launch_cfg5<8, true>(p, s) : launch_cfg5<8, false>(p, s);
+    if (K <= 64) return launch_cfg5<4>(p, s);
+    if (K <= 128) return launch_cfg5<8>(p, s);
+    return K <= 256 ? launch_cfg5<16>(p, s) : launch_cfg5<32>(p, s);
 }
 
 tt_status launch_gemm_v4(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
@@ -186,7 +202,7 @@ tt_status launch_gemm_v4(int count, const void *const *A, const void *const *B, 
                          bool vec, int ksplit, int64_t kchunk, void *stream)
 {
     core3::Params3 p;
-    const tt_status st = fill_params3(&p, core4::BM4, core4::BN4, core4::BK4, 0, count, A, B, C, M, N, K, lda, ldb, ldc, a_kc,
+    const tt_status st = fill_params3(&p, core4::BM4, core4::BN4, 1, 0, count, A, B, C, M, N, K, lda, ldb, ldc, a_kc,
                                       b_kc, relu, ksplit, kchunk);
     if (st != TT_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -196,13 +212,12 @@ tt_status launch_gemm_v4(int count, const void *const *A, const void *const *B, 
     return launch_layout4<false, true>(p, out_dtype, vec, s);
 }
 
-// K (and a K chunk) a multiple of 64
 tt_status launch_gemm_v6(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc, bool b_kc, int out_dtype, int relu, bool vec,
                          int ksplit, int64_t kchunk, void *stream)
 {
     core3::Params3 p;
-    const tt_status st = fill_params3(&p, core6::BM6, core6::BN6, core6::BK6, 0, count, A, B, C, M, N, K, lda, ldb, ldc, a_kc, b_kc,
+    const tt_status st = fill_params3(&p, core6::BM6, core6::BN6, 1, 0, count, A, B, C, M, N, K, lda, ldb, ldc, a_kc, b_kc,
                                       relu, ksplit, kchunk);
     if (st != TT_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);

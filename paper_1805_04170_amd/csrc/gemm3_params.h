@@ -9,7 +9,7 @@
 
 namespace tt {
 
-// tile_m x tile_n output tiles, K tiles of k_tile; cus: compute units to fill (persistent engine; 0: one workgroup per
+// tile_m x tile_n output tiles, K a multiple of k_tile (1: any); cus: compute units to fill (persistent engine; 0: one workgroup per
 // output tile).  Returns TT_EUNSUPPORTED when the engine does not take the product.
 inline tt_status fill_params3(core3::Params3 *p, int tile_m, int tile_n, int k_tile, int cus, int count, const void *const *A,
                               const void *const *B, void *const *C, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,

@@ -15,7 +15,7 @@
 //     transpose reads as in gemm_core2.h;
 //   - fragments, k-steps and write-out of gemm_mma.h, a K tile being one k-step.  8 x (256 x 4608 x 1024) A B^T, 288 tiles:
 //     32.9 -> 30.3 us (31.3 on gemm_core6.h); where tiles leave CUs empty gemm_core6.h is the faster one;
-//   - K must be a multiple of 32; a workgroup computes one tile and ends (the other resident workgroup and the next
+//   - the last K tile may be short; a workgroup computes one tile and ends (the other resident workgroup and the next
 //     one queued cover its start-up and wind-down).
 #pragma once
 #include <cstdint>
@@ -65,7 +65,15 @@ template <int ROWS, bool KC> __device__ __forceinline__ void chunk_offsets(int r
     }
 }
 
-template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED>
+// k of this thread's chunk i inside its tile
+template <int ROWS, bool KC> __device__ __forceinline__ int k_of(int i)
+{
+    if constexpr (KC) return (int)((threadIdx.x & 3) ^ (-(threadIdx.x >> 4) & 3)) * 8;
+    else return (int)threadIdx.x / (ROWS / 8) + kThreads4 / (ROWS / 8) * i;
+}
+
+// TAIL: klen is no multiple of 32, what is missing is read as zeros
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL = false>
 __device__ __forceinline__ void tile_product4(const char *abase, int lda, const char *bbase, int ldb, void *Cv, int ldc, int M,
                                               int N, int klen, int m0, int n0, bool relu, char *smem)
 {
@@ -80,14 +88,16 @@ __device__ __forceinline__ void tile_product4(const char *abase, int lda, const 
     chunk_offsets<BN4, B_KC>(n0, N, ldb, vob);
     const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024u;
     const uint64_t astep = A_KC ? BK4 * 2u : (uint64_t)BK4 * (uint64_t)lda * 2u, bstep = B_KC ? BK4 * 2u : (uint64_t)BK4 * (uint64_t)ldb * 2u;
-    const int nk = klen / BK4;
+    const int nk = (klen + BK4 - 1) / BK4, tail = klen - (nk - 1) * BK4; // K tiles, values of K in the last one
 
     // K tile to ask for next; past the end the last one is fetched again, so that the wait counts stay the same
     uint64_t ab = uniform64(abase), bb = uniform64(bbase);
     int left = nk - 1;
     auto issue_one = [&](int i, uint32_t stage) {
-        if (i < kLoadsA) dev::lds_dma16(voa[i], ab, stage + wave_lds + (uint32_t)i * (kThreads4 * 16u));
-        else dev::lds_dma16(vob[i - kLoadsA], bb, stage + kABytes + wave_lds + (uint32_t)(i - kLoadsA) * (kThreads4 * 16u));
+        const bool short_tile = TAIL && left <= 0;
+        if (i < kLoadsA) core2::chunk_or_zero(voa[i], ab, !short_tile || k_of<BM4, A_KC>(i) < tail, short_tile, stage + wave_lds + (uint32_t)i * (kThreads4 * 16u));
+        else core2::chunk_or_zero(vob[i - kLoadsA], bb, !short_tile || k_of<BN4, B_KC>(i - kLoadsA) < tail, short_tile,
+                                  stage + kABytes + wave_lds + (uint32_t)(i - kLoadsA) * (kThreads4 * 16u));
     };
     auto advance = [&]() {
         if (left > 0) {

@@ -1,5 +1,5 @@
 // Fifth bf16 MFMA engine: products with a SHORT contraction and a LARGE result, C_s = A_s^T B_s with A_s stored K x M and
-// B_s stored K x N (both with K as the slow dimension) and K = 128, 256 or 512.  These are the weight gradients
+// B_s stored K x N (both with K as the slow dimension) and K up to 512.  These are the weight gradients
 // dC/dW_l = x_l^T df(dC/dx_{l+1}) of Sec. 2.1 of arXiv 1805.04170 at a per-shard batch of 128 / 256: 2 K flops per result
 // element, so the product is bound by writing C, and the job of the kernel is to keep the chip writing.
 //
@@ -59,7 +59,7 @@ struct Params5 {
     const void *A[64]; // K x M row-major (A^T is the left operand)
     const void *B[64]; // K x N row-major
     void *C[64];       // M x N row-major, bf16
-    int32_t M, N;
+    int32_t M, N, K;
     int32_t lda, ldb, ldc;
     int32_t panels, ntiles; // per shard
     int32_t total;          // count * panels * ntiles
@@ -85,10 +85,11 @@ __device__ __forceinline__ bf16x8 read_frag_b5(const char *lds, int cbase, int k
 
 using core2::uniform64;
 
-// KT = K / 16 (8, 16 or 32).  NTS: non-temporal stores.  256 threads; smem: smem_bytes5<KT>() bytes, 16-byte aligned.
-template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Params5 &p, char *smem)
+// KT = K / 16, rounded up to 4, 8, 16 or 32.  TAIL: K is no multiple of 16 KT, what is missing is read as zeros.  NTS: non-temporal stores.  256 threads; smem: smem_bytes5<KT>() bytes, 16-byte aligned.
+template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panels(const Params5 &p, char *smem)
 {
-    static_assert(KT == 8 || KT == 16 || KT == 32, "K = 128, 256 or 512");
+    static_assert(NT5 == 64 && kStoresPerUnit5 == 8, "a wave's part of a unit");
+    static_assert(KT == 4 || KT == 8 || KT == 16 || KT == 32, "K up to 64, 128, 256 or 512");
     constexpr int STB = stage_bytes5<KT>();
     constexpr int NLB = KT / 2; // B loads per thread and unit: k-rows tid / 8 + 32 i
     constexpr int ACH = KT * 8; // k-rows per A staging step (half of K): fills both stages
@@ -98,7 +99,7 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm0 = (int)wave * 64;
     const uint32_t lds0 = dev::lds_addr(smem);
-    const int M = p.M, ldc = p.ldc;
+    const int M = p.M, N = p.N, K = p.K, ldc = p.ldc;
 
     // contiguous run of units; workgroup numbers go round-robin over the XCDs, so give every XCD a contiguous range
     const uint32_t bid = blockIdx.x, grid = (uint32_t)p.grid;
@@ -108,7 +109,8 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
 
     // lane parts of the load addresses
     const uint32_t bkl = (uint32_t)tid >> 3, bpc = (uint32_t)tid & 7u;
-    const uint32_t voff_b = bkl * (uint32_t)p.ldb * 2u + ((bpc ^ (((bkl >> 1) & 1u) << 1)) << 4);
+    const uint32_t voff_b = bkl * (uint32_t)p.ldb * 2u;
+    const int b_col = (int)(bpc ^ (((bkl >> 1) & 1u) << 1)) * 8;
     const uint32_t akl = (uint32_t)tid >> 5, apc = (uint32_t)tid & 31u;
     const int a_chunk = (int)(apc ^ ((akl & 3u) << 1));
 
@@ -153,7 +155,8 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
 #pragma unroll
                 for (int i = 0; i < NLA; ++i) {
                     const uint64_t sb = uniform64(abase + (size_t)(c * ACH + 8 * i) * (size_t)p.lda * 2);
-                    dev::lds_dma16(voff_a, sb, lds0 + (wave * 64u + (uint32_t)i * kThreads5) * 16u);
+                    const int k = c * ACH + 8 * i;
+                    core2::chunk_or_zero(voff_a, sb, !TAIL || k + (int)akl < K, TAIL && k + 8 > K, lds0 + (wave * 64u + (uint32_t)i * kThreads5) * 16u);
                 }
                 __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(0));
                 __syncthreads();
@@ -167,21 +170,23 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
 
         const char *bbase = reinterpret_cast<const char *>(p.B[shard]);
         auto issue_b = [&](int nt, int stage) {
+            int col = nt * NT5 + b_col;
+            col = col < N ? col : N - 8; // columns past N are never stored
 #pragma unroll
             for (int i = 0; i < NLB; ++i) {
-                const uint64_t sb = uniform64(bbase + (size_t)nt * (NT5 * 2) + (size_t)(32 * i) * (size_t)p.ldb * 2);
-                dev::lds_dma16(voff_b, sb, lds0 + (uint32_t)stage * STB + (wave * 64u + (uint32_t)i * kThreads5) * 16u);
+                const uint64_t sb = uniform64(bbase + (size_t)(32 * i) * (size_t)p.ldb * 2);
+                core2::chunk_or_zero(voff_b + (uint32_t)col * 2u, sb, !TAIL || 32 * i + (int)bkl < K, TAIL && 32 * (i + 1) > K,
+                                     lds0 + (uint32_t)stage * STB + (wave * 64u + (uint32_t)i * kThreads5) * 16u);
             }
         };
         issue_b(nt0, 0);
         int cs = 0;
-        // rows m0 + wm0 .. + 63 of this wave all inside C: its stores are unconditional and their number is fixed
-        const bool full = __builtin_amdgcn_readfirstlane((int)(m0 + wm0 + 64 <= M)) != 0;
+        bool behind = false; // the previous unit's stores are all that may be outstanding besides this unit's loads
         uint16_t *Cs = reinterpret_cast<uint16_t *>(p.C[shard]);
 
         for (int q = 0; q < run; ++q) {
             // my chunks of this unit's B tile have landed: everything but the previous unit's stores is complete
-            if (q > 0 && full) __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(S));
+            if (behind) __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(S));
             else __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(0));
             __syncthreads(); // everyone's have; everyone has finished reading the other stage
             if (q + 1 < run) issue_b(nt0 + q + 1, cs ^ 1);
@@ -216,6 +221,10 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
             // ---- epilogue: 32 rows of the wave's 64 at a time through its strip, then out as 16-byte pieces of whole
             // 128-byte rows (8 lanes per row, 8 rows per store instruction)
             const int n0 = (nt0 + q) * NT5;
+            // everything this wave stores lies inside C: its stores are unconditional and their number is fixed
+            const int rows_in = M - m0 - wm0, cols_in = N - n0;
+            const bool whole = __builtin_amdgcn_readfirstlane((rows_in < cols_in ? rows_in : cols_in) >= NT5 ? 1 : 0) != 0;
+            behind = whole;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
 #pragma unroll
@@ -237,8 +246,8 @@ template <int KT, bool NTS> __device__ __forceinline__ void run_panels(const Par
                     const int row0 = m0 + wm0 + i * 32 + 8 * v; // wave-uniform: first of the 8 rows this instruction stores
                     const u32x4 o = t[v];
                     char *dst = reinterpret_cast<char *>(Cs) + ((size_t)row0 * ldc + n0) * 2 + st_off;
-                    if (full) dev::store16<NTS>(dst, o);
-                    else if (row0 + (lane >> 3) < M) dev::store16<NTS>(dst, o);
+                    if (whole) dev::store16<NTS>(dst, o);
+                    else if (row0 + (lane >> 3) < M && n0 + (lane & 7) * 8 < N) dev::store16<NTS>(dst, o); // (N: a multiple of 8)
                 }
                 __builtin_amdgcn_wave_barrier();
             }

@@ -11,7 +11,7 @@
 //     one and six of the other, each loaded by two waves of their own, 87 us instead of 68 where the weights come from HBM,
 //     and three and four the same 68;
 //   - at most 256 registers per lane: given 512, the compiler moves accumulators between the two halves of the file (75 us);
-//   - LDS layouts of gemm_core2.h; K must be a multiple of 64.
+//   - LDS layouts of gemm_core2.h; the last K tile may be short.
 // 8 x (256 x 3136 x 4096) A B^T, weights in the memory-side cache 64.1 -> 48.4 us, from HBM 71 -> 68 (3.0 TB/s of weights);
 // 8 x (256 x 4096 x 3136) A B 58 -> 50, from HBM 72 -> 60 (gemm_core4.h before it also ran on gemm_mma.h).
 #pragma once
@@ -64,10 +64,17 @@ template <int ROWS, bool KC> __device__ __forceinline__ void chunk_offsets6(int 
     }
 }
 
-// C tile (m0, n0) of C = A B over K = klen (a multiple of 64) starting at the operands' k = 0 as given by abase / bbase;
+// k of this thread's chunk i inside its tile
+template <int ROWS, bool KC> __device__ __forceinline__ int k_of(int i)
+{
+    if constexpr (KC) return (int)((threadIdx.x & 7) ^ ((threadIdx.x >> 4) & 7)) * 8;
+    else return (int)threadIdx.x / (ROWS / 8) + kThreads6 / (ROWS / 8) * i;
+}
+
+// C tile (m0, n0) of C = A B over K = klen (TAIL: no multiple of 64, what is missing is read as zeros) starting at the operands' k = 0 as given by abase / bbase;
 // A is M x K with pitch lda (A_KC) or K x M, B is N x K with pitch ldb (B_KC) or K x N (rows contiguous: fragments through
 // LDS transpose reads).  256 threads; smem: kSmem6 bytes, 16-byte aligned.  STAGED: rows of C take 16-byte stores.
-template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED>
+template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL>
 __device__ __forceinline__ void tile_product6(const char *abase, int lda, const char *bbase, int ldb, void *Cv, int ldc, int M,
                                               int N, int klen, int m0, int n0, bool relu, char *smem)
 {
@@ -83,14 +90,16 @@ __device__ __forceinline__ void tile_product6(const char *abase, int lda, const 
     const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 1024u;
     const uint64_t astep = A_KC ? (uint64_t)BK6 * 2 : (uint64_t)BK6 * (uint64_t)lda * 2;
     const uint64_t bstep = B_KC ? (uint64_t)BK6 * 2 : (uint64_t)BK6 * (uint64_t)ldb * 2;
-    const int nk = klen / BK6;
+    const int nk = (klen + BK6 - 1) / BK6, tail = klen - (nk - 1) * BK6; // K tiles, values of K in the last one
 
     // K tile to ask for next; past the end the last one is fetched again, so that the wait counts stay the same
     uint64_t ab = core2::uniform64(abase), bb = core2::uniform64(bbase);
     int left = nk - 1;
     auto issue_one = [&](int i, uint32_t stage) {
-        if (i < kLoadsA6) dev::lds_dma16(voa[i], ab, stage + wave_lds + (uint32_t)i * (kThreads6 * 16u));
-        else dev::lds_dma16(vob[i - kLoadsA6], bb, stage + kABytes6 + wave_lds + (uint32_t)(i - kLoadsA6) * (kThreads6 * 16u));
+        const bool short_tile = TAIL && left <= 0;
+        if (i < kLoadsA6) core2::chunk_or_zero(voa[i], ab, !short_tile || k_of<BM6, A_KC>(i) < tail, short_tile, stage + wave_lds + (uint32_t)i * (kThreads6 * 16u));
+        else core2::chunk_or_zero(vob[i - kLoadsA6], bb, !short_tile || k_of<BN6, B_KC>(i - kLoadsA6) < tail, short_tile,
+                                  stage + kABytes6 + wave_lds + (uint32_t)(i - kLoadsA6) * (kThreads6 * 16u));
     };
     auto advance = [&]() {
         if (left > 0) {

@@ -85,6 +85,7 @@ __device__ __forceinline__ void k_step(f32x4 (&acc)[TM][TN], const Frags<TM, TN>
                                        const char *At, const char *Bt, int ks, Issue &&issue)
 {
     constexpr int MM = TM * TN, SL = MM / 2, RD = TM + TN;
+    static_assert(MM % 2 == 0 && SL >= 2, "slots");
     constexpr int RS = RA::kc && RB::kc ? SL / 2 : SL * 3 / 4;
     constexpr int L0 = SPREAD ? 0 : SL / 2, LS = SL - L0;
     int mm = 0, rd = 0, ld = 0;
@@ -122,8 +123,8 @@ template <int TM, int TN> __device__ __forceinline__ void clear(f32x4 (&acc)[TM]
 // at a time are turned round and leave as 16-byte vectors of whole row segments (VEC), or, where C's rows do not take
 // those, element by element with the lanes of a wave side by side.
 constexpr int kStripBytes = 16 * (64 + 8) * 2; // per wave
-template <bool OUT_BF16, bool VEC, int TM, int TN>
-__device__ __forceinline__ void store_block(const f32x4 (&acc)[TM][TN], char *strip, void *Cv, int ldc, int row0, int col0, int M, int N,
+template <bool OUT_BF16, bool VEC, bool NTS, int TM, int TN>
+__device__ __forceinline__ void store_block_as(const f32x4 (&acc)[TM][TN], char *strip, void *Cv, int ldc, int row0, int col0, int M, int N,
                                             bool relu, int lane)
 {
     constexpr int E = OUT_BF16 ? 2 : 4, JW = OUT_BF16 ? (TN < 4 ? TN : 4) : (TN < 2 ? TN : 2); // blocks side by side
@@ -158,7 +159,7 @@ __device__ __forceinline__ void store_block(const f32x4 (&acc)[TM][TN], char *st
                     const int row = row0 + i * 16 + lrow, col = col0 + jb * 16 + vc * EPV;
                     const u32x4 o = *reinterpret_cast<const u32x4 *>(strip + lrow * PITCH + vc * 16);
                     if (row < M && col < N) // N is a multiple of the vector's length here: a vector is all in or all out
-                        __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(Cv) + ((size_t)row * ldc + col) * E));
+                        dev::store16<NTS>(reinterpret_cast<char *>(Cv) + ((size_t)row * ldc + col) * E, o);
                 }
             } else {
                 constexpr int RPI = 64 / W; // rows per store
@@ -175,6 +176,17 @@ __device__ __forceinline__ void store_block(const f32x4 (&acc)[TM][TN], char *st
             }
             __builtin_amdgcn_wave_barrier();
         }
+}
+
+// Non-temporal stores (fp32 partial sums of 16 x (512 x 2048 x 2048) 61 us, plain ones 66), except into rows that begin inside a
+// 64-byte piece of memory: parts of such a piece leave with different stores, and non-temporal ones are not put together again
+// (9072 x 11856 of K = 40 on gemm_core5.h 129 -> 86 us with plain ones, rows of 64-byte pieces 37.6 / 41.9 at 6936 x 7456).
+template <bool OUT_BF16, bool VEC, int TM, int TN>
+__device__ __forceinline__ void store_block(const f32x4 (&acc)[TM][TN], char *strip, void *Cv, int ldc, int row0, int col0, int M, int N,
+                                            bool relu, int lane)
+{
+    if (!VEC || ldc % (OUT_BF16 ? 32 : 16) == 0) store_block_as<OUT_BF16, VEC, true>(acc, strip, Cv, ldc, row0, col0, M, N, relu, lane);
+    else store_block_as<OUT_BF16, VEC, false>(acc, strip, Cv, ldc, row0, col0, M, N, relu, lane);
 }
 
 } // namespace mma

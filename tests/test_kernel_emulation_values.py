@@ -104,6 +104,23 @@ def test_line_wide_k_tiles_engine_values(lockstep_gemm, tmp_path, out_dt, tb):
         check(lockstep_gemm, str(tmp_path), 2, 256, 136, 320, 0, tb, "bf16", "f32", False, 51, ksplit=2, env=env)   # chunks of 192 and 128
 
 
+@pytest.mark.parametrize("ta,tb", LAYOUTS)
+@pytest.mark.parametrize("engine", ["4", "6"])
+def test_short_last_k_tile_values(lockstep_gemm, tmp_path, engine, ta, tb):
+    # K ends in the first tile, after 8 of 32 or of 64 values, in the middle of a tile
+    for i, K in enumerate((8, 72, 104) + ((37,) if ta and not tb else ())):
+        check(lockstep_gemm, str(tmp_path), 1, 264, 264, K, ta, tb, "bf16", "bf16" if i % 2 else "f32", bool(i % 2), 55 + i, env={"TT_GEMM_ENGINE": engine})
+
+
+@pytest.mark.parametrize("K", [1, 40, 64, 72, 219, 300])
+def test_panel_in_registers_engine_values_at_other_k_and_widths(lockstep_gemm, tmp_path, K):
+    # K inside the next of 64, 128, 256, 512; the last unit 8 columns wide (rows of 16-byte pieces), or whole
+    env = {"EMU_CUS": "1", "TT_GEMM_ENGINE": "5"}
+    out = check(lockstep_gemm, str(tmp_path), 1, 264, 136, K, 1, 0, "bf16", "bf16", True, 90, env=env)
+    assert int(out.split()[3]) == (1 if K > 256 else 2) * 256
+    check(lockstep_gemm, str(tmp_path), 1, 256, 192, K, 1, 0, "bf16", "bf16", False, 91, env=env)
+
+
 def test_line_wide_k_tiles_engine_as_the_library_chooses_it(lockstep_gemm, tmp_path):
     # a skinny data-gradient shaped product (one row of tiles, 128 of them for 256 CUs, K of four tiles): no switch set
     check(lockstep_gemm, str(tmp_path), 32, 256, 392, 256, 0, 1, "bf16", "bf16", False, 52)
