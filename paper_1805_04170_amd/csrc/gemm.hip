@@ -141,6 +141,48 @@ template <bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_v2(Gem
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
 
+// BM x 128 tiles straight into LDS, four waves, three stages of 64 (72 KB for 64 rows: two workgroups per CU)
+constexpr int kRowsStages = 3;
+template <int BM, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC>
+__global__ __launch_bounds__(core::kThreads, 2) void gemm_bf16_rows_kernel(const GemmParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem2[];
+    const int logical = core::logical_block(p.per_xcd, p.total);
+    if (logical < 0) return;
+    const int tiles = p.tiles_m * p.tiles_n;
+    const int vshard = logical / tiles;
+    const int t = logical - vshard * tiles;
+    int tm, tn;
+    core::grouped_tile(t, p.tiles_m, p.tiles_n, &tm, &tn);
+    const int shard = vshard / p.ksplit;
+    const int kbeg = (vshard - shard * p.ksplit) * p.kchunk;
+    const int klen = p.K - kbeg < p.kchunk ? p.K - kbeg : p.kchunk;
+    using LA = std::conditional_t<A_KC, core2::DenseKCT<core::kThreads>, core2::DenseRCT<core::kThreads>>;
+    using LB = std::conditional_t<B_KC, core2::DenseKCT<core::kThreads>, core2::DenseRCT<core::kThreads>>;
+    LA la;
+    la.base = reinterpret_cast<const char *>(p.A[shard]) + (size_t)kbeg * (A_KC ? 2 : 2 * (size_t)p.lda);
+    la.ld = p.lda; la.rows = p.M; la.K = klen;
+    LB lb;
+    lb.base = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
+    lb.ld = p.ldb; lb.rows = p.N; lb.K = klen;
+    core2::tile_product<OUT_BF16, VEC, BM, 128, 2, 2, kRowsStages>(la, lb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * BM, tn * 128, p.relu != 0, smem2);
+}
+
+template <int BM, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_rows_cfg(GemmParams &p, int count, hipStream_t s)
+{
+    auto kern = gemm_bf16_rows_kernel<BM, A_KC, B_KC, OUT_BF16, VEC>;
+    constexpr size_t smem = (size_t)kRowsStages * (BM + 128) * core::BK * 2;
+    if (ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem) != TT_OK) return TT_EDEVICE;
+    p.tiles_m = (p.M + BM - 1) / BM;
+    p.tiles_n = (p.N + 127) / 128;
+    const int64_t total = (int64_t)p.tiles_m * p.tiles_n * count * p.ksplit;
+    if (total >= (int64_t(1) << 30)) return TT_EUNSUPPORTED;
+    p.total = (int32_t)total;
+    p.per_xcd = (int32_t)((total + kXcds - 1) / kXcds);
+    hipLaunchKernelGGL(kern, dim3((uint32_t)p.per_xcd * kXcds), dim3(core::kThreads), smem, s, p);
+    return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
+}
+
 template <int BM, int BN, int WM, int WN, int DEPTH, bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC>
 tt_status launch_mfma_cfg(GemmParams &p, int count, hipStream_t s)
 {
@@ -188,6 +230,21 @@ bool two_tiles_ahead(int64_t M, int64_t N, int64_t K, int64_t outs, bool a_kc)
     return !a_kc && (M % 128 == 0 || (tiles_n * 128 - N) * 16 <= N || K >= 768);
 }
 
+// Products with at most 128 rows whose tiles go straight into LDS, and their rows per tile (0: through registers).  What these
+// products wait for is memory: two K tiles on their way without a register hop, and, for 65 to 128 rows, twice as many
+// workgroups on half the rows each while two of them per CU hold all tiles.  Through registers / so, two shards, us:
+// 128 x 1024 A B^T K 512 9.3 / 8.0, 1024 14.2 / 11.5, 2048 23.7 / 18.9, x 16384 (512 tiles) 11.3 / 10.8, 18.6 / 20.1, 38.0 / 42.1;
+// A B the same (2048: 26.5 / 21.6); 8 x (72 x 1176 x 4640) A B^T 97 / 43.  Fewer rows: A B of long K only: 32 x 1024 K 512 7.2 /
+// 7.9, 1024 11.9 / 11.4, 2048 20.2 / 19.3, x 16384 14.6 / 13.5, 29.5 / 24.3 (32 rows); 48 x 1024 K 1024 12.0 / 12.9, 2048 22.6 / 21.5, x 16384
+// 31.0 / 24.5 (64 rows); A B^T 32 x 1024 K 2048 14.8 / 15.4.
+int rows_into_lds(int64_t M, int64_t N, int64_t K, int64_t outs, bool b_kc)
+{
+    if (M > 128) return 0;
+    if (M > 64) return K >= 384 && (N + 127) / 128 * 2 * outs < 512 ? 64 : 0;
+    if (b_kc) return 0;
+    return M > 32 ? (K >= 2048 ? 64 : 0) : (K >= 1024 ? 32 : 0);
+}
+
 template <bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_mfma_tile(GemmParams &p, int count, hipStream_t s)
 {
     const int tile = pick_tile(p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, count * p.ksplit);
@@ -216,6 +273,12 @@ template <bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_mfma_k
     // Where the eight-wave 256 x 256 tile is chosen, the engine that loads tiles straight into LDS is the faster one (through
     // registers / into LDS, us: A B 2048 x 8200 x 4104 260 / 210, 4 x (1000 x 4000 x 1000) 42 / 35)
     const int tile = pick_tile(p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, count * p.ksplit);
+    if constexpr (A_KC) {
+        const int rows = tuning_int("TT_GEMM_TILE", -1) < 0 ? rows_into_lds(p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, count * p.ksplit, B_KC) : 0;
+        if constexpr (!B_KC)
+            if (rows == 32) return launch_rows_cfg<32, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
+        if (rows == 64) return launch_rows_cfg<64, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
+    }
     if ((tile == 8 || (tile == 5 && tuning_int("TT_GEMM_TILE", -1) < 0)) && p.M >= 8 && p.N >= 8)
         return launch_v2<A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     return p.K % core::BK ? launch_mfma_tile<true, A_KC, B_KC, OUT_BF16, VEC>(p, count, s)

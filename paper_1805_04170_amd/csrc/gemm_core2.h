@@ -131,6 +131,7 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, 
     constexpr bool UNEVEN = BM * 8 % NT != 0; // a wave may have a chunk less than NL in a tile
     static_assert(!UNEVEN || NS == 2, "counted waits");
     constexpr bool SPREAD = (!LA::KC && !LB::KC) || NS > 2;
+    constexpr bool PLAIN_STEP = BM == 64 && NT == 512;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (wave / WN) * (TM * 16), wn0 = (wave % WN) * (TN * 16);
     const uint32_t lds0 = dev::lds_addr(smem);
@@ -145,15 +146,6 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, 
             lb.template next<BN>();
         }
     };
-    la.template begin<BM>(m0);
-    lb.template begin<BN>(n0);
-#pragma unroll
-    for (int st = 0; st < NS; ++st) {
-        if (st > 0) next(st < nk);
-#pragma unroll
-        for (int i = 0; i < NL; ++i) issue(i, lds0 + (uint32_t)st * STAGE);
-    }
-
     mma::Reader<BM, LA::KC, TM> ra;
     mma::Reader<BN, LB::KC, TN> rb;
     ra.init(wm0, lane);
@@ -161,22 +153,54 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, 
     mma::Frags<TM, TN> f0, f1;
     core::f32x4 acc[TM][TN];
     mma::clear(acc);
-    __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm((NS - 1) * NL - UNEVEN)); // this wave's chunks of the first tiles have landed
-    __syncthreads();                                                     // everyone's have
-    mma::read_frags(f0, ra, rb, smem, smem + A_BYTES, 0);
+    la.template begin<BM>(m0);
+    lb.template begin<BN>(n0);
+    if constexpr (PLAIN_STEP) {
+        // four waves per SIMD cover each other's reads: a tile's fragments when it has landed, the next tile on its way meanwhile
+#pragma unroll
+        for (int i = 0; i < NL; ++i) issue(i, lds0);
+        for (int kt = 0; kt < nk; ++kt) {
+            __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm(0)); // this wave's chunks of the tile have landed
+            __syncthreads();                                // everyone's have; everyone is done reading the other stage
+            if (kt + 1 < nk) {
+                next(true);
+#pragma unroll
+                for (int i = 0; i < NL; ++i) issue(i, lds0 + (uint32_t)((kt & 1) ^ 1) * STAGE);
+            }
+            const char *At = smem + (kt & 1) * STAGE;
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_iglp_opt(1);
+            mma::read_frags(f0, ra, rb, At, At + A_BYTES, 0);
+            mma::read_frags(f1, ra, rb, At, At + A_BYTES, 1);
+            mma::multiply(acc, f0);
+            mma::multiply(acc, f1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            if (st > 0) next(st < nk);
+#pragma unroll
+            for (int i = 0; i < NL; ++i) issue(i, lds0 + (uint32_t)st * STAGE);
+        }
 
-    int cs = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-        const char *At = smem + cs * STAGE;
-        mma::k_step<0, SPREAD>(acc, f0, f1, ra, rb, At, At + A_BYTES, 1, [](int) {});
-        // this wave has read the tile and its chunks of the next one have landed; then everyone's
-        __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm_lds((NS - 2) * NL));
-        __syncthreads();
-        next(kt + NS < nk);
-        const uint32_t lds_free = lds0 + (uint32_t)cs * STAGE;
-        cs = cs + 1 == NS ? 0 : cs + 1;
-        const char *nA = smem + cs * STAGE;
-        mma::k_step<NL, SPREAD>(acc, f1, f0, ra, rb, nA, nA + A_BYTES, 0, [&](int i) { issue(i, lds_free); });
+        __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm((NS - 1) * NL - UNEVEN)); // this wave's chunks of the first tiles have landed
+        __syncthreads();                                                     // everyone's have
+        mma::read_frags(f0, ra, rb, smem, smem + A_BYTES, 0);
+
+        int cs = 0;
+        for (int kt = 0; kt < nk; ++kt) {
+            const char *At = smem + cs * STAGE;
+            mma::k_step<0, SPREAD>(acc, f0, f1, ra, rb, At, At + A_BYTES, 1, [](int) {});
+            // this wave has read the tile and its chunks of the next one have landed; then everyone's
+            __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm_lds((NS - 2) * NL));
+            __syncthreads();
+            next(kt + NS < nk);
+            const uint32_t lds_free = lds0 + (uint32_t)cs * STAGE;
+            cs = cs + 1 == NS ? 0 : cs + 1;
+            const char *nA = smem + cs * STAGE;
+            mma::k_step<NL, SPREAD>(acc, f1, f0, ra, rb, nA, nA + A_BYTES, 0, [&](int i) { issue(i, lds_free); });
+        }
     }
     // the re-fetches have landed and all fragment reads are done before the stages are reused
     __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm_lds(0));

@@ -109,6 +109,17 @@ __device__ __forceinline__ void k_step(f32x4 (&acc)[TM][TN], const Frags<TM, TN>
     }
 }
 
+template <int TM, int TN> __device__ __forceinline__ void multiply(f32x4 (&acc)[TM][TN], const Frags<TM, TN> &f)
+{
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int jj = 0; jj < TN; ++jj) {
+            const int j = i & 1 ? TN - 1 - jj : jj;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
+        }
+}
+
 template <int TM, int TN> __device__ __forceinline__ void clear(f32x4 (&acc)[TM][TN])
 {
 #pragma unroll

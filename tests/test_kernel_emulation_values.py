@@ -112,6 +112,13 @@ def test_short_last_k_tile_values(lockstep_gemm, tmp_path, engine, ta, tb):
         check(lockstep_gemm, str(tmp_path), 1, 264, 264, K, ta, tb, "bf16", "bf16" if i % 2 else "f32", bool(i % 2), 55 + i, env={"TT_GEMM_ENGINE": engine})
 
 
+@pytest.mark.parametrize("M,K,tb", [(65, 384, 1), (128, 392, 0), (100, 520, 1), (33, 2048, 0), (64, 2056, 0), (1, 1032, 0), (32, 1024, 0)])
+def test_few_rows_straight_into_lds_values(lockstep_gemm, tmp_path, M, K, tb):
+    # 64- and 32-row tiles, full and short ones, K tails; 136 columns: the second tile with 8
+    out = check(lockstep_gemm, str(tmp_path), 1, M, 136, K, 0, tb, "bf16", "f32" if M % 2 else "bf16", bool(M % 2), 95)
+    assert int(out.split()[3]) == 8 * 256      # two or four tiles, a multiple of eight workgroups
+
+
 @pytest.mark.parametrize("K", [1, 40, 64, 72, 219, 300])
 def test_panel_in_registers_engine_values_at_other_k_and_widths(lockstep_gemm, tmp_path, K):
     # K inside the next of 64, 128, 256, 512; the last unit 8 columns wide (rows of 16-byte pieces), or whole
