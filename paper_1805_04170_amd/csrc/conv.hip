@@ -51,8 +51,8 @@ __device__ __forceinline__ u32x4 load16(const char *base, int32_t elem_off)
     return *reinterpret_cast<const u32x4 *>(base + (ptrdiff_t)elem_off * 2);
 }
 
-// A operand of forward and dgrad: rows are output pixels (n, oy, ox), k = (tap, channel) with the channel contiguous.
-// in_y = oy + off + sgn * r, in_x = ox + off + sgn * s   (forward: off = -pad, sgn = +1; dgrad: off = +pad, sgn = -1)
+// A operand of dgrad through registers: rows are input pixels (n, oy, ox), k = (tap, channel) with the channel contiguous.
+// in_y = oy + off + sgn * r, in_x = ox + off + sgn * s   (off = +pad, sgn = -1)
 template <int SLOTS, bool ONE_TAP> struct GatherKC {
     static constexpr bool KC = true;
     static constexpr bool kFence = false;
@@ -173,58 +173,37 @@ template <int BM, int BN> __device__ __forceinline__ bool tile_of(const ConvPara
     return true;
 }
 
-// OP 0: forward, 1: dgrad
-template <int BM, int BN, int WN, int DEPTH, bool KMASK, int OP, bool OUT_BF16, bool ONE_TAP, int WM = 2>
-__global__ __launch_bounds__(WM * WN * 64, WM * WN / 4) void conv_gather_a_kernel(const ConvParams p)
+template <int BM, int BN, int WN, int DEPTH, bool KMASK, bool OUT_BF16, bool ONE_TAP>
+__global__ __launch_bounds__(WN * 128, WN / 2) void conv_gather_a_kernel(const ConvParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     TileId t;
     if (!tile_of<BM, BN>(p, &t)) return;
     const ConvGeom &g = p.g;
-    constexpr int NT = WM * WN * 64;
+    constexpr int NT = WN * 128;
     GatherKC<core::Slots<BM, true, NT>::value, ONE_TAP> la;
     la.base = reinterpret_cast<const char *>(p.A[t.shard]);
     la.R = g.R; la.S = g.S;
     la.rows = p.M; la.K = p.K;
-    if (OP == 0) { la.IH = g.H; la.IW = g.W; la.OH = g.P; la.OW = g.Q; la.off = -g.pad; la.sgn = 1; la.Ch = g.Cs; }
-    else         { la.IH = g.P; la.IW = g.Q; la.OH = g.H; la.OW = g.W; la.off = g.pad;  la.sgn = -1; la.Ch = g.Ks; }
-    if constexpr (OP == 0) {
-        core::DenseKC<core::Slots<BN, true, NT>::value> lb;
-        lb.base = reinterpret_cast<const char *>(p.B[t.shard * p.members]);
-        lb.ld = p.K; lb.rows = p.N; lb.K = p.K;
-        // every wave owns 64 columns of the tile, which lie in one member's block: the wave writes through that member's
-        // pointer, moved back by the block's first column so that the tile's own column numbers address it
-        static_assert(BN / WN == 64, "a wave's columns lie in one member block");
-        void *Cw = p.C[t.shard];
-        int ldc = p.ldc;
-        if (p.members > 1) {
-            const int col0 = t.n0 + ((threadIdx.x >> 6) % WN) * 64;
-            int m = col0 / p.member_cols;
-            m = m < p.members ? m : p.members - 1; // columns past N are never stored
-            Cw = reinterpret_cast<char *>(p.C[t.shard * p.members + m]) - (ptrdiff_t)m * p.member_cols * (OUT_BF16 ? 2 : 4);
-            ldc = p.member_cols;
-        }
-        core::tile_product<BM, BN, WM, WN, DEPTH, KMASK, OUT_BF16, true>(la, lb, Cw, ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, smem);
-    } else {
-        FilterRC<core::Slots<BN, false, NT>::value> lb;
-        lb.base = reinterpret_cast<const char *>(p.B[t.shard]);
-        lb.RS = g.R * g.S; lb.Cs = g.Cs; lb.Ks = g.Ks; lb.rows = p.N; lb.K = p.K;
-        core::tile_product<BM, BN, WM, WN, DEPTH, KMASK, OUT_BF16, true>(la, lb, p.C[t.shard], p.ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, smem);
-    }
+    la.IH = g.P; la.IW = g.Q; la.OH = g.H; la.OW = g.W; la.off = g.pad; la.sgn = -1; la.Ch = g.Ks;
+    FilterRC<core::Slots<BN, false, NT>::value> lb;
+    lb.base = reinterpret_cast<const char *>(p.B[t.shard]);
+    lb.RS = g.R * g.S; lb.Cs = g.Cs; lb.Ks = g.Ks; lb.rows = p.N; lb.K = p.K;
+    core::tile_product<BM, BN, 2, WN, DEPTH, KMASK, OUT_BF16, true>(la, lb, p.C[t.shard], p.ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, smem);
 }
 
 // The gathered operand of a forward product for the engine that loads tiles straight into LDS (gemm_core2.h).  A thread's
 // chunks of a tile differ in the row only, so the tap and the channel they read are one pair per thread and tile, moved on
 // by 64 values of K from tile to tile; rows whose tap lies outside the image, and K past the end, read a chunk of zeros.
-struct GatherKC2 {
+template <int NT> struct GatherKC2 {
     static constexpr bool KC = true;
     const char *base;
     ConvGeom g;
     int M, K;
     int kc, dtap, dc;     // this lane's k inside a K tile; 64 values of K as taps and channels
     int k, tap, c;        // of this lane's chunks of the current K tile
-    int32_t pix[4];       // element offset of the source pixel at tap 0, may be negative
-    uint32_t inside[4];   // bit t: tap t reads inside the image
+    int32_t pix[8];       // element offset of the source pixel at tap 0, may be negative
+    uint32_t inside[8];   // bit t: tap t reads inside the image
     int32_t delta;        // of the current tile: what its tap and channel add to pix
     uint32_t bit;         // ... its tap's bit, 0 past the end of K
     __device__ __forceinline__ void locate()
@@ -243,8 +222,8 @@ struct GatherKC2 {
         c = kc - tap * g.Cs;
         k = 0;
 #pragma unroll
-        for (int i = 0; i < core2::loads2<ROWS>(); ++i) {
-            int row = row0 + (tid >> 3) + 64 * i;
+        for (int i = 0; i < core2::loads2<ROWS, NT>(); ++i) {
+            int row = row0 + (tid >> 3) + NT / 8 * i;
             row = row < M ? row : M - 1; // rows past the end only feed C rows that are never stored
             const int n = row / (g.P * g.Q), rem = row - n * (g.P * g.Q);
             const int y = rem / g.Q - g.pad, x = rem - (rem / g.Q) * g.Q - g.pad;
@@ -268,19 +247,21 @@ struct GatherKC2 {
     }
     template <int ROWS> __device__ __forceinline__ void issue(int i, uint32_t lds) const
     {
-        if (!core2::mine2<ROWS>(i)) return;
+        if (!core2::mine2<ROWS, NT>(i)) return;
         const char *a = base + (ptrdiff_t)(pix[i] + delta) * 2;
-        dev::lds_dma16(inside[i] & bit ? (const void *)a : (const void *)core2::g_zero_chunk, core2::chunk_lds2(lds, i));
+        dev::lds_dma16(inside[i] & bit ? (const void *)a : (const void *)core2::g_zero_chunk, core2::chunk_lds2<NT>(lds, i));
     }
 };
 
-// Forward products on BM x 256 tiles of that engine (a wave owns 64 columns, so a member's block holds all of them: see above).
+// Forward products on BM x 256 tiles of that engine.  Every wave owns 64 columns of the tile, which lie in one member's block: the
+// wave writes through that member's pointer, moved back by the block's first column so that the tile's own column numbers
+// address it.
 template <int BM, bool OUT_BF16> __global__ __launch_bounds__(core2::kThreads2, 2) void conv_gather_a2_kernel(const ConvParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     TileId t;
     if (!tile_of<BM, 256>(p, &t)) return;
-    GatherKC2 la;
+    GatherKC2<core2::kThreads2> la;
     la.base = reinterpret_cast<const char *>(p.A[t.shard]);
     la.g = p.g; la.M = p.M; la.K = p.K;
     core2::DenseKC2 lb;
@@ -313,6 +294,31 @@ __global__ __launch_bounds__(WN * 128, WN / 2) void conv_wgrad_kernel(const Conv
     lb.base = reinterpret_cast<const char *>(p.B[t.shard]);
     lb.H = g.H; lb.W = g.W; lb.P = g.P; lb.Q = g.Q; lb.S = g.S; lb.pad = g.pad; lb.Cs = g.Cs; lb.rows = p.N; lb.K = p.K;
     core::tile_product<BM, BN, 2, WN, DEPTH, KMASK, OUT_BF16, true>(la, lb, p.C[t.shard], p.ldc, p.M, p.N, p.K, t.m0, t.n0, false, smem);
+}
+
+// Forward products on BM x BN tiles, four waves, NS stages
+template <int BM, int BN, int NS, bool OUT_BF16> __global__ __launch_bounds__(core::kThreads, 2) void conv_gather_a4_kernel(const ConvParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    TileId t;
+    if (!tile_of<BM, BN>(p, &t)) return;
+    GatherKC2<core::kThreads> la;
+    la.base = reinterpret_cast<const char *>(p.A[t.shard]);
+    la.g = p.g; la.M = p.M; la.K = p.K;
+    core2::DenseKCT<core::kThreads> lb;
+    lb.base = reinterpret_cast<const char *>(p.B[t.shard * p.members]);
+    lb.ld = p.K; lb.rows = p.N; lb.K = p.K;
+    void *Cw = p.C[t.shard];
+    int ldc = p.ldc;
+    constexpr int WN = BN / 64; // a wave owns 64 columns
+    if (p.members > 1) {
+        const int col0 = t.n0 + ((threadIdx.x >> 6) % WN) * 64;
+        int m = col0 / p.member_cols;
+        m = m < p.members ? m : p.members - 1; // columns past N are never stored
+        Cw = reinterpret_cast<char *>(p.C[t.shard * p.members + m]) - (ptrdiff_t)m * p.member_cols * (OUT_BF16 ? 2 : 4);
+        ldc = p.member_cols;
+    }
+    core2::tile_product<OUT_BF16, true, BM, BN, 4 / WN, WN, NS>(la, lb, Cw, ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, reinterpret_cast<char *>(smem));
 }
 
 // ---- weight gradient with the reduction over pixels re-cut evenly --------------------------------------------------
@@ -755,56 +761,59 @@ int gather_rows(int64_t M, int64_t N, int count)
     return best;
 }
 
-template <int OP, bool OUT_BF16, bool ONE_TAP> tt_status launch_gather_a_t(ConvParams &p, int count, hipStream_t s)
+template <int BM, int BN, int NS, bool OUT_BF16> tt_status launch_a4(ConvParams &p, int count, hipStream_t s)
 {
-    const bool kmask = p.K % core::BK != 0;
-    const int tile = conv_tile(p.M, p.N, count);
-    // at most 64 output columns per shard (channels cut eight ways): 256 x 64 tiles, four waves of 64 x 64, so that no
-    // wave multiplies columns that do not exist
-    if constexpr (OP == 0) // (the filter loader of the direct data-gradient path needs 128 columns for its 256 threads)
-    if (p.N <= 64 && tuning_int("TT_CONV_TILE", -1) < 0) {
-        // 128 x 64 tiles (four waves of 32 x 64) while 256-row tiles do not give every CU two workgroups: the gather's
-        // address arithmetic and the trips to memory per K tile are what a lone workgroup spends its time on (784 x 64 x 576, eight shards: 19.8 -> 13.8 us)
-        if ((int64_t)((p.M + 255) / 256) * count < 512) {
-            constexpr size_t sm = core::smem_bytes<128, 64, 2>();
-            return kmask ? launch(conv_gather_a_kernel<128, 64, 1, 2, true, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 128, 64, 256, count, s)
-                         : launch(conv_gather_a_kernel<128, 64, 1, 2, false, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 128, 64, 256, count, s);
-        }
-        constexpr size_t sm = core::smem_bytes<256, 64, 2>();
-        return kmask ? launch(conv_gather_a_kernel<256, 64, 1, 2, true, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 256, 64, 256, count, s)
-                     : launch(conv_gather_a_kernel<256, 64, 1, 2, false, OP, OUT_BF16, ONE_TAP, 4>, sm, p, 256, 64, 256, count, s);
-    }
-    // Both operands K-contiguous: straight into LDS instead of through registers (VGG-16 conv4, 50176 x 512 x 4608, as the planner
-    // cuts it 313 us through registers, 291 with 32 x 32 x 16 MFMAs, 230 now; under the profiler)
-    if constexpr (OP == 0)
-    if (tile == 2 || tuning_int("TT_CONV_TILE", -1) == 3) {
+    return launch(conv_gather_a4_kernel<BM, BN, NS, OUT_BF16>, (size_t)NS * (BM + BN) * core::BK * 2, p, BM, BN, core::kThreads, count, s);
+}
+
+// Forward products (and data gradients as such): all tiles straight into LDS (VGG-16 conv4, 50176 x 512 x 4608, as the planner
+// cuts it 313 us through registers, 291 with 32 x 32 x 16 MFMAs, 230 now; under the profiler).
+template <bool OUT_BF16> tt_status launch_forward(ConvParams &p, int count, hipStream_t s)
+{
+    const int forced = tuning_int("TT_CONV_TILE", -1);
+    // At most 64 output columns per shard (channels cut eight ways): 128 x 64 tiles, three stages, two workgroups per CU.  256 x 64
+    // tiles through registers / so, us: 64 images of 56 x 56, 64 to 64 channels 67 / 42, 56 of 20 x 44, 384 to 64, 2 shards 51 / 43, 32 of 39 x
+    // 37, 192 to 8 on 8 shards 189 / 133; 128 x 64 ones: 32 of 14 x 14, 64 to 64, 8 shards 20.2 / 18.3
+    if (p.N <= 64 && forced < 0) return launch_a4<128, 64, 3, OUT_BF16>(p, count, s);
+    if (conv_tile(p.M, p.N, count) == 2 || forced == 3) {
         const int rows = gather_rows(p.M, p.N, count);
         if (rows == 192) return launch(conv_gather_a2_kernel<192, OUT_BF16>, core2::smem_bytes2<192>(), p, 192, 256, core2::kThreads2, count, s);
         if (rows == 224) return launch(conv_gather_a2_kernel<224, OUT_BF16>, core2::smem_bytes2<224>(), p, 224, 256, core2::kThreads2, count, s);
         return launch(conv_gather_a2_kernel<256, OUT_BF16>, core2::smem_bytes2<256>(), p, 256, 256, core2::kThreads2, count, s);
     }
-    if constexpr (OP == 1)
+    // Fewer tiles: 128 x 128, two stages, two workgroups per CU; 64 x 128 with three stages while that gives a CU no more than one.
+    // Through registers / 128 x 128 / 64 x 128, us: 16 of 28 x 28, 512 to 512 (392 tiles) 86 / 72 / 105; 10 of 43 x 45, 224 to 192 (304) 49 / 37 / 48; 20 of
+    // 13 x 44, 192 to 320 (270) 45 / 39 / 46; 16 of 29 x 32, 448 to 464, 1 x 1, 2 shards 21.6 / 18.5 / 22.2; 10 of 32 x 9, 496 to 192, 2 shards (46) 71 / 80 / 51
+    const int64_t tiles = (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) * count;
+    return tiles <= 128 ? launch_a4<64, 128, 3, OUT_BF16>(p, count, s) : launch_a4<128, 128, 2, OUT_BF16>(p, count, s);
+}
+
+// Data gradients whose filters are not flipped first (R != S or pad > R - 1): through registers
+template <bool OUT_BF16, bool ONE_TAP> tt_status launch_dgrad(ConvParams &p, int count, hipStream_t s)
+{
+    const bool kmask = p.K % core::BK != 0;
+    const int tile = conv_tile(p.M, p.N, count);
     if (tile == 2) {
         constexpr size_t sm = core::smem_bytes<256, 256>();
-        return kmask ? launch(conv_gather_a_kernel<256, 256, 4, 1, true, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s)
-                     : launch(conv_gather_a_kernel<256, 256, 4, 1, false, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s);
+        return kmask ? launch(conv_gather_a_kernel<256, 256, 4, 1, true, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s)
+                     : launch(conv_gather_a_kernel<256, 256, 4, 1, false, OUT_BF16, ONE_TAP>, sm, p, 256, 256, 512, count, s);
     }
     // too few 256 x 128 tiles for half the CUs: 128 x 128 ones
     if (tile == 0 && ((int64_t)((p.M + 255) / 256) * ((p.N + 127) / 128) * count > 128 || tuning_int("TT_CONV_TILE", -1) == 0)) {
         constexpr size_t sm = core::smem_bytes<256, 128>();
-        return kmask ? launch(conv_gather_a_kernel<256, 128, 2, 2, true, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 128, 256, count, s)
-                     : launch(conv_gather_a_kernel<256, 128, 2, 2, false, OP, OUT_BF16, ONE_TAP>, sm, p, 256, 128, 256, count, s);
+        return kmask ? launch(conv_gather_a_kernel<256, 128, 2, 2, true, OUT_BF16, ONE_TAP>, sm, p, 256, 128, 256, count, s)
+                     : launch(conv_gather_a_kernel<256, 128, 2, 2, false, OUT_BF16, ONE_TAP>, sm, p, 256, 128, 256, count, s);
     }
     constexpr size_t sm = core::smem_bytes<128, 128>();
-    return kmask ? launch(conv_gather_a_kernel<128, 128, 2, 2, true, OP, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s)
-                 : launch(conv_gather_a_kernel<128, 128, 2, 2, false, OP, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s);
+    return kmask ? launch(conv_gather_a_kernel<128, 128, 2, 2, true, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s)
+                 : launch(conv_gather_a_kernel<128, 128, 2, 2, false, OUT_BF16, ONE_TAP>, sm, p, 128, 128, 256, count, s);
 }
 
+// OP 0: forward, 1: data gradient
 template <int OP, bool OUT_BF16> tt_status launch_gather_a(ConvParams &p, int count, hipStream_t s)
 {
-    const int ch = OP == 0 ? p.g.Cs : p.g.Ks; // channels per pixel of the gathered tensor
-    return ch % core::BK == 0 ? launch_gather_a_t<OP, OUT_BF16, true>(p, count, s)
-                              : launch_gather_a_t<OP, OUT_BF16, false>(p, count, s);
+    if constexpr (OP == 0) return launch_forward<OUT_BF16>(p, count, s);
+    else return p.g.Ks % core::BK == 0 ? launch_dgrad<OUT_BF16, true>(p, count, s) : launch_dgrad<OUT_BF16, false>(p, count, s);
 }
 
 template <bool OUT_BF16> tt_status launch_wgrad(ConvParams &p, int count, hipStream_t s)

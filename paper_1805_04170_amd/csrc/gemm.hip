@@ -388,10 +388,10 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
         //  - 256 x 128 tiles, two workgroups per CU, otherwise; K that is no multiple of 32 from 128 on (8 x (300 x 4000 x 200) A B through
         //    registers 14.4, here 11.6; K 104 6.2 / 7.7).  Of the larger launches those whose K the persistent engine does not take and
         //    that are short enough for the second workgroup to be worth the narrower tile.  Direct-to-LDS engine / here, us: A^T B 6936 x
-        //    7456 K 529 84 / 67, 1001 128 / 114, 1529 178 / 163, 9072 x 11856 K 40 90 / 102; 8 x (500 x 8000) A B K 200 28.7 / 24.1, 520 45.8 / 44.0,
+        //    7456 K 529 84 / 67, 1001 128 / 114, 1529 178 / 163, 8 x (1936 x 832) K 16 10.1 / 8.6; 8 x (500 x 8000) A B K 200 28.7 / 24.1, 520 45.8 / 44.0,
         //    1032 73.9 / 90.4; A B^T K 200 28.9 / 26.8, 520 44.8 / 49.8
         const bool narrow = big_tiles < 200 ? K % 32 == 0 || kc >= 128
-                                            : K % 64 != 0 ? kc >= 64 && kc <= (!a_kc && !b_kc ? 2048 : a_kc && !b_kc ? 640 : 256)
+                                            : K % 64 != 0 ? (!a_kc && !b_kc ? kc <= 2048 : kc >= 64 && kc <= (a_kc && !b_kc ? 640 : 256))
                                                           : !a_kc && !b_kc && kc > 256 && kc < 512;
         if (engine == 4 || (engine == 0 && narrow && M > 128 && N >= 256)) {
             const tt_status st = launch_gemm_v4(count, A, B, C, M, N, K, a_contig, b_contig, N, a_kc, b_kc, out_dtype,

@@ -232,6 +232,17 @@ def test_conv_forward_on_tiles_of_every_height(on_host, monkeypatch, rows, C, K)
     on_host["conv"].run_conv(4, C, K, 9, 9, 3, 3, 1, 0, True, "", "", "", "", "", None, None, None, 61 + rows, with_dx=False)
 
 
+@pytest.mark.parametrize("C,K", [(8, 24), (16, 64), (24, 72), (64, 136)])
+def test_conv_forward_on_tiles_of_four_waves(on_host, C, K):
+    # 162 pixels end inside the second row of 128 x 64 tiles and the third of 64 x 128 ones, K of 72, 144, 216 inside a K tile
+    on_host["conv"].run_conv(2, C, K, 9, 9, 3, 3, 1, 0, False, "", "", "", "", "", None, None, None, 71 + K, with_dx=True)
+
+
+def test_conv_forward_of_many_small_tiles(on_host):
+    # 132 tiles of 128 x 128: more than get 64-row ones
+    on_host["conv"].run_conv(66, 8, 136, 16, 8, 1, 1, 0, 0, False, "", "", "", "", "", None, None, None, 79, with_dx=False)
+
+
 def test_conv_refusals(on_host):
     on_host["conv"].test_refusals()
 
