@@ -21,7 +21,7 @@
 //     way with ONE workgroup per CU: the panel takes 256 registers per lane and the two B stages 128 KB.  What it buys
 //     there is LDS traffic: only B goes through LDS (a fragment read per four products instead of three per eight),
 //     where the tile engines that read both operands through LDS transpose reads are bound by LDS;
-//   - 16 x 16 x 32 MFMAs, a B fragment of the k-step ahead in front of every four (gemm_mma.h says why): 16 x (2048 x 2048 x 512) 71 -> 67
+//   - 16 x 16 x 32 MFMAs, a B fragment ahead in front of every four (gemm_mma.h says why): 16 x (2048 x 2048 x 512) 71 -> 67
 //     us, 8 x (1152 x 4096 x 256) 26; the first VGG-16 weight gradient, bound by its 205 MB of stores, 59 either way;
 //   - the grid is persistent: each workgroup takes a contiguous run of units (shard-major, panel, column tile).
 //
@@ -195,28 +195,25 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
 
             f32x4 acc[4][4];
             mma::clear(acc);
-            // the B fragments are requested LOOK k-steps before the products that use them are issued: under load the LDS
+            // the B fragments are requested LOOK fragments before the four products that use each of them: under load the LDS
             // latency of the transpose reads is long (with one workgroup per CU, K = 512, no other wave of the SIMD fills
-            // the gap: two steps ahead there, one otherwise)
-            constexpr int LOOK = KT > 16 ? 2 : 1;
-            bf16x8 bq[LOOK + 1][4];
+            // the gap: eight ahead there; two at K = 256, where registers are short, four otherwise.  Whole k-steps ahead
+            // instead: 16 x (2048 x 2048 x 512) 69.5 -> 67.5 us, 8 x (1152 x 4096 x 128) 22.5 -> 21, K = 256 the same)
+            constexpr int LOOK = KT > 16 ? 8 : KT == 16 ? 2 : 4, NF = KS * 4;
+            bf16x8 bq[LOOK + 1];
 #pragma unroll
-            for (int a = 0; a < LOOK; ++a)
+            for (int f = 0; f < LOOK; ++f) bq[f] = read_frag_b5(Bs, 16 * (f & 3), f >> 2, lane);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) bq[a][j] = read_frag_b5(Bs, 16 * j, a, lane);
+            for (int f = 0; f < NF; ++f) {
+                if (f + LOOK < NF) bq[(f + LOOK) % (LOOK + 1)] = read_frag_b5(Bs, 16 * ((f + LOOK) & 3), (f + LOOK) >> 2, lane);
+                __builtin_amdgcn_sched_barrier(0); // (left alone, the scheduler starts the next step's products early and waits for these reads)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { // one of the fragments ahead in front of every four products
-                    if (ks + LOOK < KS) bq[(ks + LOOK) % (LOOK + 1)][i] = read_frag_b5(Bs, 16 * i, ks + LOOK, lane);
-                    __builtin_amdgcn_sched_barrier(0); // (left alone, the scheduler starts the next step's products early and waits for these reads)
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) { // operands exchanged: the accumulators hold blocks of C^T (see the strip above)
-                        const int j = i & 1 ? 3 - jj : jj;
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[ks % (LOOK + 1)][j], af[i][ks], acc[i][j], 0, 0, 0);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int ii = 0; ii < 4; ++ii) { // operands exchanged: the accumulators hold blocks of C^T (see the strip above)
+                    const int i = f & 1 ? 3 - ii : ii;
+                    acc[i][f & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[f % (LOOK + 1)], af[i][f >> 2], acc[i][f & 3], 0, 0, 0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
+            }
 
             // ---- epilogue: 32 rows of the wave's 64 at a time through its strip, then out as 16-byte pieces of whole
             // 128-byte rows (8 lanes per row, 8 rows per store instruction)
