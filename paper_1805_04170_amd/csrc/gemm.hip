@@ -200,9 +200,8 @@ tt_status launch_mfma_cfg(GemmParams &p, int count, hipStream_t s)
 }
 
 // Tile choice (TT_GEMM_TILE=0..5 overrides; tuning aid).
-//   5: 256 x 256, eight waves (two per SIMD, 128 x 64 each): the default whenever the launch has enough tiles to put
-//      work on at least half the CUs; two resident waves per SIMD cover each other's LDS / memory waits and the large
-//      tile halves operand traffic per flop.
+//   5: 256 x 256, whenever the launch has enough tiles to put work on at least half the CUs: the large tile halves operand
+//      traffic per flop.  (Straight into LDS; forced, the register-staged kernel of that size.)
 //   0: 256 x 128, four waves, two K tiles prefetched in registers: long K loops with few column tiles.
 //   1: 128 x 128, four waves, up to two workgroups per CU: small products and short K loops.
 //   2, 3, 4: 256 x 256 four-wave, 256 x 128 and 128 x 128 single-LDS-buffer variants kept for experiments.
