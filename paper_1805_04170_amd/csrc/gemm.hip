@@ -385,11 +385,12 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
             if (st != TT_EUNSUPPORTED) return st;
         }
         //  - 256 x 128 tiles, two workgroups per CU, otherwise; K that is no multiple of 32 from 128 on (8 x (300 x 4000 x 200) A B through
-        //    registers 14.4, here 11.6; K 104 6.2 / 7.7).  Of the larger launches those whose K the persistent engine does not take and
+        //    registers 14.4, here 11.6; K 104 6.2 / 7.7), but for A B^T where 256 x 256 tiles keep half the CUs busy and there are more of these
+        //    than CUs (2 x (997 x 5144 x 1288) 52 here, 42 on the larger tile).  Of the larger launches those whose K the persistent engine does not take and
         //    that are short enough for the second workgroup to be worth the narrower tile.  Direct-to-LDS engine / here, us: A^T B 6936 x
         //    7456 K 529 84 / 67, 1001 128 / 114, 1529 178 / 163, 8 x (1936 x 832) K 16 10.1 / 8.6; 8 x (500 x 8000) A B K 200 28.7 / 24.1, 520 45.8 / 44.0,
         //    1032 73.9 / 90.4; A B^T K 200 28.9 / 26.8, 520 44.8 / 49.8
-        const bool narrow = big_tiles < 200 ? K % 32 == 0 || kc >= 128
+        const bool narrow = big_tiles < 200 ? K % 32 == 0 || (kc >= 128 && !(a_kc && b_kc && big_tiles >= 128 && tiles128 > 256))
                                             : K % 64 != 0 ? (!a_kc && !b_kc ? kc <= 2048 : kc >= 64 && kc <= (a_kc && !b_kc ? 640 : 256))
                                                           : !a_kc && !b_kc && kc > 256 && kc < 512;
         if (engine == 4 || (engine == 0 && narrow && M > 128 && N >= 256)) {

@@ -94,9 +94,10 @@ __device__ __forceinline__ void tile_product4(const char *abase, int lda, const 
     uint64_t ab = uniform64(abase), bb = uniform64(bbase);
     int left = nk - 1;
     auto issue_one = [&](int i, uint32_t stage) {
-        const bool short_tile = TAIL && left <= 0;
-        if (i < kLoadsA) core2::chunk_or_zero(voa[i], ab, !short_tile || k_of<BM4, A_KC>(i) < tail, short_tile, stage + wave_lds + (uint32_t)i * (kThreads4 * 16u));
-        else core2::chunk_or_zero(vob[i - kLoadsA], bb, !short_tile || k_of<BN4, B_KC>(i - kLoadsA) < tail, short_tile,
+        // (a select per lane in every tile, not a branch in front of the last: branches cut the k-step's schedule up)
+        const int in = TAIL && left <= 0 ? tail : BK4;
+        if (i < kLoadsA) core2::chunk_or_zero(voa[i], ab, !TAIL || k_of<BM4, A_KC>(i) < in, TAIL, stage + wave_lds + (uint32_t)i * (kThreads4 * 16u));
+        else core2::chunk_or_zero(vob[i - kLoadsA], bb, !TAIL || k_of<BN4, B_KC>(i - kLoadsA) < in, TAIL,
                                   stage + kABytes + wave_lds + (uint32_t)(i - kLoadsA) * (kThreads4 * 16u));
     };
     auto advance = [&]() {

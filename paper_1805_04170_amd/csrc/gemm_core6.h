@@ -96,9 +96,10 @@ __device__ __forceinline__ void tile_product6(const char *abase, int lda, const 
     uint64_t ab = core2::uniform64(abase), bb = core2::uniform64(bbase);
     int left = nk - 1;
     auto issue_one = [&](int i, uint32_t stage) {
-        const bool short_tile = TAIL && left <= 0;
-        if (i < kLoadsA6) core2::chunk_or_zero(voa[i], ab, !short_tile || k_of<BM6, A_KC>(i) < tail, short_tile, stage + wave_lds + (uint32_t)i * (kThreads6 * 16u));
-        else core2::chunk_or_zero(vob[i - kLoadsA6], bb, !short_tile || k_of<BN6, B_KC>(i - kLoadsA6) < tail, short_tile,
+        // (a select per lane in every tile, not a branch in front of the last: branches cut the k-step's schedule up)
+        const int in = TAIL && left <= 0 ? tail : BK6;
+        if (i < kLoadsA6) core2::chunk_or_zero(voa[i], ab, !TAIL || k_of<BM6, A_KC>(i) < in, TAIL, stage + wave_lds + (uint32_t)i * (kThreads6 * 16u));
+        else core2::chunk_or_zero(vob[i - kLoadsA6], bb, !TAIL || k_of<BN6, B_KC>(i - kLoadsA6) < in, TAIL,
                                   stage + kABytes6 + wave_lds + (uint32_t)(i - kLoadsA6) * (kThreads6 * 16u));
     };
     auto advance = [&]() {
