@@ -128,7 +128,8 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
     srd[0] = strip + (lane >> 3) * (NT5 * 2) + (((lane & 7) ^ ((lane >> 4) & 7)) << 4);
     srd[1] = strip + (lane >> 3) * (NT5 * 2) + (((lane & 7) ^ ((lane >> 4) & 7) ^ 4) << 4);
     const uint32_t st_off = (uint32_t)((lane >> 3) * ldc + (lane & 7) * 8) * 2u; // lane part of the store address
-    const float floor_v = p.relu ? 0.0f : -__builtin_inff(); // the element-wise function as one maximum, no branch
+    // the element-wise function as one maximum, no branch: the maximum with NaN is the value itself, also where that is NaN or -inf
+    const float floor_v = p.relu ? 0.0f : __builtin_nanf("");
     const int per_shard = p.panels * p.ntiles;
 
     while (u < end) {

@@ -220,6 +220,23 @@ def test_bf16_panel_in_registers_engine(K):
     check(8, 1032, 3328, K, 1, 0, "bf16", "bf16", K == 128, 48)
 
 
+@pytest.mark.parametrize("count,M,N,K,ta,tb", [(1, 4104, 4096, 100, 1, 0), (1, 4104, 4096, 256, 1, 0), (1, 4096, 4104, 512, 1, 0), (2, 520, 520, 96, 1, 0),
+                                               (2, 300, 520, 1032, 0, 0), (8, 1544, 1528, 128, 0, 1), (8, 1288, 1288, 1032, 0, 0), (1, 72, 136, 392, 0, 1)])
+def test_values_that_are_not_finite_stay_what_they_are(count, M, N, K, ta, tb):
+    # a NaN and an infinity in the left operand, an infinity in the right one, on the engines that a product can run on
+    a, b = to_bf16_bits(normal_f32(97, 0, (M, K), 1.0)), to_bf16_bits(normal_f32(97, 1, (K, N), 0.05))
+    a[5, 3], a[9, 7], b[2, 20] = 0x7FC0, 0x7F80, 0xFF80
+    with np.errstate(invalid="ignore"):
+        want = bf16_bits_to_f64(a) @ bf16_bits_to_f64(b)
+    A, B = [np_to_dev(a.T if ta else a, True)] * count, [np_to_dev(b.T if tb else b, True)] * count
+    C = [torch.zeros((M, N), dtype=torch.bfloat16, device=DEV) for _ in range(count)]
+    tt.tt_shard_gemm(A, B, C, M, N, K, ta, tb, "bf16", "bf16")
+    for c in C:
+        got = bf16_bits_to_f64(dev_to_np(c))
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.isnan(got[5]).all()
+        assert np.array_equal(got == np.inf, want == np.inf) and np.array_equal(got == -np.inf, want == -np.inf)
+
+
 def test_k_zero_and_empty():
     C = [torch.full((8, 8), 5.0, dtype=torch.float32, device=DEV)]
     A = [torch.zeros((8, 1), dtype=torch.bfloat16, device=DEV)]

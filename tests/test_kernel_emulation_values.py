@@ -128,6 +128,31 @@ def test_panel_in_registers_engine_values_at_other_k_and_widths(lockstep_gemm, t
     check(lockstep_gemm, str(tmp_path), 1, 256, 192, K, 1, 0, "bf16", "bf16", False, 91, env=env)
 
 
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("env,ta,tb,K", [({"TT_GEMM_ENGINE": "5", "EMU_CUS": "1"}, 1, 0, K) for K in (64, 100, 128, 256, 512)] +
+                         [({"TT_GEMM_ENGINE": "4"}, 1, 0, 104), ({"TT_GEMM_ENGINE": "6"}, 0, 1, 104),
+                          ({"TT_GEMM_ENGINE": "3", "TT_GEMM_TILE": "5", "EMU_CUS": "8"}, 1, 0, 128), ({"TT_GEMM_ENGINE": "1", "TT_GEMM_TILE": "8"}, 0, 0, 104),
+                          ({"TT_GEMM_ENGINE": "1", "TT_GEMM_TILE": "0"}, 0, 1, 104), ({"TT_GEMM_ENGINE": "1", "TT_GEMM_TILE": "1"}, 1, 0, 104)])
+def test_values_that_are_not_finite_stay_what_they_are(lockstep_gemm, tmp_path, env, ta, tb, K, relu):
+    # a NaN and an infinity in the left operand, an infinity in the right one: rows and a column of NaN and infinities of both signs,
+    # also where sums are rounded to bf16; under the element-wise function NaN gives 0, as -inf does
+    M, N, tmp = 264, 136, str(tmp_path)
+    a, b = to_bf16_bits(normal_f32(96, 0, (M, K), 1.0)), to_bf16_bits(normal_f32(96, 1, (K, N), 0.05))
+    a[5, 3], a[9, 7], b[2, 20] = 0x7FC0, 0x7F80, 0xFF80
+    with np.errstate(invalid="ignore"):
+        want = (bf16_bits_to_f64(a)[:, :, None] * bf16_bits_to_f64(b)[None]).sum(axis=1)
+        want = np.fmax(want, 0) if relu else want
+    np.ascontiguousarray(a.T if ta else a).tofile(os.path.join(tmp, "a0.bin"))
+    np.ascontiguousarray(b.T if tb else b).tofile(os.path.join(tmp, "b0.bin"))
+    r = subprocess.run([lockstep_gemm] + [str(v) for v in (1, M, N, K, ta, tb, 1, 1, int(relu), 1, tmp)], capture_output=True, text=True, env=dict(os.environ, **env))
+    assert r.returncode == 0, r.stderr[-1500:]
+    got = bf16_bits_to_f64(np.fromfile(os.path.join(tmp, "c0.bin"), dtype=np.uint16)).reshape(M, N)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got == np.inf, want == np.inf) and np.array_equal(got == -np.inf, want == -np.inf)
+    assert relu or (np.isnan(want[5]).all() and np.isinf(want).any(axis=0)[30])
+    assert np.count_nonzero(np.isfinite(got)) > M * N * 0.9
+
+
 def test_line_wide_k_tiles_engine_as_the_library_chooses_it(lockstep_gemm, tmp_path):
     # a skinny data-gradient shaped product (one row of tiles, 128 of them for 256 CUs, K of four tiles): no switch set
     check(lockstep_gemm, str(tmp_path), 32, 256, 392, 256, 0, 1, "bf16", "bf16", False, 52)
