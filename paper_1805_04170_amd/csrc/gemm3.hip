@@ -171,26 +171,9 @@ template <bool A_KC, bool B_KC> tt_status launch_runs(core3::Params3 &p, int out
 tt_status launch_gemm_v5(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int relu, void *stream)
 {
-    if (K < 1 || K > 512 || N < 8 || N % 8 || M < 8 || M % 8 || count < 1 || count > 64)
-        return TT_EUNSUPPORTED;
-    if (lda % 8 || ldb % 8 || ldc % 8 || lda < M || ldb < N || ldc < N) return TT_EUNSUPPORTED; // 16-byte chunks and rows
-    if (K * lda >= (int64_t(1) << 30) || K * ldb >= (int64_t(1) << 30)) return TT_EUNSUPPORTED; // 32-bit byte offsets
     core5::Params5 p;
-    for (int i = 0; i < 64; ++i) {
-        p.A[i] = i < count ? A[i] : nullptr;
-        p.B[i] = i < count ? B[i] : nullptr;
-        p.C[i] = i < count ? C[i] : nullptr;
-    }
-    p.M = (int32_t)M; p.N = (int32_t)N; p.K = (int32_t)K;
-    p.lda = (int32_t)lda; p.ldb = (int32_t)ldb; p.ldc = (int32_t)ldc;
-    p.panels = (int32_t)((M + core5::PM5 - 1) / core5::PM5);
-    p.ntiles = (int32_t)((N + core5::NT5 - 1) / core5::NT5);
-    const int64_t total = (int64_t)count * p.panels * p.ntiles;
-    if (total >= (int64_t(1) << 30)) return TT_EUNSUPPORTED;
-    p.total = (int32_t)total;
-    const int64_t resident = (K <= 256 ? 2 : 1) * (int64_t)cu_count(); // two workgroups per CU; one at K = 512
-    p.grid = (int32_t)(total < resident ? total : resident);
-    p.relu = relu;
+    const tt_status st = fill_params5(&p, cu_count(), count, A, B, C, M, N, K, lda, ldb, ldc, relu);
+    if (st != TT_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (K <= 64) return launch_cfg5<4>(p, s);
     if (K <= 128) return launch_cfg5<8>(p, s);

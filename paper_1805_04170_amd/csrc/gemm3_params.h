@@ -1,10 +1,11 @@
-// Launch parameters of the persistent engine (gemm_core3.h) and of the 256 x 128 engine (gemm_core4.h): what the
+// Launch parameters of the persistent engine (gemm_core3.h), the 256 x 128 engines (gemm_core4.h, gemm_core6.h) and the panel engine (gemm_core5.h): what the
 // kernels assume about a product is checked here, on the host, and the grid geometry is derived here.  Shared by the
 // launchers and by the host build that checks the kernels' memory accesses, so that both see the same geometry.
 #pragma once
 #include <cstdint>
 #include "gemm_core3.h"
 #include "gemm_core4.h"
+#include "gemm_core5.h"
 #include "tt_internal.h"
 
 namespace tt {
@@ -66,6 +67,32 @@ inline tt_status fill_params3_runs(core3::Params3 *p, int cus, int nblk, int nre
     p->wg_per_xcd = per_xcd_cus < p->per_xcd ? per_xcd_cus : p->per_xcd;
     p->nred = nred;
     p->parts = parts;
+    return TT_OK;
+}
+
+// Panel engine: C_s = A_s^T B_s, A_s stored K x M, B_s stored K x N, K up to 512, bf16 results with 16-byte rows
+inline tt_status fill_params5(core5::Params5 *p, int cus, int count, const void *const *A, const void *const *B, void *const *C, int64_t M,
+                              int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int relu)
+{
+    if (K < 1 || K > 512 || N < 8 || N % 8 || M < 8 || M % 8 || count < 1 || count > 64) return TT_EUNSUPPORTED;
+    if (lda % 8 || ldb % 8 || ldc % 8 || lda < M || ldb < N || ldc < N) return TT_EUNSUPPORTED; // 16-byte chunks and rows
+    if (K * lda >= (int64_t(1) << 30) || K * ldb >= (int64_t(1) << 30)) return TT_EUNSUPPORTED; // 32-bit byte offsets
+    if (ldc >= (int64_t(1) << 28)) return TT_EUNSUPPORTED; // ... also of the eight rows that a store covers
+    for (int i = 0; i < 64; ++i) {
+        p->A[i] = i < count ? A[i] : nullptr;
+        p->B[i] = i < count ? B[i] : nullptr;
+        p->C[i] = i < count ? C[i] : nullptr;
+    }
+    p->M = (int32_t)M; p->N = (int32_t)N; p->K = (int32_t)K;
+    p->lda = (int32_t)lda; p->ldb = (int32_t)ldb; p->ldc = (int32_t)ldc;
+    p->panels = (int32_t)((M + core5::PM5 - 1) / core5::PM5);
+    p->ntiles = (int32_t)((N + core5::NT5 - 1) / core5::NT5);
+    const int64_t total = (int64_t)count * p->panels * p->ntiles;
+    if (total >= (int64_t(1) << 30)) return TT_EUNSUPPORTED;
+    p->total = (int32_t)total;
+    const int64_t resident = (K <= 256 ? 2 : 1) * (int64_t)cus; // two workgroups per CU; one at K = 512
+    p->grid = (int32_t)(total < resident ? total : resident);
+    p->relu = relu;
     return TT_OK;
 }
 

@@ -109,6 +109,14 @@ int main(int argc, char **argv)
         std::printf("%d\n", tt::two_tiles_ahead(std::atol(argv[3]), std::atol(argv[4]), std::atol(argv[5]), std::atol(argv[2]), std::atoi(argv[6]) == 0) ? 2 : 1);
         return 0;
     }
+    // emu_shard_gemm panel M N K: whether the panel engine takes such a product (1) or leaves it to the others (0)
+    if (argc == 5 && std::strcmp(argv[1], "panel") == 0) {
+        tt::core5::Params5 p;
+        void *none[64] = {};
+        const int64_t M = std::atol(argv[2]), N = std::atol(argv[3]), K = std::atol(argv[4]);
+        std::printf("%d\n", tt::fill_params5(&p, 256, 1, none, none, none, M, N, K, M, N, N, 0) == TT_OK);
+        return 0;
+    }
     // emu_shard_gemm last_chunk
     if (argc == 2 && std::strcmp(argv[1], "last_chunk") == 0) {
         run_last_chunks<true, true, true>(); run_last_chunks<true, true, false>(); run_last_chunks<true, false, true>(); run_last_chunks<true, false, false>();

@@ -128,6 +128,13 @@ def test_panel_in_registers_engine_values_at_other_k_and_widths(lockstep_gemm, t
     check(lockstep_gemm, str(tmp_path), 1, 256, 192, K, 1, 0, "bf16", "bf16", False, 91, env=env)
 
 
+@pytest.mark.parametrize("N,K,takes", [(2 ** 27, 1, 1), (2 ** 28 - 8, 3, 1), (2 ** 28, 1, 0), (306783384, 1, 0), (2 ** 29, 1, 0), (2 ** 28 - 8, 4, 1)])
+def test_panel_in_registers_engine_leaves_rows_too_long_for_its_offsets(lockstep_gemm, N, K, takes):
+    # a store's eight rows are addressed with 32-bit byte offsets: 7 rows of 306783384 elements are 2^32 bytes and 80
+    r = subprocess.run([lockstep_gemm, "panel", "8", str(N), str(K)], capture_output=True, text=True)
+    assert r.returncode == 0 and int(r.stdout) == takes
+
+
 @pytest.mark.parametrize("relu", [False, True])
 @pytest.mark.parametrize("env,ta,tb,K", [({"TT_GEMM_ENGINE": "5", "EMU_CUS": "1"}, 1, 0, K) for K in (64, 100, 128, 256, 512)] +
                          [({"TT_GEMM_ENGINE": "4"}, 1, 0, 104), ({"TT_GEMM_ENGINE": "6"}, 0, 1, 104),
