@@ -120,7 +120,8 @@ template <class F> inline void emu_launch(F &&body, dim3 grid, dim3 block, size_
 #endif
         }
 }
-#define hipLaunchKernelGGL(kern, grid, block, smem, stream, ...) emu_launch([&]() { kern(__VA_ARGS__); }, grid, block, smem)
+inline const char *g_emu_launched_by = ""; // the function with the last launch in it, template arguments included: what tells which kernel ran
+#define hipLaunchKernelGGL(kern, grid, block, smem, stream, ...) (g_emu_launched_by = __PRETTY_FUNCTION__, emu_launch([&]() { kern(__VA_ARGS__); }, grid, block, smem))
 
 namespace tt {
 namespace dev {

@@ -164,7 +164,7 @@ int main(int argc, char **argv)
             if (!f || std::fwrite(C[s].data(), 1, C[s].size(), f) != C[s].size()) { std::fprintf(stderr, "cannot write %s\n", path); return 66; }
             std::fclose(f);
         }
-        std::printf("ok shard_gemm values: %llu threads run\n", g_emu_threads_run);
+        std::printf("ok shard_gemm values: %llu threads run, launched by %s\n", g_emu_threads_run, g_emu_launched_by);
         return 0;
     }
     for (size_t s = 0; s < C.size(); ++s)

@@ -44,8 +44,7 @@ def check(exe, tmp, count, M, N, K, ta, tb, in_dt, out_dt, relu, seed, ksplit=1,
     e.update(env or {})
     r = subprocess.run([exe] + [str(v) for v in (count, M, N, K, ta, tb, int(bf), int(out_dt == "bf16"), int(relu), ksplit, tmp)],
                        capture_output=True, text=True, env=e)
-    if r.returncode != 0:       # (no wrong value: tests that plant a mistake do not take a fault for one)
-        raise RuntimeError(r.stdout[-400:] + r.stderr[-1500:])
+    assert r.returncode == 0, r.stdout[-400:] + r.stderr[-1500:]
     for s in range(count):
         # with a K split the launch leaves ksplit partial products per shard, to be summed
         gf = np.zeros((M, N))
@@ -329,7 +328,7 @@ def test_random_products_values(lockstep_gemm, tmp_path):
         env = switches[int(rng.integers(0, len(switches)))]
         try:
             check(lockstep_gemm, str(tmp_path), int(rng.integers(1, 3)), M, N, K, ta, tb, in_dt, out_dt, relu, 300 + case, ksplit=ksplit, env=env)
-        except (AssertionError, RuntimeError) as e:
+        except AssertionError as e:
             raise AssertionError((case, M, N, K, ta, tb, in_dt, out_dt, relu, ksplit, env, str(e)[:500]))
 
 
@@ -349,3 +348,32 @@ def test_results_do_not_depend_on_which_wave_runs_ahead(lockstep_gemm, tmp_path,
     # reversed the last wave reaches every barrier first, issues its loads first and writes its results first
     shape = (2, 520, 776, 192, 1, 0, "bf16", "bf16", True, 42) if env else (1, 264, 392, 96, 1, 0, "bf16", "bf16", True, 45)
     check(lockstep_gemm, str(tmp_path), *shape, env=dict(env, EMU_ORDER="reverse"))
+
+
+@pytest.mark.parametrize("M,N,K,ta,tb,launcher", [
+    (136, 264, 512, 0, 1, "launch_tail6<true, true, true, false>"), (136, 264, 520, 0, 1, "launch_tail6<true, true, true, true>"),
+    (136, 264, 504, 0, 1, "launch_tail4<true, true, true, true>"), (136, 264, 1032, 0, 0, "launch_tail6<true, false, true, true>"),
+    (136, 264, 1016, 0, 0, "launch_tail4<true, false, true, true>"), (136, 264, 2048, 1, 0, "launch_tail6<false, false, true, false>"),
+    (136, 264, 2056, 1, 0, "launch_tail6<false, false, true, true>"), (136, 264, 2040, 1, 0, "launch_tail4<false, false, true, true>"),
+    (65, 136, 384, 0, 1, "launch_rows_cfg<64, true, true>"), (128, 136, 392, 0, 0, "launch_rows_cfg<64, true, false>"),
+    (64, 136, 384, 0, 1, "launch_mfma_cfg"), (65, 136, 376, 0, 1, "launch_mfma_cfg"),
+    (33, 136, 2048, 0, 0, "launch_rows_cfg<64, true, false>"), (32, 136, 1024, 0, 0, "launch_rows_cfg<32, true, false>")])
+def test_products_run_on_the_kernels_that_their_rules_name(lockstep_gemm, tmp_path, M, N, K, ta, tb, launcher):
+    # either side of the lines in K and in rows, no switch set
+    out = check(lockstep_gemm, str(tmp_path), 1, M, N, K, ta, tb, "bf16", "f32", False, 97)
+    name, _, args = out.split("launched by ")[1].rpartition(" [")
+    values = dict(a.split(" = ") for a in args.rstrip("]\n").split(", "))
+    want_name, _, want = launcher.rstrip(">").partition("<")
+    assert name.split("(")[-2].split(" ")[-1].split("::")[-1] == want_name
+    order = ["A_KC", "B_KC", "STAGED", "TAIL"] if "tail" in want_name else ["BM", "A_KC", "B_KC"]
+    assert not want or [values[n] for n in order] == want.split(", ")
+
+
+@pytest.mark.parametrize("env,shape", [({}, (1, 100, 136, 520, 0, 1)), ({}, (1, 32, 136, 1032, 0, 0)), ({"TT_GEMM_ENGINE": "4"}, (1, 264, 264, 104, 1, 0)),
+                                       ({"TT_GEMM_ENGINE": "6"}, (1, 264, 264, 296, 1, 0)), ({"TT_GEMM_ENGINE": "1", "TT_GEMM_TILE": "8"}, (1, 264, 264, 72, 0, 0))])
+def test_a_wait_that_is_too_short_shows_in_the_values(lockstep_gemm, tmp_path, env, shape):
+    # rings of two and three stages, K tails: wrong values, not a fault of the emulation
+    check(lockstep_gemm, str(tmp_path), *shape, "bf16", "f32", False, 98, env=env)
+    with pytest.raises(AssertionError) as e:
+        check(lockstep_gemm, str(tmp_path), *shape, "bf16", "f32", False, 98, env=dict(env, EMU_VMCNT_SLACK="2"))
+    assert str(e.value).startswith("(")

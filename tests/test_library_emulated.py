@@ -243,6 +243,23 @@ def test_conv_forward_of_many_small_tiles(on_host):
     on_host["conv"].run_conv(66, 8, 136, 16, 8, 1, 1, 0, 0, False, "", "", "", "", "", None, None, None, 79, with_dx=False)
 
 
+@pytest.mark.parametrize("rows", [192, 224, 256])
+def test_conv_forward_waits_for_every_chunk_of_the_first_tile(on_host, monkeypatch, emulated_library, rows):
+    # K = 64 is one K tile, so that the first wait alone decides; on 224 rows half the waves have a load less than the rest.  One
+    # more load in flight than the kernel asks for must show in the values
+    monkeypatch.setenv("TT_CONV_TILE", "3")
+    monkeypatch.setenv("TT_CONV_ROWS", str(rows))
+    case = (4, 64, 264, 9, 9, 1, 1, 0, 0, True, "", "", "", "", "", None, None, None, 65)
+    on_host["conv"].run_conv(*case, with_dx=False)
+    slack = ctypes.c_int.in_dll(ctypes.CDLL(emulated_library), "g_emu_vmcnt_slack")
+    slack.value = 1
+    try:
+        with pytest.raises(AssertionError, match="fwd"):
+            on_host["conv"].run_conv(*case, with_dx=False)
+    finally:
+        slack.value = 0
+
+
 def test_conv_refusals(on_host):
     on_host["conv"].test_refusals()
 
