@@ -92,14 +92,22 @@ __device__ __forceinline__ void tile_product6(const char *abase, int lda, const 
     const uint64_t bstep = B_KC ? (uint64_t)BK6 * 2 : (uint64_t)BK6 * (uint64_t)ldb * 2;
     const int nk = (klen + BK6 - 1) / BK6, tail = klen - (nk - 1) * BK6; // K tiles, values of K in the last one
 
+    // Rows contiguous and a tail, whose selects need registers: one lane offset per operand, a chunk's k-row is part of the scalar base
+    // (with an offset per chunk A^T B spilled, and a reload's wait is one for every load on its way: 8 x (1024 x 1024 x 2056) 58 us, now
+    // 44, 8 x (512 x 1024 x 4104) 98, now 68)
+    constexpr bool ONE_A = TAIL && !A_KC, ONE_B = TAIL && !B_KC;
+    const uint64_t arow = ONE_A ? (uint64_t)(kThreads6 / (BM6 / 8)) * (uint64_t)lda * 2 : 0;
+    const uint64_t brow = ONE_B ? (uint64_t)(kThreads6 / (BN6 / 8)) * (uint64_t)ldb * 2 : 0;
+
     // K tile to ask for next; past the end the last one is fetched again, so that the wait counts stay the same
     uint64_t ab = core2::uniform64(abase), bb = core2::uniform64(bbase);
     int left = nk - 1;
     auto issue_one = [&](int i, uint32_t stage) {
         // (a select per lane in every tile, not a branch in front of the last: branches cut the k-step's schedule up)
         const int in = TAIL && left <= 0 ? tail : BK6;
-        if (i < kLoadsA6) core2::chunk_or_zero(voa[i], ab, !TAIL || k_of<BM6, A_KC>(i) < in, TAIL, stage + wave_lds + (uint32_t)i * (kThreads6 * 16u));
-        else core2::chunk_or_zero(vob[i - kLoadsA6], bb, !TAIL || k_of<BN6, B_KC>(i - kLoadsA6) < in, TAIL,
+        if (i < kLoadsA6) core2::chunk_or_zero(voa[ONE_A ? 0 : i], ab + i * arow, !TAIL || k_of<BM6, A_KC>(i) < in, TAIL,
+                                               stage + wave_lds + (uint32_t)i * (kThreads6 * 16u));
+        else core2::chunk_or_zero(vob[ONE_B ? 0 : i - kLoadsA6], bb + (i - kLoadsA6) * brow, !TAIL || k_of<BN6, B_KC>(i - kLoadsA6) < in, TAIL,
                                   stage + kABytes6 + wave_lds + (uint32_t)(i - kLoadsA6) * (kThreads6 * 16u));
     };
     auto advance = [&]() {
