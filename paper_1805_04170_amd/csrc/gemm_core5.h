@@ -104,8 +104,11 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
     // contiguous run of units; workgroup numbers go round-robin over the XCDs, so give every XCD a contiguous range
     const uint32_t bid = blockIdx.x, grid = (uint32_t)p.grid;
     const uint32_t lw = grid % core::kXcds == 0 ? (bid % core::kXcds) * (grid / core::kXcds) + bid / core::kXcds : bid;
-    int64_t u = (int64_t)lw * p.total / grid;
-    const int64_t end = (int64_t)(lw + 1) * p.total / grid;
+    // (units lw total / grid to (lw + 1) total / grid, no product past 32 bits: total < 2^30, grid < 2^15.  With 64-bit divisions, here and
+    // at every panel, the code spilled at K = 256: 8 x (1024 x 2048 x 256) 13.8 -> 12.7 us)
+    const uint32_t each = (uint32_t)p.total / grid, rest = (uint32_t)p.total % grid;
+    int u = (int)(lw * each + lw * rest / grid);
+    const int end = (int)((lw + 1) * each + (lw + 1) * rest / grid);
 
     // lane parts of the load addresses
     const uint32_t bkl = (uint32_t)tid >> 3, bpc = (uint32_t)tid & 7u;
@@ -133,10 +136,9 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
     const int per_shard = p.panels * p.ntiles;
 
     while (u < end) {
-        const int shard = (int)(u / per_shard);
-        const int r = (int)(u - (int64_t)shard * per_shard);
+        const int shard = u / per_shard, r = u - shard * per_shard;
         const int panel = r / p.ntiles, nt0 = r - panel * p.ntiles;
-        const int run = (int)(end - u < (int64_t)(p.ntiles - nt0) ? end - u : (int64_t)(p.ntiles - nt0));
+        const int run = end - u < p.ntiles - nt0 ? end - u : p.ntiles - nt0;
         const int m0 = panel * PM5;
 
         // ---- the panel's slice of A^T into registers, half of K at a time through the (idle) B stages
@@ -157,7 +159,7 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
                 for (int i = 0; i < NLA; ++i) {
                     const uint64_t sb = uniform64(abase + (size_t)(c * ACH + 8 * i) * (size_t)p.lda * 2);
                     const int k = c * ACH + 8 * i;
-                    core2::chunk_or_zero(voff_a, sb, !TAIL || k + (int)akl < K, TAIL && k + 8 > K, lds0 + (wave * 64u + (uint32_t)i * kThreads5) * 16u);
+                    core2::chunk_or_zero(voff_a, sb, !TAIL || k + (int)akl < K, TAIL, lds0 + (wave * 64u + (uint32_t)i * kThreads5) * 16u);
                 }
                 __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm(0));
                 __syncthreads();
@@ -176,7 +178,7 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
 #pragma unroll
             for (int i = 0; i < NLB; ++i) {
                 const uint64_t sb = uniform64(bbase + (size_t)(32 * i) * (size_t)p.ldb * 2);
-                core2::chunk_or_zero(voff_b + (uint32_t)col * 2u, sb, !TAIL || 32 * i + (int)bkl < K, TAIL && 32 * (i + 1) > K,
+                core2::chunk_or_zero(voff_b + (uint32_t)col * 2u, sb, !TAIL || 32 * i + (int)bkl < K, TAIL,
                                      lds0 + (uint32_t)stage * STB + (wave * 64u + (uint32_t)i * kThreads5) * 16u);
             }
         };

@@ -37,8 +37,8 @@ def test_kernels_with_loads_in_flight_keep_their_values_in_registers(tmp_path):
             f.write(obj)
         notes = subprocess.run([READELF, "--notes", path], capture_output=True, text=True, check=True).stdout
         for name, spilled in re.findall(r"\.symbol:\s+(\S+)\.kd.*?\.vgpr_spill_count:\s+(\d+)", notes, re.S):
-            kernel = re.search(r"(gemm_bf16_(?:v2|v3|v4|v6|rows)|conv_gather_a[24]|conv_wgrad_split2)_kernel", name)
+            kernel = re.search(r"(gemm_bf16_(?:v2|v3|v4|v6|rows|v5(?=_kernelILi\d+ELb[01]ELb0E))|conv_gather_a[24]|conv_wgrad_split2)_kernel", name)
             if kernel:
                 seen.setdefault(kernel.group(1), []).append((name, int(spilled)))
-    assert len(seen) == 8
+    assert len(seen) == 9
     assert not [k for ks in seen.values() for k in ks if k[1]]
