@@ -223,6 +223,11 @@ def test_forward_tiles_loaded_straight_into_lds(C, R):
     run_straight_into_lds(130, C, R)    # 130 tiles of 256 x 256, short ones among them
 
 
+def test_forward_tiles_of_256_rows():
+    # 65520 pixels are 256 tiles of 256 rows (more of 224 or 192 than a round takes), the last one short; K of a K tile and a tail
+    run_conv(130, 72, 136, 21, 24, 1, 1, 0, 0, True, "", "", "", "", "", None, None, None, 196)
+
+
 def test_shards_that_share_their_left_operand_run_as_one_product():
     # 64 or 128 columns per shard and the left operand replicated over the cuts that split them: forward and data gradient
     # run one product per group of shards, every wave writing into its own shard's result

@@ -220,6 +220,31 @@ def test_bf16_panel_in_registers_engine(K):
     check(8, 1032, 3328, K, 1, 0, "bf16", "bf16", K == 128, 48)
 
 
+@pytest.mark.parametrize("K", [1, 40, 64, 72, 128, 219])
+def test_bf16_panel_in_registers_engine_at_other_k_and_widths(K):
+    # any K inside the next of 64, 128 and 256; the last unit of a panel 8 columns wide, the last panel with 8 rows
+    check(2, 2056, 4104, K, 1, 0, "bf16", "bf16", K == 72, 110)
+
+
+@pytest.mark.parametrize("out_dt", ["bf16", "f32"])
+@pytest.mark.parametrize("ta,tb,K", [(0, 1, 512), (0, 1, 520), (0, 0, 1024), (0, 0, 1032), (1, 0, 2048), (1, 0, 2056), (1, 1, 2104)])
+def test_bf16_k_tiles_of_64_two_on_their_way(ta, tb, K, out_dt):
+    # the 256 x 128 engine with three stages of 64, every layout, whole and short last K tiles
+    check(2, 264, 392, K, ta, tb, "bf16", out_dt, K % 64 == 0, 111)
+
+
+@pytest.mark.parametrize("ta,tb,K", [(0, 0, 1032), (0, 1, 520), (1, 0, 2056), (1, 1, 264)])
+def test_bf16_large_products_of_short_last_k_tiles(ta, tb, K):
+    # more 256 x 256 tiles than CUs and K outside what the other engines take: the direct-to-LDS kernel of that size
+    check(8, 1288, 1288, K, ta, tb, "bf16", "bf16", True, 112)
+
+
+@pytest.mark.parametrize("M,N,K,tb", [(65, 136, 384, 1), (128, 264, 392, 0), (72, 1176, 4640, 1), (33, 136, 2056, 0), (32, 264, 1032, 0), (1, 136, 1024, 0)])
+def test_bf16_few_rows_straight_into_lds(M, N, K, tb):
+    # 64- and 32-row tiles with three stages: whole and short rows, columns and K tiles
+    check(2, M, N, K, 0, tb, "bf16", "f32" if M % 2 else "bf16", M % 2 == 0, 113)
+
+
 @pytest.mark.parametrize("count,M,N,K,ta,tb", [(1, 4104, 4096, 100, 1, 0), (1, 4104, 4096, 256, 1, 0), (1, 4096, 4104, 512, 1, 0), (2, 520, 520, 96, 1, 0),
                                                (2, 300, 520, 1032, 0, 0), (8, 1544, 1528, 128, 0, 1), (8, 1288, 1288, 1032, 0, 0), (1, 72, 136, 392, 0, 1)])
 def test_values_that_are_not_finite_stay_what_they_are(count, M, N, K, ta, tb):
