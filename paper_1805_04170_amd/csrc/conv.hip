@@ -52,14 +52,14 @@ __device__ __forceinline__ u32x4 load16(const char *base, int32_t elem_off)
 }
 
 // A operand of dgrad through registers: rows are input pixels (n, oy, ox), k = (tap, channel) with the channel contiguous.
-// in_y = oy + off + sgn * r, in_x = ox + off + sgn * s   (off = +pad, sgn = -1)
+// in_y = oy + pad - r, in_x = ox + pad - s
 template <int SLOTS, bool ONE_TAP> struct GatherKC {
     static constexpr bool KC = true;
     static constexpr bool kFence = false;
     const char *base;
-    int IH, IW, OH, OW, R, S, off, sgn, Ch; // Ch: channels per pixel of the source
+    int IH, IW, OH, OW, R, S, pad, Ch; // Ch: channels per pixel of the source
     int rows, K;
-    int32_t pix[SLOTS];   // element offset of source pixel (n, oy + off, ox + off), may be negative
+    int32_t pix[SLOTS];   // element offset of source pixel (n, oy + pad, ox + pad): of tap 0
     uint32_t taps[SLOTS]; // bit t set: tap t reads inside the image
     // per K tile, when a tile lies inside one tap (Ch a multiple of the tile depth): the tap and the offset of the
     // tile's first channel relative to pix[]
@@ -70,11 +70,11 @@ template <int SLOTS, bool ONE_TAP> struct GatherKC {
         row = row < rows ? row : rows - 1;
         const int n = row / (OH * OW), rem = row - n * (OH * OW);
         const int oy = rem / OW, ox = rem - oy * OW;
-        pix[slot] = ((n * IH + oy + off) * IW + ox + off) * Ch;
+        pix[slot] = ((n * IH + oy + pad) * IW + ox + pad) * Ch;
         uint32_t m = 0;
         for (int r = 0; r < R; ++r)
             for (int s = 0; s < S; ++s) {
-                const int iy = oy + off + sgn * r, ix = ox + off + sgn * s;
+                const int iy = oy + pad - r, ix = ox + pad - s;
                 if (iy >= 0 && iy < IH && ix >= 0 && ix < IW) m |= 1u << (r * S + s);
             }
         taps[slot] = m;
@@ -85,7 +85,7 @@ template <int SLOTS, bool ONE_TAP> struct GatherKC {
         const int kk = k0 < K ? k0 : 0;
         tile_tap = kk / Ch;
         const int r = tile_tap / S, s = tile_tap - r * S;
-        tile_delta = sgn * (r * IW + s) * Ch + (kk - tile_tap * Ch);
+        tile_delta = (kk - tile_tap * Ch) - (r * IW + s) * Ch;
     }
     __device__ __forceinline__ u32x4 load_masked(int slot, int k) const
     {
@@ -96,7 +96,7 @@ template <int SLOTS, bool ONE_TAP> struct GatherKC {
         const int tap = k / Ch, c = k - tap * Ch;
         const int r = tap / S, s = tap - r * S;
         const bool ok = k < K && ((taps[slot] >> tap) & 1u);
-        const int32_t o = pix[slot] + sgn * (r * IW + s) * Ch + c;
+        const int32_t o = pix[slot] - (r * IW + s) * Ch + c;
         return and_mask(load16(base, ok ? o : 0), ok);
     }
     __device__ __forceinline__ u32x4 load(int slot, int k) const { return load_masked(slot, k); }
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(WN * 128, WN / 2) void conv_gather_a_kernel(const C
     la.base = reinterpret_cast<const char *>(p.A[t.shard]);
     la.R = g.R; la.S = g.S;
     la.rows = p.M; la.K = p.K;
-    la.IH = g.P; la.IW = g.Q; la.OH = g.H; la.OW = g.W; la.off = g.pad; la.sgn = -1; la.Ch = g.Ks;
+    la.IH = g.P; la.IW = g.Q; la.OH = g.H; la.OW = g.W; la.pad = g.pad; la.Ch = g.Ks;
     FilterRC<core::Slots<BN, false, NT>::value> lb;
     lb.base = reinterpret_cast<const char *>(p.B[t.shard]);
     lb.RS = g.R * g.S; lb.Cs = g.Cs; lb.Ks = g.Ks; lb.rows = p.N; lb.K = p.K;
@@ -732,7 +732,8 @@ template <typename Kern> tt_status launch(Kern kern, size_t smem, ConvParams &p,
 }
 
 // Tile choice as for the dense products: 256 x 256 with eight waves when the launch has enough tiles, else 256 x 128
-// or 128 x 128 with four waves.  TT_CONV_TILE=0|1|2 overrides (tuning aid).
+// or 128 x 128 with four waves.  TT_CONV_TILE=0|1|2 overrides (tuning aid; forward products know 256 x 256, also as 3, and
+// four waves).
 int conv_tile(int64_t M, int64_t N, int count)
 {
     const int forced = tuning_int("TT_CONV_TILE", -1);

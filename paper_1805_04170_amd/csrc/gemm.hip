@@ -58,7 +58,7 @@ __device__ __forceinline__ void run_bf16_tile(const P &p, int logical, uint16_t 
 }
 
 template <int BM, int BN, int WM, int WN, int DEPTH, bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC>
-__global__ __launch_bounds__(WM * WN * 64, (WM * WN / 4) * (DEPTH == 0 ? (BM == 128 ? 3 : 2) : 1)) void gemm_bf16_kernel(const GemmParams p)
+__global__ __launch_bounds__(WM * WN * 64, WM * WN / 4) void gemm_bf16_kernel(const GemmParams p)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     const int logical = core::logical_block(p.per_xcd, p.total);
@@ -199,17 +199,16 @@ tt_status launch_mfma_cfg(GemmParams &p, int count, hipStream_t s)
     return hipGetLastError() == hipSuccess ? TT_OK : TT_EDEVICE;
 }
 
-// Tile choice (TT_GEMM_TILE=0..5 overrides; tuning aid).
+// Tile choice (TT_GEMM_TILE overrides; tuning aid).
 //   5: 256 x 256, whenever the launch has enough tiles to put work on at least half the CUs: the large tile halves operand
-//      traffic per flop.  (Straight into LDS; forced, the register-staged kernel of that size.)
+//      traffic per flop.  (The persistent engine, or gemm_core2.h.)
 //   0: 256 x 128, four waves, two K tiles prefetched in registers: long K loops with few column tiles.
 //   1: 128 x 128, four waves, up to two workgroups per CU: small products and short K loops.
-//   2, 3, 4: 256 x 256 four-wave, 256 x 128 and 128 x 128 single-LDS-buffer variants kept for experiments.
-//   8: 256 x 256, eight waves, second engine (gemm_core2.h): tiles loaded straight into LDS.
+//   8 (forced only): 256 x 256 on gemm_core2.h.
 int pick_tile(int64_t M, int64_t N, int64_t K, int count)
 {
     const int forced = tuning_int("TT_GEMM_TILE", -1);
-    if ((forced >= 0 && forced <= 5) || forced == 8) return forced;
+    if (forced == 0 || forced == 1 || forced == 5 || forced == 8) return forced;
     const int64_t big = ((M + 255) / 256) * ((N + 255) / 256) * count;
     if (M > 128 && N > 128 && big >= 128) return 5;
     return (M > 128 && K >= 1024) ? 0 : 1;
@@ -247,10 +246,6 @@ int rows_into_lds(int64_t M, int64_t N, int64_t K, int64_t outs, bool b_kc)
 template <bool KMASK, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_mfma_tile(GemmParams &p, int count, hipStream_t s)
 {
     const int tile = pick_tile(p.M, p.N, p.ksplit > 1 ? p.kchunk : p.K, count * p.ksplit);
-    if (tile == 5) return launch_mfma_cfg<256, 256, 2, 4, 1, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
-    if (tile == 4) return launch_mfma_cfg<128, 128, 2, 2, 0, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
-    if (tile == 3) return launch_mfma_cfg<256, 128, 2, 2, 0, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
-    if (tile == 2) return launch_mfma_cfg<256, 256, 2, 2, 1, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     if (tile == 0) return launch_mfma_cfg<256, 128, 2, 2, 2, KMASK, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     if (tuning_int("TT_GEMM_TILE", -1) < 0) {
         // Few rows (a small batch against streamed weights): a 128-row tile would take in, store to LDS and multiply rows that
@@ -278,7 +273,7 @@ template <bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_mfma_k
             if (rows == 32) return launch_rows_cfg<32, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
         if (rows == 64) return launch_rows_cfg<64, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     }
-    if ((tile == 8 || (tile == 5 && tuning_int("TT_GEMM_TILE", -1) < 0)) && p.M >= 8 && p.N >= 8)
+    if ((tile == 8 || tile == 5) && p.M >= 8 && p.N >= 8) // (chosen, 5 has far more; forced, it may not)
         return launch_v2<A_KC, B_KC, OUT_BF16, VEC>(p, count, s);
     return p.K % core::BK ? launch_mfma_tile<true, A_KC, B_KC, OUT_BF16, VEC>(p, count, s)
                           : launch_mfma_tile<false, A_KC, B_KC, OUT_BF16, VEC>(p, count, s);

@@ -123,8 +123,10 @@ template <int KT, bool NTS, bool TAIL> tt_status launch_tail5(core5::Params5 &p,
 template <int KT> tt_status launch_cfg5(core5::Params5 &p, hipStream_t s)
 {
     // (rows that begin inside a 64-byte piece: see mma::store_block)
-    if (p.ldc % 32 == 0) return p.K == KT * 16 ? launch_tail5<KT, true, false>(p, s) : launch_tail5<KT, true, true>(p, s);
-    return p.K == KT * 16 ? launch_tail5<KT, false, false>(p, s) : launch_tail5<KT, false, true>(p, s);
+    const bool nts = p.ldc % 32 == 0;
+    if (p.K == KT * 16) return nts ? launch_tail5<KT, true, false>(p, s) : launch_tail5<KT, false, false>(p, s);
+    if constexpr (KT == 32 && !kTuning) return TT_EUNSUPPORTED; // (K between 256 and 512 goes elsewhere, launch_gemm)
+    else return nts ? launch_tail5<KT, true, true>(p, s) : launch_tail5<KT, false, true>(p, s);
 }
 
 int cu_count()

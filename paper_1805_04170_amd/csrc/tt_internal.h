@@ -9,6 +9,11 @@ namespace tt {
 
 // Launch heuristics can be overridden through environment variables only in development builds (-DTT_TUNING); the
 // product build reads no environment and every launch decision is a pure function of the call's arguments.
+#ifdef TT_TUNING
+constexpr bool kTuning = true;
+#else
+constexpr bool kTuning = false;
+#endif
 inline int tuning_int(const char *name, int dflt)
 {
 #ifdef TT_TUNING
@@ -19,7 +24,6 @@ inline int tuning_int(const char *name, int dflt)
     return dflt;
 #endif
 }
-
 
 constexpr int kMaxShards = 1 << TT_MAX_K;
 
