@@ -38,7 +38,7 @@ struct ConvParams {
     void *C[kMaxShards];
     ConvGeom g;
     int32_t M, N, K, ldc;
-    int32_t tiles_m, tiles_n, per_xcd, total, relu;
+    int32_t tiles_m, tiles_n, per_xcd, total, relu, nts;
     // Fused shards (forward kernel only): members > 1 means one product covers `members` shards that share the left
     // operand; its N columns are those shards' column blocks side by side, member_cols (a multiple of 64) each, B is
     // their filter blocks lying one after the other in memory, and the result columns of member m of group g go to
@@ -276,7 +276,7 @@ template <int BM, bool OUT_BF16> __global__ __launch_bounds__(core2::kThreads2, 
         Cw = reinterpret_cast<char *>(p.C[t.shard * p.members + m]) - (ptrdiff_t)m * p.member_cols * (OUT_BF16 ? 2 : 4);
         ldc = p.member_cols;
     }
-    core2::tile_product2<OUT_BF16, true, BM>(la, lb, Cw, ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, reinterpret_cast<char *>(smem));
+    core2::tile_product2<OUT_BF16, true, BM>(la, lb, Cw, ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, reinterpret_cast<char *>(smem), p.nts != 0);
 }
 
 template <int BM, int BN, int WN, int DEPTH, bool KMASK, bool OUT_BF16>
@@ -318,7 +318,7 @@ template <int BM, int BN, int NS, bool OUT_BF16> __global__ __launch_bounds__(co
         Cw = reinterpret_cast<char *>(p.C[t.shard * p.members + m]) - (ptrdiff_t)m * p.member_cols * (OUT_BF16 ? 2 : 4);
         ldc = p.member_cols;
     }
-    core2::tile_product<OUT_BF16, true, BM, BN, 4 / WN, WN, NS>(la, lb, Cw, ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, reinterpret_cast<char *>(smem));
+    core2::tile_product<OUT_BF16, true, BM, BN, 4 / WN, WN, NS>(la, lb, Cw, ldc, p.M, p.N, p.K, t.m0, t.n0, p.relu != 0, reinterpret_cast<char *>(smem), p.nts != 0);
 }
 
 // ---- weight gradient with the reduction over pixels re-cut evenly --------------------------------------------------
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(core2::kThreads2, BM == 64 ? 4 : 2) void conv_wgrad
     lb.H = g.H; lb.W = g.W; lb.P = g.P; lb.Q = g.Q; lb.S = g.S; lb.pad = g.pad; lb.Cs = g.Cs; lb.rows = p.N; lb.Ns = g.Ns;
     lb.s16 = pixel_step(16, g.P, g.Q);
     lb.s64 = pixel_step(64, g.P, g.Q);
-    core2::tile_product2<false, true, BM>(la, lb, p.C[bp], p.ldc, p.M, p.N, K, m0, n0, false, reinterpret_cast<char *>(smem));
+    core2::tile_product2<false, true, BM>(la, lb, p.C[bp], p.ldc, p.M, p.N, K, m0, n0, false, reinterpret_cast<char *>(smem), p.nts != 0);
 }
 
 // Filters [Ks][R][S][Cs] -> [Cs][R][S][Ks] with the taps reversed: with these the gradient w.r.t. the input IS a forward
@@ -930,6 +930,7 @@ tt_status launch_conv(int op, int count, const void *const *A, const void *const
     else return TT_EINVAL;
     if (K < 8) return TT_EUNSUPPORTED;
     p.M = (int32_t)M; p.N = (int32_t)N; p.K = (int32_t)K; p.ldc = (int32_t)N;
+    p.nts = non_temporal_results(N * (int64_t)ob, M * N * (int64_t)ob * count);
     // algorithmic bytes: each tensor of the shard touched once
     const uint64_t x_b = (uint64_t)(Ns * H * W * Cs) * 2, y_b = (uint64_t)(Ns * P * Q * Ks), w_b = (uint64_t)(Ks * R * S * Cs);
     const uint64_t bytes = op == TT_OP_FWD ? x_b + w_b * 2 + y_b * ob
@@ -1010,6 +1011,7 @@ tt_status launch_conv_wgrad_split(int k, int nblk, int nred, const uint8_t *blk_
     p.members = 1;
     p.member_cols = 0;
     p.M = (int32_t)Ks; p.N = (int32_t)(R * S * Cs); p.K = (int32_t)pixels; p.ldc = p.N;
+    p.nts = non_temporal_results(4 * (int64_t)p.N, 4 * (int64_t)p.M * p.N * nblk * parts);
     w.sp.parts = parts; w.sp.nred = nred; w.sp.ktps = (int32_t)ktps;
     const uint64_t x_b = (uint64_t)(Ns * H * W * Cs) * 2, y_b = (uint64_t)(pixels * Ks) * 2, w_b = (uint64_t)(Ks * R * S * Cs) * 4;
     ProfileScope scope(stream, TT_K_CONV_WGRAD, n, p.M, p.N, p.K, (x_b + y_b) * (uint64_t)n + w_b * (uint64_t)(nblk * parts),
@@ -1114,6 +1116,7 @@ tt_status launch_conv_fused(int op, int groups, int members, const void *const *
     p.members = members;
     p.member_cols = (int32_t)cols;
     p.M = (int32_t)M; p.N = (int32_t)N; p.K = (int32_t)K; p.ldc = (int32_t)N;
+    p.nts = non_temporal_results(cols * (obf ? 2 : 4), M * N * (obf ? 2 : 4) * groups);
     return obf ? launch_gather_a<0, true>(p, groups, s) : launch_gather_a<0, false>(p, groups, s);
 }
 

@@ -27,6 +27,7 @@ template <int NS, int NC> struct GemmParamsT { // tables of NS shards and NC out
     int32_t per_xcd;  // logical workgroups per XCD (grid = per_xcd * 8)
     int32_t total;    // tiles_m * tiles_n * count * ksplit
     int32_t relu;
+    int32_t nts;      // non-temporal stores (the engines of gemm_mma.h)
     int32_t ksplit;   // each shard's K range is cut into ksplit chunks of kchunk (a multiple of 64); chunk c of shard s
     int32_t kchunk;   // writes its own output C[s * ksplit + c] (partial sums, added up by the reduction kernel)
 };
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(core2::kThreads2, 2) void gemm_bf16_v2_kernel(const
     LB lb;
     lb.base = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
     lb.ld = p.ldb; lb.rows = p.N; lb.K = klen;
-    core2::tile_product2<OUT_BF16, VEC>(la, lb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * 256, tn * 256, p.relu != 0, smem2);
+    core2::tile_product2<OUT_BF16, VEC>(la, lb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * 256, tn * 256, p.relu != 0, smem2, p.nts != 0);
 }
 
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_v2(GemmParams &p, int count, hipStream_t s)
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(core::kThreads, 2) void gemm_bf16_rows_kernel(const
     LB lb;
     lb.base = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
     lb.ld = p.ldb; lb.rows = p.N; lb.K = klen;
-    core2::tile_product<OUT_BF16, VEC, BM, 128, 2, 2, kRowsStages>(la, lb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * BM, tn * 128, p.relu != 0, smem2);
+    core2::tile_product<OUT_BF16, VEC, BM, 128, 2, 2, kRowsStages>(la, lb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * BM, tn * 128, p.relu != 0, smem2, p.nts != 0);
 }
 
 template <int BM, bool A_KC, bool B_KC, bool OUT_BF16, bool VEC> tt_status launch_rows_cfg(GemmParams &p, int count, hipStream_t s)
@@ -342,6 +343,7 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
         p.lda = (int32_t)a_contig;
         p.ldb = (int32_t)b_contig;
         p.ldc = (int32_t)N;
+        p.nts = non_temporal_results(N * (int64_t)out_b, M * N * (int64_t)out_b * count * ksplit);
         p.ksplit = ksplit;
         p.kchunk = (int32_t)kchunk;
         const bool a_kc = !trans_a, b_kc = trans_b != 0;
@@ -440,6 +442,7 @@ template <class P> void fill_pair_half(P *p, const GemmCall &c, bool dgrad, int 
     p->total = p->tiles_m * p->tiles_n * c.count * c.ksplit;
     p->per_xcd = (p->total + kXcds - 1) / kXcds;
     p->relu = 0;
+    p->nts = 1;
     p->ksplit = c.ksplit;
     p->kchunk = (int32_t)(c.ksplit == 1 ? c.K : ((c.K + c.ksplit - 1) / c.ksplit + 63) / 64 * 64);
 }

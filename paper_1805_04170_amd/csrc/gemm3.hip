@@ -40,7 +40,7 @@ __global__ __launch_bounds__(core4::kThreads4, 2) void gemm_bf16_v4_kernel(const
     const char *abase = reinterpret_cast<const char *>(p.A[shard]) + (size_t)kbeg * (A_KC ? 2 : 2 * (size_t)p.lda);
     const char *bbase = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
     core4::tile_product4<A_KC, B_KC, OUT_BF16, STAGED, TAIL>(abase, p.lda, bbase, p.ldb, p.C[vshard], p.ldc, p.M, p.N, klen,
-                                                       tm * core4::BM4, tn * core4::BN4, p.relu != 0, smem4);
+                                                       tm * core4::BM4, tn * core4::BN4, p.relu != 0, smem4, p.nts != 0);
 }
 
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL> tt_status launch_tail4(core3::Params3 &p, hipStream_t s)
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(core6::kThreads6, 2) void gemm_bf16_v6_kernel(const
     const char *abase = reinterpret_cast<const char *>(p.A[shard]) + (size_t)kbeg * (A_KC ? 2 : 2 * (size_t)p.lda);
     const char *bbase = reinterpret_cast<const char *>(p.B[shard]) + (size_t)kbeg * (B_KC ? 2 : 2 * (size_t)p.ldb);
     core6::tile_product6<A_KC, B_KC, OUT_BF16, STAGED, TAIL>(abase, p.lda, bbase, p.ldb, p.C[vshard], p.ldc, p.M, p.N, klen, tm * core6::BM6,
-                                                       tn * core6::BN6, p.relu != 0, smem4);
+                                                       tn * core6::BN6, p.relu != 0, smem4, p.nts != 0);
 }
 
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL> tt_status launch_tail6(core3::Params3 &p, hipStream_t s)
@@ -166,6 +166,12 @@ template <bool A_KC, bool B_KC> tt_status launch_runs(core3::Params3 &p, int out
     return launch_cfg<A_KC, B_KC, false, true, SPREAD, true>(p, s);
 }
 
+void set_store(core3::Params3 *p, int out_dtype, int64_t outs)
+{
+    const int64_t row = (out_dtype == TT_BF16 ? int64_t(2) : int64_t(4)) * p->N;
+    p->nts = non_temporal_results(row, row * p->M * outs);
+}
+
 } // namespace
 
 // C_s = A_s^T B_s, A_s stored K x M, B_s stored K x N, K up to 512, bf16 result with 16-byte rows.
@@ -190,6 +196,7 @@ tt_status launch_gemm_v4(int count, const void *const *A, const void *const *B, 
     const tt_status st = fill_params3(&p, core4::BM4, core4::BN4, 1, 0, count, A, B, C, M, N, K, lda, ldb, ldc, a_kc,
                                       b_kc, relu, ksplit, kchunk);
     if (st != TT_OK) return st;
+    set_store(&p, out_dtype, count * ksplit);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (a_kc && b_kc) return launch_layout4<true, true>(p, out_dtype, vec, s);
     if (a_kc && !b_kc) return launch_layout4<true, false>(p, out_dtype, vec, s);
@@ -205,6 +212,7 @@ tt_status launch_gemm_v6(int count, const void *const *A, const void *const *B, 
     const tt_status st = fill_params3(&p, core6::BM6, core6::BN6, 1, 0, count, A, B, C, M, N, K, lda, ldb, ldc, a_kc, b_kc,
                                       relu, ksplit, kchunk);
     if (st != TT_OK) return st;
+    set_store(&p, out_dtype, count * ksplit);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (a_kc && b_kc) return launch_layout6<true, true>(p, out_dtype, vec, s);
     if (a_kc && !b_kc) return launch_layout6<true, false>(p, out_dtype, vec, s);
@@ -220,6 +228,7 @@ tt_status launch_gemm_v3(int count, const void *const *A, const void *const *B, 
     const tt_status st = fill_params3(&p, core3::BM3, core3::BN3, 64, cu_count(), count, A, B, C, M, N, K, lda, ldb, ldc, a_kc,
                                       b_kc, relu, ksplit, kchunk);
     if (st != TT_OK) return st;
+    set_store(&p, out_dtype, count * ksplit);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (a_kc && b_kc) return launch_layout<true, true>(p, out_dtype, vec, s);
     if (a_kc && !b_kc) return launch_layout<true, false>(p, out_dtype, vec, s);
@@ -234,6 +243,7 @@ tt_status launch_gemm_v3_runs(int nblk, int nred, int parts, const void *const *
     core3::Params3 p;
     const tt_status st = fill_params3_runs(&p, cu_count(), nblk, nred, parts, A, B, C, M, N, K, lda, ldb, ldc, a_kc, b_kc, relu);
     if (st != TT_OK) return st;
+    set_store(&p, out_dtype, nblk * parts);
     if (!a_kc && b_kc) return TT_EUNSUPPORTED;
     // (recorded only once the launch is certain: a refused product is launched, and recorded, shard by shard)
     ProfileScope scope(stream, !a_kc ? TT_K_GEMM_TN : b_kc ? TT_K_GEMM_NT : TT_K_GEMM_NN, nblk * nred, M, N, K,

@@ -39,6 +39,7 @@ inline tt_status fill_params3(core3::Params3 *p, int tile_m, int tile_n, int k_t
         if (per_xcd_cus < p->wg_per_xcd) p->wg_per_xcd = per_xcd_cus;
     }
     p->relu = relu;
+    p->nts = 1;
     p->ksplit = ksplit;
     p->kchunk = (int32_t)(ksplit > 1 ? kchunk : K);
     p->nred = p->parts = 1;

@@ -122,7 +122,8 @@ static_assert(smem_bytes2<BM2>() == kSmemBytes && 8 * mma::kStripBytes <= smem_b
 
 // C tile (m0, n0) of C = A B on WM x WN waves and NS stages of LDS; smem: NS (BM + BN) 128 bytes, 16-byte aligned.
 template <bool OUT_BF16, bool VEC_STORE, int BM, int BN, int WM, int WN, int NS, class LA, class LB>
-__device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, int M, int N, int K, int m0, int n0, bool relu, char *smem)
+__device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, int M, int N, int K, int m0, int n0, bool relu, char *smem,
+                                             bool nts = true)
 {
     constexpr int NT = WM * WN * 64, TM = BM / WM / 16, TN = BN / WN / 16;
     static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0 && (LA::KC || 512 % BM == 0), "tile sides");
@@ -205,7 +206,7 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, 
     // the re-fetches have landed and all fragment reads are done before the stages are reused
     __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm_lds(0));
     __syncthreads();
-    mma::store_block<OUT_BF16, VEC_STORE>(acc, smem + wave * mma::kStripBytes, Cv, ldc, m0 + wm0, n0 + wn0, M, N, relu, lane);
+    mma::store_block<OUT_BF16, VEC_STORE>(acc, smem + wave * mma::kStripBytes, Cv, ldc, m0 + wm0, n0 + wn0, M, N, relu, lane, nts);
 }
 
 // ... on BM x 256 tiles; 512 threads; smem: smem_bytes2<BM>(), 16-byte aligned.
@@ -213,9 +214,9 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, 
 // tiles come out at better numbers (conv.hip).
 template <bool OUT_BF16, bool VEC_STORE, int BM = BM2, class LA, class LB>
 __device__ __forceinline__ void tile_product2(LA &la, LB &lb, void *Cv, int ldc, int M, int N, int K, int m0,
-                                              int n0, bool relu, char *smem)
+                                              int n0, bool relu, char *smem, bool nts = true)
 {
-    tile_product<OUT_BF16, VEC_STORE, BM, BN2, 2, 4, 2>(la, lb, Cv, ldc, M, N, K, m0, n0, relu, smem);
+    tile_product<OUT_BF16, VEC_STORE, BM, BN2, 2, 4, 2>(la, lb, Cv, ldc, M, N, K, m0, n0, relu, smem, nts);
 }
 
 } // namespace core2

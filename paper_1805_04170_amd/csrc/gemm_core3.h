@@ -51,6 +51,7 @@ struct Params3 {
     int32_t wg_per_xcd;  // resident workgroups per XCD (grid = 8 * wg_per_xcd)
     int32_t total;       // tiles_m * tiles_n * count * ksplit
     int32_t relu;
+    int32_t nts;         // non-temporal stores
     int32_t ksplit, kchunk;
     int32_t nred, parts; // RUNS (below): shards per output block, runs their K tiles are cut into
 };
@@ -256,7 +257,7 @@ __device__ __forceinline__ void run_tiles(const Params3 &p, char *smem)
             fb.advance(p);
         }
         mma::store_block<OUT_BF16, STAGED>(acc, smem + NS * kStage3 + wave * mma::kStripBytes, p.C[cur.vshard], p.ldc, cur.m0 + wm0,
-                                           cur.n0 + wn0, p.M, p.N, relu, lane);
+                                           cur.n0 + wn0, p.M, p.N, relu, lane, p.nts != 0);
         ++jc;
         if (!tile_of<RUNS>(p, jc, &cur)) break;
     }

@@ -75,7 +75,7 @@ template <int ROWS, bool KC> __device__ __forceinline__ int k_of(int i)
 // TAIL: klen is no multiple of 32, what is missing is read as zeros
 template <bool A_KC, bool B_KC, bool OUT_BF16, bool STAGED, bool TAIL = false>
 __device__ __forceinline__ void tile_product4(const char *abase, int lda, const char *bbase, int ldb, void *Cv, int ldc, int M,
-                                              int N, int klen, int m0, int n0, bool relu, char *smem)
+                                              int N, int klen, int m0, int n0, bool relu, char *smem, bool nts = true)
 {
     constexpr int TM = 8, TN = 4, WN = 2; // 2 x 2 waves, 128 x 64 per wave
     constexpr int LPS = kLoadsA + kLoadsB;
@@ -146,7 +146,7 @@ __device__ __forceinline__ void tile_product4(const char *abase, int lda, const 
     // the re-fetches issued past the end have landed and every wave is done with the ring: it can be reused / given up
     __builtin_amdgcn_s_waitcnt(core3::waitcnt_vm_lds(0));
     __syncthreads();
-    mma::store_block<OUT_BF16, STAGED>(acc, smem + wave * mma::kStripBytes, Cv, ldc, m0 + wm0, n0 + wn0, M, N, relu, lane);
+    mma::store_block<OUT_BF16, STAGED>(acc, smem + wave * mma::kStripBytes, Cv, ldc, m0 + wm0, n0 + wn0, M, N, relu, lane, nts);
 }
 
 } // namespace core4

@@ -189,14 +189,12 @@ __device__ __forceinline__ void store_block_as(const f32x4 (&acc)[TM][TN], char 
         }
 }
 
-// Non-temporal stores (fp32 partial sums of 16 x (512 x 2048 x 2048) 61 us, plain ones 66), except into rows that begin inside a
-// 64-byte piece of memory: parts of such a piece leave with different stores, and non-temporal ones are not put together again
-// (9072 x 11856 of K = 40 on gemm_core5.h 129 -> 86 us with plain ones, rows of 64-byte pieces 37.6 / 41.9 at 6936 x 7456).
+// nts: non-temporal stores (non_temporal_results in tt_internal.h says when)
 template <bool OUT_BF16, bool VEC, int TM, int TN>
 __device__ __forceinline__ void store_block(const f32x4 (&acc)[TM][TN], char *strip, void *Cv, int ldc, int row0, int col0, int M, int N,
-                                            bool relu, int lane)
+                                            bool relu, int lane, bool nts)
 {
-    if (!VEC || ldc % (OUT_BF16 ? 32 : 16) == 0) store_block_as<OUT_BF16, VEC, true>(acc, strip, Cv, ldc, row0, col0, M, N, relu, lane);
+    if (!VEC || nts) store_block_as<OUT_BF16, VEC, true>(acc, strip, Cv, ldc, row0, col0, M, N, relu, lane);
     else store_block_as<OUT_BF16, VEC, false>(acc, strip, Cv, ldc, row0, col0, M, N, relu, lane);
 }
 

@@ -25,6 +25,20 @@ inline int tuning_int(const char *name, int dflt)
 #endif
 }
 
+// Whether a launch of the tile engines (gemm_mma.h) stores its results, rows of row_bytes, all_bytes together, non-temporally.
+// Rows of whole 64-byte pieces: always (fp32 partial sums of 16 x (512 x 2048 x 2048) 61 us, plain ones 66).  Rows that begin inside
+// such a piece leave parts of it with different stores, and non-temporal ones are not put together again: plain / non-temporal, us,
+// 8 x (M x 1000) fp32 of 12 MB 10.1 / 9.7, 16 MB 10.6 / 10.4, 24 MB 11.3 / 13.8, 48 MB 16.9 / 25.5; 8 x (M x 2040) of 16 MB 10.2 / 10.6, 32 MB
+// 12.9 / 16.6; bf16 8 x (M x 1000) of 16 MB 10.8 / 10.8, 32 MB 16.7 / 21.0; 8 x (M x 1032) of 24 MB 14.8 / 16.7.  Up to 16 MB, where neither is
+// the faster one by itself, plain stores cost the launches behind them: they push operands out of the caches (AlexNet's last layer,
+// partial sums of 256 x 1000: backward launch 13.6 us behind non-temporal ones, 16.5 behind plain ones).
+inline int non_temporal_results(int64_t row_bytes, int64_t all_bytes)
+{
+    const int forced = tuning_int("TT_NTS", -1);
+    if (forced >= 0) return forced;
+    return row_bytes % 64 == 0 || all_bytes <= (int64_t(16) << 20);
+}
+
 constexpr int kMaxShards = 1 << TT_MAX_K;
 
 // Letter used internally for a cut whose shards hold different partial sums (output of form F3).

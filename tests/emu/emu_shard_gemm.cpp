@@ -21,6 +21,7 @@ alignas(16) thread_local char smem2[160 * 1024], smem3[160 * 1024], smem4[160 * 
 #include "gemm.hip"
 #include "gemm3.hip"
 #include "gemm_small.hip"
+#include "exec_common.h"
 
 namespace tt {
 ProfileScope::ProfileScope(void *, int, int, int64_t, int64_t, int64_t, uint64_t, uint64_t) : slot(-1), stream(nullptr) {}
@@ -115,6 +116,16 @@ int main(int argc, char **argv)
         void *none[64] = {};
         const int64_t M = std::atol(argv[2]), N = std::atol(argv[3]), K = std::atol(argv[4]);
         std::printf("%d\n", tt::fill_params5(&p, 256, 1, none, none, none, M, N, K, M, N, N, 0) == TT_OK);
+        return 0;
+    }
+    // emu_shard_gemm store row_bytes all_bytes: whether results leave with non-temporal stores
+    if (argc == 4 && std::strcmp(argv[1], "store") == 0) {
+        std::printf("%d\n", tt::non_temporal_results(std::atol(argv[2]), std::atol(argv[3])));
+        return 0;
+    }
+    // emu_shard_gemm runs M N K blocks shards_per_block: into how many runs their K tiles are cut
+    if (argc == 7 && std::strcmp(argv[1], "runs") == 0) {
+        std::printf("%d\n", tt::pick_runs(std::atol(argv[2]), std::atol(argv[3]), std::atol(argv[4]), std::atoi(argv[5]), std::atoi(argv[6])));
         return 0;
     }
     // emu_shard_gemm last_chunk

@@ -377,3 +377,9 @@ def test_a_wait_that_is_too_short_shows_in_the_values(lockstep_gemm, tmp_path, e
     with pytest.raises(AssertionError) as e:
         check(lockstep_gemm, str(tmp_path), *shape, "bf16", "f32", False, 98, env=dict(env, EMU_VMCNT_SLACK="2"))
     assert str(e.value).startswith("(")
+
+
+@pytest.mark.parametrize("row,total,nts", [(4096, 2 ** 30, 1), (4000, 8 * 256 * 4000, 1), (4000, 2 ** 24, 1), (4000, 2 ** 24 + 4000, 0), (2000, 2 ** 26, 0), (2048, 2 ** 26, 1)])
+def test_rows_that_begin_inside_a_64_byte_piece_are_stored_for_the_caches_from_16_mb_on(lockstep_gemm, row, total, nts):
+    # smaller results would push the operands of the launches behind them out
+    assert int(subprocess.run([lockstep_gemm, "store", str(row), str(total)], capture_output=True, text=True, check=True).stdout) == nts
