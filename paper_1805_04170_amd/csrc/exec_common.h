@@ -167,14 +167,15 @@ inline int pick_ksplit(int64_t M, int64_t N, int64_t K, int count, int dtype, bo
 // Shards that an F3 cut makes add up into the same output block, and where they run one product each, every one of them
 // writes its whole block as an fp32 partial sum for the reduction to read again (16 x 512 x 8192 in the F3^4 layer: 268 MB).
 // How a block's K range is cut is free, so it is cut into as many runs as fill the chip, and no more (gemm_core3.h).
-// 16 shards of 512 x 8192 x 512: product 105 -> 72 us, reduction 49 -> 16 (4 runs, one item of 32 K tiles per CU).  Forward calls, a
-// product per shard / runs, us: 256 x 8192 x 8192 on 16 shards 94 / 71, 2048 x 8192-2048 on 8 120 / 95, 2048 x 8192-8192 on 4 324 / 259, 520 x
-// 8192-8192 on 4 137 / 122, 520 x 4096-12288 on 4 127 / 114; next to the line 264 x 16384-4096 on 4 85 / 84, 512 x 16384-8192 on 8 in two
-// blocks 150 / 153.  Sums of more values of K are held in fp32 than before; of the stored bf16 results 3 in 10000 instead of 2 are not
+// Forward calls, a product per shard / runs, us: 512 x 8192-8192 on 16 shards 138 / 79 (4 runs, one item of 32 K tiles per CU), 256 x 8192-8192
+// on 16 76 / 56, 2048 x 8192-2048 on 8 104 / 81, 2048 x 8192-8192 on 4 285 / 210, 520 x 8192-8192 on 4 114 / 103, 520 x 4096-12288 on 4 106 / 90,
+// 384 x 8192-12288 on 8 122 / 107, 1536 x 4096-8192 on 2 126 / 99; next to the line 264 x 16384-4096 on 4 64 / 92 (4 runs), 512 x 16384-8192 on
+// 8 in two blocks 150 / 150.  Sums of more values of K are held in fp32 than before; of the stored bf16 results 3 in 10000 instead of 2 are not
 // the rounded exact value, and their error against 64 bits agrees to seven digits (1.6586029e-3 at 512 x 8192-8192 on 16).
-// Returns the number of runs, or 0 where a product per shard is no slower.  The estimate, in microseconds with all CUs at
-// work: 2.0 per K tile of a 256 x 256 tile, 9 to write its fp32 results (5 in bf16), 5.5 TB/s for the reduction (4 TB/s
-// for the copy into the stored tiling that one bf16 result needs).
+// Returns the number of runs, or 0 where a product per shard is no slower.  The estimate, in microseconds, is the least-squares fit to 60
+// such calls with every number of runs (6.5 % off at the root of the mean square): 1.25 per K tile of a round of 256 x 256 tiles,
+// 0.38 per MB of partial sums, written and read again (0.13 per MB of a single result's fp32 size), 10 to start.  It takes the
+// fastest number of runs, or one within 0.5 % of it, of all the calls above.
 inline int pick_runs(int64_t M, int64_t N, int64_t K, int nblk, int nred)
 {
     if (nred < 2 || K % 64 || N % 8) return 0;
@@ -187,7 +188,7 @@ inline int pick_runs(int64_t M, int64_t N, int64_t K, int nblk, int nred)
     const double blk = 4.0 * (double)M * (double)N * nblk;
     const auto us = [&](int64_t parts) {
         const double rounds = (double)((tiles * parts + cus - 1) / cus), len = (double)((all + parts - 1) / parts);
-        return parts == 1 ? rounds * (len * 2.0 + 5.0) + blk / 4.0e6 : rounds * (len * 2.0 + 9.0) + blk * (double)parts / 5.5e6;
+        return rounds * len * 1.25 + blk * (parts == 1 ? 0.13e-6 : 0.38e-6 * (double)parts) + 10.0;
     };
     int best = 0;
     double best_us = 0.95 * us(nred);

@@ -70,10 +70,13 @@ tt_status filter_view(Sharded *s, const void *const *ptrs, const tt_tiling &t, i
 
 // Number of partial sums per filter block, and the tile engine, for the weight gradient with an evenly cut reduction
 // range.  The work items (output tiles times partial sums) run in rounds of as many as the chip holds; a round takes as long
-// as one item's K tiles; every partial sum is written and read once more by the reduction.  Times in microseconds from
-// measured rates on MI355X with the chip full: engine 1 (256 x 128 tiles, 512 resident) 3.9 us per K tile, engine 2 (256 x 256,
-// 256 resident) 2.6 us, engines 3 and 4 (128 and 64 x 256, 256 and 512 resident) 1.9 and 2.4; 4 us to start and write an item;
-// partial sums at 4 TB/s, at 8 while they stay in the caches.  What it replaced where a shard's pixels are no multiple of 64 or it has at most 128 output channels,
+// as one item's K tiles; every partial sum is written and read once more by the reduction.  Engine 1: 256 x 128 tiles, 512
+// resident; 2: 256 x 256, 256 resident; 3 and 4: 128 and 64 x 256, 256 and 512 resident.  The costs below compare them; as times they
+// are high: filter gradients of VGG-16 conv4 split over the batch take 3.7 us per K tile of a round on engine 1 and 1.7, 1.2 and 1.5
+// on 2, 3 and 4, for 3.9, 2.6, 1.9 and 2.4 here.  With those rates in their place one of eleven filter gradients tried goes elsewhere,
+// and is slower there (96 x 34 x 46 pixels, 128 to 384 channels, 8 shards 217 -> 231).  Rule / fastest of any engine and 20 numbers of
+// sums, us: conv4 229 / 228, 16 x 28 x 28, 512 to 512, not cut 81 / 80, 32 x 56 x 56, 256 to 256, not cut 129 / 128, 64 x 28 x 28, 256 to 512, 4 shards
+// 129 / 129, 64 x 14 x 14, 512 to 512, 8 shards 99 / 98, 32 x 28 x 28, 128 to 128, 4 shards 32 / 32, 24 x 35 x 41, 384 to 64, 8 shards 55 / 51.  What it replaced where a shard's pixels are no multiple of 64 or it has at most 128 output channels,
 // one workgroup per tile and shard (batch-split group of images): 96 x 34 x 46 pixels, 128 to 384 channels, 8 shards 493 -> 266 us;
 // 24 x 35 x 41, 384 to 64, 8 shards 97 -> 38; 14 x 42 x 35, 80 to 96, 1x1 filters, 2 shards 209 -> 23; 32 x 14 x 14, 64 to 64, 8 shards 29 -> 24.
 struct WgradChoice { int parts, engine; };

@@ -383,3 +383,10 @@ def test_a_wait_that_is_too_short_shows_in_the_values(lockstep_gemm, tmp_path, e
 def test_rows_that_begin_inside_a_64_byte_piece_are_stored_for_the_caches_from_16_mb_on(lockstep_gemm, row, total, nts):
     # smaller results would push the operands of the launches behind them out
     assert int(subprocess.run([lockstep_gemm, "store", str(row), str(total)], capture_output=True, text=True, check=True).stdout) == nts
+
+
+@pytest.mark.parametrize("M,N,K,blocks,shards,runs", [(512, 8192, 512, 1, 16, 4), (2048, 2048, 1024, 1, 8, 4), (2048, 8192, 2048, 1, 4, 1), (520, 8192, 2048, 1, 4, 2),
+                                                      (384, 12288, 1024, 1, 8, 2), (520, 12288, 1024, 1, 4, 1), (264, 4096, 4096, 1, 4, 0), (256, 8192, 4096, 2, 4, 0)])
+def test_shards_that_add_up_are_cut_into_the_runs_that_measured_fastest(lockstep_gemm, M, N, K, blocks, shards, runs):
+    r = subprocess.run([lockstep_gemm, "runs"] + [str(v) for v in (M, N, K, blocks, shards)], capture_output=True, text=True, check=True)
+    assert int(r.stdout) == runs
