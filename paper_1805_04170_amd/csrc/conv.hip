@@ -468,7 +468,7 @@ template <bool TAIL> struct SegDenseRC2 {
     {
         constexpr int CPR = ROWS / 8; // chunks per k-row
         const int kr = threadIdx.x / CPR, pc = threadIdx.x % CPR;
-        int r0 = row0 + ((pc ^ ((kr & 3) << 1)) << 3);
+        int r0 = row0 + ((pc ^ mma::rc_swizzle<ROWS>(kr)) << 3);
         r0 = r0 < rows ? r0 : rows - 8; // rows past the end only feed C rows that are never stored
         voff = ((uint32_t)kr * (uint32_t)ld + (uint32_t)r0) * 2u;
         k0 = 0;

@@ -7,7 +7,8 @@
 // each lane chooses WHICH global chunk it fetches, which gives an XOR swizzle for free):
 //   K-contiguous operand  tile[row][8 chunks of 8 k]   chunk position p of row r holds k-chunk p ^ ((r >> 1) & 7);
 //                         fragments are plain 16-byte reads.
-//   row-contiguous operand tile[k][ROWS / 8 chunks of 8 rows]  chunk position p of k-row k holds row-chunk p ^ ((k & 3) << 1);
+//   row-contiguous operand tile[k][ROWS / 8 chunks of 8 rows]  chunk position p of k-row k holds row-chunk p ^ ((k & 3) << 1)
+//                         (64 rows: see rc_swizzle in gemm_mma.h);
 //                         fragments are two ds_read_b64_tr_b16 (LDS transpose reads): within 16 lanes, lane i receives
 //                         element i % 4 of the 4-element rows addressed by lanes 4e + i / 4, e = 0..3, so addressing
 //                         row (k0 + j / 4, rows 4 (j % 4) ..) from lane j hands lane i the values (k0 + e, row i).
@@ -98,7 +99,7 @@ template <int NT> struct DenseRCT {
     {
         constexpr int CPR = ROWS / 8;
         const int kr = threadIdx.x / CPR, pc = threadIdx.x % CPR;
-        int r = row0 + ((pc ^ ((kr & 3) << 1)) << 3);
+        int r = row0 + ((pc ^ mma::rc_swizzle<ROWS>(kr)) << 3);
         r = r < rows ? r : rows - 8;
         voff = ((uint32_t)kr * (uint32_t)ld + (uint32_t)r) * 2u;
         k = 0;
@@ -157,23 +158,22 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, void *Cv, int ldc, 
     la.template begin<BM>(m0);
     lb.template begin<BN>(n0);
     if constexpr (PLAIN_STEP) {
-        // four waves per SIMD cover each other's reads: a tile's fragments when it has landed, the next tile on its way meanwhile
+        // four waves per SIMD cover each other's reads: a tile's fragments when it has landed, the next tile on its way meanwhile.
+        // (What a tile waits for is its predecessor's loads, so what stands in front of these is kept short.)
 #pragma unroll
         for (int i = 0; i < NL; ++i) issue(i, lds0);
         for (int kt = 0; kt < nk; ++kt) {
+            next(kt + 1 < nk);                              // (its divisions while the tile is still on its way)
             __builtin_amdgcn_s_waitcnt(mma::waitcnt_vm(0)); // this wave's chunks of the tile have landed
             __syncthreads();                                // everyone's have; everyone is done reading the other stage
             if (kt + 1 < nk) {
-                next(true);
 #pragma unroll
                 for (int i = 0; i < NL; ++i) issue(i, lds0 + (uint32_t)((kt & 1) ^ 1) * STAGE);
             }
             const char *At = smem + (kt & 1) * STAGE;
             __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_iglp_opt(1);
             mma::read_frags(f0, ra, rb, At, At + A_BYTES, 0);
-            mma::read_frags(f1, ra, rb, At, At + A_BYTES, 1);
-            mma::multiply(acc, f0);
+            mma::k_step<0, false>(acc, f0, f1, ra, rb, At, At + A_BYTES, 1, [](int) {});
             mma::multiply(acc, f1);
             __builtin_amdgcn_sched_barrier(0);
         }

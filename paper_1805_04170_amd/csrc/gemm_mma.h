@@ -29,6 +29,13 @@ using core::u32x4;
 constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 constexpr int waitcnt_vm_lds(int n) { return waitcnt_vm(n) & ~(15 << 8); }
 
+// Row-contiguous operands, tile[k][ROWS / 8 chunks of 8 rows]: chunk position p of k-row k holds row-chunk p ^ rc_swizzle(k).  A
+// transpose read of 16 x 32 takes eight pieces of 32 bytes at a time, of k-rows k0 .. k0 + 3 and k0 + 8 .. k0 + 11.  Tiles of 64 rows
+// (k-rows of 128 bytes, two to a turn of the banks) have all eight in different banks by bits 1 and 3 of k; by bits 0 and 1,
+// as wider tiles, two each share theirs (filter gradient of 24 x 35 x 41 pixels, 384 to 64 channels, 8 shards 55.6 -> 54.5 us with the
+// order of the reads in gemm_core2.h; 0.9 M cycles of conflicts -> 0.6 M in one of 32 x 14 x 14, 64 to 64, 8 shards).
+template <int ROWS> __device__ __forceinline__ int rc_swizzle(int k) { return ROWS == 64 ? (k & 2) | ((k >> 1) & 4) : (k & 3) << 1; }
+
 // Fragments (16 rows x 32 k, 8 values of K per lane) of an operand tile of ROWS rows and 64 k in LDS; layouts as in gemm_core2.h.
 // T: 16-row blocks of a wave, from row w0 on (a multiple of 16 T, of 64 where T is 4 or more).
 // BK = 32: one k-step; rows of 64 bytes, chunk position p of row r holds k-chunk p ^ (-(r >> 2) & 3).
@@ -46,7 +53,7 @@ template <int ROWS, bool KC, int T, int BK = 64> struct Reader {
             const int k = q * 8 + (r >> 2), c = (w0 >> 3) + ((r & 3) >> 1);
 #pragma unroll
             for (int i = 0; i < NOFF; ++i)
-                off[i] = (uint32_t)(k * (ROWS * 2) + (((c + 2 * i) ^ ((k & 3) << 1)) << 4) + (r & 1) * 8);
+                off[i] = (uint32_t)(k * (ROWS * 2) + (((c + 2 * i) ^ rc_swizzle<ROWS>(k)) << 4) + (r & 1) * 8);
         }
     }
     __device__ __forceinline__ bf16x8 read(const char *tile, int ks, int i) const
