@@ -372,7 +372,9 @@ tt_status launch_gemm(int count, const void *const *A, const void *const *B, voi
         //    of 48 KB: the same tile with K tiles of 64 and one workgroup per CU (gemm_core6.h).  gemm_core4.h / gemm_core6.h, eight
         //    shards of 256 rows, us: A B^T to 4096 columns K 256 9.2 / 9.6, 512 13.2 / 12.4, 1024 27.7 / 21.8, 2048 52.5 / 43.3 (1024
         //    columns 7.4 / 8.3, 10.7 / 10.5, 16.5 / 15.2, 28.4 / 24.5); A B 11.2 / 12.0, 15.1 / 15.3, 28.4 / 23.3, 51.5 / 40.4; A^T B to
-        //    2048 columns, K 2048 38.9 / 33.9, 8 x (512 x 512 x 1024) 16.6 / 17.3; 288 tiles of K 1024 A B^T 30.3 / 31.3
+        //    2048 columns, K 2048 38.9 / 33.9, 8 x (512 x 512 x 1024) 16.6 / 17.3; 288 tiles of K 1024 A B^T 30.3 / 31.3.  Short last K tiles:
+        //    A^T B 8 x (1024 x 1024) K 1032 25.5 / 27.0, 2056 38.0 / 39.9, 3000 54.8 / 53.2, 4104 70.6 / 70.4, fp32 4 x (1024 x 2048 x 2088) 44.0 /
+        //    42.5; 8 x (256 x 2048) A B^T K 520 11.9 / 12.6, 1032 24.2 / 21.3, A B K 1032 21.2 / 21.1
         const int64_t kc = ksplit > 1 ? kchunk : K;
         const int64_t tiles128 = ((M + 255) / 256) * ((N + 127) / 128) * count * ksplit;
         if (engine == 6 || (engine == 0 && big_tiles < 200 && M > 128 && N >= 256 && tiles128 <= 256 &&

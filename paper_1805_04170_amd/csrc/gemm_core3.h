@@ -13,9 +13,8 @@
 // Ring shape: two stages of 64 measured best; thinner, deeper rings (BK = 32, four or five stages) fetch half lines of a
 // K-contiguous operand and lose 10 % (gemm_mma.h).
 //
-// LDS layouts follow gemm_core2.h.  Further differences:
-//   - the loads are inline assembly with a scalar base and a 32-bit lane offset, computed once per output tile
-//     (the builtin form makes the compiler put s_waitcnt vmcnt(0) in front of every fragment read);
+// LDS layouts follow gemm_core2.h, and so do the loads (inline assembly, a scalar base and a 32-bit lane offset, computed once per
+// output tile; the builtin form makes the compiler put s_waitcnt vmcnt(0) in front of every fragment read).  Differences:
 //   - K must be a multiple of 64 (no tail handling in the K direction; the launcher falls back otherwise);
 //   - results go through a small wave-private LDS strip that lies outside the ring, so the epilogue needs no workgroup
 //     barrier and never touches a stage that a prefetch may be filling.

@@ -28,16 +28,15 @@
 namespace tt {
 namespace core4 {
 
-
 constexpr int kThreads4 = 256;
 constexpr int BM4 = 256, BN4 = 128, BK4 = 32, NS4 = 3;
 constexpr int kABytes = BM4 * BK4 * 2, kBBytes = BN4 * BK4 * 2, kStage4 = kABytes + kBBytes; // 16 KB + 8 KB
 constexpr size_t kSmem4 = (size_t)NS4 * kStage4;                                              // 72 KB
 constexpr int kLoadsA = kABytes / 16 / kThreads4, kLoadsB = kBBytes / 16 / kThreads4;        // 4 and 2 per thread
 
-// lane offsets of this thread's 16-byte chunks of one operand tile (ROWS x 32), see the layouts above
 using core2::uniform64;
 
+// lane offsets of this thread's 16-byte chunks of one operand tile (ROWS x 32), see the layouts above
 template <int ROWS, bool KC> __device__ __forceinline__ void chunk_offsets(int row0, int rows, int ld, uint32_t *voff)
 {
     const int tid = threadIdx.x;

@@ -182,14 +182,15 @@ tt_status launch_gemm_v3_runs(int nblk, int nred, int parts, const void *const *
 tt_status launch_gemm_runs(int nblk, int nred, int parts, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                            int64_t K, int trans_a, int trans_b, int out_dtype, int act, void *stream);
 
-// Same contract for the 256 x 128 engine with two workgroups per CU (gemm_core4.h); K a multiple of 32.
+// Panel engine (gemm_core5.h): C_s = A_s^T B_s, A_s stored K x M, B_s stored K x N, K from 1 to 256 or 512, bf16 results with
+// 16-byte rows of less than 2^28 elements.
 tt_status launch_gemm_v5(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int relu, void *stream);
+// The contract of launch_gemm_v3 for the 256 x 128 engine with two workgroups per CU (gemm_core4.h), any K and chunks of it
 tt_status launch_gemm_v4(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc, bool b_kc, int out_dtype, int relu,
                          bool vec, int ksplit, int64_t kchunk, void *stream);
-// The same tile with K tiles of 64 and one workgroup per CU for products whose left operand has K contiguous
-// (gemm_core6.h); K and a K chunk multiples of 64.
+// ... and for the same tile with K tiles of 64 and one workgroup per CU (gemm_core6.h)
 tt_status launch_gemm_v6(int count, const void *const *A, const void *const *B, void *const *C, int64_t M, int64_t N,
                          int64_t K, int64_t lda, int64_t ldb, int64_t ldc, bool a_kc, bool b_kc, int out_dtype, int relu, bool vec,
                          int ksplit, int64_t kchunk, void *stream);
