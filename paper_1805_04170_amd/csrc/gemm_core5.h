@@ -105,10 +105,14 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
     const uint32_t bid = blockIdx.x, grid = (uint32_t)p.grid;
     const uint32_t lw = grid % core::kXcds == 0 ? (bid % core::kXcds) * (grid / core::kXcds) + bid / core::kXcds : bid;
     // (units lw total / grid to (lw + 1) total / grid, no product past 32 bits: total < 2^30, grid < 2^15.  With 64-bit divisions, here and
-    // at every panel, the code spilled at K = 256: 8 x (1024 x 2048 x 256) 13.8 -> 12.7 us)
+    // at every panel, the code spilled at K = 256: 8 x (1024 x 2048 x 256) 13.8 -> 12.7 us, 8 x (1568 x 4096 x 192) 38 -> 35)
     const uint32_t each = (uint32_t)p.total / grid, rest = (uint32_t)p.total % grid;
-    int u = (int)(lw * each + lw * rest / grid);
-    const int end = (int)((lw + 1) * each + (lw + 1) * rest / grid);
+    // Quotients are uniform, but come out in vector registers, and with them a unit's addresses unless told so.  Scalar / vector, us: K =
+    // 512 16 x (512 x 8192), in a step, 77 / 79; K = 256, where scalar registers are as short, 8 x (1024 x 2048) 13.5 / 12.7, 8 x (1568 x 4096) K
+    // 192 36.4 / 35
+    const auto uniform = [](int v) { return KT == 16 ? v : __builtin_amdgcn_readfirstlane(v); };
+    int u = uniform(lw * each + lw * rest / grid);
+    const int end = uniform((lw + 1) * each + (lw + 1) * rest / grid);
 
     // lane parts of the load addresses
     const uint32_t bkl = (uint32_t)tid >> 3, bpc = (uint32_t)tid & 7u;
@@ -136,8 +140,8 @@ template <int KT, bool NTS, bool TAIL> __device__ __forceinline__ void run_panel
     const int per_shard = p.panels * p.ntiles;
 
     while (u < end) {
-        const int shard = u / per_shard, r = u - shard * per_shard;
-        const int panel = r / p.ntiles, nt0 = r - panel * p.ntiles;
+        const int shard = uniform(u / per_shard), r = u - shard * per_shard;
+        const int panel = uniform(r / p.ntiles), nt0 = r - panel * p.ntiles;
         const int run = end - u < p.ntiles - nt0 ? end - u : p.ntiles - nt0;
         const int m0 = panel * PM5;
 
